@@ -176,16 +176,30 @@ def run(s):
 
 @functools.lru_cache(maxsize=None)
 def _load(model, tokens):
-    """(local experts that get at least one row, local rows per token) for a batch of `tokens`: conventional top-K
-    of logits drawn from the router's law (at most 4096 tokens: by then every expert that is used at all is)."""
+    """(local experts that get at least one row, local rows per token) for a batch of `tokens`: the collaboration-
+    constrained selection on logits drawn from the router's law, lists profiled on conventional top-K (at most 4096
+    tokens: by then every expert that is used at all is)."""
     w = WORKLOADS[MODELS[model]]
     rng = np.random.default_rng(11)
+    bias = _popularity(w)
+
+    def logits(n):
+        l = rng.standard_normal((n, w.groups))[:, _group_of(w)] + 0.02 * w.d ** 0.5 * rng.standard_normal((n, w.E))
+        return l if bias is None else l + bias
+
+    chosen = np.zeros((PROFILE_TOKENS, w.E))
+    np.put_along_axis(chosen, np.argsort(-logits(PROFILE_TOKENS), axis=1)[:, :w.K], 1.0, axis=1)
+    counts = chosen.T @ chosen
+    np.fill_diagonal(counts, -1.0)
+    allowed = np.zeros((w.E, w.E), dtype=bool)
+    np.put_along_axis(allowed, np.argsort(-counts, axis=1, kind="stable")[:, :w.Tc], True, axis=1)
     rows = used = 0.0
     n, reps = min(tokens, 4096), max(1, min(16, 256 // tokens))
-    bias = _popularity(w)
     for _ in range(reps):
-        l = rng.standard_normal((n, w.groups))[:, _group_of(w)] + 0.02 * w.d ** 0.5 * rng.standard_normal((n, w.E))
-        top = np.argsort(-(l if bias is None else l + bias), axis=1)[:, :w.K]
+        l = logits(n)
+        first = np.argmax(l, axis=1)
+        others = np.argsort(-np.where(allowed[first], l, -np.inf), axis=1)[:, :w.K - 1]
+        top = np.concatenate([first[:, None], others], axis=1)
         local = top[top < w.n_local]
         rows += local.size / n / reps
         used += np.unique(local).size / reps
