@@ -299,6 +299,38 @@ int c2r_combine(const void *y_perm, c2r_dtype dt, const float *gates, const int3
                 int64_t T, int d, int K, const void *y_shared, void *y, void *stream);
 
 /*
+ * The whole layer (Sec. 3.1, Sec. 3.3) in one host call: c2r_route, c2r_permute, the expert FFN and c2r_combine
+ * on the buffers of *layer, enqueued on `stream` in that order.  It does what those calls do one by one - the
+ * same kernels, checks and results - and exists because a decoding step's kernels are shorter than a dozen calls
+ * through a language binding.  Nothing of *layer is kept.  An error of a later stage is returned after the
+ * earlier stages have been enqueued.
+ * Sizes and device pointers are those of the entry points of the same names; every field is 64 bits wide.  The
+ * pointers that are set choose the form of the expert FFN:
+ *   x_perm          : rows are scattered by c2r_permute and both passes run as c2r_expert_ffn (h in ws_ffn)
+ *   h               : the gate/up pass gathers (c2r_expert_ffn_gate_up_gather / _down), and with h_shared, too, the
+ *                     shared expert rides in the same launches (c2r_expert_ffn_*_with_shared)
+ *   neither         : c2r_expert_ffn_gather (h in ws_ffn)
+ * The shared expert (F_shared > 0) when it does not ride: off_shared = int32 {0, T} on the device and either
+ * h_shared (two passes) or ws_shared (c2r_expert_ffn).  Both h and x_perm set: C2R_ERR_INVALID_ARG.
+ */
+typedef struct {
+    int64_t T, d, E, K, F, dtype, Tc, E_local, F_shared, fuse_shared;
+    const float *Wg, *bias;
+    const int32_t *collab_idx, *local_slot;
+    const void *w_gate, *w_up, *w_down, *ws_gate, *ws_up, *ws_down;
+    int32_t *topk_idx;
+    float *gates;
+    int32_t *counts, *offsets, *perm, *inv_perm;
+    void *x_perm, *h, *y_perm;
+    const int32_t *off_shared;
+    void *h_shared, *y_shared;
+    void *ws_route, *ws_permute, *ws_ffn, *ws_shared;
+    int64_t ws_route_bytes, ws_permute_bytes, ws_ffn_bytes, ws_shared_bytes;
+    void *y;
+} c2r_layer;
+int c2r_layer_forward(const c2r_layer *layer, const void *x, void *stream);
+
+/*
  * Zero-redundancy dispatch index (Sec. 3.4: a token whose experts share a device travels
  * there once and is replicated on arrival), built on one GPU.  For a
  * map expert -> device, every token gets ONE copy per device that hosts at least one of its

@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from typing import Optional
 
 import torch
@@ -24,7 +25,7 @@ _ERRNAMES = {-1: "C2R_ERR_INVALID_ARG", -2: "C2R_ERR_UNSUPPORTED", -3: "C2R_ERR_
 EXPORTS = ["c2r_version", "c2r_route_chunk", "c2r_workspace_bytes", "c2r_build_coactivation",
            "c2r_collaborators", "c2r_route", "c2r_route_from_logits", "c2r_profile_from_logits", "c2r_permute", "c2r_permute_noalloc", "c2r_expert_ffn",
            "c2r_expert_ffn_gate_up", "c2r_expert_ffn_gate_up_gather", "c2r_expert_ffn_gather", "c2r_expert_ffn_down",
-           "c2r_expert_ffn_gate_up_with_shared", "c2r_expert_ffn_down_with_shared", "c2r_combine",
+           "c2r_expert_ffn_gate_up_with_shared", "c2r_expert_ffn_down_with_shared", "c2r_combine", "c2r_layer_forward",
            "c2r_place_experts", "c2r_dedup_dispatch", "c2r_combine_partial", "c2r_combine_copies",
            "c2r_collaboration_degree", "c2r_distinct_devices"]
 
@@ -67,6 +68,7 @@ def lib():
                                                          i32, vp, vp, vp, vp]
         L.c2r_expert_ffn_down_with_shared.argtypes = [vp, i32, vp, i32, i64, i32, i32, vp, vp, i64, i32, vp, vp, vp, vp]
         L.c2r_combine.argtypes = [vp, i32, vp, vp, i64, i32, i32, vp, vp, vp]
+        L.c2r_layer_forward.argtypes = [C.c_char_p, vp, vp]
         L.c2r_place_experts.argtypes = [vp, i32, i32, vp, vp]
         L.c2r_dedup_dispatch.argtypes = [vp, i64, i32, i32, vp, i32, vp, vp, vp, vp, vp, sz, vp]
         L.c2r_combine_partial.argtypes = [vp, i32, vp, vp, vp, vp, vp, i64, i64, i32, i32, vp, vp]
@@ -92,6 +94,13 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
     return C.c_void_p(t.data_ptr())
+
+
+def _addr(t: Optional[torch.Tensor]) -> int:
+    if t is None:
+        return 0
+    assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
+    return t.data_ptr()
 
 
 def _stream():
@@ -419,7 +428,7 @@ class C2RLayer:
         self.w = (w_gate, w_up, w_down)
         self.local_slot, self.shared = local_slot, shared
         dev = device
-        dt = F32 if dtype == torch.float32 else BF16
+        dt = self._dt = F32 if dtype == torch.float32 else BF16
         i32 = dict(dtype=torch.int32, device=dev)
         self.idx = torch.empty((T, K), **i32)
         self.gates = torch.empty((T, K), dtype=torch.float32, device=dev)
@@ -467,6 +476,31 @@ class C2RLayer:
             self.side = torch.cuda.Stream(device=dev)          # default priority
             self.ev = {k: torch.cuda.Event() for k in ("x", "shared_gate_up", "gate_up", "shared_down")}
 
+    _LAYER = struct.Struct("<10q26Q4qQ")   # c2r_layer
+
+    def _args(self):
+        """The fields of c2r_layer, gathered from the attributes as they are now."""
+        p = _addr
+        w, dtype, El, F, d = self.w, self.y.dtype, self.E_local, self.F, self.d
+        assert w[0].shape == w[1].shape == (El, F, d) and w[2].shape == (El, d, F)
+        assert w[0].dtype == w[1].dtype == w[2].dtype == dtype
+        assert self.Wg.shape == (d, self.E) and self.Wg.dtype == torch.float32
+        sh = self.shared if self.shared is not None else (None, None, None)
+        if self.shared is not None:
+            Fs = sh[0].shape[-2]
+            assert sh[0].shape == sh[1].shape == (1, Fs, d) and sh[2].shape == (1, d, Fs) and sh[0].dtype == dtype
+        collab = self.collab_idx
+        a = self.__dict__.get
+        return self._LAYER.pack(
+            self.T, self.d, self.E, self.K, self.F, self._dt, 0 if collab is None else collab.shape[1], self.E_local,
+            0 if self.shared is None else Fs, self.fuse_shared,
+            p(self.Wg), p(self.bias), p(collab), p(self.local_slot), p(w[0]), p(w[1]), p(w[2]),
+            p(sh[0]), p(sh[1]), p(sh[2]), p(self.idx), p(self.gates), p(self.counts), p(self.offsets), p(self.perm),
+            p(self.inv_perm), p(self.x_perm), p(self.h), p(self.y_perm), p(a("off_shared")), p(a("h_shared")),
+            p(self.y_shared), p(self.ws_route), p(self.ws_perm), p(a("ws_ffn")), p(a("ws_shared")),
+            self.ws_route.numel(), self.ws_perm.numel(), 0 if self.fuse_gather else self.ws_ffn.numel(),
+            self.ws_shared.numel() if "ws_shared" in self.__dict__ else 0, p(self.y))
+
     # names of the stages forward() may run, in the order a trace lists them
     STAGES = ("route", "permute", "ffn_gate_up", "ffn_down", "shared_gate_up", "shared_down", "combine")
 
@@ -482,6 +516,12 @@ class C2RLayer:
         STAGES; each pair is recorded on the stream its stage runs on (timing events, made by
         the caller).  only: run just that stage on the buffers a previous full call left
         (for timing a stage on its own)."""
+        if trace is None and only is None and not self.overlap:
+            # one call for the whole layer: through the binding stage by stage the host needs about 85 us per
+            # forward, more than the kernels of a decoding step take
+            assert x.shape == (self.T, self.d) and x.dtype == self.y.dtype
+            _check("c2r_layer_forward", lib().c2r_layer_forward(self._args(), _ptr(x), _stream()))
+            return self.y
         main = torch.cuda.current_stream()
         side = self.side if self.overlap else main
 

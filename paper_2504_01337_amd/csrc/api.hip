@@ -234,3 +234,55 @@ extern "C" int c2r_expert_ffn_down_with_shared(const void *h, c2r_dtype dt, cons
                                                    static_cast<uint16_t *>(y_perm), d, nullptr, 1, 1);
     return launch_ffn_bf16_dma(1, routed, &shared, st);
 }
+
+// ---- the layer in one host call ----
+extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *stream) {
+    if (!layer || (layer->h && layer->x_perm)) return C2R_ERR_INVALID_ARG;
+    const c2r_layer &L = *layer;
+    const c2r_dtype dt = static_cast<c2r_dtype>(L.dtype);
+    const int d = (int)L.d, E = (int)L.E, K = (int)L.K, F = (int)L.F, El = (int)L.E_local, Fs = (int)L.F_shared;
+    const int64_t T = L.T, A = T * K;
+    const bool shared = Fs > 0, rides = shared && L.fuse_shared != 0;
+    if (shared && !rides) {
+        int rc;
+        if (L.h_shared)
+            rc = c2r_expert_ffn_gate_up(x, dt, L.off_shared, 1, T, d, Fs, L.ws_gate, L.ws_up, L.h_shared, stream);
+        else
+            rc = c2r_expert_ffn(x, dt, L.off_shared, 1, T, d, Fs, L.ws_gate, L.ws_up, L.ws_down, L.y_shared, L.ws_shared,
+                                (size_t)L.ws_shared_bytes, stream);
+        if (rc != C2R_OK) return rc;
+    }
+    int rc = c2r_route(x, dt, L.Wg, L.bias, T, d, E, K, L.collab_idx, (int)L.Tc, L.topk_idx, L.gates, nullptr, L.ws_route,
+                       (size_t)L.ws_route_bytes, stream);
+    if (rc != C2R_OK) return rc;
+    rc = c2r_permute(x, dt, L.topk_idx, T, d, E, K, L.local_slot, El, L.counts, L.offsets, L.perm, L.inv_perm, L.x_perm,
+                     L.ws_permute, (size_t)L.ws_permute_bytes, stream);
+    if (rc != C2R_OK) return rc;
+    if (L.h) {
+        if (rides)
+            rc = c2r_expert_ffn_gate_up_with_shared(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, Fs,
+                                                    L.ws_gate, L.ws_up, L.h_shared, stream);
+        else
+            rc = c2r_expert_ffn_gate_up_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, stream);
+    } else if (L.x_perm) {
+        rc = c2r_expert_ffn(L.x_perm, dt, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.w_down, L.y_perm, L.ws_ffn,
+                            (size_t)L.ws_ffn_bytes, stream);
+    } else {
+        rc = c2r_expert_ffn_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.w_down, L.y_perm,
+                                   L.ws_ffn, (size_t)L.ws_ffn_bytes, stream);
+    }
+    if (rc != C2R_OK) return rc;
+    if (shared && !rides && L.h_shared) {
+        rc = c2r_expert_ffn_down(L.h_shared, dt, L.off_shared, 1, T, d, Fs, L.ws_down, L.y_shared, stream);
+        if (rc != C2R_OK) return rc;
+    }
+    if (L.h) {
+        if (rides)
+            rc = c2r_expert_ffn_down_with_shared(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, T, Fs, L.h_shared,
+                                                 L.ws_down, L.y_shared, stream);
+        else
+            rc = c2r_expert_ffn_down(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, stream);
+        if (rc != C2R_OK) return rc;
+    }
+    return c2r_combine(L.y_perm, dt, L.gates, L.inv_perm, T, d, K, shared ? L.y_shared : nullptr, L.y, stream);
+}

@@ -1,0 +1,56 @@
+"""C2RLayer.forward in one native call (c2r_layer_forward) gives what the same stages give one by one, in every form the
+layer takes: gather fused or not, padded widths, shared expert riding in the routed launches, beside them, or in full
+precision."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,T,d,E,K,F,Fs,local,kw", [
+    ("bf16", 70, 128, 12, 4, 192, 320, False, {}), ("bf16", 300, 64, 8, 2, 128, 64, True, {}),
+    ("bf16", 33, 128, 8, 3, 64, 128, False, {"fuse_shared": False}),
+    ("bf16", 33, 128, 8, 3, 64, 128, False, {"fuse_gather": False}),
+    ("bf16", 40, 64, 16, 4, 88, 0, False, {}), ("bf16", 40, 64, 16, 4, 88, 72, True, {}),
+    ("bf16", 9, 72, 5, 2, 64, 0, False, {}), ("f32", 65, 64, 8, 2, 96, 0, False, {}), ("f32", 10, 64, 7, 2, 32, 64, True, {})])
+def test_one_call_equals_the_stages(dtype, T, d, E, K, F, Fs, local, kw):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(T * 7 + F)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    w = lambda *sh: dev((rng.standard_normal(sh) * 0.05).astype(np.float32), dtype)
+    El, ls = E, None
+    if local:
+        El = E // 2
+        ls = np.full(E, -1, dtype=np.int32)
+        ls[np.sort(rng.permutation(E)[:El])] = np.arange(El, dtype=np.int32)
+    collab = np.stack([rng.permutation([j for j in range(E) if j != i])[:K + 1] for i in range(E)]).astype(np.int32)
+    shared = (w(1, Fs, d), w(1, Fs, d), w(1, d, Fs)) if Fs else None
+    layer = c2r.C2RLayer(T, d, E, K, F, tdt, dev(rng.standard_normal((d, E)).astype(np.float32)), None, dev(collab),
+                         w(El, F, d), w(El, F, d), w(El, d, F), local_slot=dev(ls), E_local=El, shared=shared, **kw)
+    x = dev(rng.standard_normal((T, d)).astype(np.float32), dtype)
+    y = layer.forward(x).clone()
+    got = [t.clone() for t in (layer.idx, layer.gates, layer.counts, layer.offsets, layer.inv_perm)]
+    layer.y.zero_()
+    y2 = layer.forward(x, trace={})                    # a trace goes stage by stage
+    torch.cuda.synchronize()
+    assert y.any() and torch.equal(y, y2)
+    for a, b in zip(got, (layer.idx, layer.gates, layer.counts, layer.offsets, layer.inv_perm)):
+        assert torch.equal(a, b)
+
+
+def test_one_call_rejects_what_the_stages_reject():
+    from paper_2504_01337_amd import c2r
+    z = lambda *sh: torch.zeros(sh, dtype=torch.float32, device="cuda")
+    layer = c2r.C2RLayer(4, 16, 4, 3, 8, torch.float32, z(16, 4), None, torch.zeros((4, 1), dtype=torch.int32, device="cuda"),
+                         z(4, 8, 16), z(4, 8, 16), z(4, 16, 8))
+    with pytest.raises(c2r.C2RError):                  # a list shorter than K - 1
+        layer.forward(z(4, 16))
+    layer.collab_idx = None
+    with pytest.raises(AssertionError):
+        layer.forward(z(5, 16))
+    layer.w = (z(4, 8, 16), z(4, 8, 16), z(4, 8, 16))
+    with pytest.raises(AssertionError):
+        layer.forward(z(4, 16))
