@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libc2r_hip.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "route.hip", "coact.hip", "permute.hip", "combine.hip", "ffn_f32.hip", "ffn_bf16.hip", "ffn_bf16_dma.hip", "ffn_skinny.hip",
+SOURCES = ["api.hip", "route.hip", "coact.hip", "permute.hip", "combine.hip", "ffn_f32.hip", "ffn_bf16.hip", "ffn_bf16_dma.hip", "ffn_skinny.hip", "ffn_mid.hip",
            "dedup.hip", "metrics.hip"]
 # benchmark equipment (a matrix-pipe ceiling probe): its own library, loaded by bench.py only
 AID_SRC = os.path.join(HERE, "bench_aids", "probe.hip")

@@ -24,80 +24,9 @@
 #include <type_traits>
 
 #include "ffn_common.h"
+#include "ffn_copy.h"
 
 namespace c2r {
-
-// 16 bytes per lane, global -> LDS, without passing through registers.  `lds` is the
-// wave-uniform start of the 1024-byte run; lane l's data lands at lds + 16*l.
-// Written as inline assembly on purpose: when the compiler sees the copy as an LDS write
-// it guards later LDS reads with vmcnt(0) whenever its alias bookkeeping loses track
-// (it does across this kernel's unrolled ring), which serialises the pipeline.  Hidden
-// from it, the only waits on copies are the ones this file states (wait_copies_but).
-// The source is a wave-uniform base (scalar registers) plus a 32-bit byte offset per lane:
-// no 64-bit address arithmetic per copy, and half the address bits to send.
-__device__ __forceinline__ void copy16_to_lds(const unsigned char *base, uint32_t off, unsigned char *lds) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    const uint32_t lds_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
-    asm volatile(
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %0, %1"
-        :
-        : "v"(off), "s"(base), "s"(lds_addr)
-        : "memory", "m0");
-#endif
-}
-
-// A pointer the compiler may keep in scalar registers (the value is the same in every lane).
-__device__ __forceinline__ const unsigned char *uniform_ptr(const unsigned char *p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return reinterpret_cast<const unsigned char *>(((uint64_t)hi << 32) | lo);
-}
-
-// Wait until at most N of this wave's copies are still in flight (they complete in order);
-// the other counters are left alone.
-template <int N>
-__device__ __forceinline__ void wait_copies_but() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-#endif
-}
-
-// vmcnt(0) and lgkmcnt(0): this wave's copies have landed and its LDS reads have returned.
-__device__ __forceinline__ void wait_copies_and_lds() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_s_waitcnt(0x0070);
-#endif
-}
-
-// lgkmcnt(0) alone: this wave's LDS reads have returned and its LDS writes are done; whatever
-// it has in flight to or from memory (the epilogue's stores) stays in flight.
-__device__ __forceinline__ void wait_lds_only() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-#endif
-}
-
-// Same, and this wave's LDS reads have returned (lgkmcnt(0)).
-template <int N>
-__device__ __forceinline__ void wait_copies_but_and_lds() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
-#endif
-}
-
-// Bare workgroup barrier.  __syncthreads() (and any workgroup fence) also drains every
-// outstanding copy (vmcnt(0)), which would serialise the slices in flight; here the
-// caller states exactly which copies must have landed (wait_copies_but) and the
-// scheduling fences keep the compiler from moving LDS reads across the barrier.
-__device__ __forceinline__ void lds_barrier() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-#endif
-}
 
 // The launch arguments as the tile function reads them: through the constant address space
 // (scalar loads from the kernel-argument segment).
@@ -859,8 +788,10 @@ FfnProblem ffn_bf16_dma_problem(int pass, const uint16_t *a, int lda, const int3
     return P;
 }
 
-bool ffn_skinny_takes(const FfnProblem &P);
+bool ffn_skinny_takes(int pass, const FfnProblem &P);
 int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st);
+int ffn_mid_rows(int pass, const FfnLaunch &L);
+int launch_ffn_mid(int pass, int tile_rows, FfnLaunch L, hipStream_t st);
 
 // Launches one pass over one problem (second == nullptr) or over two in ONE grid: the second
 // must be a single group (E_local == 1).
@@ -870,8 +801,8 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     if (second && second->E_local != 1) return C2R_ERR_INVALID_ARG;
     // Few rows: the kernel of ffn_skinny.hip.  Each problem is judged by itself, whatever else the call computes, so that
     // a row's bits do not depend on the entry point; where the two disagree they are launched one after the other.
-    const bool few = ffn_skinny_takes(first);
-    if (second && ffn_skinny_takes(*second) != few) {
+    const bool few = ffn_skinny_takes(pass, first);
+    if (second && ffn_skinny_takes(pass, *second) != few) {
         const int rc = launch_ffn_bf16_dma(pass, first, nullptr, st);
         return rc != C2R_OK ? rc : launch_ffn_bf16_dma(pass, *second, nullptr, st);
     }
@@ -885,6 +816,8 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     L.has_ragged = ragged ? 1 : 0;
     L.has_single = single ? 1 : 0;
     if (few) return launch_ffn_skinny(pass, L, st);
+    // More rows, but not enough to fill the chip with 256 x 256 tiles: the kernel of ffn_mid.hip (same bits as this one).
+    if (const int tile_rows = ffn_mid_rows(pass, L)) return launch_ffn_mid(pass, tile_rows, L, st);
     // one workgroup per CU (fewer if the bound on the tiles is smaller), whatever the number of tiles
     int64_t tiles = 0;
     if (ragged)

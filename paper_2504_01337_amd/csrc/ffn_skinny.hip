@@ -280,10 +280,17 @@ static void skinny_launch(FfnLaunch L, hipStream_t st) {
     ffn_skinny_kernel<MODE, NFR, NFS><<<dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st>>>(L);
 }
 
-// Up to this many rows a problem takes this kernel (one chunk of a single group; four rows per expert of the largest
-// layer).  At 60 experts + shared, top-4: 64 tokens 124 us against 178, 100 tokens 162 against 196 for the two passes, but
-// by then the gate/up pass of the tile kernel is the faster one; at 16 experts 84 against 99 us at 100 tokens, even at 200.
-bool ffn_skinny_takes(const FfnProblem &P) { return P.A_cap <= (P.E_local == 1 ? SKINNY_BM : 4 * SKINNY_BM); }
+// Up to this many rows a problem takes this kernel; beyond, ffn_mid.hip.  Microseconds of a layer call with this kernel /
+// with that one in the pass:
+//   gate/up: 60 experts + shared: 16 tokens 122.0 / 130.6, 24 tokens 129.7 / 132.0, 32 tokens 143.4 / 137.6, 64 tokens
+//     207 / 191; 16 experts of d 4096: 4 tokens 56.8 / 57.0, 16 tokens 76.9 / 73.2, 64 tokens 101 / 91.
+//   down (narrower workgroups, so the longest contraction is cut finer here): 60 experts + shared: 16 tokens 121.7 / 138.1,
+//     32 tokens 142.8 / 158.1, 48 tokens 162.2 / 155.1; 16 experts: 40 tokens 80.7 / 81.0, 100 tokens 96.8 / 94.0.
+// (At four experts per token both rules cut the routed groups and a shared expert at the same batch.)
+bool ffn_skinny_takes(int pass, const FfnProblem &P) {
+    if (pass == 1) return P.A_cap <= (P.E_local == 1 ? 40 : 160);
+    return P.A_cap <= (P.E_local == 1 ? 16 : (P.E_local < 32 ? 2 * P.E_local : 64));
+}
 
 int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st) {
     drop_stale_error();

@@ -1,0 +1,75 @@
+"""GPU parity of the expert FFN kernel for batches between decoding and prefill (ffn_mid.hip).  It sums in the tile kernel's
+order, and which of the two runs follows from the rows ALLOTTED, so the same rows in a larger allotment have to give the same
+bits; the oracle bar is the one of every bf16 pass (tests/helpers.py)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_01337_amd import workloads as wl
+from helpers import TOL, dev, host, max_rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def c2r():
+    from paper_2504_01337_amd import c2r as m
+    m.lib()
+    return m
+
+
+# edges of the 32-, 64- and 128-row tiles and of their 16-row fragments, groups of several tiles, empty groups, one group
+# only, fewer tiles than workgroups and tiles of a single 64-wide k-slice (a workgroup crosses several in its first ring);
+# k tails and padding columns (88, 688, 1400), column tails (72, 136), rows past the allotment's use
+@pytest.mark.parametrize("d,F,sizes,spare", [
+    (64, 64, [90], 0), (64, 64, [200], 0), (64, 72, [31, 32, 33, 0, 15, 16, 17, 1], 60), (192, 88, [63, 64, 65, 129, 0, 1], 5),
+    (320, 688, [127, 128, 48, 0], 20), (704, 136, [5] * 60, 0), (64, 1400, [97, 300, 2], 0), (512, 192, [250, 1, 255], 0)])
+def test_mid_rows_against_oracle_and_tile_kernel(c2r, orc, d, F, sizes, spare):
+    rng = np.random.default_rng(d * 3 + F)
+    E = len(sizes)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n = int(offsets[-1])
+    assert (n + spare) // E < 250 and n + spare > 64
+    x = wl.round_bf16(rng.standard_normal((n, d)).astype(np.float32))
+    wg, wu, wd = [wl.round_bf16((rng.standard_normal(s) * 0.05).astype(np.float32)) for s in ((E, F, d), (E, F, d), (E, d, F))]
+    w = [dev(a, "bf16") for a in (wg, wu, wd)]
+    got = []
+    for cap in (n + spare, 600 * E + n):
+        xa = torch.full((cap, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        xa[:n] = dev(x, "bf16")
+        y = torch.full((cap, d), 123.0, dtype=torch.bfloat16, device="cuda")
+        ws = torch.full((c2r.workspace_bytes(c2r.STAGE_EXPERT_FFN, cap, d, E, 1, F, c2r.BF16),), 255, dtype=torch.uint8,
+                        device="cuda")                                    # stale scratch: NaNs as bf16
+        c2r.expert_ffn(xa, dev(offsets), *w, ws=ws, out=y)
+        torch.cuda.synchronize()
+        assert torch.all(y[n:] == 123.0)
+        got.append(y[:n])
+    assert torch.equal(got[0], got[1])
+    ref = orc.expert_ffn_rows(x, np.repeat(np.arange(E), sizes).astype(np.int32), wg, wu, wd)
+    assert max_rel_err(host(got[0]), ref) <= TOL["bf16"]
+
+
+# the gathered first pass (row numbers held in LDS: up to 4096 of them), alone and with a shared expert riding along
+@pytest.mark.parametrize("E,K,T,d,F,Fs", [(60, 4, 70, 128, 64, 320), (60, 4, 250, 64, 64, 128), (40, 4, 1024, 64, 64, 64),
+                                          (40, 4, 1025, 64, 64, 64), (1, 1, 100, 64, 128, 64)])
+def test_mid_entry_points_agree_bit_for_bit(c2r, E, K, T, d, F, Fs):
+    rng = np.random.default_rng(E * 1000 + T)
+    idx = np.stack([rng.permutation(E)[:K] for _ in range(T)]).astype(np.int32)
+    r = lambda *s: dev((rng.standard_normal(s) * 0.1).astype(np.float32), "bf16")
+    x, wg, wu, wd = r(T, d), r(E, F, d), r(E, F, d), r(E, d, F)
+    sg, su, sd = r(1, Fs, d), r(1, Fs, d), r(1, d, Fs)
+    counts, offsets, perm, inv, x_perm = c2r.permute(x, dev(idx), E)
+    z = lambda rows, cols: torch.zeros(rows, cols, dtype=torch.bfloat16, device="cuda")
+    h, y, hs, ys = [z(T * K, F) for _ in range(3)], [z(T * K, d) for _ in range(2)], [z(T, Fs) for _ in range(2)], [z(T, d) for _ in range(2)]
+    off_s = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    c2r.expert_ffn_gate_up(x_perm, offsets, wg, wu, h[0])
+    c2r.expert_ffn_gate_up_gather(x, perm, K, offsets, wg, wu, h[1])
+    c2r.expert_ffn_gate_up(x, off_s, sg, su, hs[0])
+    c2r.expert_ffn_down(h[0], offsets, wd, y[0])
+    c2r.expert_ffn_down(hs[0], off_s, sd, ys[0])
+    if E > 1:
+        c2r.expert_ffn_gate_up_with_shared(x, perm, K, offsets, wg, wu, h[2], sg, su, hs[1])
+        c2r.expert_ffn_down_with_shared(h[2], offsets, wd, y[1], hs[1], sd, ys[1])
+        assert torch.equal(h[0], h[2]) and torch.equal(hs[0], hs[1])
+        assert torch.equal(y[0], y[1]) and torch.equal(ys[0], ys[1])
+    assert torch.equal(h[0], h[1]) and h[0].any() and y[0].any() and ys[0].any()
