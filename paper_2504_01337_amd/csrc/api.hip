@@ -252,11 +252,9 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
                                 (size_t)L.ws_shared_bytes, stream);
         if (rc != C2R_OK) return rc;
     }
-    int rc = c2r_route(x, dt, L.Wg, L.bias, T, d, E, K, L.collab_idx, (int)L.Tc, L.topk_idx, L.gates, nullptr, L.ws_route,
-                       (size_t)L.ws_route_bytes, stream);
-    if (rc != C2R_OK) return rc;
-    rc = c2r_permute(x, dt, L.topk_idx, T, d, E, K, L.local_slot, El, L.counts, L.offsets, L.perm, L.inv_perm, L.x_perm,
-                     L.ws_permute, (size_t)L.ws_permute_bytes, stream);
+    int rc = route_and_permute(x, dt, L.Wg, L.bias, T, d, E, K, L.collab_idx, (int)L.Tc, L.topk_idx, L.gates, L.ws_route,
+                               (size_t)L.ws_route_bytes, L.local_slot, El, L.counts, L.offsets, L.perm, L.inv_perm, L.x_perm,
+                               L.ws_permute, (size_t)L.ws_permute_bytes, stream);
     if (rc != C2R_OK) return rc;
     if (L.h) {
         if (rides)

@@ -39,6 +39,19 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) { return pack_bf16x2(f, 0.0f) & 0xffffu; }
 
+// permute.hip: the argument checks of c2r_permute, and its row scatter alone.
+int permute_check(const void *x, c2r_dtype dt, const int32_t *topk_idx, int64_t T, int d, int E, int K,
+                  const int32_t *local_slot, int E_local, int32_t *counts, int32_t *offsets, int32_t *perm,
+                  int32_t *inv_perm, void *x_perm, void *ws, size_t ws_bytes);
+int permute_rows(const void *x, c2r_dtype dt, int64_t T, int d, int K, const int32_t *inv_perm, void *x_perm,
+                 hipStream_t st);
+// route.hip
+int route_and_permute(const void *x, c2r_dtype dt, const float *Wg, const float *bias, int64_t T, int d, int E, int K,
+                      const int32_t *collab_idx, int Tc, int32_t *topk_idx, float *gates, void *ws_route,
+                      size_t ws_route_bytes, const int32_t *local_slot, int E_local, int32_t *counts, int32_t *offsets,
+                      int32_t *perm, int32_t *inv_perm, void *x_perm, void *ws_permute, size_t ws_permute_bytes,
+                      void *stream);
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (C2R_WAVE - 1); }
 
 }  // namespace c2r

@@ -410,6 +410,66 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
     }
 }
 
+// The same partial sums for small batches, on v_mfma_f32_16x16x4_f32: 16 experts x 16 tokens, four k per instruction,
+// added as four fused multiply-adds in ascending k (checked on the chip against chains of fmaf like the 32 x 32 x 2 form:
+// bit identical), so that this too is the declared order.  What bounds a small batch is the length of ONE chain: 256 k are
+// 64 instructions of 32 cycles here, 0.9 us, against two interleaved chains of 128 instructions of 64 cycles in the kernel
+// above, 7 us.  A workgroup of four waves takes one k-chunk: NEB expert blocks x 4 / NEB token tiles of 16.  W_g goes
+// straight from memory into operand registers (a lane's 64 values of its expert, all in flight together; rows need no
+// padding to 16 bytes, so an E that is no multiple of 4 needs no repacked copy), x through LDS.
+// Measured (both kernels of the stage, E 60, d 2048): 1 token 21.0 -> 12.8 us; E 8, d 4096: 16.0 -> 8.7 us.
+template <bool BF16, int NEB>
+__global__ __launch_bounds__(256) void route_partial_small_kernel(const void *__restrict__ x, const float *__restrict__ Wg,
+                                                                  int E, int ep, int64_t T, int d, int nchunk,
+                                                                  float *__restrict__ part) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef typename std::conditional<BF16, uint16_t, float>::type elem;
+    constexpr int NT = 4 / NEB, TOK = 16 * NT, VEC = 16 / sizeof(elem), CH = C2R_CANON_CHUNK;
+    constexpr int PITCH = CH + VEC, STEPS = CH / 4;
+    __shared__ __attribute__((aligned(16))) elem xs[TOK * PITCH];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int chunk = blockIdx.x % nchunk, k0 = chunk * CH, len = min(d - k0, CH);  // len: a multiple of 8
+    const int64_t t0 = (int64_t)(blockIdx.x / nchunk) * TOK;
+    const int eb = wave % NEB, tt = wave / NEB, col = lane & 15, kk = lane >> 4;
+    const int e = eb * 16 + col;
+    const float *wp = Wg + (size_t)(k0 + kk) * E + (e < E ? e : 0);  // (sums of experts past E are never read)
+    float w[STEPS];
+    const bool whole = len == CH;
+    if (whole) {
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) w[i] = wp[(size_t)(4 * i) * E];
+    }
+    for (int i = tid; i < TOK * (CH / VEC); i += 256) {
+        const int tok = i / (CH / VEC), c = i % (CH / VEC) * VEC;
+        const int64_t t = t0 + tok < T ? t0 + tok : T - 1;
+        if (c < len)
+            *reinterpret_cast<uint4 *>(&xs[tok * PITCH + c]) =
+                *reinterpret_cast<const uint4 *>(static_cast<const elem *>(x) + t * d + k0 + c);
+    }
+    __syncthreads();
+    const elem *xr = &xs[(tt * 16 + col) * PITCH + kk];
+    auto xval = [&](int i) __attribute__((always_inline)) {
+        if constexpr (BF16) return __uint_as_float((uint32_t)xr[4 * i] << 16);
+        else return xr[4 * i];
+    };
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (whole) {
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i], xval(i), acc, 0, 0, 0);
+    } else {
+        for (int i = 0; i < len / 4; ++i)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wp[(size_t)(4 * i) * E], xval(i), acc, 0, 0, 0);
+    }
+    // register i: expert 4 * (lane / 16) + i of the block, token lane % 16
+    const int64_t t = t0 + tt * 16 + col;
+    float *dst = part + ((size_t)(t >> 6) * nchunk + chunk) * ep * 64 + (t & 63);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int ei = eb * 16 + kk * 4 + i;
+        if (ei < ep && t < (T + 63) / 64 * 64) dst[(size_t)ei * 64] = acc[i];
+    }
+}
+
 // Among experts whose bit is set in m: the largest logit, first one standing
 // unless a later one is strictly larger (so ties and NaNs go to the lower index).
 template <int EP>
@@ -443,17 +503,26 @@ __global__ __launch_bounds__(ROWMAJOR ? 64 : SEL_WAVES * 64) void route_select_k
 
     const uint64_t all = E >= 64 ? ~0ull : ((1ull << E) - 1ull);
     // one 64-bit collaborator mask per expert; the list entries are spread over all the threads
-    // (one thread walking a whole list would wait for Tc loads one after another)
+    // (one thread walking a whole list would wait for Tc loads one after another).  With chunk
+    // partials a thread's first four entries are requested ahead of the partial sums and go into
+    // the masks after them, so that the two trips to memory are one.
+    constexpr int AHEAD = ROWMAJOR ? 0 : 4;
     if (threadIdx.x < C2R_MAX_E)
         mask_tab[threadIdx.x] = (!collab_idx && (int)threadIdx.x < E) ? all & ~(1ull << threadIdx.x) : 0ull;
+    const int nlist = collab_idx ? E * Tc : 0;
+    auto allow = [&](int i, int v) __attribute__((always_inline)) {
+        const int e = i / Tc;
+        if (v >= 0 && v < E && v != e)
+            atomicOr(reinterpret_cast<unsigned long long *>(&mask_tab[e]), 1ull << v);
+    };
+    int32_t ahead[AHEAD > 0 ? AHEAD : 1];
     if (collab_idx) {
         __syncthreads();
-        const int n = E * Tc;
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) ahead[u] = collab_idx[min((int)(threadIdx.x + u * blockDim.x), nlist - 1)];
+        if (AHEAD == 0) {
 #pragma unroll 4
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            const int v = collab_idx[i], e = i / Tc;
-            if (v >= 0 && v < E && v != e)
-                atomicOr(reinterpret_cast<unsigned long long *>(&mask_tab[e]), 1ull << v);
+            for (int i = threadIdx.x; i < nlist; i += blockDim.x) allow(i, collab_idx[i]);
         }
     }
 
@@ -554,6 +623,14 @@ __global__ __launch_bounds__(ROWMAJOR ? 64 : SEL_WAVES * 64) void route_select_k
                 for (int i = 0; i < 4; ++i) tile[(4 * tq4 + i) * LP + e] = sum[j][i];
             }
         }
+        if (collab_idx) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                const int i = threadIdx.x + u * blockDim.x;
+                if (i < nlist) allow(i, ahead[u]);
+            }
+            for (int i = threadIdx.x + AHEAD * blockDim.x; i < nlist; i += blockDim.x) allow(i, collab_idx[i]);
+        }
         __syncthreads();
         // Selection by all the waves: four lanes per token, each over a quarter of the experts.
         constexpr int EQ = EP / 4;
@@ -609,6 +686,35 @@ __global__ __launch_bounds__(ROWMAJOR ? 64 : SEL_WAVES * 64) void route_select_k
         uint64_t m = mask_tab[e0];
         const float g0 = expf(v0 - v0);  // 1, or NaN when the largest logit is infinite or a NaN
         float den = g0;
+        if (K <= 8) {  // the usual case: the token's slots stay in registers until the gates are known
+            int es[8];
+            float gs[8];
+            es[0] = e0;
+            gs[0] = g0;
+#pragma unroll
+            for (int s = 1; s < 8; ++s) {
+                es[s] = -1;
+                gs[s] = 0.0f;
+                if (s < K) {
+                    float v;
+                    pick4(m, es[s], v);
+                    if (es[s] >= 0) {
+                        m &= ~(1ull << es[s]);
+                        gs[s] = expf(v - v0);
+                    }
+                    den += gs[s];
+                }
+            }
+            if (sub == 0) {
+#pragma unroll
+                for (int s = 0; s < 8; ++s)
+                    if (s < K) {
+                        topk_idx[(size_t)tq * K + s] = es[s];
+                        gates[(size_t)tq * K + s] = gs[s] / den;
+                    }
+            }
+            return;
+        }
         if (sub == 0) {
             topk_idx[(size_t)tq * K] = e0;
             gates[(size_t)tq * K] = g0;
@@ -1010,6 +1116,166 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
     }
 }
 
+// Selection AND dispatch index of a batch of at most 64 tokens and 1024 assignments, one workgroup: what
+// route_select_kernel and permute_by_slot_kernel (permute.hip) do, in one launch instead of two.
+// A launch costs such a batch as much as its work.  Layer call at 60 experts, 1 token: 59 -> 54 us.  Sixteen waves, so that the chunk
+// results of a whole batch are one load each in flight per thread, and a token has sixteen lanes to scan its experts.
+constexpr int FIN_WAVES = 16, FIN_TOKENS = 64, FIN_ASSIGNMENTS = 1024;
+
+__global__ __launch_bounds__(FIN_WAVES * 64) void route_finish_small_kernel(
+    const float *__restrict__ part, int ep, int nchunk, const float *__restrict__ bias, int T, int E, int K,
+    const int32_t *__restrict__ collab_idx, int Tc, const int32_t *__restrict__ local_slot, int E_local,
+    int32_t *__restrict__ topk_idx, float *__restrict__ gates, int32_t *__restrict__ counts,
+    int32_t *__restrict__ offsets, int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    constexpr int LP = C2R_MAX_E + 1;
+    __shared__ float tile[FIN_TOKENS * LP];
+    __shared__ uint64_t mask_tab[C2R_MAX_E];
+    __shared__ int32_t slot_tab[C2R_MAX_E], n_of[C2R_MAX_E];
+    __shared__ int32_t slots[FIN_ASSIGNMENTS];
+    __shared__ float gbuf[FIN_ASSIGNMENTS], den_of[FIN_TOKENS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint64_t all = E >= 64 ? ~0ull : ((1ull << E) - 1ull);
+
+    // (a thread's first list entry is requested ahead of the partial sums: one trip to memory instead of two)
+    const int nlist = collab_idx ? E * Tc : 0;
+    const int32_t listed = collab_idx ? collab_idx[min(tid, nlist - 1)] : 0;
+    // ---- logits: a thread adds up the chunk results (left to right) of one expert and four tokens ----
+    {
+        const int e = tid >> 4, quad = tid & 15;
+        if (e < ep && quad * 4 < T) {
+            const float *p = part + (size_t)e * 64 + quad * 4;
+            f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int c0 = 0; c0 < nchunk; c0 += 8) {
+                f32x4 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    v[u] = *reinterpret_cast<const f32x4 *>(p + (size_t)min(c0 + u, nchunk - 1) * ep * 64);
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (c0 + u < nchunk) sum = c0 + u == 0 ? v[u] : sum + v[u];
+            }
+            if (bias && e < E) sum = sum + bias[e];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tile[(quad * 4 + i) * LP + e] = sum[i];
+        }
+    }
+    // ---- collaborator masks and the slot of every expert ----
+    if (tid < C2R_MAX_E) {
+        mask_tab[tid] = (!collab_idx && tid < E) ? all & ~(1ull << tid) : 0ull;
+        const int s = tid < E ? (local_slot ? local_slot[tid] : tid) : -1;
+        slot_tab[tid] = s >= 0 && s < E_local ? s : -1;
+    }
+    if (collab_idx) {
+        __syncthreads();
+        for (int i = tid; i < nlist; i += FIN_WAVES * 64) {
+            const int v = i == tid ? listed : collab_idx[i], e = i / Tc;
+            if (v >= 0 && v < E && v != e)
+                atomicOr(reinterpret_cast<unsigned long long *>(&mask_tab[e]), 1ull << v);
+        }
+    }
+    __syncthreads();
+
+    // ---- selection: sixteen lanes per token, four experts each; see route_select_kernel for the rule ----
+    const int t = tid >> 4, sub = tid & 15;
+    if (t < T) {  // (the sixteen lanes of a token stay together)
+        float l[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) l[j] = sub * 4 + j < E ? tile[t * LP + sub * 4 + j] : 0.0f;
+        auto pick = [&](uint64_t m, int &bi, float &bv) __attribute__((always_inline)) {
+            const uint32_t mloc = (uint32_t)(m >> (sub * 4));
+            bi = -1;
+            bv = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool take = ((mloc >> j) & 1u) != 0 && (l[j] > bv || (bi < 0 && l[j] == l[j]));
+                bv = take ? l[j] : bv;
+                bi = take ? sub * 4 + j : bi;
+            }
+#pragma unroll
+            for (int xr = 1; xr <= 8; xr <<= 1) {
+                const int obi = __shfl_xor(bi, xr);
+                const float obv = __shfl_xor(bv, xr);
+                const bool first = (sub & xr) == 0;  // this lane's part holds the lower indices
+                const int abi = first ? bi : obi, bbi = first ? obi : bi;
+                const float abv = first ? bv : obv, bbv = first ? obv : bv;
+                const bool later = abi < 0 || (bbi >= 0 && bbv > abv);
+                bi = later ? bbi : abi;
+                bv = later ? bbv : abv;
+            }
+            if (m != 0) {  // a NaN stands only as the first allowed expert
+                const int f = __ffsll((unsigned long long)m) - 1;
+                const float lf = tile[t * LP + f];
+                if (lf != lf) {
+                    bi = f;
+                    bv = lf;
+                }
+            }
+        };
+        int e;
+        float v, v0 = 0.0f, den = 0.0f;
+        uint64_t m = all;
+        for (int s = 0; s < K; ++s) {
+            pick(m, e, v);
+            float g = 0.0f;
+            if (s == 0) {
+                v0 = v;
+                m = mask_tab[e];
+                g = expf(v0 - v0);  // 1, or NaN when the largest logit is infinite or a NaN
+            } else if (e >= 0) {
+                m &= ~(1ull << e);
+                g = expf(v - v0);
+            }
+            den = s == 0 ? g : den + g;
+            if (sub == 0) {
+                topk_idx[t * K + s] = e;
+                slots[t * K + s] = e >= 0 ? slot_tab[e] : -1;
+                gbuf[t * K + s] = g;
+            }
+        }
+        if (sub == 0) den_of[t] = den;
+    }
+    __syncthreads();
+
+    // ---- dispatch index: a wave counts the assignments of slots wave, wave + 16, ..., then hands out their positions in
+    //      order (the stable order of a = t * K + s) ----
+    const int A = T * K;
+    if (tid < A) gates[tid] = gbuf[tid] / den_of[tid / K];
+    for (int s = wave; s < E_local; s += FIN_WAVES) {
+        int n = 0;
+        for (int a0 = 0; a0 < A; a0 += 64) n += __popcll(__ballot(a0 + lane < A && slots[a0 + lane] == s));
+        if (lane == 0) n_of[s] = n;
+    }
+    __syncthreads();
+    const int n = lane < E_local ? n_of[lane] : 0;
+    int incl = n;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
+    }
+    if (wave == 0 && lane < E_local) {
+        counts[lane] = n;
+        offsets[lane] = incl - n;
+        if (lane == E_local - 1) offsets[E_local] = incl;
+    }
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    for (int s = wave; s < E_local; s += FIN_WAVES) {
+        int run = __shfl(incl - n, s);
+        for (int a0 = 0; a0 < A; a0 += 64) {
+            const bool mine = a0 + lane < A && slots[a0 + lane] == s;
+            const uint64_t b = __ballot(mine);
+            if (mine) {
+                const int p = run + __popcll(b & lt);
+                perm[p] = a0 + lane;
+                inv_perm[a0 + lane] = p;
+            }
+            run += __popcll(b);
+        }
+    }
+    if (tid < A && slots[tid] < 0) inv_perm[tid] = -1;
+}
+
 static int check_route_args(int64_t T, int E, int K, const int32_t *collab_idx, int Tc) {
     if (T < 0 || E < 1 || K < 1 || K > E) return C2R_ERR_INVALID_ARG;
     if (collab_idx && Tc < K - 1) return C2R_ERR_INVALID_ARG;
@@ -1035,6 +1301,16 @@ static RouteLayout route_layout(int64_t T, int d, int E) {
     L.part_bytes = round_up((size_t)L.nchunk * L.EP * (size_t)L.Tpad * sizeof(float), 256);
     L.wpad_bytes = (E % 4) ? round_up((size_t)d * L.EP * sizeof(float), 256) : 0;
     return L;
+}
+
+// Whether a batch takes route_partial_small_kernel: up to 6144 waves (16 experts x 16 tokens x one chunk each).  Beyond, every
+// workgroup's own copy of its W_g rows is what it spends its time on.  Microseconds of the stage, without / with it:
+//   E 60, d 2048: 1 token 21.0 / 12.8, 512 tokens 22.0 / 14.2, 3000 tokens 25.2 / 24.1, 4096 tokens 26.8 / 28.0;
+//   E 16, d 4096: 1 token 13.1 / 9.9, 4096 tokens 20.8 / 18.8, 6000 tokens 26.7 / 25.8; E 8, d 4096: 1 token 16.0 / 8.7,
+//     4096 tokens 19.4 / 16.6, 6000 tokens 23.3 / 23.9; E 8, d 256: 12.6 / 10.0 at every size up to 12000 tokens.
+static inline int route_expert_blocks(int EP) { return EP > 32 ? 4 : EP > 16 ? 2 : 1; }
+static inline bool route_small(int64_t T, int nchunk, int EP) {
+    return T <= 12288 && (T + 15) / 16 * nchunk * route_expert_blocks(EP) <= 6144;
 }
 
 size_t route_workspace_bytes(int64_t T, int d, int E) {
@@ -1070,10 +1346,16 @@ using namespace c2r;
 
 extern "C" int c2r_route_chunk(void) { return C2R_CANON_CHUNK; }
 
-extern "C" int c2r_route(const void *x, c2r_dtype x_dt, const float *Wg, const float *bias,
-                         int64_t T, int d, int E, int K, const int32_t *collab_idx, int Tc,
-                         int32_t *topk_idx, float *gates, float *logits_out, void *ws,
-                         size_t ws_bytes, void *stream) {
+// What route_finish_small_kernel writes besides the selection.
+struct DispatchOut {
+    const int32_t *local_slot;
+    int E_local;
+    int32_t *counts, *offsets, *perm, *inv_perm;
+};
+
+static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const float *bias, int64_t T, int d, int E, int K,
+                      const int32_t *collab_idx, int Tc, int32_t *topk_idx, float *gates, float *logits_out, void *ws,
+                      size_t ws_bytes, const DispatchOut *dispatch, void *stream) {
     drop_stale_error();
     int rc = check_route_args(T, E, K, collab_idx, Tc);
     if (rc != C2R_OK) return rc;
@@ -1088,16 +1370,36 @@ extern "C" int c2r_route(const void *x, c2r_dtype x_dt, const float *Wg, const f
     float *part = static_cast<float *>(ws);
     const float *W = Wg;
     int ldw = E;
+    if (!L.wpad_bytes && !aligned(Wg, 16)) return C2R_ERR_INVALID_ARG;
+    const int64_t ntiles = L.Tpad / 64;
+    if (route_small(T, L.nchunk, L.EP)) {
+        const int neb = route_expert_blocks(L.EP), tok = 64 / neb;
+        const dim3 g((unsigned)((T + tok - 1) / tok * L.nchunk)), b(256);
+#define C2R_SMALL_LAUNCH(BF)                                                                               \
+    switch (neb) {                                                                                         \
+        case 4: route_partial_small_kernel<BF, 4><<<g, b, 0, st>>>(x, Wg, E, L.EP, T, d, L.nchunk, part); break; \
+        case 2: route_partial_small_kernel<BF, 2><<<g, b, 0, st>>>(x, Wg, E, L.EP, T, d, L.nchunk, part); break; \
+        default: route_partial_small_kernel<BF, 1><<<g, b, 0, st>>>(x, Wg, E, L.EP, T, d, L.nchunk, part);       \
+    }
+        if (x_dt == C2R_BF16) { C2R_SMALL_LAUNCH(true) } else { C2R_SMALL_LAUNCH(false) }
+#undef C2R_SMALL_LAUNCH
+        if (dispatch) {
+            route_finish_small_kernel<<<dim3(1), dim3(FIN_WAVES * 64), 0, st>>>(
+                part, L.EP, L.nchunk, bias, (int)T, E, K, collab_idx, Tc, dispatch->local_slot, dispatch->E_local, topk_idx,
+                gates, dispatch->counts, dispatch->offsets, dispatch->perm, dispatch->inv_perm);
+            return launch_status();
+        }
+        C2R_EP_SWITCH(L.EP, route_select_kernel<EP, false><<<dim3((unsigned)ntiles), dim3(SEL_WAVES * 64), 0, st>>>(
+                                part, L.nchunk, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out));
+        return launch_status();
+    }
     if (L.wpad_bytes) {
         float *Wp = reinterpret_cast<float *>(static_cast<char *>(ws) + L.part_bytes);
         const int64_t n = (int64_t)d * L.EP;
         pack_router_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(Wg, d, E, L.EP, Wp);
         W = Wp;
         ldw = L.EP;
-    } else if (!aligned(Wg, 16)) {
-        return C2R_ERR_INVALID_ARG;
     }
-    const int64_t ntiles = L.Tpad / 64;
     // Four waves per workgroup share the W sub-tiles.  On the matrix pipe a wave tile is always
     // 32 tokens (the pipelined form of the kernel; at E = 60, d = 2048 it beats 64-token tiles
     // at every batch size: 191 vs 238 us for the stage at T = 65536).  On the vector pipe a batch
@@ -1145,6 +1447,38 @@ extern "C" int c2r_route(const void *x, c2r_dtype x_dt, const float *Wg, const f
     C2R_EP_SWITCH(L.EP, route_select_kernel<EP, false><<<dim3((unsigned)ntiles), dim3(SEL_WAVES * 64), 0, st>>>(
                             part, nchunk_out, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out));
     return launch_status();
+}
+
+extern "C" int c2r_route(const void *x, c2r_dtype x_dt, const float *Wg, const float *bias,
+                         int64_t T, int d, int E, int K, const int32_t *collab_idx, int Tc,
+                         int32_t *topk_idx, float *gates, float *logits_out, void *ws,
+                         size_t ws_bytes, void *stream) {
+    return route_impl(x, x_dt, Wg, bias, T, d, E, K, collab_idx, Tc, topk_idx, gates, logits_out, ws, ws_bytes, nullptr,
+                      stream);
+}
+
+// c2r_route followed by c2r_permute, for the layer call.
+int c2r::route_and_permute(const void *x, c2r_dtype dt, const float *Wg, const float *bias, int64_t T, int d, int E, int K,
+                           const int32_t *collab_idx, int Tc, int32_t *topk_idx, float *gates, void *ws_route,
+                           size_t ws_route_bytes, const int32_t *local_slot, int E_local, int32_t *counts, int32_t *offsets,
+                           int32_t *perm, int32_t *inv_perm, void *x_perm, void *ws_permute, size_t ws_permute_bytes,
+                           void *stream) {
+    int rc;
+    if (T >= 1 && T <= FIN_TOKENS && K >= 1 && T * K <= FIN_ASSIGNMENTS && E >= 1 && d >= 1 &&
+        route_small(T, (d + C2R_CANON_CHUNK - 1) / C2R_CANON_CHUNK, ep_of(E))) {
+        rc = permute_check(x, dt, topk_idx, T, d, E, K, local_slot, E_local, counts, offsets, perm, inv_perm, x_perm,
+                           ws_permute, ws_permute_bytes);
+        if (rc != C2R_OK) return rc;
+        const DispatchOut out = {local_slot, E_local, counts, offsets, perm, inv_perm};
+        rc = route_impl(x, dt, Wg, bias, T, d, E, K, collab_idx, Tc, topk_idx, gates, nullptr, ws_route, ws_route_bytes, &out,
+                        stream);
+        if (rc != C2R_OK || !x_perm) return rc;
+        return permute_rows(x, dt, T, d, K, inv_perm, x_perm, static_cast<hipStream_t>(stream));
+    }
+    rc = c2r_route(x, dt, Wg, bias, T, d, E, K, collab_idx, Tc, topk_idx, gates, nullptr, ws_route, ws_route_bytes, stream);
+    if (rc != C2R_OK) return rc;
+    return c2r_permute(x, dt, topk_idx, T, d, E, K, local_slot, E_local, counts, offsets, perm, inv_perm, x_perm, ws_permute,
+                       ws_permute_bytes, stream);
 }
 
 // Selection from stored logits; with Cmat the tokens' expert pairs are counted as well (then topk_idx

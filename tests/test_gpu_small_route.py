@@ -1,0 +1,70 @@
+"""Router and dispatch index of small batches: the partial sums on 16 x 16 x 4 matrix instructions (bit-exact logits in the
+declared order) and, inside the layer call, selection and index in one launch (what the separate stages give, bit for bit)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_01337_amd import workloads as wl
+from helpers import GATE_RTOL, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def c2r():
+    from paper_2504_01337_amd import c2r as m
+    m.lib()
+    return m
+
+
+# token tiles of 16, 32 and 64 (by the expert count) and their remainders; expert blocks of 16 and their remainders, rows of W_g
+# that are no whole 16-byte vectors; chunks of 256, shorter ones and ragged last ones; and the first batches past the rule, which
+# take the other kernel (12289 tokens of one chunk, 1537 and 3073 tokens of 16 and 8)
+@pytest.mark.parametrize("T,E,d,dtype", [
+    (1, 60, 2048, "bf16"), (15, 64, 256, "bf16"), (17, 61, 520, "bf16"), (33, 33, 264, "f32"), (31, 32, 8, "bf16"),
+    (65, 17, 1032, "f32"), (64, 16, 512, "bf16"), (63, 3, 24, "f32"), (130, 9, 1000, "bf16"), (1000, 8, 256, "f32"), (2, 1, 16, "bf16"),
+    (3072, 34, 2048, "bf16"), (3088, 34, 2048, "bf16"), (12288, 5, 264, "f32"), (12289, 5, 264, "f32"), (12289, 20, 248, "bf16")])
+def test_small_route_logits_bit_exact(c2r, orc, T, E, d, dtype):
+    rng = np.random.default_rng(T + E + d)
+    x = rng.standard_normal((T, d)).astype(np.float32) * np.exp2(rng.integers(-6, 7, size=(T, 1))).astype(np.float32)
+    x = wl.round_bf16(x) if dtype == "bf16" else x
+    Wg = rng.standard_normal((d, E)).astype(np.float32)
+    bias = rng.standard_normal(E).astype(np.float32)
+    K = min(E, 4)
+    idx, gates, logits = c2r.route(dev(x, dtype), dev(Wg), dev(bias), K, None, want_logits=True)
+    ref = orc.logits_canon_f32(x, Wg, bias)
+    assert np.array_equal(host(logits), ref)
+    ri, rg = orc.route(ref, K)
+    assert np.array_equal(host(idx), ri)
+    # logits of up to 64 sqrt(d) here: the bound of GATE_RTOL with |a_s| up to 104, where a gate is flushed to zero
+    np.testing.assert_allclose(host(gates), rg, rtol=114 / 34 * GATE_RTOL, atol=1e-37)
+
+
+# one workgroup's selection and index: 1 to 64 tokens, up to 1024 assignments (64 x 16), and the first calls past either limit;
+# lists that cannot fill the slots, NaN and infinite logits, experts that are not local
+@pytest.mark.parametrize("T,E,K,El,dtype", [(1, 60, 4, 60, "bf16"), (64, 60, 4, 15, "bf16"), (65, 60, 4, 15, "bf16"), (64, 64, 16, 64, "bf16"),
+                                            (61, 64, 17, 30, "bf16"), (5, 3, 3, 3, "f32"), (63, 17, 1, 9, "f32"), (37, 8, 2, 8, "f32")])
+def test_layer_call_of_a_small_batch_routes_like_the_stages(c2r, T, E, K, El, dtype):
+    rng = np.random.default_rng(T * E + K)
+    d, F = 64, 64
+    w = lambda *s: dev((rng.standard_normal(s) * 0.1).astype(np.float32), dtype)
+    ls = None
+    if El < E:
+        ls = np.full(E, -1, dtype=np.int32)
+        ls[rng.permutation(E)[:El]] = rng.permutation(El).astype(np.int32)
+    lists = rng.integers(-1, E + 2, size=(E, max(K, 2))).astype(np.int32)  # duplicates, the expert itself, out of range
+    bias = rng.standard_normal(E).astype(np.float32)
+    if E > 8:
+        bias[[2, 7]] = np.nan, np.inf
+    layer = c2r.C2RLayer(T, d, E, K, F, torch.bfloat16 if dtype == "bf16" else torch.float32,
+                         dev(rng.standard_normal((d, E)).astype(np.float32)), dev(bias), dev(lists), w(El, F, d), w(El, F, d),
+                         w(El, d, F), local_slot=dev(ls), E_local=El)
+    x = w(T, d)
+    layer.forward(x)
+    idx, gates, _ = c2r.route(x, layer.Wg, layer.bias, K, layer.collab_idx)
+    counts, offsets, perm, inv, _ = c2r.permute(x, idx, E, layer.local_slot, El)
+    torch.cuda.synchronize()
+    assert torch.equal(layer.idx, idx) and torch.equal(layer.gates.view(torch.int32), gates.view(torch.int32))
+    assert torch.equal(layer.counts, counts) and torch.equal(layer.offsets, offsets) and torch.equal(layer.inv_perm, inv)
+    n = int(offsets[-1])
+    assert torch.equal(layer.perm[:n], perm[:n]) and bool((layer.perm[n:] == -1).all())
