@@ -115,8 +115,9 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
     int smt = 0;
     XcdRange rs, ra, rb;
     rs.first = rs.cnt = ra.first = ra.cnt = rb.first = rb.cnt = 0;
+    const int sbm = L.single_rows;
     if (have_sg) {
-        smt = (shi - slo + BM - 1) / BM;
+        smt = (shi - slo + sbm - 1) / sbm;
         rs = equal_range(smt * L.p[1].ntn, xcd);
     }
     RaggedMap rmap;
@@ -159,7 +160,7 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
         int mt;
         single_group_tile_at(smt, L.p[1].ntn, rs.first + o_rank, mt, tile_nt);
         g.expert = 0;
-        g.row_begin = slo + mt * BM + ts.sub * (BM / ts.nsub);  // of this workgroup's part of the tile
+        g.row_begin = slo + mt * sbm + ts.sub * (sbm / ts.nsub);  // of this workgroup's part of the tile
         g.row_end = shi;
     } else {
         const RaggedTile tr = is_b ? ragged_short_tile_at<BM>(rmap, L.p[0].ntn, rb.first + b_before)
@@ -182,7 +183,8 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
     const int n0 = tile_nt * BNF;
     int rows = g.row_end - g.row_begin;  // may exceed the tile (clamped by the row guards below)
     if (rows <= 0) return;
-    if (tile_nsub > 1 && rows > BM / tile_nsub) rows = BM / tile_nsub;
+    const int part = (second ? sbm : BM) / tile_nsub;  // (a whole full tile's rows are clamped below)
+    if (part < BM && rows > part) rows = part;
     const bool short_tile = rows <= LM;        // workgroup-uniform
     const bool tiny_tile = rows <= TM_T;
 
@@ -675,7 +677,7 @@ __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_kernel(const FfnLaun
     // the first wave works the queues; its lane x < 8 keeps the number of slots of XCD x's list
     int my_len = 0;
     if (tid < 64) {
-        const int n_s = (sg_hi - sg_lo + S::BM - 1) / S::BM * (L.has_single ? L.p[1].ntn : 0);
+        const int n_s = (sg_hi - sg_lo + L.single_rows - 1) / L.single_rows * (L.has_single ? L.p[1].ntn : 0);
         int totA = 0, totB = 0;
         if (L.has_ragged) {
             const RaggedMap m = ragged_map_of<S::BM>(grp_lo, grp_hi);
@@ -793,6 +795,20 @@ int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st);
 int ffn_mid_rows(int pass, const FfnLaunch &L);
 int launch_ffn_mid(int pass, int tile_rows, FfnLaunch L, hipStream_t st);
 
+// Rows of the single group's tiles.  Fewer tiles than a quarter of the CUs, each a chain of k-slices much longer than those
+// beside it, are what a launch then waits for (a shared expert's down pass: 88 slices, 120 us, against 22): cut lower, the
+// same tiles are more, and shorter too (a 64-row tile has three slices in flight instead of one).  Microseconds of a layer
+// call with 256 / 128 / 64 rows in the down pass (60 experts + shared, d 2048, F 1408 / 5632): 600 tokens 261 / 248 / 217,
+// 1000 tokens 290 / 270 / 255, 1300 tokens 316 / 301 / 311, 1600 tokens 340 / 320 / 347, 2000 tokens 379 / 374 / 399, 2500
+// tokens 416 / 431 / 456 (every part reads the weights again).  In the gate/up pass, whose chains are alike, it only costs:
+// 1000 tokens 290 -> 304 with 128 rows.
+static int single_tile_rows(const FfnProblem *ragged, const FfnProblem *single) {
+    constexpr int BM = 256;
+    if (!single || (ragged && single->Kdim < 2 * ragged->Kdim)) return BM;
+    const int64_t tiles = ((int64_t)single->A_cap + BM - 1) / BM * single->ntn;
+    return tiles <= 40 ? BM / 4 : (tiles < 64 ? BM / 2 : BM);
+}
+
 // Launches one pass over one problem (second == nullptr) or over two in ONE grid: the second
 // must be a single group (E_local == 1).
 int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, hipStream_t st) {
@@ -823,7 +839,8 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     if (ragged)
         tiles += 8 * ragged_per_xcd_bound(((int64_t)ragged->A_cap + BM - 1) / BM + ragged->E_local, ragged->E_local,
                                           ragged->ntn);
-    if (single) tiles += 8 * single_per_xcd_bound(((int64_t)single->A_cap + BM - 1) / BM + 1, single->ntn);
+    L.single_rows = single_tile_rows(ragged, single);
+    if (single) tiles += 8 * single_per_xcd_bound(((int64_t)single->A_cap + L.single_rows - 1) / L.single_rows + 1, single->ntn);
     tiles += 8 * CUS_PER_XCD;  // (row parts of the last rounds)
     const int64_t grid = tiles < 8 * CUS_PER_XCD ? tiles : 8 * CUS_PER_XCD;
     static std::atomic<unsigned> next_set{0};

@@ -339,6 +339,7 @@ struct FfnProblem {
 struct FfnLaunch {
     FfnProblem p[2];            // p[0]: the ragged problem (several groups), p[1]: the single group
     int has_ragged, has_single;  // which of the two the launch carries (at least one)
+    int single_rows;             // tile kernel: rows of the single group's tiles (64, 128 or 256)
 };
 
 }  // namespace c2r

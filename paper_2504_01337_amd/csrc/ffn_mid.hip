@@ -16,7 +16,7 @@
 //
 // Microseconds of a layer call, tile kernel -> this one (60 experts + shared, d 2048, F 1408 / 5632, top-4; 16 experts,
 // d 4096, F 688, top-4):
-//   60 experts: 64 tokens 212 -> 165, 131 tokens 252 -> 179, 256 tokens (down pass only) 262 -> 196, 500 tokens 270 -> 226;
+//   60 experts: 64 tokens 212 -> 165, 131 tokens 252 -> 179, 256 tokens (down pass only) 210 -> 185;
 //   16 experts: 64 tokens 107 -> 78, 180 tokens 115 -> 88, 256 tokens 126 -> 106, 500 tokens 143 -> 128;
 //   15 of the 60 experts, 131 tokens 79 -> 65.
 #include "ffn_common.h"
@@ -273,7 +273,7 @@ static void mid_launch(int tile_rows, const FfnLaunch &L, hipStream_t st) {
 // against 143; 700 tokens: 172 against 155); down 32 -> 64 at 24, -> 128 at 64.  A shared expert's rows count half in the
 // gate/up pass (it alone: 96 tokens 208 us with 64 rows against 217 with 32; 256 tokens 279 against 262 of the tile
 // kernel) and a quarter in the down pass, where the tile kernel is left with its few long tiles for longest (256 tokens:
-// 196 against 262 us, 500: 226 against 270, 700: 293 with 128 rows against 280).
+// 185 against 210 us, 350: 208 against 211, 500: 212 against 212).
 int ffn_mid_rows(int pass, const FfnLaunch &L) {
     int r = 0;
     for (int q = 0; q < 2; ++q) {

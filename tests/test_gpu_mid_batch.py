@@ -73,3 +73,26 @@ def test_mid_entry_points_agree_bit_for_bit(c2r, E, K, T, d, F, Fs):
         assert torch.equal(h[0], h[2]) and torch.equal(hs[0], hs[1])
         assert torch.equal(y[0], y[1]) and torch.equal(ys[0], ys[1])
     assert torch.equal(h[0], h[1]) and h[0].any() and y[0].any() and ys[0].any()
+
+
+# the tile kernel cuts a single group with a long contraction into 64-row (d 2048: up to 1280 rows), 128-row or 256-row tiles:
+# alone and beside routed groups it gives the bits of any other cut
+@pytest.mark.parametrize("T", [513, 639, 1025, 1280, 1281, 1793])
+def test_lower_tiles_of_a_single_group_change_no_bits(c2r, T):
+    rng = np.random.default_rng(T)
+    d, F, Fs, E, K = 2048, 64, 192, 6, 2
+    r = lambda *s: dev((rng.standard_normal(s) * 0.1).astype(np.float32), "bf16")
+    h, hs, wd, sd = r(T * K, F), r(T, Fs), r(E, d, F), r(1, d, Fs)
+    offsets = torch.tensor(np.linspace(0, T * K, E + 1).round().astype(np.int32), device="cuda")
+    z = lambda rows: torch.zeros(rows, d, dtype=torch.bfloat16, device="cuda")
+    y, ys, alone, tall, y2 = z(T * K), z(T), z(T), z(3000), z(T * K)
+    c2r.expert_ffn_down_with_shared(h, offsets, wd, y, hs, sd, ys)
+    off = lambda n: torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    c2r.expert_ffn_down(hs, off(T), sd, alone)
+    c2r.expert_ffn_down(torch.cat([hs, torch.zeros(3000 - T, Fs, dtype=torch.bfloat16, device="cuda")]), off(T), sd, tall)
+    c2r.expert_ffn_down(h, offsets, wd, y2)
+    torch.cuda.synchronize()
+    assert ys.any() and torch.equal(ys, alone) and torch.equal(ys, tall[:T]) and not tall[T:].any()
+    assert torch.equal(y, y2)
+    ref = hs.double() @ sd[0].double().t()
+    assert ((ys.double() - ref).abs().max() / ref.abs().max()).item() <= TOL["bf16"]
