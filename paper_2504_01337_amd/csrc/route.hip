@@ -439,12 +439,19 @@ __global__ __launch_bounds__(256) void route_partial_small_kernel(const void *__
 #pragma unroll
         for (int i = 0; i < STEPS; ++i) w[i] = wp[(size_t)(4 * i) * E];
     }
-    for (int i = tid; i < TOK * (CH / VEC); i += 256) {
-        const int tok = i / (CH / VEC), c = i % (CH / VEC) * VEC;
+    // (every load is issued before the first store: in a loop of load and store each would wait for its own trip to memory)
+    constexpr int NV = TOK * (CH / VEC) / 256;
+    uint4 xv[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const int i = tid + u * 256, tok = i / (CH / VEC), c = i % (CH / VEC) * VEC;
         const int64_t t = t0 + tok < T ? t0 + tok : T - 1;
-        if (c < len)
-            *reinterpret_cast<uint4 *>(&xs[tok * PITCH + c]) =
-                *reinterpret_cast<const uint4 *>(static_cast<const elem *>(x) + t * d + k0 + c);
+        xv[u] = *reinterpret_cast<const uint4 *>(static_cast<const elem *>(x) + t * d + k0 + min(c, len - VEC));
+    }
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const int i = tid + u * 256;
+        *reinterpret_cast<uint4 *>(&xs[i / (CH / VEC) * PITCH + i % (CH / VEC) * VEC]) = xv[u];
     }
     __syncthreads();
     const elem *xr = &xs[(tt * 16 + col) * PITCH + kk];
