@@ -1,0 +1,42 @@
+"""Combine by whole row pieces, and the dispatch index's two block sizes."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_01337_amd import workloads as wl
+from helpers import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def c2r():
+    from paper_2504_01337_amd import c2r as m
+    m.lib()
+    return m
+
+
+# rows of one, two and three 2 KB pieces, and ones that are not whole pieces (the other kernel); 1 to 64 slots and one more; few and
+# odd token counts; tokens without any local slot, rows that nobody points at hold NaNs
+@pytest.mark.parametrize("dtype,T,K,d", [("bf16", 1, 1, 1024), ("bf16", 37, 4, 2048), ("bf16", 5, 64, 1024), ("bf16", 6, 65, 1024),
+                                         ("bf16", 9, 3, 3072), ("bf16", 9, 3, 1536), ("f32", 33, 7, 512), ("f32", 3, 2, 1536)])
+def test_combine_by_row_pieces(c2r, orc, dtype, T, K, d):
+    rng = np.random.default_rng(T + K + d)
+    store = wl.round_bf16 if dtype == "bf16" else (lambda a: a)
+    A = T * K
+    inv = rng.permutation(A).astype(np.int32).reshape(T, K)
+    inv[rng.random((T, K)) < 0.4] = -1
+    inv[T // 2] = -1
+    yp = store(rng.standard_normal((A, d)).astype(np.float32))
+    gates = rng.random((T, K)).astype(np.float32)
+    ys = store(rng.standard_normal((T, d)).astype(np.float32))
+    used = np.zeros(A, dtype=bool)
+    used[inv[inv >= 0]] = True
+    poisoned = np.where(used[:, None], yp, np.float32(np.nan))
+    for shared in (None, ys):
+        y = c2r.combine(dev(poisoned, dtype), dev(gates), dev(inv.reshape(-1)), None if shared is None else dev(shared, dtype))
+        ref = orc.combine(yp, gates, inv.reshape(-1), T, K, shared)
+        # one rounding of the result, and K + 1 of the fp32 sum
+        tol = 2.0 ** -8 if dtype == "bf16" else (K + 1) * 2.0 ** -24
+        scale = max((np.abs(gates).sum(1).max() + 1) * max(np.abs(yp).max(), np.abs(ys).max()), 1.0)
+        assert np.abs(host(y) - ref).max() <= tol * (scale if dtype == "f32" else max(np.abs(ref).max(), 1.0))
