@@ -40,3 +40,32 @@ def test_combine_by_row_pieces(c2r, orc, dtype, T, K, d):
         tol = 2.0 ** -8 if dtype == "bf16" else (K + 1) * 2.0 ** -24
         scale = max((np.abs(gates).sum(1).max() + 1) * max(np.abs(yp).max(), np.abs(ys).max()), 1.0)
         assert np.abs(host(y) - ref).max() <= tol * (scale if dtype == "f32" else max(np.abs(ref).max(), 1.0))
+
+
+# 256 tokens per block up to 32768 tokens where the scratch has room, 1024 otherwise: scratch of exactly what the larger blocks need is
+# enough at every size
+@pytest.mark.parametrize("T,K,n_dev", [(1, 4, 5), (255, 4, 3), (256, 2, 64), (257, 4, 4), (5000, 4, 60), (32768, 4, 4), (32769, 4, 4),
+                                       (2000, 9, 7)])
+def test_dispatch_index_at_both_block_sizes(c2r, orc, T, K, n_dev):
+    rng = np.random.default_rng(T + n_dev)
+    E = 64
+    idx = np.argsort(rng.random((T, E)), axis=1)[:, :K].astype(np.int32)
+    idx[rng.random((T, K)) < 0.1] = -1
+    devmap = rng.integers(-1, n_dev, size=E).astype(np.int32)
+    rc, ro, rt, rr = orc.dedup_dispatch(idx, E, devmap, n_dev)
+    least = ((T + 1023) // 1024 * n_dev * 4 + 255) // 256 * 256
+    for ws in (None, torch.empty(least, dtype=torch.uint8, device="cuda")):
+        if ws is None:
+            counts, offsets, tok, row = c2r.dedup_dispatch(dev(idx), E, dev(devmap), n_dev)
+        else:
+            i32 = dict(dtype=torch.int32, device="cuda")
+            counts, offsets = torch.empty(n_dev, **i32), torch.empty(n_dev + 1, **i32)
+            tok, row = torch.full((T * K,), -1, **i32), torch.empty(T * K, **i32)
+            i, m = dev(idx), dev(devmap)
+            p = lambda t: t.data_ptr()
+            assert c2r.lib().c2r_dedup_dispatch(p(i), T, K, E, p(m), n_dev, p(counts), p(offsets), p(tok), p(row), p(ws),
+                                                ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        n = int(ro[-1])
+        assert np.array_equal(host(counts), rc) and np.array_equal(host(offsets), ro)
+        assert np.array_equal(host(tok)[:n], rt[:n]) and np.array_equal(host(row).reshape(-1), np.asarray(rr).reshape(-1))
