@@ -493,6 +493,22 @@ __device__ __forceinline__ void pick(const float (&l)[EP], uint64_t m, int &bi, 
     }
 }
 
+// One merge step of a selection spread over neighbouring lanes: the partner's candidate (fetched by a data-parallel-primitive
+// move, a tenth of an LDS shuffle's latency: 1.8 us of the 8.6 that one token's selection takes) against this lane's, the part
+// with the lower expert indices first; a later one only if it is strictly larger.  upper: this lane's part is the later one.
+template <int DPP>
+__device__ __forceinline__ void merge_lower(int upper, int &bi, float &bv) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const int obi = __builtin_amdgcn_mov_dpp(bi, DPP, 0xf, 0xf, true);
+    const float obv = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(bv), DPP, 0xf, 0xf, true));
+    const int abi = upper ? obi : bi, bbi = upper ? bi : obi;
+    const float abv = upper ? obv : bv, bbv = upper ? bv : obv;
+    const bool later = abi < 0 || (bbi >= 0 && bbv > abv);
+    bi = later ? bbi : abi;
+    bv = later ? bbv : abv;
+#endif
+}
+
 // ROWMAJOR (stored logits [T, E]): one wave per 64 tokens.  Otherwise (chunk partials):
 // SEL_WAVES waves per 64 tokens; each sums the chunks of a quarter of the experts (the
 // loads of one wave alone cover the memory latency four times worse) and leaves its
@@ -667,17 +683,8 @@ __global__ __launch_bounds__(ROWMAJOR ? 64 : SEL_WAVES * 64) void route_select_k
                 bv = take ? lq[j] : bv;
                 bi = take ? sub * EQ + j : bi;
             }
-#pragma unroll
-            for (int xr = 1; xr <= 2; xr <<= 1) {
-                const int obi = __shfl_xor(bi, xr);
-                const float obv = __shfl_xor(bv, xr);
-                const bool first = (sub & xr) == 0;  // this lane's part holds the lower indices
-                const int abi = first ? bi : obi, bbi = first ? obi : bi;
-                const float abv = first ? bv : obv, bbv = first ? obv : bv;
-                const bool later = abi < 0 || (bbi >= 0 && bbv > abv);
-                bi = later ? bbi : abi;
-                bv = later ? bbv : abv;
-            }
+            merge_lower<0xB1>(sub & 1, bi, bv);  // quad_perm 1,0,3,2
+            merge_lower<0x4E>(sub & 2, bi, bv);  // quad_perm 2,3,0,1
             if (m != 0) {
                 const int f = __ffsll((unsigned long long)m) - 1;
                 const float lf = tile[tl * LP + f];
@@ -1199,17 +1206,10 @@ __global__ __launch_bounds__(FIN_WAVES * 64) void route_finish_small_kernel(
                 bv = take ? l[j] : bv;
                 bi = take ? sub * 4 + j : bi;
             }
-#pragma unroll
-            for (int xr = 1; xr <= 8; xr <<= 1) {
-                const int obi = __shfl_xor(bi, xr);
-                const float obv = __shfl_xor(bv, xr);
-                const bool first = (sub & xr) == 0;  // this lane's part holds the lower indices
-                const int abi = first ? bi : obi, bbi = first ? obi : bi;
-                const float abv = first ? bv : obv, bbv = first ? obv : bv;
-                const bool later = abi < 0 || (bbi >= 0 && bbv > abv);
-                bi = later ? bbi : abi;
-                bv = later ? bbv : abv;
-            }
+            merge_lower<0xB1>(sub & 1, bi, bv);   // quad_perm 1,0,3,2
+            merge_lower<0x4E>(sub & 2, bi, bv);   // quad_perm 2,3,0,1
+            merge_lower<0x141>(sub & 4, bi, bv);  // row_half_mirror: the other quad, whose lanes agree by now
+            merge_lower<0x140>(sub & 8, bi, bv);  // row_mirror: the other eight lanes
             if (m != 0) {  // a NaN stands only as the first allowed expert
                 const int f = __ffsll((unsigned long long)m) - 1;
                 const float lf = tile[t * LP + f];
