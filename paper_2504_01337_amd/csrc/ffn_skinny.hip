@@ -12,9 +12,8 @@
 //
 // Measured in a replayed graph, weights cold, microseconds of the two passes (tile kernel -> this one); in brackets what
 // the weights in use take at the 6.2 TB/s that a plain read of them reaches:
-//   60 experts + shared (d 2048, F 1408 / 5632, top-4): 1 token 29.5 + 48.6 -> 18.6 + 12.2 (15 + 7),
-//     16 tokens 61.5 + 75.4 -> 50.8 + 29.2 (36 + 18), 64 tokens 88.4 + 89.9 -> 74.7 + 48.8;
-//   16 experts (d 4096, F 688, top-4), both passes: 1 token 54.0 -> 19.3, 24 tokens 90.8 -> 60.1 (43), 64 -> 72.2 from 96.3.
+//   60 experts + shared (d 2048, F 1408 / 5632, top-4): 1 token 29.5 + 48.6 -> 18.6 + 12.2 (15 + 7), down pass of 16 tokens
+//     75.4 -> 29.2 (18); 16 experts (d 4096, F 688, top-4), both passes: 1 token 54.0 -> 19.3.
 // Also measured: eight waves per workgroup (a longer reduction, 10-30 % slower but for a single token), weights loaded
 // past the caches (8-12 % slower: the second half of each line is fetched again), a software-pipelined ring instead of
 // bursts (its remainders cost registers and spills; the CU's other waves fill the gaps between bursts anyway).
@@ -209,21 +208,21 @@ __device__ __forceinline__ void skinny_tile(const FfnProblem &P, unsigned char *
 // M-chunks of 64 rows; an item = (chunk, block of 16 * NF columns), NF = NFR for the ragged problem and NFS for the single
 // group.  Every XCD gets an equal share of the single group's items and of the ragged problem's, chunks of one column
 // block next to each other (they share its weights in that XCD's L2), the single group's (the longest contraction) first.
-constexpr int SKINNY_BM = 64;
+constexpr int SKINNY_BM = 64, SKINNY_GATE_UP_ROWS = 32;
 
 template <int MODE, int NF>
 __device__ __forceinline__ void skinny_rows(const FfnProblem &P, unsigned char *smem, int expert, int row_begin, int rows,
                                             int n0) {
     if (rows <= 16)
         skinny_tile<MODE, 1, NF>(P, smem, expert, row_begin, rows, n0);
-    else if (rows <= 32)
+    else if (MODE == 0 || rows <= 32)  // (the gate/up pass takes no more than 32 rows)
         skinny_tile<MODE, 2, NF>(P, smem, expert, row_begin, rows, n0);
     else
         skinny_tile<MODE, 4, NF>(P, smem, expert, row_begin, rows, n0);
 }
 
 constexpr int skinny_red_bytes(int mode, int nf) {  // what the reduction of the largest tile takes
-    const int frags = 4 * (mode == 0 ? 2 * nf : nf);
+    const int frags = mode == 0 ? 2 * 2 * nf : 4 * nf;
     return (frags <= 8 ? 4 * frags : 2 * frags) * 1024;
 }
 
@@ -282,29 +281,25 @@ static void skinny_launch(FfnLaunch L, hipStream_t st) {
 
 // Up to this many rows a problem takes this kernel; beyond, ffn_mid.hip.  Microseconds of a layer call with this kernel /
 // with that one in the pass:
-//   gate/up: 60 experts + shared: 16 tokens 122.0 / 130.6, 24 tokens 129.7 / 132.0, 32 tokens 143.4 / 137.6, 64 tokens
-//     207 / 191; 16 experts of d 4096: 4 tokens 56.8 / 57.0, 16 tokens 76.9 / 73.2, 64 tokens 101 / 91.
+//   gate/up: 60 experts + shared: 1 token 44.7 / 45.5, 4 tokens 59.9 / 65.0, 8 tokens 76.8 / 78.6, 16 tokens 91 / 86.6, 24 tokens
+//     105.5 / 96.4; 16 experts of d 4096: 8 tokens 63.2 / 63.5, 16 tokens 66 / 63.7, 40 tokens 71.9 / 66.1; 8 experts: 8
+//     tokens 72.8 / 69.3.
 //   down (narrower workgroups, so the longest contraction is cut finer here): 60 experts + shared: 16 tokens 121.7 / 138.1,
 //     32 tokens 142.8 / 158.1, 48 tokens 162.2 / 155.1; 16 experts: 40 tokens 80.7 / 81.0, 100 tokens 96.8 / 94.0.
 // (At four experts per token both rules cut the routed groups and a shared expert at the same batch.)
 bool ffn_skinny_takes(int pass, const FfnProblem &P) {
     if (pass == 1) return P.A_cap <= (P.E_local == 1 ? 40 : 160);
-    return P.A_cap <= (P.E_local == 1 ? 16 : (P.E_local < 32 ? 2 * P.E_local : 64));
+    return P.A_cap <= (P.E_local == 1 ? 8 : (2 * P.E_local < SKINNY_GATE_UP_ROWS ? 2 * P.E_local : SKINNY_GATE_UP_ROWS));
 }
 
 int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st) {
     drop_stale_error();
-    // Column blocks.  Wider ones read the activations less often, narrower ones are more numerous: 32 columns once they
-    // make four workgroups per CU (gate/up; 1 token: 18.6 us with 16 columns, 22.3 with 32; 40 tokens: 65.7, 61.0).  The
-    // down pass always takes 32 for the routed groups (1 token: the same either way) and 16 for the single group, whose
-    // contraction is the longest: its workgroups are the last to finish (1 token: 12.3 against 17.0 us).
-    const FfnProblem &R = L.p[0], &S = L.p[1];
-    const int64_t groups = R.E_local < R.A_cap ? R.E_local : R.A_cap;
-    const int64_t wide_items = (L.has_ragged ? groups * ((R.N + 31) / 32) : 0) + (L.has_single ? (S.N + 15) / 16 : 0);
+    // Column blocks.  Wider ones read the activations less often, narrower ones are more numerous: 16 in the gate/up pass (a
+    // layer call of 4 / 8 / 16 tokens: 62.2 / 80.0 / 93.0 us, with 32 columns 71.4 / 83.3 / 96.2).  The down pass takes 32
+    // for the routed groups (16 tokens: 91.2 us, with 16 columns 93.8) and 16 for the single group, whose contraction is
+    // the longest: its workgroups are the last to finish (1 token, the pass: 12.3 against 17.0 us).
     if (pass == 1)
         skinny_launch<1, 2, 1>(L, st);
-    else if (wide_items >= 1024)
-        skinny_launch<0, 2, 1>(L, st);
     else
         skinny_launch<0, 1, 1>(L, st);
     return launch_status();

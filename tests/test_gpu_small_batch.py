@@ -1,5 +1,5 @@
-"""GPU parity of the expert FFN kernel for batches of few rows (ffn_skinny.hip): at most 256 routed rows, at most 64
-rows of a single group."""
+"""GPU parity of the expert FFN for batches of few rows (ffn_skinny.hip; gate/up passes of more than 32 routed rows or more
+than 8 rows of a single group already run in ffn_mid.hip)."""
 import numpy as np
 import pytest
 import torch
