@@ -16,7 +16,7 @@
 //
 // Microseconds of a layer call, tile kernel -> this one (60 experts + shared, d 2048, F 1408 / 5632, top-4; 16 experts,
 // d 4096, F 688, top-4):
-//   60 experts: 64 tokens 212 -> 165, 131 tokens 252 -> 179, 256 tokens (down pass only) 210 -> 185;
+//   60 experts: 64 tokens 212 -> 165, 131 tokens 252 -> 164, 256 tokens (down pass only) 210 -> 185;
 //   16 experts: 64 tokens 107 -> 78, 180 tokens 115 -> 88, 256 tokens 126 -> 106, 500 tokens 143 -> 128;
 //   15 of the 60 experts, 131 tokens 79 -> 65.
 #include "ffn_common.h"
@@ -268,24 +268,28 @@ static void mid_launch(int tile_rows, const FfnLaunch &L, hipStream_t st) {
 }
 
 // Rows of the tiles this kernel should cut the launch into; 0: the tile kernel is the better one (or the only one).
-// Lower tiles leave more copies in flight, higher ones read the weights (from L2) less often; measured crossings in rows
-// per expert r: gate/up 32 -> 64 rows at r = 25 to 45, -> 128 at 50, tile kernel from 128 (16 experts, 500 tokens: 128 us
-// against 143; 700 tokens: 172 against 155); down 32 -> 64 at 24, -> 128 at 64.  A shared expert's rows count half in the
-// gate/up pass (it alone: 96 tokens 208 us with 64 rows against 217 with 32; 256 tokens 279 against 262 of the tile
-// kernel) and a quarter in the down pass, where the tile kernel is left with its few long tiles for longest (256 tokens:
-// 185 against 210 us, 350: 208 against 211, 500: 212 against 212).
+// Lower tiles leave more copies in flight, higher ones read the weights (from L2) less often.  Microseconds of a layer call
+// with 32 / 64 / 128 rows / the tile kernel in the pass, r rows per expert on average (16 experts, d 4096, F 688) or n rows
+// of a shared expert (60 experts, d 2048, F 1408 / 5632):
+//   gate/up: r = 25: 74.5 / 72.7 / 79.6 / 87, r = 55: 114 / 91 / 97 / 110, r = 75: 116 / 105 / 99 / 113, r = 125: - / 146 / 128 /
+//     143, r = 175: - / 178 / 172 / 155; n = 64: 137 / 147 / 150 / 156, n = 110: 176 / 162 / 175 / 166, n = 160: 191 / 165 / 172 /
+//     169, n = 200: 232 / 200 / 204 / 185;
+//   down: r = 25: 80 / 74 / 75.5 / 90, r = 40: 90 / 78 / 80 / 94, r = 55: 106 / 96 / 91 / 101, r = 75: 118 / 108 / 98 / 106, r = 100:
+//     - / 118 / 116 / 113; n = 90: 152 / 162 / 162 / 192, n = 131: 173 / 165 / 174 / 204, n = 300: 221 / 194 / 200 / 216,
+//     n = 511: - / - / 210 / 212.
 int ffn_mid_rows(int pass, const FfnLaunch &L) {
-    int r = 0;
+    int rows = 0;
     for (int q = 0; q < 2; ++q) {
         const FfnProblem &P = L.p[q];
         if (!(q == 0 ? L.has_ragged : L.has_single)) continue;
         if (P.gather && (P.A_cap > MID_ROW_TABLE || P.gather_rows > 65536)) return 0;
-        const int mean = q == 0 ? P.A_cap / P.E_local : P.A_cap / (pass == 0 ? 2 : 4);
-        r = mean > r ? mean : r;
+        static constexpr int up_to[2][2][3] = {{{20, 64, 150}, {64, 179, 179}}, {{20, 45, 90}, {100, 340, 511}}};
+        const int mean = q == 0 ? P.A_cap / P.E_local : P.A_cap, *most = up_to[pass][q];
+        if (mean > most[2]) return 0;
+        const int fit = mean <= most[0] ? 32 : (mean <= most[1] ? 64 : 128);
+        rows = fit > rows ? fit : rows;
     }
-    if (r >= 128) return 0;
-    if (pass == 0) return r <= 32 ? 32 : (r <= 50 ? 64 : 128);
-    return r <= 24 ? 32 : (r <= 64 ? 64 : 128);
+    return rows;
 }
 
 int launch_ffn_mid(int pass, int tile_rows, FfnLaunch L, hipStream_t st) {
