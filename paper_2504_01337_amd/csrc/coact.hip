@@ -88,10 +88,13 @@ __global__ __launch_bounds__(64) void collaborators_kernel(const int32_t *__rest
     const bool valid = j < E && j != i;
     const int32_t c = valid ? C[(size_t)i * E + j] : 0;
     int rank = 0;
+    for (int q0 = 0; q0 < E; q0 += 8) {
 #pragma unroll
-    for (int q = 0; q < C2R_MAX_E; ++q) {
-        const int32_t cq = __builtin_amdgcn_readlane(c, q);
-        rank += q < E && q != i && (cq > c || (cq == c && q < j));
+        for (int u = 0; u < 8; ++u) {
+            const int q = q0 + u;
+            const int32_t cq = __builtin_amdgcn_readlane(c, q);
+            rank += q < E && q != i && (cq > c || (cq == c && q < j));
+        }
     }
     const bool in_list = valid && rank < n;
     if (in_list && collab_idx) collab_idx[(size_t)i * n + rank] = j;
