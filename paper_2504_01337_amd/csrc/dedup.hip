@@ -15,8 +15,8 @@
 namespace c2r {
 
 constexpr int DB_THREADS = 256;
-constexpr int DB_SPAN = DB_THREADS * 4;         // tokens per block; with few tokens DB_SPAN_FEW
-constexpr int DB_SPAN_FEW = DB_THREADS, DB_FEW_TOKENS = 32768;
+constexpr int DB_SPAN = DB_THREADS * 4;  // tokens per block (with few tokens a quarter or a half of that)
+constexpr int DB_FEW_TOKENS = 32768;
 
 __device__ __forceinline__ int device_of(int e, int E, const int32_t *__restrict__ expert_device, int n_dev) {
     if (e < 0 || e >= E) return -1;
@@ -69,7 +69,7 @@ __device__ __forceinline__ uint64_t device_set(const int32_t *__restrict__ topk_
 template <int DB_ITEMS>
 __global__ __launch_bounds__(DB_THREADS) void dedup_count_kernel(
     const int32_t *__restrict__ topk_idx, int64_t T, int K, int E, const int32_t *__restrict__ expert_device,
-    int n_dev, int32_t *__restrict__ block_counts) {
+    int n_dev, uint16_t *__restrict__ block_counts) {
     __shared__ int32_t hist[C2R_MAX_E], dev_tab[C2R_MAX_E];
     if (threadIdx.x < C2R_MAX_E) hist[threadIdx.x] = 0;
     load_device_table(dev_tab, E, expert_device, n_dev);
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(DB_THREADS) void dedup_count_kernel(
         }
     }
     __syncthreads();
-    if ((int)threadIdx.x < n_dev) block_counts[(size_t)blockIdx.x * n_dev + threadIdx.x] = hist[threadIdx.x];
+    if ((int)threadIdx.x < n_dev) block_counts[(size_t)blockIdx.x * n_dev + threadIdx.x] = (uint16_t)hist[threadIdx.x];
 }
 
 // Every block derives the start of its (block, device) runs itself from the block
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(DB_THREADS) void dedup_count_kernel(
 template <int DB_ITEMS>
 __global__ __launch_bounds__(DB_THREADS) void dedup_rank_kernel(
     const int32_t *__restrict__ topk_idx, int64_t T, int K, int E, const int32_t *__restrict__ expert_device,
-    int n_dev, const int32_t *__restrict__ block_counts, int nblocks, int32_t *__restrict__ send_counts,
+    int n_dev, const uint16_t *__restrict__ block_counts, int nblocks, int32_t *__restrict__ send_counts,
     int32_t *__restrict__ send_offsets, int32_t *__restrict__ send_token, int32_t *__restrict__ send_row) {
     constexpr int DB_STEPS = DB_THREADS * DB_ITEMS / C2R_WAVE;  // wave steps per block
     __shared__ int32_t step_cnt[DB_STEPS][C2R_MAX_E];
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(256) void combine_copies_kernel(
 
 size_t dedup_workspace_bytes(int64_t T, int n_dev) {
     if (T <= 0 || n_dev <= 0) return 0;
-    const int64_t span = T <= DB_FEW_TOKENS ? DB_SPAN_FEW : DB_SPAN, nblocks = (T + span - 1) / span;
+    const int64_t nblocks = (T + DB_SPAN - 1) / DB_SPAN;
     return round_up((size_t)nblocks * n_dev * sizeof(int32_t), 256);
 }
 
@@ -304,27 +304,28 @@ extern "C" int c2r_dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int
     if (T * (int64_t)K >= (1ll << 31)) return C2R_ERR_UNSUPPORTED;
     if (!expert_device || !send_counts || !send_offsets) return C2R_ERR_INVALID_ARG;
     if (T > 0 && (!topk_idx || !send_token || !send_row)) return C2R_ERR_INVALID_ARG;
-    const int64_t nblocks = T > 0 ? (T + DB_SPAN - 1) / DB_SPAN : 1, few = (T + DB_SPAN_FEW - 1) / DB_SPAN_FEW;
-    const size_t need = round_up((size_t)nblocks * n_dev * sizeof(int32_t), 256);
+    const size_t need = dedup_workspace_bytes(T > 0 ? T : 1, n_dev);
     if (!ws || ws_bytes < need || !aligned(ws, 256)) return C2R_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    // Few tokens: one per thread, or two, so that more than a handful of CUs work (8192 tokens, 4 devices: 7.4 + 11.9 us with
+    // four per thread, 3.8 + 5.4 with one).  The block counts are 16 bits wide: those of half-size blocks take what the scratch has
+    // always had to hold at least, those of quarter-size blocks go where there is room.
+    const int64_t quarter = (T + DB_SPAN / 4 - 1) / (DB_SPAN / 4);
+    const int items = T > DB_FEW_TOKENS ? 4 : ((size_t)quarter * n_dev * sizeof(uint16_t) <= ws_bytes ? 1 : 2);
+    const int64_t span = DB_THREADS * items, nblocks = T > 0 ? (T + span - 1) / span : 1;
     if (nblocks >= (1ll << 31)) return C2R_ERR_UNSUPPORTED;
-    int32_t *block_counts = static_cast<int32_t *>(ws);
-    const dim3 block(DB_THREADS);
-    // Few tokens: one per thread, so that more than a handful of CUs work (8192 tokens, 4 devices: 7.4 + 11.9 us
-    // with four per thread, 4.0 + 5.7 so), where the
-    // caller's scratch has room for that many block counts.
-    if (T > 0 && T <= DB_FEW_TOKENS && ws_bytes >= (size_t)few * n_dev * sizeof(int32_t)) {
-        const dim3 grid((unsigned)few);
-        dedup_count_kernel<1><<<grid, block, 0, st>>>(topk_idx, T, K, E, expert_device, n_dev, block_counts);
-        dedup_rank_kernel<1><<<grid, block, 0, st>>>(topk_idx, T, K, E, expert_device, n_dev, block_counts, (int)few,
-                                                     send_counts, send_offsets, send_token, send_row);
-        return launch_status();
+    uint16_t *block_counts = static_cast<uint16_t *>(ws);
+    const dim3 grid((unsigned)nblocks), block(DB_THREADS);
+#define C2R_DEDUP_LAUNCH(ITEMS)                                                                                      \
+    dedup_count_kernel<ITEMS><<<grid, block, 0, st>>>(topk_idx, T, K, E, expert_device, n_dev, block_counts);        \
+    dedup_rank_kernel<ITEMS><<<grid, block, 0, st>>>(topk_idx, T, K, E, expert_device, n_dev, block_counts, (int)nblocks, \
+                                                     send_counts, send_offsets, send_token, send_row)
+    switch (items) {
+        case 1: C2R_DEDUP_LAUNCH(1); break;
+        case 2: C2R_DEDUP_LAUNCH(2); break;
+        default: C2R_DEDUP_LAUNCH(4);
     }
-    const dim3 grid((unsigned)nblocks);
-    dedup_count_kernel<4><<<grid, block, 0, st>>>(topk_idx, T, K, E, expert_device, n_dev, block_counts);
-    dedup_rank_kernel<4><<<grid, block, 0, st>>>(topk_idx, T, K, E, expert_device, n_dev, block_counts, (int)nblocks,
-                                                 send_counts, send_offsets, send_token, send_row);
+#undef C2R_DEDUP_LAUNCH
     return launch_status();
 }
 

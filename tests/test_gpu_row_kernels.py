@@ -1,4 +1,4 @@
-"""Combine by whole row pieces, and the dispatch index's two block sizes."""
+"""Combine by whole row pieces, and the dispatch index's three block sizes."""
 import numpy as np
 import pytest
 import torch
@@ -42,11 +42,11 @@ def test_combine_by_row_pieces(c2r, orc, dtype, T, K, d):
         assert np.abs(host(y) - ref).max() <= tol * (scale if dtype == "f32" else max(np.abs(ref).max(), 1.0))
 
 
-# 256 tokens per block up to 32768 tokens where the scratch has room, 1024 otherwise: scratch of exactly what the larger blocks need is
-# enough at every size
+# up to 32768 tokens 256 of them per block where the scratch has room, 512 otherwise, and 1024 beyond: scratch of exactly what the
+# call asks for and plenty of it
 @pytest.mark.parametrize("T,K,n_dev", [(1, 4, 5), (255, 4, 3), (256, 2, 64), (257, 4, 4), (5000, 4, 60), (32768, 4, 4), (32769, 4, 4),
                                        (2000, 9, 7)])
-def test_dispatch_index_at_both_block_sizes(c2r, orc, T, K, n_dev):
+def test_dispatch_index_at_every_block_size(c2r, orc, T, K, n_dev):
     rng = np.random.default_rng(T + n_dev)
     E = 64
     idx = np.argsort(rng.random((T, E)), axis=1)[:, :K].astype(np.int32)
@@ -54,7 +54,8 @@ def test_dispatch_index_at_both_block_sizes(c2r, orc, T, K, n_dev):
     devmap = rng.integers(-1, n_dev, size=E).astype(np.int32)
     rc, ro, rt, rr = orc.dedup_dispatch(idx, E, devmap, n_dev)
     least = ((T + 1023) // 1024 * n_dev * 4 + 255) // 256 * 256
-    for ws in (None, torch.empty(least, dtype=torch.uint8, device="cuda")):
+    assert c2r.workspace_bytes(c2r.STAGE_DEDUP_DISPATCH, T, 0, n_dev, K, 0, c2r.F32) == least
+    for ws in (None, torch.empty(least, dtype=torch.uint8, device="cuda"), torch.empty(4 * least, dtype=torch.uint8, device="cuda")):
         if ws is None:
             counts, offsets, tok, row = c2r.dedup_dispatch(dev(idx), E, dev(devmap), n_dev)
         else:
