@@ -1,6 +1,7 @@
 // Router logits (Eq. 1) and collaboration-constrained selection (Sec. 3.3, step 2).
 //
-// Two kernels.
+// Two kernels (small batches have forms of their own: route_partial_small_kernel, and route_finish_small_kernel, which
+// also builds the dispatch index).
 //  route_partial_kernel: an fp32 GEMM over one 256-long k-chunk in which every (token,
 //    expert) sum is built with one fused multiply-add per k in ascending k - exactly the
 //    ABI's declared order - either by one thread on the vector pipe (up to 8 experts) or by
