@@ -202,7 +202,11 @@ int c2r_permute_noalloc(const void *x, c2r_dtype dt, const int32_t *topk_idx, in
  *     y_perm[r] = W_down,e ( silu(W_gate,e x_perm[r]) * (W_up,e x_perm[r]) )
  * with silu(z) = z / (1 + exp(-z)), no biases, un-weighted by the gate.
  * bf16: products accumulate in fp32; the hidden activation is rounded to bf16
- * once, y_perm once.  fp32: fp32 throughout.
+ * once, y_perm once.  fp32: fp32 throughout.  A row's result depends on that row and its expert's
+ * weights alone, bit for bit, not on A_cap, the other rows or the number of rows: which kernel a
+ * call takes follows from its sizes, and all that serve one shape add in the same order (bf16: one
+ * order where d is a multiple of 64 and h is padded to 64 columns or F is a multiple of 64, as in
+ * every call but the split ones with another F, and one order for all other shapes).
  * offsets : int32[E_local+1] in DEVICE memory (as written by c2r_permute)
  * A_cap   : rows allocated in x_perm / y_perm (>= offsets[E_local], e.g. T*K)
  * w_gate, w_up : [E_local, F, d] of dt;  w_down : [E_local, d, F] of dt

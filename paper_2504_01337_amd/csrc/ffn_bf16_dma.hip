@@ -790,7 +790,7 @@ FfnProblem ffn_bf16_dma_problem(int pass, const uint16_t *a, int lda, const int3
     return P;
 }
 
-bool ffn_skinny_takes(int pass, const FfnProblem &P);
+bool ffn_skinny_takes(int pass, const FfnLaunch &L);
 int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st);
 int ffn_mid_rows(int pass, const FfnLaunch &L);
 int launch_ffn_mid(int pass, int tile_rows, FfnLaunch L, hipStream_t st);
@@ -815,13 +815,6 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     drop_stale_error();
     constexpr int BM = 256, WM = 2, WN = 4;
     if (second && second->E_local != 1) return C2R_ERR_INVALID_ARG;
-    // Few rows: the kernel of ffn_skinny.hip.  Each problem is judged by itself, whatever else the call computes, so that
-    // a row's bits do not depend on the entry point; where the two disagree they are launched one after the other.
-    const bool few = ffn_skinny_takes(pass, first);
-    if (second && ffn_skinny_takes(pass, *second) != few) {
-        const int rc = launch_ffn_bf16_dma(pass, first, nullptr, st);
-        return rc != C2R_OK ? rc : launch_ffn_bf16_dma(pass, *second, nullptr, st);
-    }
     // the kernel expects the ragged problem (more than one group) in p[0], a single group in p[1]
     FfnLaunch L;
     const FfnProblem *single = second ? second : (first.E_local == 1 ? &first : nullptr);
@@ -831,8 +824,9 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     L.p[1] = single ? *single : *ragged;
     L.has_ragged = ragged ? 1 : 0;
     L.has_single = single ? 1 : 0;
-    if (few) return launch_ffn_skinny(pass, L, st);
-    // More rows, but not enough to fill the chip with 256 x 256 tiles: the kernel of ffn_mid.hip (same bits as this one).
+    // Few rows: the kernel of ffn_skinny.hip.  More, but not enough to fill the chip with 256 x 256 tiles: that of ffn_mid.hip.
+    // Every output is the same chain of the same matrix instructions in all three, so a row's bits do not depend on the choice.
+    if (ffn_skinny_takes(pass, L)) return launch_ffn_skinny(pass, L, st);
     if (const int tile_rows = ffn_mid_rows(pass, L)) return launch_ffn_mid(pass, tile_rows, L, st);
     // one workgroup per CU (fewer if the bound on the tiles is smaller), whatever the number of tiles
     int64_t tiles = 0;

@@ -76,4 +76,12 @@ __device__ __forceinline__ void lds_barrier() {
 #endif
 }
 
+// What this wave wrote to LDS is there, then the workgroup's barrier; loads in flight into registers stay in flight (a
+// __syncthreads() would wait for them).  The clobber keeps the compiler from moving or forwarding LDS accesses across.
+__device__ __forceinline__ void lds_hand_over() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
+}
+
 }  // namespace c2r

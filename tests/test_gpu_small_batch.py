@@ -1,5 +1,8 @@
-"""GPU parity of the expert FFN for batches of few rows (ffn_skinny.hip; gate/up passes of more than 32 routed rows or more
-than 8 rows of a single group already run in ffn_mid.hip)."""
+"""GPU parity of the expert FFN for batches of few rows (ffn_skinny.hip; passes of more rows than its limits already run in
+ffn_mid.hip)."""
+import os
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -21,8 +24,8 @@ def _weights(rng, E, d, F):
     return [wl.round_bf16((rng.standard_normal(s) * 0.05).astype(np.float32)) for s in ((E, F, d), (E, F, d), (E, d, F))]
 
 
-# fragment edges (15, 16, 17, 32, 33, 48, 49 rows), chunk edges (63, 64, 65 rows), empty groups, 64 groups, more rows
-# allotted than used; contraction lengths of 1, 2, 3, 5, 8, 11 and 22 64-wide units (waves without any, remainders of a
+# batches on both sides of the limits: fragment edges (15, 16, 17, 32, 33, 48, 49 rows), 63, 64 and 65 rows, empty groups, 64
+# groups, more rows allotted than used; contraction lengths of 1, 2, 3, 5, 8, 11 and 22 64-wide units (waves without any, remainders of a
 # burst), widths that are no multiple of 64 (k tail and padding columns) and of 16 (column tail)
 @pytest.mark.parametrize("d,F,sizes,spare", [
     (64, 64, [1], 0), (64, 64, [1, 0, 3], 0), (128, 192, [15, 16, 17, 0, 32, 33, 48, 49], 0),
@@ -75,3 +78,54 @@ def test_few_rows_entry_points_agree_bit_for_bit(c2r, E, K, T, d, F, Fs):
     assert torch.equal(h[0], h[1]) and torch.equal(h[0], h[2]) and torch.equal(hs[0], hs[1])
     assert torch.equal(y[0], y[1]) and torch.equal(y[0], y[2]) and torch.equal(ys[0], ys[1])
     assert h[0].any() and y[0].any() and ys[0].any()
+
+
+def _limit(name):
+    """A row limit of the kernel, from its source: cases that a changed limit moves to another kernel fail loudly."""
+    path = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2504_01337_amd", "csrc", "ffn_skinny.hip")
+    with open(path) as f:
+        return int(re.search(r"\b%s = (\d+)" % name, f.read()).group(1))
+
+
+def _both_allotments(c2r, d, F, sizes, x, w, poison=0.0):
+    """The rows of sizes allotted as they are (few rows) and in a large buffer (the tile kernel): y of each."""
+    E, n = len(sizes), sum(sizes)
+    offsets = dev(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
+    got = []
+    for cap in (n, 600 * E + n):
+        xa = torch.full((cap, d), poison, dtype=torch.bfloat16, device="cuda")
+        xa[:n] = x
+        y = torch.full((cap, d), 123.0, dtype=torch.bfloat16, device="cuda")
+        ws = torch.full((c2r.workspace_bytes(c2r.STAGE_EXPERT_FFN, cap, d, E, 1, F, c2r.BF16),), 255, dtype=torch.uint8,
+                        device="cuda")
+        c2r.expert_ffn(xa, offsets, *w, ws=ws, out=y)
+        torch.cuda.synchronize()
+        assert torch.all(y[n:] == 123.0)
+        got.append(y[:n])
+    return got
+
+
+# The sums are the tile kernel's, so a row has the same bits whatever is allotted around it.  Both passes few rows: one and
+# two 16-row fragments (15, 16, 17, 31, 32 rows of a group), a single group of 1 to 8.  The down pass alone: 33 to 64 rows, several
+# 64-row chunks (65, 130), a single group up to its limit, 40 and 64 groups; with 16 groups the four-waves-per-SIMD form meets
+# groups of more than one fragment.  Contractions of 1 to 88 units, ends inside a unit, bursts that come out even and not.
+@pytest.mark.parametrize("both,d,F,sizes", [
+    (True, 64, 64, [1]), (True, 320, 88, [8]), (True, 704, 72, [1, 0, 3]), (True, 2048, 1408, [17, 15] + [0] * 14),
+    (True, 512, 688, [0, 16, 1, 7] + [0] * 16), (True, 4032, 136, [1, 31] + [0] * 14), (True, 192, 5632, [32] + [0] * 15),
+    (False, 128, 5632, [9]), (False, 192, 88, [16]), (False, 64, 1400, [17]), (False, 64, 192, [32]),
+    (False, 128, 192, [15, 16, 17, 0, 32, 33]), (False, 64, 1400, [63, 64, 1]), (False, 192, 688, [65, 0, 2]),
+    (False, 64, 320, [130, 9]), (False, 320, 704, [3] * 40), (False, 128, 136, [1] * 64), (False, 64, 1408, [65, 33, 20] + [0] * 13)])
+def test_few_rows_have_the_bits_of_any_allotment(c2r, orc, both, d, F, sizes):
+    rng = np.random.default_rng(d * 5 + F)
+    E, n = len(sizes), sum(sizes)
+    if E == 1:
+        assert n <= _limit("SKINNY_UP_SINGLE" if both else "SKINNY_DOWN_SINGLE")
+    else:
+        assert n <= (min(_limit("SKINNY_UP_ROWS"), _limit("SKINNY_UP_PER_GROUP") * E) if both else _limit("SKINNY_DOWN_ROWS"))
+        assert n <= E or E * -(-d // 64) < 1024
+    x = wl.round_bf16(rng.standard_normal((n, d)).astype(np.float32))
+    w = _weights(rng, E, d, F)
+    few, many = _both_allotments(c2r, d, F, sizes, dev(x, "bf16"), [dev(a, "bf16") for a in w], float("nan"))
+    assert torch.equal(few, many)
+    ref = orc.expert_ffn_rows(x, np.repeat(np.arange(E), sizes).astype(np.int32), *w)
+    assert max_rel_err(host(few), ref) <= 1e-2
