@@ -1374,6 +1374,7 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
     if (!aligned(x, 16) || !aligned(Wg, 4)) return C2R_ERR_INVALID_ARG;
     const RouteLayout L = route_layout(T, d, E);
     if (!ws || ws_bytes < L.part_bytes + L.wpad_bytes || !aligned(ws, 256)) return C2R_ERR_WORKSPACE;
+    if (Tc == 0) collab_idx = nullptr;  // (K is 1: no list is asked.  The kernels request entries ahead and need one to be there.)
     hipStream_t st = static_cast<hipStream_t>(stream);
     float *part = static_cast<float *>(ws);
     const float *W = Wg;

@@ -68,3 +68,33 @@ def test_layer_call_of_a_small_batch_routes_like_the_stages(c2r, T, E, K, El, dt
     assert torch.equal(layer.counts, counts) and torch.equal(layer.offsets, offsets) and torch.equal(layer.inv_perm, inv)
     n = int(offsets[-1])
     assert torch.equal(layer.perm[:n], perm[:n]) and bool((layer.perm[n:] == -1).all())
+
+
+# K = 1 takes lists of no entries (Tc >= K - 1); the array then holds nothing that may be read, also where it is not NULL.  (The pointer
+# lies inside an allocation here.)  Batches of the two routers, and the one-launch selection and index of the layer call.
+@pytest.mark.parametrize("T,E,d,dtype", [(1, 60, 256, "bf16"), (70, 8, 64, "f32"), (12289, 5, 264, "f32")])
+def test_lists_without_entries(c2r, orc, T, E, d, dtype):
+    rng = np.random.default_rng(T + E)
+    x = rng.standard_normal((T, d)).astype(np.float32)
+    x = wl.round_bf16(x) if dtype == "bf16" else x
+    Wg = rng.standard_normal((d, E)).astype(np.float32)
+    xd, Wd, lists = dev(x, dtype), dev(Wg), torch.full((64,), 3, dtype=torch.int32, device="cuda")
+    idx, gates = torch.empty((T, 1), dtype=torch.int32, device="cuda"), torch.empty((T, 1), dtype=torch.float32, device="cuda")
+    dt = c2r.BF16 if dtype == "bf16" else c2r.F32
+    ws = torch.empty(max(256, c2r.workspace_bytes(c2r.STAGE_ROUTE, T, d, E, 1, 0, dt)), dtype=torch.uint8, device="cuda")
+    empty = lists.data_ptr() + 128
+    assert c2r.lib().c2r_route(xd.data_ptr(), dt, Wd.data_ptr(), None, T, d, E, 1, empty, 0, idx.data_ptr(), gates.data_ptr(), None,
+                               ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == c2r.OK
+    torch.cuda.synchronize()
+    ri, rg = orc.route(orc.logits_canon_f32(x, Wg, None), 1)
+    assert np.array_equal(host(idx), ri) and np.array_equal(host(gates), rg.astype(np.float32))
+    w = lambda *s: dev((rng.standard_normal(s) * 0.1).astype(np.float32), dtype)
+    layer = c2r.C2RLayer(T, d, E, 1, 64, xd.dtype, Wd, None, None, w(E, 64, d), w(E, 64, d), w(E, d, 64))
+    y = layer.forward(xd).clone()
+    fields = list(layer._LAYER.unpack(layer._args()))
+    assert fields[6] == 0 and fields[12] == 0                          # Tc, collab_idx
+    fields[12] = empty
+    layer.idx.fill_(-7)
+    assert c2r.lib().c2r_layer_forward(layer._LAYER.pack(*fields), xd.data_ptr(), torch.cuda.current_stream().cuda_stream) == c2r.OK
+    torch.cuda.synchronize()
+    assert np.array_equal(host(layer.idx), ri) and torch.equal(layer.y, y)
