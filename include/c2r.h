@@ -311,11 +311,12 @@ int c2r_combine(const void *y_perm, c2r_dtype dt, const float *gates, const int3
  * Sizes and device pointers are those of the entry points of the same names; every field is 64 bits wide.  The
  * pointers that are set choose the form of the expert FFN:
  *   x_perm          : rows are scattered by c2r_permute and both passes run as c2r_expert_ffn (h in ws_ffn)
- *   h               : the gate/up pass gathers (c2r_expert_ffn_gate_up_gather / _down), and with h_shared, too, the
- *                     shared expert rides in the same launches (c2r_expert_ffn_*_with_shared)
+ *   h               : the gate/up pass gathers (c2r_expert_ffn_gate_up_gather / _down)
  *   neither         : c2r_expert_ffn_gather (h in ws_ffn)
- * The shared expert (F_shared > 0) when it does not ride: off_shared = int32 {0, T} on the device and either
- * h_shared (two passes) or ws_shared (c2r_expert_ffn).  Both h and x_perm set: C2R_ERR_INVALID_ARG.
+ * Both h and x_perm set: C2R_ERR_INVALID_ARG.
+ * The shared expert (F_shared > 0; 0: there is none) rides in the routed launches (c2r_expert_ffn_*_with_shared) if
+ * fuse_shared is not 0 and both h and h_shared are set.  Otherwise it runs by itself, ahead of the routed groups, and needs
+ * off_shared = int32 {0, T} on the device and either h_shared (two passes) or ws_shared (c2r_expert_ffn).
  */
 typedef struct {
     int64_t T, d, E, K, F, dtype, Tc, E_local, F_shared, fuse_shared;

@@ -242,7 +242,7 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
     const c2r_dtype dt = static_cast<c2r_dtype>(L.dtype);
     const int d = (int)L.d, E = (int)L.E, K = (int)L.K, F = (int)L.F, El = (int)L.E_local, Fs = (int)L.F_shared;
     const int64_t T = L.T, A = T * K;
-    const bool shared = Fs > 0, rides = shared && L.fuse_shared != 0;
+    const bool shared = Fs > 0, rides = shared && L.fuse_shared != 0 && L.h && L.h_shared;  // (else it runs by itself)
     if (shared && !rides) {
         int rc;
         if (L.h_shared)

@@ -117,6 +117,35 @@ def test_argument_errors_before_launch():
     assert L.c2r_combine(null, 1, null, null, 0, 64, 2, null, null, null) == c2r.OK
 
 
+def _layer(**kw):
+    """A c2r_layer of 16 tokens with a shared expert, every pointer set but those of the other forms."""
+    from paper_2504_01337_amd.c2r import C2RLayer
+    names = ["T", "d", "E", "K", "F", "dtype", "Tc", "E_local", "F_shared", "fuse_shared", "Wg", "bias", "collab_idx", "local_slot",
+             "w_gate", "w_up", "w_down", "ws_gate", "ws_up", "ws_down", "topk_idx", "gates", "counts", "offsets", "perm", "inv_perm",
+             "x_perm", "h", "y_perm", "off_shared", "h_shared", "y_shared", "ws_route", "ws_permute", "ws_ffn", "ws_shared",
+             "ws_route_bytes", "ws_permute_bytes", "ws_ffn_bytes", "ws_shared_bytes", "y"]
+    v = dict.fromkeys(names, 0x1000)
+    v.update(T=16, d=64, E=8, K=2, F=64, dtype=1, Tc=0, E_local=8, F_shared=64, fuse_shared=1, collab_idx=0, local_slot=0, x_perm=0, h=0,
+             ws_route_bytes=1 << 20, ws_permute_bytes=1 << 20, ws_ffn_bytes=1 << 20, ws_shared_bytes=1 << 20)
+    assert set(kw) <= set(names)
+    v.update(kw)
+    return C2RLayer._LAYER.pack(*(v[n] for n in names))
+
+
+def test_layer_call_errors_before_launch():
+    c2r = _lib()
+    p, null = ctypes.c_void_p(0x1000), ctypes.c_void_p(0)
+    forward = lambda **kw: c2r.lib().c2r_layer_forward(_layer(**kw), p, null)
+    assert c2r.lib().c2r_layer_forward(None, p, null) == c2r.ERR_INVALID_ARG
+    assert forward(h=0x1000, x_perm=0x1000) == c2r.ERR_INVALID_ARG
+    # without h the shared expert cannot ride: it runs by itself, first, and these calls lack what it then needs
+    for form in ({}, {"x_perm": 0x1000}):
+        assert forward(off_shared=0, **form) == c2r.ERR_INVALID_ARG
+        assert forward(h_shared=0, ws_shared=0, **form) == c2r.ERR_WORKSPACE
+    assert forward(h=0x1000, h_shared=0, off_shared=0) == c2r.ERR_INVALID_ARG
+    assert forward(h=0x1000, fuse_shared=0, off_shared=0) == c2r.ERR_INVALID_ARG
+
+
 def test_workload_rounding_and_shapes():
     import numpy as np
     from paper_2504_01337_amd import workloads as wl

@@ -54,3 +54,26 @@ def test_one_call_rejects_what_the_stages_reject():
     layer.w = (z(4, 8, 16), z(4, 8, 16), z(4, 8, 16))
     with pytest.raises(AssertionError):
         layer.forward(z(4, 16))
+
+
+# fuse_shared asks for the shared expert to ride in the routed launches; in a form that has none to ride in (rows scattered, or h in the
+# workspace) it still has to be computed
+@pytest.mark.parametrize("dtype,F,Fs,kw", [("bf16", 64, 128, {"fuse_gather": False}), ("bf16", 88, 72, {}), ("bf16", 88, 128, {}),
+                                           ("f32", 32, 64, {})])
+def test_a_shared_expert_that_cannot_ride_is_computed(dtype, F, Fs, kw):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(F + Fs)
+    T, d, E, K = 33, 64, 8, 2
+    w = lambda *sh: dev((rng.standard_normal(sh) * 0.05).astype(np.float32), dtype)
+    layer = c2r.C2RLayer(T, d, E, K, F, torch.bfloat16 if dtype == "bf16" else torch.float32, w(d, E).float(), None, None,
+                         w(E, F, d), w(E, F, d), w(E, d, F), shared=(w(1, Fs, d), w(1, Fs, d), w(1, d, Fs)), **kw)
+    x = w(T, d)
+    y = layer.forward(x, trace={}).clone()             # stage by stage
+    fields = list(layer._LAYER.unpack(layer._args()))
+    assert fields[9] == 0 and fields[27] == 0          # fuse_shared, h
+    fields[9] = 1
+    layer.y_shared.fill_(5.0)
+    layer.y.zero_()
+    assert c2r.lib().c2r_layer_forward(layer._LAYER.pack(*fields), x.data_ptr(), torch.cuda.current_stream().cuda_stream) == c2r.OK
+    torch.cuda.synchronize()
+    assert torch.equal(layer.y, y)
