@@ -280,7 +280,8 @@ int c2r_expert_ffn_gather(const void *x, c2r_dtype dt, const int32_t *perm, int6
  *   down    : y_perm[r, j]   = W_down,e[j,:] . h[r];   y_shared[t, j] = Ws_down[j,:] . h_shared[t]
  * x : [T, d];  perm, offsets : as written by c2r_permute;  h : [A_cap, F];  y_perm : [A_cap, d]
  * ws_gate, ws_up : [F_shared, d];  ws_down : [d, F_shared];  h_shared : [T, F_shared];
- * y_shared : [T, d].  A_cap == 0 runs the shared expert alone.
+ * y_shared : [T, d].  A_cap == 0 runs the shared expert alone; with E_local == 1 (two single groups)
+ * a pass takes two launches.
  * Limits: bf16; d, F and F_shared multiples of 64; T*d*2 < 2^32; else C2R_ERR_UNSUPPORTED.
  */
 int c2r_expert_ffn_gate_up_with_shared(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K,

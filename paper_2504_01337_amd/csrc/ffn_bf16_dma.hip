@@ -809,17 +809,20 @@ static int single_tile_rows(const FfnProblem *ragged, const FfnProblem *single) 
     return tiles <= 40 ? BM / 4 : (tiles < 64 ? BM / 2 : BM);
 }
 
-// Launches one pass over one problem (second == nullptr) or over two in ONE grid: the second
-// must be a single group (E_local == 1).
+// Launches one pass over one problem (second == nullptr) or over two: the second must be a single
+// group (E_local == 1).  Two go into ONE grid unless the first is a single group as well.
 int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, hipStream_t st) {
     drop_stale_error();
     constexpr int BM = 256, WM = 2, WN = 4;
     if (second && second->E_local != 1) return C2R_ERR_INVALID_ARG;
+    if (second && first.E_local == 1) {  // (a launch holds one single group)
+        const int rc = launch_ffn_bf16_dma(pass, first, nullptr, st);
+        return rc != C2R_OK ? rc : launch_ffn_bf16_dma(pass, *second, nullptr, st);
+    }
     // the kernel expects the ragged problem (more than one group) in p[0], a single group in p[1]
     FfnLaunch L;
     const FfnProblem *single = second ? second : (first.E_local == 1 ? &first : nullptr);
     const FfnProblem *ragged = first.E_local != 1 ? &first : nullptr;
-    if (second && !ragged) return C2R_ERR_INVALID_ARG;  // (two single groups: launch them one by one)
     L.p[0] = ragged ? *ragged : *single;
     L.p[1] = single ? *single : *ragged;
     L.has_ragged = ragged ? 1 : 0;

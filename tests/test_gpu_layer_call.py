@@ -77,3 +77,25 @@ def test_a_shared_expert_that_cannot_ride_is_computed(dtype, F, Fs, kw):
     assert c2r.lib().c2r_layer_forward(layer._LAYER.pack(*fields), x.data_ptr(), torch.cuda.current_stream().cuda_stream) == c2r.OK
     torch.cuda.synchronize()
     assert torch.equal(layer.y, y)
+
+
+# a device with one local expert and the shared one: two single groups, at sizes of every FFN kernel (few rows, both sides of their limits,
+# between, tiles); the same bits as the shared expert on its own
+@pytest.mark.parametrize("T", [1, 4, 5, 9, 33, 90, 700])
+def test_one_local_expert_beside_a_shared_one(T):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(T)
+    d, E, K, F, Fs = 128, 6, 2, 64, 192
+    w = lambda *sh: dev((rng.standard_normal(sh) * 0.05).astype(np.float32), "bf16")
+    ls = dev(np.array([-1, -1, 0, -1, -1, -1], dtype=np.int32))
+    args = (T, d, E, K, F, torch.bfloat16, w(d, E).float(), None, None, w(1, F, d), w(1, F, d), w(1, d, F))
+    shared = (w(1, Fs, d), w(1, Fs, d), w(1, d, Fs))
+    x = w(T, d)
+    got = []
+    for fuse in (True, False):
+        layer = c2r.C2RLayer(*args, local_slot=ls, E_local=1, shared=shared, fuse_shared=fuse)
+        assert layer.fuse_shared == fuse
+        got.append(layer.forward(x).clone())
+        assert torch.equal(layer.forward(x, trace={}), got[-1])
+    torch.cuda.synchronize()
+    assert got[0].any() and torch.equal(got[0], got[1])
