@@ -516,7 +516,7 @@ class C2RLayer:
         STAGES; each pair is recorded on the stream its stage runs on (timing events, made by
         the caller).  only: run just that stage on the buffers a previous full call left
         (for timing a stage on its own)."""
-        if trace is None and only is None and not self.overlap:
+        if trace is None and only is None and not self.overlap and self.T:  # (an empty x_perm has no address to tell the form by)
             # one call for the whole layer: through the binding stage by stage the host needs about 85 us per
             # forward, more than the kernels of a decoding step take
             assert x.shape == (self.T, self.d) and x.dtype == self.y.dtype

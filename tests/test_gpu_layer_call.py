@@ -99,3 +99,19 @@ def test_one_local_expert_beside_a_shared_one(T):
         assert torch.equal(layer.forward(x, trace={}), got[-1])
     torch.cuda.synchronize()
     assert got[0].any() and torch.equal(got[0], got[1])
+
+
+# a batch without tokens: an empty y and zero counts where the stages take one; gather-fused forms refuse it, as their calls do
+@pytest.mark.parametrize("dtype,kw,shared", [("f32", {}, False), ("f32", {}, True), ("bf16", {"fuse_gather": False}, True)])
+def test_no_tokens(dtype, kw, shared):
+    from paper_2504_01337_amd import c2r
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    d, E, F = 64, 4, 64
+    w = lambda *sh: torch.ones(sh, dtype=tdt, device="cuda")
+    layer = c2r.C2RLayer(0, d, E, 2, F, tdt, w(d, E).float(), None, None, w(E, F, d), w(E, F, d), w(E, d, F),
+                         shared=(w(1, F, d), w(1, F, d), w(1, d, F)) if shared else None, **kw)
+    layer.counts.fill_(-7)
+    layer.offsets.fill_(-7)
+    y = layer.forward(w(0, d))
+    torch.cuda.synchronize()
+    assert y.shape == (0, d) and not layer.counts.any() and not layer.offsets.any()
