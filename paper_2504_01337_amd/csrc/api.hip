@@ -239,6 +239,11 @@ extern "C" int c2r_expert_ffn_down_with_shared(const void *h, c2r_dtype dt, cons
 extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *stream) {
     if (!layer || (layer->h && layer->x_perm)) return C2R_ERR_INVALID_ARG;
     const c2r_layer &L = *layer;
+    if (L.dtype != C2R_F32 && L.dtype != C2R_BF16) return C2R_ERR_INVALID_ARG;
+    for (int64_t v : {L.d, L.E, L.K, L.F, L.Tc, L.E_local, L.F_shared})  // (the stages take them as int)
+        if (v != (int64_t)(int)v) return C2R_ERR_UNSUPPORTED;
+    for (int64_t v : {L.ws_route_bytes, L.ws_permute_bytes, L.ws_ffn_bytes, L.ws_shared_bytes})
+        if (v < 0) return C2R_ERR_WORKSPACE;
     const c2r_dtype dt = static_cast<c2r_dtype>(L.dtype);
     const int d = (int)L.d, E = (int)L.E, K = (int)L.K, F = (int)L.F, El = (int)L.E_local, Fs = (int)L.F_shared;
     const int64_t T = L.T, A = T * K;

@@ -138,6 +138,12 @@ def test_layer_call_errors_before_launch():
     forward = lambda **kw: c2r.lib().c2r_layer_forward(_layer(**kw), p, null)
     assert c2r.lib().c2r_layer_forward(None, p, null) == c2r.ERR_INVALID_ARG
     assert forward(h=0x1000, x_perm=0x1000) == c2r.ERR_INVALID_ARG
+    # fields of 64 bits whose lower 32 would pass
+    for name in ("d", "E", "K", "F", "Tc", "E_local", "F_shared"):
+        assert forward(off_shared=0, **{name: (1 << 32) + 64 if name in ("d", "F", "F_shared") else (1 << 32) + 4}) == c2r.ERR_UNSUPPORTED
+    assert forward(dtype=1 << 32) == forward(dtype=2) == c2r.ERR_INVALID_ARG
+    for name in ("ws_route_bytes", "ws_permute_bytes", "ws_ffn_bytes", "ws_shared_bytes"):
+        assert forward(off_shared=0, **{name: -1}) == c2r.ERR_WORKSPACE
     # without h the shared expert cannot ride: it runs by itself, first, and these calls lack what it then needs
     for form in ({}, {"x_perm": 0x1000}):
         assert forward(off_shared=0, **form) == c2r.ERR_INVALID_ARG
