@@ -801,10 +801,14 @@ int launch_ffn_mid(int pass, int tile_rows, FfnLaunch L, hipStream_t st);
 // call with 256 / 128 / 64 rows in the down pass (60 experts + shared, d 2048, F 1408 / 5632): 600 tokens 261 / 248 / 217,
 // 1000 tokens 290 / 270 / 255, 1300 tokens 316 / 301 / 311, 1600 tokens 340 / 320 / 347, 2000 tokens 379 / 374 / 399, 2500
 // tokens 416 / 431 / 456 (every part reads the weights again).  In the gate/up pass, whose chains are alike, it only costs:
-// 1000 tokens 290 -> 304 with 128 rows.
+// 1000 tokens 290 -> 304 with 128 rows.  A group that runs alone gains from the cut in either pass if its own contraction is
+// long: with 256 rows / by this rule, gate/up of d 4096, F 1344: 256 rows 50.7 / 42.1, 600 rows 52.0 / 45.6, 1000 rows 53.8 / 53.9;
+// d 2048, F 1408: 256 rows 29.0 / 26.2; d 1024, F 512: 256 rows 18.0 / 15.3, 600 rows 18.3 / 17.8, 1000 rows 18.9 / 20.1; down, d 2048: F
+// 5632: 600 rows 64.3 / 54.5; F 1408: 600 rows 22.4 / 21.4.  Below 1024 it does not: down of d 1024, F 512: 600 rows 12.8 / 13.9, 1000 rows
+// 13.0 / 16.5.
 static int single_tile_rows(const FfnProblem *ragged, const FfnProblem *single) {
     constexpr int BM = 256;
-    if (!single || (ragged && single->Kdim < 2 * ragged->Kdim)) return BM;
+    if (!single || single->Kdim < (ragged ? 2 * ragged->Kdim : 1024)) return BM;
     const int64_t tiles = ((int64_t)single->A_cap + BM - 1) / BM * single->ntn;
     return tiles <= 40 ? BM / 4 : (tiles < 64 ? BM / 2 : BM);
 }
