@@ -274,7 +274,9 @@ static void skinny_launch(FfnLaunch L, hipStream_t st) {
 //   down: 60 experts + shared, 1 token 12.9 / 35.0, 8 tokens 23.9 / 33.7, 16 tokens 27.3 / 37.2, 24 tokens 33.8 / 40.3 (a layer call
 //     of 32 tokens 117 / 125, 40 tokens 125.7 / 124.7); 8 experts, 4 tokens 15.8 / 18.2; 15 of 60 experts, 16 tokens 9.7 / 12.2.
 //     Routed groups alone whose tiles there make two rounds of its 512 workgroups go over at a row per group: 16 experts
-//     (N 4096), 4 tokens 19.0 / 20.4, 8 tokens 22.5 / 21.1, 24 tokens 24.5 / 22.0.
+//     (N 4096), 4 tokens 19.0 / 20.4, 8 tokens 22.5 / 21.1, 24 tokens 24.5 / 22.0; groups of more than 16 rows, which need the form
+//     of three waves per SIMD, go over unless its tiles are few: 8 groups, N 4096, 160 rows 15.1 / 11.2, 4 groups, 100 rows
+//     9.5 / 9.0, but 2 groups, N 2048, 100 rows 10.6 / 16.7, N 4096 8.1 / 11.0 (weights warm).
 // (The rows per group are those allotted; a device that holds a quarter of the experts has a quarter of them in use.)
 constexpr int SKINNY_UP_ROWS = 32, SKINNY_UP_PER_GROUP = 2, SKINNY_UP_SINGLE = 8;
 constexpr int SKINNY_DOWN_ROWS = 160, SKINNY_DOWN_BESIDE = 128, SKINNY_DOWN_SINGLE = 32;
@@ -286,7 +288,8 @@ bool ffn_skinny_takes(int pass, const FfnLaunch &L) {
     if (pass == 0) return R.A_cap <= SKINNY_UP_ROWS && R.A_cap <= SKINNY_UP_PER_GROUP * R.E_local;
     if (L.has_single) return R.A_cap <= SKINNY_DOWN_BESIDE;
     const int64_t mid_tiles = (int64_t)(R.E_local < R.A_cap ? R.E_local : R.A_cap) * ((R.N + 63) / 64);
-    return R.A_cap <= SKINNY_DOWN_ROWS && (R.A_cap <= R.E_local || mid_tiles < 1024);
+    return R.A_cap <= SKINNY_DOWN_ROWS && (R.A_cap <= R.E_local || mid_tiles < 1024) &&
+           (R.A_cap <= 16 * R.E_local || mid_tiles <= 128);
 }
 
 int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st) {
