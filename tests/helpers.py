@@ -1,5 +1,8 @@
 """Shared plumbing of the GPU parity tests: host<->device copies and the
 oracle-side pipeline.  No arithmetic of the method lives here."""
+import os
+import re
+
 import numpy as np
 import torch
 
@@ -84,3 +87,30 @@ class OracleLayer:
         self.local_slot = wl.local_slot(w)
         self.counts, self.offsets, self.perm, self.inv_perm = orc.permute(
             self.idx, w.E, self.local_slot, w.n_local)
+
+
+def _csrc(name):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    with open(os.path.join(root, "paper_2504_01337_amd", "csrc", name)) as f:
+        return f.read()
+
+
+def ffn_kernel(which, E, A_cap, N):
+    """Which kernel a bf16 expert-FFN pass over one problem takes ("few": ffn_skinny.hip, "mid", "tile"): pass 0 (gate/up) or 1
+    (down), E groups with A_cap rows allotted, N output columns.  The limits are read from the sources, so that a test whose
+    sizes a changed limit moves to another kernel fails instead of testing that one twice."""
+    src = _csrc("ffn_skinny.hip")
+    lim = {k: int(re.search(r"\bSKINNY_%s = (\d+)" % k, src).group(1))
+           for k in ("UP_ROWS", "UP_PER_GROUP", "UP_SINGLE", "DOWN_ROWS", "DOWN_SINGLE")}
+    tiles = min(E, A_cap) * -(-N // 64)
+    if E == 1:
+        few = A_cap <= lim["DOWN_SINGLE" if which else "UP_SINGLE"]
+    elif which == 0:
+        few = A_cap <= min(lim["UP_ROWS"], lim["UP_PER_GROUP"] * E)
+    else:
+        few = A_cap <= lim["DOWN_ROWS"] and (A_cap <= E or tiles < 1024) and (A_cap <= 16 * E or tiles <= 128)
+    if few:
+        return "few"
+    table = re.search(r"up_to\[2\]\[2\]\[3\] = ([{}\d, ]+);", _csrc("ffn_mid.hip")).group(1)
+    most = [int(v) for v in re.findall(r"\d+", table)][which * 6 + (3 if E == 1 else 0) + 2]
+    return "mid" if A_cap // E <= most else "tile"

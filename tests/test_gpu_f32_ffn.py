@@ -11,10 +11,12 @@ pytestmark = pytest.mark.gpu
 
 
 # contraction lengths that end inside a 16-, 32- and 64-wide group of k (8, 24, 40, 72, 136, 520) and that do not; widths that end
-# inside a 16-, 32-, 64- and 128-wide column block; groups of 1, 15 to 17, 31 to 33, 127 to 129 and no rows
+# inside a 16-, 32-, 64- and 128-wide column block; groups of 1, 15 to 17, 31 to 33, 127 to 129 and no rows.  The last two: some 4000
+# rows and a contraction of 512 and more, where the direct kernel's waves take 32 x 32 in the down pass
 @pytest.mark.parametrize("d,F,sizes,spare", [
     (8, 8, [1], 0), (24, 40, [15, 16, 17, 0, 1], 3), (72, 136, [31, 32, 33, 127, 128, 129], 0), (64, 512, [40] * 8, 0),
-    (520, 264, [300, 0, 2, 61], 0), (256, 512, [128] * 8, 0), (1032, 72, [600, 700], 0)])
+    (520, 264, [300, 0, 2, 61], 0), (256, 512, [128] * 8, 0), (1032, 72, [600, 700], 0), (256, 512, [900, 33, 0, 1000, 511, 513, 1, 1042], 0),
+    (264, 520, [15, 1500, 17, 800, 0, 1200, 64, 404], 0)])
 def test_f32_rows_against_oracle_and_between_kernels(orc, d, F, sizes, spare):
     from paper_2504_01337_amd import c2r
     rng = np.random.default_rng(d + F)

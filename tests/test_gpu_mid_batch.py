@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2504_01337_amd import workloads as wl
-from helpers import TOL, dev, host, max_rel_err
+from helpers import TOL, dev, ffn_kernel, host, max_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -21,15 +21,22 @@ def c2r():
 # edges of the 32-, 64- and 128-row tiles and of their 16-row fragments, groups of several tiles, empty groups, one group
 # only, fewer tiles than workgroups and tiles of a single 64-wide k-slice (a workgroup crosses several in its first ring);
 # k tails and padding columns (88, 688, 1400), column tails (72, 136), rows past the allotment's use
-@pytest.mark.parametrize("d,F,sizes,spare", [
-    (64, 64, [90], 0), (64, 64, [200], 0), (64, 72, [31, 32, 33, 0, 15, 16, 17, 1], 60), (192, 88, [63, 64, 65, 129, 0, 1], 5),
-    (320, 688, [127, 128, 48, 0], 20), (704, 136, [5] * 60, 0), (64, 1400, [97, 300, 2], 0), (512, 192, [250, 1, 255], 0)])
-def test_mid_rows_against_oracle_and_tile_kernel(c2r, orc, d, F, sizes, spare):
+# (first column: the passes that run in this kernel; in the others, and where the rule has moved on, the tile kernel runs twice)
+@pytest.mark.parametrize("mid,d,F,sizes,spare", [
+    ("both", 64, 64, [90], 0), ("down", 64, 64, [200], 0), ("both", 64, 72, [31, 32, 33, 0, 15, 16, 17, 1], 60),
+    ("both", 192, 88, [63, 64, 65, 129, 0, 1], 5), ("both", 320, 688, [127, 128, 48, 0], 20), ("both", 704, 136, [5] * 60, 0),
+    ("gate/up", 64, 1400, [97, 300, 2], 0), ("none", 512, 192, [250, 1, 255], 0),
+    # several chunks of a group in every tile height: 128 rows, 64, and 32 (a single group; 60 groups of which one holds most)
+    ("both", 512, 192, [160, 1, 105], 0), ("both", 128, 320, [100, 33, 40, 0], 0), ("both", 192, 136, [64], 0), ("both", 64, 704, [33], 0),
+    ("both", 128, 64, [90] + [1] * 59, 100), ("both", 64, 128, [178, 1], 0)])
+def test_mid_rows_against_oracle_and_tile_kernel(c2r, orc, mid, d, F, sizes, spare):
     rng = np.random.default_rng(d * 3 + F)
     E = len(sizes)
     offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     n = int(offsets[-1])
-    assert (n + spare) // E < 250 and n + spare > 64
+    assert [ffn_kernel(0, E, n + spare, F), ffn_kernel(1, E, n + spare, d)] == [
+        "mid" if mid in ("both", "gate/up") else "tile", "mid" if mid in ("both", "down") else "tile"]
+    assert {ffn_kernel(0, E, 600 * E + n, F), ffn_kernel(1, E, 600 * E + n, d)} == {"tile"}
     x = wl.round_bf16(rng.standard_normal((n, d)).astype(np.float32))
     wg, wu, wd = [wl.round_bf16((rng.standard_normal(s) * 0.05).astype(np.float32)) for s in ((E, F, d), (E, F, d), (E, d, F))]
     w = [dev(a, "bf16") for a in (wg, wu, wd)]
