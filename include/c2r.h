@@ -245,8 +245,8 @@ int c2r_expert_ffn_down(const void *h, c2r_dtype dt, const int32_t *offsets, int
  * c2r_expert_ffn_gate_up with the row gather of the dispatch (Sec. 3.1) folded in: row p of
  * the sorted order is read as x[perm[p] / K] instead of x_perm[p], so c2r_permute can be
  * called with x_perm == NULL and the [T*K, d] copy is never written.  Same result bit for
- * bit.  x: [T, d] of dt; perm: int32[A_cap] as written by c2r_permute (entries at
- * positions >= offsets[E_local] are never read).  Limits: bf16, d and F multiples of 64,
+ * bit.  x: [T, d] of dt; perm: int32[A_cap] as written by c2r_permute (whatever
+ * stands at positions >= offsets[E_local] changes nothing).  Limits: bf16, d and F multiples of 64,
  * T*d*2 < 2^32; otherwise C2R_ERR_UNSUPPORTED (use c2r_permute's x_perm instead).
  */
 int c2r_expert_ffn_gate_up_gather(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K,

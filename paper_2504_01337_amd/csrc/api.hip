@@ -1,5 +1,5 @@
 // Host entry points that do not belong to a single kernel file: version,
-// workspace query, and the expert-FFN dispatcher (fp32 vector path / bf16 MFMA path).
+// workspace query, the expert-FFN dispatcher (fp32, bf16 and its fast shapes), and the layer in one call.
 #include "c2r_internal.h"
 
 namespace c2r {

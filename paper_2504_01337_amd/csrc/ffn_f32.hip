@@ -7,13 +7,15 @@
 // k = 4q .. 4q + 3 of row i of a 16-wide step, so that the four v_mfma_f32_16x16x4_f32 of a step add k = c, 4 + c, 8 + c,
 // 12 + c for c = 0 .. 3: they give the same bits.
 //   ffn_f32_direct_kernel: every wave works alone, without LDS, on 16 * MF rows x 16 * NC columns; loads go straight into
-//     registers, two to four steps ahead, and the waves of a workgroup take neighbouring columns of the same rows, which
+//     registers, four steps at a time with the next four in flight, and the waves of a workgroup take neighbouring columns of the same rows, which
 //     meet in the CU's cache.  Short chains and many waves: for few rows.
 //   ffn_f32_tile_kernel: 128 rows x 128 weight rows per workgroup of four waves, 128-byte k-slices through two LDS stages
 //     that asynchronous copies fill, two workgroups per CU: a quarter of the other one's traffic out of L2.
-// Microseconds gate/up + down (vector-pipe kernel before -> now), 8 experts: d 256, F 512: 2 rows 24 + 28 -> 7 + 7, 1024 rows
-// 27 + 30 -> 12 + 10, 4096 rows 37 + 36 -> 28 + 19, 16384 rows 123 + 70 -> 85 + 48 (101 + 90 TFLOP/s); d 1024, F 1376: 256 rows
-// 99 + 84 -> 34 + 22, 16384 rows 1164 + 619 -> 800 + 399 (115 TFLOP/s).  Against 64-bit sums the error is what it was (5.9e-7).
+// Microseconds gate/up + down of each pass replayed by itself, operands in L2 (vector-pipe kernel before -> now), 8 experts: d 256,
+// F 512: 2 rows 24 + 28 -> 7.0 + 6.8, 1024 rows 28 + 34 -> 12.3 + 9.9, 4096 rows 34 + 34 -> 26 + 19.5, 16384 rows 115 + 65 -> 83 + 48
+// (103 + 90 TFLOP/s); d 1024, F 1376: 256 rows 109 + 84 -> 36 + 22, 16384 rows 1113 + 604 -> 807 + 402 (115 TFLOP/s).  Inside a layer
+// call the operands come from farther away: 1024 rows 30 + 33 -> 22 + 18, 4096 rows 48 + 37 -> 44 + 36 (profiled).  Against
+// 64-bit sums the layer's error is what it was (1 to 8192 tokens: 5.6e-7 to 6.1e-7, 5.6e-7 to 6.3e-7 before).
 #include "ffn_common.h"
 #include "ffn_copy.h"
 
@@ -27,7 +29,8 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_direct_kernel(const float *__r
                                                                 int ldo, int nwg) {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     constexpr int NB = MODE == 0 ? 2 * NC : NC, BM = 16 * MF, BN = 16 * NC;
-    constexpr int U = MF * NB > 4 ? 2 : 4;  // 16-wide steps requested together
+    constexpr int U = 4;  // 16-wide steps requested together
+    static_assert(MF * NB <= 4, "two sets of U steps fit the registers");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // workgroup -> (row tile, four column blocks), column blocks fastest, a contiguous eighth of them per XCD: the row tile
     // is then read into one L2

@@ -11,12 +11,12 @@
 // its first slice to its last.  (One workgroup per tile instead, the same tile: 99 against 72 us for the gate/up pass of
 // 16 tokens; each start waits for the launch, the offsets, the row numbers and the first weights one after the other.)
 //
-// Every output is one chain of v_mfma_f32_16x16x32_bf16 over ascending k, as in ffn_bf16_dma.hip: the two kernels give
-// the same bits, so which of them runs may depend on what else the launch carries.
+// Every output is one chain of v_mfma_f32_16x16x32_bf16 over ascending k, as in ffn_bf16_dma.hip and ffn_skinny.hip: the
+// kernels give the same bits, so which of them runs may depend on what else the launch carries.
 //
 // Microseconds of a layer call, tile kernel -> this one (60 experts + shared, d 2048, F 1408 / 5632, top-4; 16 experts,
 // d 4096, F 688, top-4):
-//   60 experts: 64 tokens 212 -> 165, 131 tokens 252 -> 164, 256 tokens (down pass only) 210 -> 185;
+//   60 experts: 64 tokens 212 -> 165, 131 tokens 256 -> 169, 256 tokens (down pass only) 210 -> 185;
 //   16 experts: 64 tokens 107 -> 78, 180 tokens 115 -> 88, 256 tokens 126 -> 106, 500 tokens 143 -> 128;
 //   15 of the 60 experts, 131 tokens 79 -> 65.
 #include "ffn_common.h"
@@ -277,6 +277,8 @@ static void mid_launch(int tile_rows, const FfnLaunch &L, hipStream_t st) {
 //   down: r = 25: 80 / 74 / 75.5 / 90, r = 40: 90 / 78 / 80 / 94, r = 55: 106 / 96 / 91 / 101, r = 75: 118 / 108 / 98 / 106, r = 100:
 //     - / 118 / 116 / 113; n = 90: 152 / 162 / 162 / 192, n = 131: 173 / 165 / 174 / 204, n = 300: 221 / 194 / 200 / 216,
 //     n = 511: - / - / 210 / 212.
+// (r counts the rows allotted.  A device that holds a quarter of the experts has a quarter of them in use: its tiles are higher
+// than its rows would ask for, 15 of 60 experts at 131 tokens 65.)
 int ffn_mid_rows(int pass, const FfnLaunch &L) {
     int rows = 0;
     for (int q = 0; q < 2; ++q) {
