@@ -488,7 +488,9 @@ class C2RLayer:
         sh = self.shared if self.shared is not None else (None, None, None)
         if self.shared is not None:
             Fs = sh[0].shape[-2]
-            assert sh[0].shape == sh[1].shape == (1, Fs, d) and sh[2].shape == (1, d, Fs) and sh[0].dtype == dtype
+            assert sh[0].shape == sh[1].shape and sh[0].shape[-2:] == (Fs, d) and sh[2].shape[-2:] == (d, Fs) and sh[0].dtype == dtype
+            # (riding in the routed launches it may come without the leading 1)
+            assert self.fuse_shared or all(t.dim() == 3 and t.shape[0] == 1 for t in sh)
         collab = self.collab_idx
         a = self.__dict__.get
         return self._LAYER.pack(

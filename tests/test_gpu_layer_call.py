@@ -115,3 +115,18 @@ def test_no_tokens(dtype, kw, shared):
     y = layer.forward(w(0, d))
     torch.cuda.synchronize()
     assert y.shape == (0, d) and not layer.counts.any() and not layer.offsets.any()
+
+
+# what the stage that takes a riding shared expert accepts, the one call accepts too: weights without the leading 1 (F_shared = d there: the
+# constructor reads F_shared from the second dimension)
+def test_shared_weights_without_the_leading_dimension():
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(3)
+    T, d, E, K, F = 20, 64, 4, 2, 64
+    w = lambda *sh: dev((rng.standard_normal(sh) * 0.05).astype(np.float32), "bf16")
+    shared = (w(d, d), w(d, d), w(d, d))
+    args = (T, d, E, K, F, torch.bfloat16, w(d, E).float(), None, None, w(E, F, d), w(E, F, d), w(E, d, F))
+    flat, full = c2r.C2RLayer(*args, shared=shared), c2r.C2RLayer(*args, shared=tuple(t[None] for t in shared))
+    assert flat.fuse_shared and full.fuse_shared
+    x = w(T, d)
+    assert torch.equal(flat.forward(x), full.forward(x)) and torch.equal(flat.forward(x), flat.forward(x, trace={}))
