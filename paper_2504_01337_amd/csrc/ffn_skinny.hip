@@ -13,9 +13,10 @@
 // bits are the same at every batch size and through every entry point.  Only the loads are parallel; the waves pass the sums
 // on through LDS, each adding the k range that it has loaded.
 //
-// Measured, microseconds of the two passes, weights cold (tile kernel -> this one): 60 experts + shared (d 2048, F 1408 /
-// 5632, top-4): 1 token 33 + 52 -> 23.2 + 12.9, down pass of 16 tokens 79 -> 27.3; 16 experts (d 4096, F 688, top-4): 1 token
-// 58 -> 18.9 + 7.3.  A partial sum per wave, added at the end (another order of summation), took 21.2 + 14.4, 30.3 and 14.8 + 6.0.
+// Measured, microseconds of gate/up + down in a kernel trace, three layers of weights in turn (tile kernel -> this one): 60
+// experts + shared (d 2048, F 1408 / 5632, top-4): 1 token 33.3 + 64.8 -> 22.9 + 12.8, down pass of 16 tokens 76.0 -> 27.3; 16 experts
+// (d 4096, F 688, top-4): 1 token 41.3 + 17.7 -> 18.0 + 7.4.  A partial sum per wave, added at the end (another order of
+// summation), took 21.3 + 14.5, 30.4 and 14.6 + 6.0.
 #include <type_traits>
 
 #include "ffn_common.h"
