@@ -631,7 +631,7 @@ def main():
                                 "the kernel's own duration in the rocprofv3 trace)"}
     else:
         # (the fp32 matrix peak is the vector peak; few rows take the direct kernel, many the tile kernel)
-        roofline = {"kernel": "ffn_f32_direct_kernel<0> or ffn_f32_tile_kernel<0>" + both + " (gate/up + SwiGLU)", "bound": "mfma",
+        roofline = {"kernel": "ffn_f32_ring_kernel<0>" + both + " (gate/up + SwiGLU)", "bound": "mfma",
                     "achieved": dom_fl / dom_ms / 1e9, "peak": PEAK["valu_f32_TFLOPs"], "unit": "TFLOP/s",
                     "frac": dom_fl / dom_ms / 1e9 / PEAK["valu_f32_TFLOPs"], "traffic": None,
                     "avg_launch_ms": dom_ms, "launches_per_step": n_launch, "launches_timed": dom_launches_timed}

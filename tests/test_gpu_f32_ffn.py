@@ -40,3 +40,26 @@ def test_f32_rows_against_oracle_and_between_kernels(orc, d, F, sizes, spare):
     assert torch.equal(got[0], got[1])
     ref = orc.expert_ffn_rows(x, np.repeat(np.arange(E), sizes).astype(np.int32), *w)
     assert max_rel_err(host(got[0]), ref) <= TOL["f32"]
+
+
+# edges of the 32- and 64-row tiles, column blocks of 32 and 64, contractions of one to four 32-wide slices and a ragged last one
+@pytest.mark.parametrize("d,F,sizes", [(64, 32, [63, 64, 65]), (96, 72, [95, 96, 97, 31, 32, 33]), (104, 128, [1, 0, 62, 66]), (32, 96, [129, 2])])
+def test_f32_tile_edges_between_allotments(orc, d, F, sizes):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(d * F)
+    E, n = len(sizes), sum(sizes)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    w = [(rng.standard_normal(s) * 0.1).astype(np.float32) for s in ((E, F, d), (E, F, d), (E, d, F))]
+    wd = [dev(a) for a in w]
+    got = []
+    for cap in (n, 64 * 1280 + n, 32 * 1025 + n):  # the small tiles, the 64-row tiles, and the small ones' shallower ring
+        xa = torch.zeros((cap, d), device="cuda")
+        xa[:n] = dev(x)
+        y = torch.full((cap, d), 5.0, device="cuda")
+        c2r.expert_ffn(xa, dev(offsets), *wd, out=y)
+        assert torch.all(y[n:] == 5.0)
+        got.append(y[:n])
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    ref = orc.expert_ffn_rows(x, np.repeat(np.arange(E), sizes).astype(np.int32), *w)
+    assert max_rel_err(host(got[0]), ref) <= TOL["f32"]
