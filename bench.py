@@ -630,7 +630,7 @@ def main():
                                 "timed region (a pair brackets the marker latency too: a few per cent more than "
                                 "the kernel's own duration in the rocprofv3 trace)"}
     else:
-        # (the fp32 matrix peak is the vector peak; few rows take the direct kernel, many the tile kernel)
+        # (the fp32 matrix peak is the vector peak)
         roofline = {"kernel": "ffn_f32_ring_kernel<0>" + both + " (gate/up + SwiGLU)", "bound": "mfma",
                     "achieved": dom_fl / dom_ms / 1e9, "peak": PEAK["valu_f32_TFLOPs"], "unit": "TFLOP/s",
                     "frac": dom_fl / dom_ms / 1e9 / PEAK["valu_f32_TFLOPs"], "traffic": None,

@@ -1,7 +1,7 @@
 // Router logits (Eq. 1) and collaboration-constrained selection (Sec. 3.3, step 2).
 //
-// Two kernels (small batches have forms of their own: route_partial_small_kernel, and route_finish_small_kernel, which
-// also builds the dispatch index).
+// Two kernels (small batches have forms of their own: route_partial_small_kernel, route_select_small_kernel, and
+// route_finish_small_kernel, which also builds the dispatch index).
 //  route_partial_kernel: an fp32 GEMM over one 256-long k-chunk in which every (token,
 //    expert) sum is built with one fused multiply-add per k in ascending k - exactly the
 //    ABI's declared order - either by one thread on the vector pipe (up to 8 experts) or by
@@ -1186,6 +1186,138 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
     }
 }
 
+// The best allowed expert of one token (see route_select_kernel for the rule), by the token's sixteen lanes: lane sub holds
+// the logits l of experts 4 sub .. 4 sub + 3, row is the token's logits in LDS, m the allowed experts.
+__device__ __forceinline__ void pick_by_sixteen(const float (&l)[4], const float *row, uint64_t m, int sub, int &bi, float &bv) {
+    const uint32_t mloc = (uint32_t)(m >> (sub * 4));
+    bi = -1;
+    bv = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const bool take = ((mloc >> j) & 1u) != 0 && (l[j] > bv || (bi < 0 && l[j] == l[j]));
+        bv = take ? l[j] : bv;
+        bi = take ? sub * 4 + j : bi;
+    }
+    merge_lower<0xB1>(sub & 1, bi, bv);   // quad_perm 1,0,3,2
+    merge_lower<0x4E>(sub & 2, bi, bv);   // quad_perm 2,3,0,1
+    merge_lower<0x141>(sub & 4, bi, bv);  // row_half_mirror: the other quad, whose lanes agree by now
+    merge_lower<0x140>(sub & 8, bi, bv);  // row_mirror: the other eight lanes
+    if (m != 0) {  // a NaN stands only as the first allowed expert
+        const int f = __ffsll((unsigned long long)m) - 1;
+        const float lf = row[f];
+        if (lf != lf) {
+            bi = f;
+            bv = lf;
+        }
+    }
+}
+
+// route_select_kernel for batches that its 64-token workgroups would leave most of the chip idle with: sixteen tokens per
+// workgroup.  What bounds such a selection is the trip of a workgroup's chunk results - 128 KB for 64 tokens of 60 experts and 8 chunks, at
+// the rate one CU pulls from memory - and the length of its scans: a quarter of the one, sixteen lanes per token on the other.
+constexpr int SEL16_TOKENS = 16;
+
+__global__ __launch_bounds__(256) void route_select_small_kernel(
+    const float *__restrict__ part, int ep, int nchunk, const float *__restrict__ bias, int64_t T, int E, int K,
+    const int32_t *__restrict__ collab_idx, int Tc, int32_t *__restrict__ topk_idx, float *__restrict__ gates,
+    float *__restrict__ logits_out) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    constexpr int LP = C2R_MAX_E + 1;
+    __shared__ float tile[SEL16_TOKENS * LP];
+    __shared__ uint64_t mask_tab[C2R_MAX_E];
+    const int tid = threadIdx.x;
+    const int64_t t0 = (int64_t)blockIdx.x * SEL16_TOKENS;
+    const uint64_t all = E >= 64 ? ~0ull : ((1ull << E) - 1ull);
+    {
+        // a thread's share: one expert (its chunk results of four tokens, and a quarter of its list); all loads of the usual sizes in
+        // flight together
+        const int e = tid >> 2, quad = tid & 3;
+        constexpr int AHEAD = 4;
+        int32_t listed[AHEAD];
+        const int last = E * Tc - 1;
+        if (collab_idx) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) listed[u] = collab_idx[min(e * Tc + quad + 4 * u, last)];
+        }
+        const float *p = part + ((size_t)(t0 >> 6) * nchunk * ep + (e < ep ? e : 0)) * 64 + (t0 & 63) + quad * 4;
+        f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int c0 = 0; c0 < nchunk; c0 += 8) {
+            f32x4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v[u] = *reinterpret_cast<const f32x4 *>(p + (size_t)min(c0 + u, nchunk - 1) * ep * 64);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (c0 + u < nchunk) sum = c0 + u == 0 ? v[u] : sum + v[u];
+        }
+        if (bias && e < E) sum = sum + bias[e];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tile[(quad * 4 + i) * LP + e] = sum[i];
+        uint64_t m = collab_idx ? 0ull : all;
+        if (collab_idx) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+                if (quad + 4 * u < Tc && listed[u] >= 0 && listed[u] < E) m |= 1ull << listed[u];
+            for (int i = quad + 4 * AHEAD; i < Tc; i += 4) {
+                const int v = e < E ? collab_idx[e * Tc + i] : -1;
+                if (v >= 0 && v < E) m |= 1ull << v;
+            }
+#if defined(__HIP_DEVICE_COMPILE__)
+            int lo = (int)(uint32_t)m, hi = (int)(uint32_t)(m >> 32);
+            lo |= __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xf, 0xf, true);
+            hi |= __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xf, 0xf, true);
+            lo |= __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xf, 0xf, true);
+            hi |= __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xf, 0xf, true);
+            m = (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32);
+#endif
+        }
+        if (quad == 0) mask_tab[e] = m & ~(1ull << e);
+    }
+    __syncthreads();
+    const int sub = tid & 15;
+    const int64_t t = t0 + (tid >> 4);
+    if (t >= T) return;  // (the sixteen lanes of a token leave together)
+    const float *row = &tile[(tid >> 4) * LP];
+    float l[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) l[j] = sub * 4 + j < E ? row[sub * 4 + j] : 0.0f;
+    if (logits_out) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (sub * 4 + j < E) logits_out[(size_t)t * E + sub * 4 + j] = l[j];
+    }
+    int e, mine = -1;  // lane s of a token keeps its slot s (slots past the sixteenth go out at once, unscaled)
+    float v, v0 = 0.0f, den = 0.0f, mine_g = 0.0f;
+    uint64_t m = all;
+    for (int s = 0; s < K; ++s) {
+        pick_by_sixteen(l, row, m, sub, e, v);
+        float g = 0.0f;
+        if (s == 0) {
+            v0 = v;
+            m = mask_tab[e];
+            g = expf(v0 - v0);  // 1, or NaN when the largest logit is infinite or a NaN
+        } else if (e >= 0) {
+            m &= ~(1ull << e);
+            g = expf(v - v0);
+        }
+        den = s == 0 ? g : den + g;
+        if (s == sub) {
+            mine = e;
+            mine_g = g;
+        }
+        if (s >= 16 && sub == 0) {
+            topk_idx[(size_t)t * K + s] = e;
+            gates[(size_t)t * K + s] = g;
+        }
+    }
+    if (sub < K) {
+        topk_idx[(size_t)t * K + sub] = mine;
+        gates[(size_t)t * K + sub] = mine_g / den;
+    }
+    if (sub == 0)
+        for (int s = 16; s < K; ++s) gates[(size_t)t * K + s] = gates[(size_t)t * K + s] / den;
+}
+
 // Selection AND dispatch index of a batch of at most 64 tokens and 1024 assignments, one workgroup: what
 // route_select_kernel and permute_by_slot_kernel (permute.hip) do, in one launch instead of two.
 // A launch costs such a batch as much as its work: 60 experts, 1 token, 9.3 + 6.4 us in two launches, 7.8 in one.  Sixteen waves, so that the chunk
@@ -1252,34 +1384,11 @@ __global__ __launch_bounds__(FIN_WAVES * 64) void route_finish_small_kernel(
         float l[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) l[j] = sub * 4 + j < E ? tile[t * LP + sub * 4 + j] : 0.0f;
-        auto pick = [&](uint64_t m, int &bi, float &bv) __attribute__((always_inline)) {
-            const uint32_t mloc = (uint32_t)(m >> (sub * 4));
-            bi = -1;
-            bv = 0.0f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool take = ((mloc >> j) & 1u) != 0 && (l[j] > bv || (bi < 0 && l[j] == l[j]));
-                bv = take ? l[j] : bv;
-                bi = take ? sub * 4 + j : bi;
-            }
-            merge_lower<0xB1>(sub & 1, bi, bv);   // quad_perm 1,0,3,2
-            merge_lower<0x4E>(sub & 2, bi, bv);   // quad_perm 2,3,0,1
-            merge_lower<0x141>(sub & 4, bi, bv);  // row_half_mirror: the other quad, whose lanes agree by now
-            merge_lower<0x140>(sub & 8, bi, bv);  // row_mirror: the other eight lanes
-            if (m != 0) {  // a NaN stands only as the first allowed expert
-                const int f = __ffsll((unsigned long long)m) - 1;
-                const float lf = tile[t * LP + f];
-                if (lf != lf) {
-                    bi = f;
-                    bv = lf;
-                }
-            }
-        };
         int e;
         float v, v0 = 0.0f, den = 0.0f;
         uint64_t m = all;
         for (int s = 0; s < K; ++s) {
-            pick(m, e, v);
+            pick_by_sixteen(l, &tile[t * LP], m, sub, e, v);
             float g = 0.0f;
             if (s == 0) {
                 v0 = v;
@@ -1409,6 +1518,22 @@ using namespace c2r;
 
 extern "C" int c2r_route_chunk(void) { return C2R_CANON_CHUNK; }
 
+// Selection from chunk results.
+static int launch_select(const float *part, int EP_, int nchunk, const float *bias, int64_t T, int E, int K,
+                         const int32_t *collab_idx, int Tc, int32_t *topk_idx, float *gates, float *logits_out, hipStream_t st) {
+    // Up to 8192 tokens the 64-token workgroups are at most half as many as the CUs.  Microseconds of the kernel (64 / 16 tokens per
+    // workgroup), 60 experts, d 2048: 131 tokens 10.5 / 5.4, 1000 tokens 11.9 / 6.2, 8192 tokens 11.9 / 9.3; 16 experts, d 4096, 4096 tokens
+    // 7.2 / 6.5.  Beyond, with every CU at work, the shorter scans count (the stage: 16384 tokens 52.7 / 54.2, 65536 tokens 155 / 157).
+    if (T <= 8192) {
+        route_select_small_kernel<<<dim3((unsigned)((T + SEL16_TOKENS - 1) / SEL16_TOKENS)), dim3(256), 0, st>>>(
+            part, EP_, nchunk, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out);
+        return launch_status();
+    }
+    C2R_EP_SWITCH(EP_, route_select_kernel<EP, false><<<dim3((unsigned)((T + 63) / 64)), dim3(SEL_WAVES * 64), 0, st>>>(
+                           part, nchunk, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out));
+    return launch_status();
+}
+
 // What route_finish_small_kernel writes besides the selection.
 struct DispatchOut {
     const int32_t *local_slot;
@@ -1453,9 +1578,7 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
                 gates, dispatch->counts, dispatch->offsets, dispatch->perm, dispatch->inv_perm);
             return launch_status();
         }
-        C2R_EP_SWITCH(L.EP, route_select_kernel<EP, false><<<dim3((unsigned)ntiles), dim3(SEL_WAVES * 64), 0, st>>>(
-                                part, L.nchunk, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out));
-        return launch_status();
+        return launch_select(part, L.EP, L.nchunk, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out, st);
     }
     if (L.wpad_bytes) {
         float *Wp = reinterpret_cast<float *>(static_cast<char *>(ws) + L.part_bytes);
@@ -1512,9 +1635,7 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
 #undef C2R_ROUTE_TE
 #undef C2R_ROUTE_LAUNCH_ALL
 #undef C2R_ROUTE_LAUNCH
-    C2R_EP_SWITCH(L.EP, route_select_kernel<EP, false><<<dim3((unsigned)ntiles), dim3(SEL_WAVES * 64), 0, st>>>(
-                            part, nchunk_out, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out));
-    return launch_status();
+    return launch_select(part, L.EP, nchunk_out, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out, st);
 }
 
 extern "C" int c2r_route(const void *x, c2r_dtype x_dt, const float *Wg, const float *bias,

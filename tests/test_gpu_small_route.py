@@ -98,3 +98,26 @@ def test_lists_without_entries(c2r, orc, T, E, d, dtype):
     assert c2r.lib().c2r_layer_forward(layer._LAYER.pack(*fields), xd.data_ptr(), torch.cuda.current_stream().cuda_stream) == c2r.OK
     torch.cuda.synchronize()
     assert np.array_equal(host(layer.idx), ri) and torch.equal(layer.y, y)
+
+
+# selection with sixteen tokens per workgroup: remainders of a tile, lists shorter and longer than a thread requests ahead, more slots
+# than a token has lanes, special values, and the first batch that goes back to the 64-token kernel
+@pytest.mark.parametrize("T,E,K,Tc", [(1, 64, 4, 16), (65, 60, 4, 16), (79, 64, 16, 63), (80, 64, 17, 40), (33, 63, 40, 62), (100, 5, 1, 3),
+                                      (129, 17, 2, 17), (8192, 36, 4, 9), (8193, 36, 4, 9)])
+def test_small_selection_against_oracle(c2r, orc, T, E, K, Tc):
+    rng = np.random.default_rng(T + E * K)
+    x = rng.standard_normal((T, 64)).astype(np.float32)
+    Wg = np.round(rng.standard_normal((64, E)) * 2).astype(np.float32) / 4
+    bias = rng.standard_normal(E).astype(np.float32)
+    if E > 8:
+        bias[[2, 7]] = np.nan, -np.inf
+    # Tc entries with the expert itself and a duplicate among them where the slots leave room; out-of-range ones only for the GPU
+    lists = np.stack([rng.permutation(np.delete(np.arange(E), e))[np.arange(Tc) % (E - 1)] for e in range(E)]).astype(np.int32)
+    if Tc - 2 >= K - 1:
+        lists[:, 1], lists[:, Tc - 1] = lists[:, 0], np.arange(E)
+    padded = np.concatenate([np.full((E, 1), -1), lists, np.full((E, 1), E + 1)], axis=1).astype(np.int32)
+    for cl, gl in ((None, None), (lists, padded)):
+        idx, gates, logits = c2r.route(dev(x), dev(Wg), dev(bias), K, None if gl is None else dev(gl), want_logits=True)
+        ri, rg = orc.route(host(logits), K, cl)
+        assert np.array_equal(host(idx), ri)
+        np.testing.assert_allclose(host(gates), rg, rtol=GATE_RTOL, atol=1e-37)
