@@ -792,8 +792,8 @@ FfnProblem ffn_bf16_dma_problem(int pass, const uint16_t *a, int lda, const int3
 
 bool ffn_skinny_takes(int pass, const FfnLaunch &L);
 int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st);
-int ffn_mid_rows(int pass, const FfnLaunch &L);
-int launch_ffn_mid(int pass, int tile_rows, FfnLaunch L, hipStream_t st);
+bool ffn_mid_rows(int pass, const FfnLaunch &L, int (&rows)[2]);
+int launch_ffn_mid(int pass, const int (&tile_rows)[2], FfnLaunch L, hipStream_t st);
 
 // Rows of the single group's tiles.  Fewer tiles than a quarter of the CUs, each a chain of k-slices much longer than those
 // beside it, are what a launch then waits for (a shared expert's down pass: 88 slices, 120 us, against 22): cut lower, the
@@ -834,7 +834,8 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     // Few rows: the kernel of ffn_skinny.hip.  More, but not enough to fill the chip with 256 x 256 tiles: that of ffn_mid.hip.
     // Every output is the same chain of the same matrix instructions in all three, so a row's bits do not depend on the choice.
     if (ffn_skinny_takes(pass, L)) return launch_ffn_skinny(pass, L, st);
-    if (const int tile_rows = ffn_mid_rows(pass, L)) return launch_ffn_mid(pass, tile_rows, L, st);
+    int tile_rows[2];
+    if (ffn_mid_rows(pass, L, tile_rows)) return launch_ffn_mid(pass, tile_rows, L, st);
     // one workgroup per CU (fewer if the bound on the tiles is smaller), whatever the number of tiles
     int64_t tiles = 0;
     if (ragged)

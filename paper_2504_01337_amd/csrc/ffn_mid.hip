@@ -28,118 +28,73 @@ constexpr int MID_BR = 64;               // weight rows of a tile: 64 output col
 constexpr int MID_ROW_TABLE = 4096;      // sorted rows whose source row (16 bits) a workgroup keeps in LDS
 constexpr int MID_WG_PER_XCD = 2 * CUS_PER_XCD;
 
-// What a launch walks: items = (chunk of at most AR rows of one group, column block), the single group's first, then the
-// ragged problem's; inside a group the chunks of a column block follow one another.
-struct MidList {
-    GroupMap gm;                 // of the ragged problem (per lane)
-    int slo, shi, schunks;       // the single group's row range and chunks
-    int n_single, n_ragged;      // items
-};
+constexpr int mid_stages(int ar) { return ar == 32 ? 6 : ar == 64 ? 4 : 3; }
+constexpr int mid_lds_bytes(int ar) { return mid_stages(ar) * (ar + MID_BR) * 128; }
 
-struct MidItem {
-    int expert, row_begin, rows, n0, nk;
-    bool single;
-};
-
-// A group of n rows is cut into ceil(n / AR) chunks of equal height (a multiple of 16, so none is empty).
-template <int MODE, int AR>
-__device__ __forceinline__ MidItem mid_item_at(const FfnLaunch &L, const MidList &m, int item) {
-    constexpr int BN = MODE == 0 ? MID_BR / 2 : MID_BR;
-    MidItem t;
-    t.single = item < m.n_single;
-    int lo, hi, chunks, local;
-    if (t.single) {
-        t.expert = 0;
-        lo = m.slo;
-        hi = m.shi;
-        chunks = m.schunks;
-        local = item;
-        t.nk = (L.p[1].Kdim + 63) / 64;
-    } else {
-        const int ntn = L.p[0].ntn;
-        item -= m.n_single;
-        const uint64_t hit = __ballot(item >= m.gm.first * ntn && item < (m.gm.first + m.gm.tiles) * ntn);
-        const int e = hit ? __ffsll((unsigned long long)hit) - 1 : 0;
-        t.expert = __builtin_amdgcn_readfirstlane(e);
-        lo = __builtin_amdgcn_readlane(m.gm.lo, t.expert);
-        hi = __builtin_amdgcn_readlane(m.gm.hi, t.expert);
-        chunks = __builtin_amdgcn_readlane(m.gm.tiles, t.expert);
-        local = item - __builtin_amdgcn_readlane(m.gm.first, t.expert) * ntn;
-        t.nk = (L.p[0].Kdim + 63) / 64;
+// Where gate/up gathers, the source row of every sorted row.
+__device__ __forceinline__ void mid_row_table(const FfnProblem &P, uint16_t *row_of) {
+    for (int p = threadIdx.x; p < P.A_cap; p += 256) {
+        const int g = P.gather[p], r = g > 0 ? (int)((uint32_t)g / (uint32_t)P.gather_div) : 0;
+        row_of[p] = (uint16_t)(r < P.gather_rows ? r : P.gather_rows - 1);  // an out-of-range entry cannot leave A
     }
-    const int height = ((hi - lo + chunks - 1) / chunks + 15) / 16 * 16;  // <= AR
-    t.row_begin = lo + local % chunks * height;
-    t.rows = hi - t.row_begin < height ? hi - t.row_begin : height;
-    t.n0 = local / chunks * BN;
-    return t;
+    __syncthreads();
 }
 
-// First item whose start, in slices, is not below `s` (kS, kR: slices of a single / ragged item).
-__device__ __forceinline__ int mid_first_item(int64_t s, const MidList &m, int kS, int kR) {
-    const int64_t single = (int64_t)m.n_single * kS;
-    return s < single ? (int)((s + kS - 1) / kS) : m.n_single + (int)((s - single + kR - 1) / kR);
-}
-
-template <int MODE, int AR, int NSTAGE>
-__global__ __launch_bounds__(256, 2) void ffn_mid_kernel(const FfnLaunch L) {
+// Workgroup w of the nwg that walk one problem, its groups in gm (chunks of AR rows).  Items = (chunk of at most AR rows of one
+// group, column block); the workgroup takes a contiguous run of them, an equal share (they all have the same k-slices).  A group's
+// items are numbered in blocks of `run` columns - the length of a workgroup's run - chunk after chunk inside a block, so that the
+// chunks of a column block, which read the same weights, are walked by neighbouring workgroups at the same time and the weights come
+// into that XCD's L2 once.  (Chunks of a column block one after the other in one workgroup: by the second the weights were gone; the
+// gate/up pass of 131 tokens fetched 1.37 times its weights.)
+template <int MODE, int AR>
+__device__ __forceinline__ void mid_walk(const FfnProblem &P, const GroupMap &gm, unsigned char *smem, const uint16_t *row_of,
+                                         int w, int nwg) {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    constexpr int ROWB = 128, A_BYTES = AR * ROWB, STAGE_BYTES = (AR + MID_BR) * ROWB;
+    constexpr int NSTAGE = mid_stages(AR), ROWB = 128, A_BYTES = AR * ROWB, STAGE_BYTES = (AR + MID_BR) * ROWB;
     constexpr int GA = AR / 32, GB = 2, NCOPY = GA + GB;  // 8-row copies per wave and slice
     constexpr int MF = AR / 32;                           // 16-row fragments per wave
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[NSTAGE * STAGE_BYTES];
-    __shared__ uint16_t row_of[MODE == 0 ? MID_ROW_TABLE : 1];
+    constexpr int BN = MODE == 0 ? MID_BR / 2 : MID_BR;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-
-    // ---- the list, and this workgroup's share of it: a contiguous run of items with an equal share of the k-slices
-    //      (consecutive workgroups of an XCD walk neighbouring items and share their operands in its L2) ----
-    MidList m;
-    m.slo = m.shi = m.schunks = m.n_single = m.n_ragged = 0;
-    if (L.has_single) {
-        const FfnProblem &S = L.p[1];
-        int lo = S.offsets ? S.offsets[0] : S.row_lo, hi = S.offsets ? S.offsets[1] : S.row_hi;
-        lo = lo < 0 ? 0 : (lo > S.A_cap ? S.A_cap : lo);
-        hi = hi < lo ? lo : (hi > S.A_cap ? S.A_cap : hi);
-        m.slo = __builtin_amdgcn_readfirstlane(lo);
-        m.shi = __builtin_amdgcn_readfirstlane(hi);
-        m.schunks = (m.shi - m.slo + AR - 1) / AR;
-        m.n_single = m.schunks * S.ntn;
-    }
-    m.gm = build_group_map<AR>(L.p[0].offsets, L.has_ragged ? L.p[0].E_local : 0, L.p[0].A_cap);
-    if (L.has_ragged) m.n_ragged = __builtin_amdgcn_readfirstlane(m.gm.total_mtiles) * L.p[0].ntn;
-    const int kS = (L.p[1].Kdim + 63) / 64, kR = (L.p[0].Kdim + 63) / 64;
-    const int64_t all = (int64_t)m.n_single * kS + (int64_t)m.n_ragged * kR;
-    const int nwg = (int)gridDim.x, w = (int)(blockIdx.x & 7) * (nwg >> 3) + (int)(blockIdx.x >> 3);
-    const int first = mid_first_item(all * w / nwg, m, kS, kR), last = mid_first_item(all * (w + 1) / nwg, m, kS, kR);
+    const int ntn = P.ntn, N = P.N, Kdim = P.Kdim, nk = (Kdim + 63) / 64;
+    const int n_items = __builtin_amdgcn_readfirstlane(gm.total_mtiles) * ntn;
+    const int run = max(1, min(ntn, n_items / nwg));
+    const int first = (int)((int64_t)n_items * w / nwg), last = (int)((int64_t)n_items * (w + 1) / nwg);
     if (first >= last) return;
-    const int s_items = last < m.n_single ? last - first : (first < m.n_single ? m.n_single - first : 0);
-    const int total = s_items * kS + (last - first - s_items) * kR;  // slices
+    const int total = (last - first) * nk;  // slices
 
-    if (MODE == 0 && L.p[L.has_ragged ? 0 : 1].gather) {  // the source row of every sorted row
-        const FfnProblem &P = L.p[L.has_ragged ? 0 : 1];
-        for (int p = threadIdx.x; p < P.A_cap; p += 256) {
-            const int g = P.gather[p], r = g > 0 ? (int)((uint32_t)g / (uint32_t)P.gather_div) : 0;
-            row_of[p] = (uint16_t)(r < P.gather_rows ? r : P.gather_rows - 1);  // an out-of-range entry cannot leave A
-        }
-        __syncthreads();
-    }
+    // A group of n rows is cut into ceil(n / AR) chunks of equal height (a multiple of 16, so none is empty).
+    struct Item {
+        int expert, row_begin, rows, n0;
+    };
+    auto item_at = [&](int item) __attribute__((always_inline)) {
+        const uint64_t hit = __ballot(item >= gm.first * ntn && item < (gm.first + gm.tiles) * ntn);
+        Item t;
+        t.expert = __builtin_amdgcn_readfirstlane(hit ? __ffsll((unsigned long long)hit) - 1 : 0);
+        const int lo = __builtin_amdgcn_readlane(gm.lo, t.expert), hi = __builtin_amdgcn_readlane(gm.hi, t.expert);
+        const int chunks = __builtin_amdgcn_readlane(gm.tiles, t.expert);
+        const int local = item - __builtin_amdgcn_readlane(gm.first, t.expert) * ntn;
+        const int block = local / (chunks * run), rem = local - block * chunks * run, cols = min(run, ntn - block * run);
+        const int height = ((hi - lo + chunks - 1) / chunks + 15) / 16 * 16;  // <= AR
+        t.row_begin = lo + rem / cols * height;
+        t.rows = hi - t.row_begin < height ? hi - t.row_begin : height;
+        t.n0 = (block * run + rem % cols) * BN;
+        return t;
+    };
 
     // ---- copies: lane l of a copy lands on row l/8, chunk position l%8 of an 8-row group and therefore fetches chunk
     //      (l%8) ^ key(row), which leaves the tile swizzled for the fragment reads ----
     const int lrow = lane >> 3, lpos = lane & 7;
     const int chunkc[2] = {lpos ^ swz_key(lrow), lpos ^ swz_key(8 + lrow)};  // in even / odd 8-row groups
-    int i_item = first, i_kt = 0, i_nk = 0, i_K = 0;  // the next slice to request
+    const bool gather = MODE == 0 && P.gather != nullptr;
+    const uint16_t *const B = MODE == 0 && wave >= 2 ? P.B1 : P.B0;  // (pass 0: 32 gate rows, then their 32 up rows)
+    int i_item = first, i_kt = 0;  // the next slice to request
     const unsigned char *i_A = nullptr, *i_B = nullptr;
     uint32_t offA[GA], rowB[GB];
     auto open_item = [&]() __attribute__((always_inline)) {
-        const MidItem t = mid_item_at<MODE, AR>(L, m, i_item);
-        const FfnProblem &P = L.p[t.single ? 1 : 0];
-        const bool gather = MODE == 0 && P.gather != nullptr;
+        const Item t = item_at(i_item);
         i_kt = 0;
-        i_nk = t.nk;
-        i_K = P.Kdim;
         i_A = uniform_ptr(reinterpret_cast<const unsigned char *>(gather ? P.A : P.A + (size_t)t.row_begin * P.lda));
-        const uint16_t *B = MODE == 0 && wave >= 2 ? P.B1 : P.B0;  // (pass 0: 32 gate rows, then their 32 up rows)
-        i_B = uniform_ptr(reinterpret_cast<const unsigned char *>(B + (size_t)t.expert * P.N * P.Kdim));
+        i_B = uniform_ptr(reinterpret_cast<const unsigned char *>(B + (size_t)t.expert * N * Kdim));
 #pragma unroll
         for (int i = 0; i < GA; ++i) {
             int r = (wave * GA + i) * 8 + lrow;
@@ -150,17 +105,17 @@ __global__ __launch_bounds__(256, 2) void ffn_mid_kernel(const FfnLaunch L) {
 #pragma unroll
         for (int i = 0; i < GB; ++i) {
             const int r = (wave * GB + i) * 8 + lrow, c = t.n0 + (MODE == 0 ? r & 31 : r);
-            rowB[i] = (uint32_t)(c < P.N ? c : P.N - 1) * (uint32_t)P.Kdim * 2u;
+            rowB[i] = (uint32_t)(c < N ? c : N - 1) * (uint32_t)Kdim * 2u;
         }
     };
     auto request = [&](int stage) __attribute__((always_inline)) {
-        if (i_kt == i_nk) {
+        if (i_kt == nk) {
             ++i_item;
             open_item();
         }
         unsigned char *s = smem + stage * STAGE_BYTES;
         const uint32_t kb = (uint32_t)i_kt * ROWB;
-        const int left = i_K - i_kt * 64;  // a weight chunk past K is taken from the start of its row: it meets A's zeros
+        const int left = Kdim - i_kt * 64;  // a weight chunk past K is taken from the start of its row: it meets A's zeros
 #pragma unroll
         for (int i = 0; i < GB; ++i)
             copy16_to_lds(i_B, rowB[i] + (MODE == 1 && chunkc[i] * 8 >= left ? 0u : kb + (uint32_t)chunkc[i] * 16u),
@@ -181,7 +136,7 @@ __global__ __launch_bounds__(256, 2) void ffn_mid_kernel(const FfnLaunch L) {
         rdB[j] = (uint32_t)A_BYTES + (uint32_t)((MODE == 0 ? j * 32 + wn * 16 : wn * 32 + j * 16) + fr) * ROWB;
     f32x4 acc[MF][2];
     int item = first, kt = 0, stage = 0;
-    MidItem t = mid_item_at<MODE, AR>(L, m, item);
+    Item t = item_at(item);
     int nf = (t.rows - wm * 16 + 31) / 32;  // this wave's fragments that hold rows (<= 0: none)
 #pragma unroll
     for (int i = 0; i < MF; ++i)
@@ -222,10 +177,9 @@ __global__ __launch_bounds__(256, 2) void ffn_mid_kernel(const FfnLaunch L) {
                             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[q][j], a[q][i], acc[i][j], 0, 0, 0);
         }
         stage = stage == NSTAGE - 1 ? 0 : stage + 1;
-        if (++kt < t.nk) continue;
+        if (++kt < nk) continue;
 
         // ---- the item's last slice: results out, accumulators cleared, next item ----
-        const FfnProblem &P = L.p[t.single ? 1 : 0];
         uint16_t *out = P.out + (size_t)t.row_begin * P.ldo;
 #pragma unroll
         for (int i = 0; i < MF; ++i) {
@@ -238,7 +192,7 @@ __global__ __launch_bounds__(256, 2) void ffn_mid_kernel(const FfnLaunch L) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = MODE == 0 ? silu_mul(acc[i][0][e], acc[i][1][e]) : acc[i][j][e];
                     uint2 pk = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-                    if (col >= P.N) {  // pass 0 keeps the padding columns of h at zero for pass 1's k tail
+                    if (col >= N) {  // pass 0 keeps the padding columns of h at zero for pass 1's k tail
                         if (col >= P.zero_to) continue;
                         pk = make_uint2(0, 0);
                     }
@@ -250,60 +204,131 @@ __global__ __launch_bounds__(256, 2) void ffn_mid_kernel(const FfnLaunch L) {
         }
         kt = 0;
         if (++item < last) {
-            t = mid_item_at<MODE, AR>(L, m, item);
+            t = item_at(item);
             nf = (t.rows - wm * 16 + 31) / 32;
         }
     }
 }
 
-template <int MODE>
-static void mid_launch(int tile_rows, const FfnLaunch &L, hipStream_t st) {
-    const dim3 g(8 * MID_WG_PER_XCD), b(256);
-    if (tile_rows == 32)
-        ffn_mid_kernel<MODE, 32, 6><<<g, b, 0, st>>>(L);
-    else if (tile_rows == 64)
-        ffn_mid_kernel<MODE, 64, 4><<<g, b, 0, st>>>(L);
-    else
-        ffn_mid_kernel<MODE, 128, 3><<<g, b, 0, st>>>(L);
+// The single group as a map of one group.
+template <int AR>
+__device__ __forceinline__ GroupMap mid_single_map(const FfnProblem &S) {
+    int lo = S.offsets ? S.offsets[0] : S.row_lo, hi = S.offsets ? S.offsets[1] : S.row_hi;
+    lo = lo < 0 ? 0 : (lo > S.A_cap ? S.A_cap : lo);
+    hi = hi < lo ? lo : (hi > S.A_cap ? S.A_cap : hi);
+    GroupMap m;
+    m.total_mtiles = (hi - lo + AR - 1) / AR;
+    const bool own = lane_id() == 0;
+    m.lo = own ? lo : 0;
+    m.hi = own ? hi : 0;
+    m.tiles = own ? m.total_mtiles : 0;
+    m.first = 0;
+    return m;
 }
 
-// Rows of the tiles this kernel should cut the launch into; 0: the tile kernel is the better one (or the only one).
-// Lower tiles leave more copies in flight, higher ones read the weights (from L2) less often.  Microseconds of a layer call
-// with 32 / 64 / 128 rows / the tile kernel in the pass, r rows per expert on average (16 experts, d 4096, F 688) or n rows
-// of a shared expert (60 experts, d 2048, F 1408 / 5632):
-//   gate/up: r = 25: 74.5 / 72.7 / 79.6 / 87, r = 55: 114 / 91 / 97 / 110, r = 75: 116 / 105 / 99 / 113, r = 125: - / 146 / 128 /
-//     143, r = 175: - / 178 / 172 / 155; n = 64: 137 / 147 / 150 / 156, n = 110: 176 / 162 / 175 / 166, n = 160: 191 / 165 / 172 /
-//     169, n = 200: 232 / 200 / 204 / 185;
-//   down: r = 25: 80 / 74 / 75.5 / 90, r = 40: 90 / 78 / 80 / 94, r = 55: 106 / 96 / 91 / 101, r = 75: 118 / 108 / 98 / 106, r = 100:
-//     - / 118 / 116 / 113; n = 90: 152 / 162 / 162 / 192, n = 131: 173 / 165 / 174 / 204, n = 300: 221 / 194 / 200 / 216,
-//     n = 511: - / - / 210 / 212.
+// How many of an XCD's workgroups walk the single group when there are ragged items as well: a multiple of its chunks (see mid_walk)
+// that leaves the longest walk, in slices, as short as possible.  Lane l tries (l + 1) * chunks.
+__device__ __forceinline__ int mid_single_share(int chunks, int s_items, int kS, int r_items, int kR) {
+    const int n = (lane_id() + 1) * chunks;
+    int cost = 0x7fffffff;
+    if (n < MID_WG_PER_XCD) {
+        const int cs = (s_items + 8 * n - 1) / (8 * n) * kS;
+        const int rest = 8 * (MID_WG_PER_XCD - n), cr = (r_items + rest - 1) / rest * kR;
+        cost = min(max(cs, cr), 0xffffff) << 6 | lane_id();
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) cost = min(cost, __shfl_xor(cost, off));
+    // (chunks is at most 16 here: a single group of more rows takes the tile kernel)
+    return __builtin_amdgcn_readfirstlane(cost == 0x7fffffff ? 1 : ((cost & 63) + 1) * chunks);
+}
+
+// ARR, ARS: rows of the ragged problem's and of the single group's tiles.  The two walk on workgroups of their own, the same number in
+// every XCD (all of the single group's in one XCD made that one finish last: the down pass of 64 tokens 52 against 42 us).
+template <int MODE, int ARR, int ARS>
+__global__ __launch_bounds__(256, 2) void ffn_mid_kernel(const FfnLaunch L) {
+    constexpr int LDS = mid_lds_bytes(ARR) > mid_lds_bytes(ARS) ? mid_lds_bytes(ARR) : mid_lds_bytes(ARS);
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS];
+    __shared__ uint16_t row_of[MODE == 0 ? MID_ROW_TABLE : 1];
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const GroupMap gm = build_group_map<ARR>(L.p[0].offsets, L.has_ragged ? L.p[0].E_local : 0, L.p[0].A_cap);
+    int ns = 0;  // workgroups of an XCD that walk the single group
+    if (L.has_single) {
+        const GroupMap sm = mid_single_map<ARS>(L.p[1]);
+        const int chunks = __builtin_amdgcn_readfirstlane(sm.total_mtiles);
+        const int r_items = L.has_ragged ? __builtin_amdgcn_readfirstlane(gm.total_mtiles) * L.p[0].ntn : 0;
+        if (chunks > 0)
+            ns = r_items == 0 ? MID_WG_PER_XCD
+                              : mid_single_share(chunks, chunks * L.p[1].ntn, (L.p[1].Kdim + 63) / 64, r_items, (L.p[0].Kdim + 63) / 64);
+        if (slot < ns) {
+            if (MODE == 0 && L.p[1].gather) mid_row_table(L.p[1], row_of);  // (one routed group)
+            mid_walk<MODE, ARS>(L.p[1], sm, smem, row_of, xcd * ns + slot, 8 * ns);
+            return;
+        }
+    }
+    if (!L.has_ragged) return;
+    if (MODE == 0 && L.p[0].gather) mid_row_table(L.p[0], row_of);
+    mid_walk<MODE, ARR>(L.p[0], gm, smem, row_of, xcd * (MID_WG_PER_XCD - ns) + slot - ns, 8 * (MID_WG_PER_XCD - ns));
+}
+
+template <int MODE>
+static void mid_launch(int ragged_rows, int single_rows, const FfnLaunch &L, hipStream_t st) {
+    const dim3 g(8 * MID_WG_PER_XCD), b(256);
+#define C2R_MID(ARR, ARS) ffn_mid_kernel<MODE, ARR, ARS><<<g, b, 0, st>>>(L)
+#define C2R_MID_S(ARR)                                             \
+    switch (single_rows) {                                         \
+        case 128: C2R_MID(ARR, 128); break;                        \
+        case 64: C2R_MID(ARR, 64); break;                          \
+        default: C2R_MID(ARR, 32);                                 \
+    }
+    switch (ragged_rows) {
+        case 128: C2R_MID_S(128) break;
+        case 64: C2R_MID_S(64) break;
+        default: C2R_MID_S(32)
+    }
+#undef C2R_MID_S
+#undef C2R_MID
+}
+
+// Whether a launch takes this kernel, and the rows of its ragged and its single tiles; else the tile kernel is the better one (or the only one).
+// Lower tiles leave more copies in flight, higher ones read the weights (from L2) less often.  Microseconds of a layer call with
+// 32 / 64 / 128 rows, r rows per expert on average (16 experts, d 4096, F 688) or n rows of a shared expert (60 experts, d 2048, F 1408 /
+// 5632):
+//   ragged groups alone: r = 6: 72.9 / 74.3 / 86.7, r = 15: 76.7 / 77.5 / 87, r = 25: 90.8 / 82.0 / 90.4, r = 45: 115 / 89 / 95, r = 64: 132 /
+//     108 / 104, r = 88: 150 / 132 / 115, r = 125: 167 / 146 / 131 (tile kernel 143; down pass r = 100: 118 / 116 / 113 with it);
+//   beside a shared expert, ragged and shared tiles of 32+32 / 64+32 / 32+64 / 64+64 rows: n = 24: 107 / 106 / 108 / 108, n = 64: 133 / 134 / 145 /
+//     147, n = 90: 145 / 142 / 147 / 141, n = 131: 163 / 159 / 160 / 161, n = 178: 187 / 190 / 181 / 174; down pass alone n = 300: 197 / 197 /
+//     195 / 187, n = 500: 236 / 228 / 234 / 210 (64+128 216, the tile kernel 212 at 511).  (The skewed groups beside it hold up to eight
+//     times the mean: 64 rows from a mean of 5.)
 // (r counts the rows allotted.  A device that holds a quarter of the experts has a quarter of them in use: its tiles are higher
-// than its rows would ask for, 15 of 60 experts at 131 tokens 65.)
-int ffn_mid_rows(int pass, const FfnLaunch &L) {
-    int rows = 0;
+// than its rows would ask for, 15 of 60 experts at 300 tokens 67.0 / 65.0 / 71.9.)
+constexpr int MID_LOW_BESIDE = 4;
+
+bool ffn_mid_rows(int pass, const FfnLaunch &L, int (&rows)[2]) {
+    rows[0] = rows[1] = 0;
     for (int q = 0; q < 2; ++q) {
         const FfnProblem &P = L.p[q];
         if (!(q == 0 ? L.has_ragged : L.has_single)) continue;
-        if (P.gather && (P.A_cap > MID_ROW_TABLE || P.gather_rows > 65536)) return 0;
-        static constexpr int up_to[2][2][3] = {{{20, 64, 150}, {64, 179, 179}}, {{20, 45, 90}, {100, 340, 511}}};
+        if (P.gather && (P.A_cap > MID_ROW_TABLE || P.gather_rows > 65536)) return false;
+        static constexpr int up_to[2][2][3] = {{{20, 64, 150}, {64, 179, 179}}, {{20, 45, 90}, {100, 511, 511}}};
         const int mean = q == 0 ? P.A_cap / P.E_local : P.A_cap, *most = up_to[pass][q];
-        if (mean > most[2]) return 0;
-        const int fit = mean <= most[0] ? 32 : (mean <= most[1] ? 64 : 128);
-        rows = fit > rows ? fit : rows;
+        if (mean > most[2]) return false;
+        rows[q] = mean <= (q == 0 && L.has_single ? MID_LOW_BESIDE : most[0]) ? 32 : (mean <= most[1] ? 64 : 128);
     }
-    return rows;
+    if (!rows[0]) rows[0] = rows[1];
+    if (!rows[1]) rows[1] = rows[0];
+    return true;
 }
 
-int launch_ffn_mid(int pass, int tile_rows, FfnLaunch L, hipStream_t st) {
+int launch_ffn_mid(int pass, const int (&tile_rows)[2], FfnLaunch L, hipStream_t st) {
     drop_stale_error();
     for (FfnProblem &P : L.p) {
         const int cols = P.zero_to > P.N ? P.zero_to : P.N, bn = pass == 0 ? MID_BR / 2 : MID_BR;
         P.ntn = (cols + bn - 1) / bn;
     }
     if (pass == 0)
-        mid_launch<0>(tile_rows, L, st);
+        mid_launch<0>(tile_rows[0], tile_rows[1], L, st);
     else
-        mid_launch<1>(tile_rows, L, st);
+        mid_launch<1>(tile_rows[0], tile_rows[1], L, st);
     return launch_status();
 }
 

@@ -103,3 +103,37 @@ def test_lower_tiles_of_a_single_group_change_no_bits(c2r, T):
     assert torch.equal(y, y2)
     ref = hs.double() @ sd[0].double().t()
     assert ((ys.double() - ref).abs().max() / ref.abs().max()).item() <= TOL["bf16"]
+
+
+# two problems in one launch, tiles of their own heights and workgroups of their own: routed groups even, skewed, one holding all and
+# none holding any; single groups of one to eight chunks, short and long beside the routed ones
+@pytest.mark.parametrize("T,E,d,F,Fs,sizes", [
+    (20, 10, 128, 64, 1024, [8] * 10), (131, 60, 192, 128, 64, [100, 70] + [6] * 58), (179, 30, 64, 704, 320, [0] * 29 + [716]),
+    (70, 12, 704, 64, 64, [0] * 12), (500, 60, 64, 192, 1408, [400, 129, 65] + [24] * 57), (65, 40, 256, 320, 64, [65, 0, 33, 1] * 10)])
+def test_mid_two_problems_against_each_alone(c2r, T, E, d, F, Fs, sizes):
+    rng = np.random.default_rng(T * E)
+    n = sum(sizes)
+    r = lambda *s: dev((rng.standard_normal(s) * 0.1).astype(np.float32), "bf16")
+    z = lambda rows, cols: torch.zeros(rows, cols, dtype=torch.bfloat16, device="cuda")
+    offsets = dev(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
+    x, wg, wu, wd, sg, su, sd = r(T, d), r(E, F, d), r(E, F, d), r(E, d, F), r(1, Fs, d), r(1, Fs, d), r(1, d, Fs)
+    perm = dev(rng.integers(0, T * 4, size=max(n, 1)).astype(np.int32))
+    cap = max(n, T * 4)
+    assert ffn_kernel(1, 1, T, d) == "mid" or T <= 32
+    h, y, hs, ys = z(cap, F), z(cap, d), z(T, Fs), z(T, d)
+    full = torch.zeros(cap, dtype=torch.int32, device="cuda")
+    full[:n] = perm[:n]
+    c2r.expert_ffn_gate_up_with_shared(x, full, 4, offsets, wg, wu, h, sg, su, hs)
+    c2r.expert_ffn_down_with_shared(h, offsets, wd, y, hs, sd, ys)
+    big = 600 * E + n                               # allotments of the tile kernel
+    xa, h2, y2 = z(big, d), z(big, F), z(big, d)
+    xa[:n] = x[torch.div(full[:n], 4, rounding_mode="floor").long()]
+    c2r.expert_ffn_gate_up(xa, offsets, wg, wu, h2)
+    c2r.expert_ffn_down(h2, offsets, wd, y2)
+    xs, hs2, ys2 = z(3000, d), z(3000, Fs), z(3000, d)
+    xs[:T] = x
+    off = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    c2r.expert_ffn_gate_up(xs, off, sg, su, hs2)
+    c2r.expert_ffn_down(hs2, off, sd, ys2)
+    assert torch.equal(h[:n], h2[:n]) and torch.equal(y[:n], y2[:n]) and not h[n:].any() and not y[n:].any()
+    assert hs.any() and torch.equal(hs, hs2[:T]) and torch.equal(ys, ys2[:T])
