@@ -881,6 +881,21 @@ __global__ __launch_bounds__(ROWMAJOR ? 64 : SEL_WAVES * 64) void route_select_k
     for (int s = 0; s < K; ++s) gates[(size_t)t * K + s] = gates[(size_t)t * K + s] / den;
 }
 
+// The largest of the 64 lanes' values, in every lane.  Every lane must be active.
+__device__ __forceinline__ int wave_max(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int LOWEST = (int)0x80000000;
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1, 3
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2, 3
+    v = __builtin_amdgcn_readlane(v, 63);
+#endif
+    return v;
+}
+
 // Selection from stored logits [T, E] (the profiling pass of Sec. 3.2 routes 2^20 tokens of stored
 // router outputs), for E a multiple of 4 and K <= 4.  What the kernel has to do is stream the
 // logits, so the arithmetic per token is kept small:
@@ -888,17 +903,19 @@ __global__ __launch_bounds__(ROWMAJOR ? 64 : SEL_WAVES * 64) void route_select_k
 //    16 i + 4 sub (64 contiguous bytes per quad and load, every load of a 64-token group in flight
 //    at once), and the values go to LDS transposed, [column][token], the token position XOR-ed with
 //    16 sub so that neither these writes nor the reads of phase 2 meet on a bank.
-//  * phase 2, one lane per token.  A logit becomes an order-preserving integer (-0 counted as +0)
-//    whose low 6 bits are replaced by 63 - column: the largest few of these keys - a chain of one
-//    max and a few med3 per value, no index bookkeeping - are the largest logits WITH their
-//    columns, ties to the lower column, provided the keys' upper 26 bits differ among the ones
-//    kept and the next one below them (then the replaced bits decided nothing).  Without lists the
+//  * phase 2, one lane per token.  The low 6 bits of a logit (-0 stored as +0) are replaced by 63 - column: the largest few of these
+//    keys, compared as floats - a chain of one max and a few med3 per value, no index bookkeeping - are the largest logits WITH
+//    their columns, provided the keys' upper 26 bits differ among the ones kept and the next one below them (then the replaced
+//    bits decided nothing).  Without lists the
 //    chain keeps five keys of the E columns: the token's K experts and the guard.  With lists it
 //    keeps two (top-1 and guard), then walks the top-1's collaborator list ONLY (built once per
 //    workgroup from the 64-bit masks, ascending: duplicates, the expert itself and out-of-range
 //    entries are gone) keeping four: Tc visits instead of (K - 1) E.
 //  * A token that fails the proviso, or has a NaN or an infinity among its logits, takes the
-//    literal scan (first one standing unless a later one is strictly larger) for every slot.
+//    literal scan (first one standing unless a later one is strictly larger) for every slot.  Of 2^20 tokens of 60 normal logits some
+//    300 do, one lane's scan is 15 us of LDS reads one after the other, and a launch ends with its last wave: the whole wave
+//    scans such a token, a lane per column (2^20 tokens 60 -> 51.6 us, 65536 tokens 20 -> 14.6; with the keys compared as floats instead
+//    of made order-preserving integers first, three instructions of ten per logit, 48.8 and 13.7; the stream alone 40).
 // COUNT: the token's expert pairs are added to the co-activation matrix (Eq. 2) on the spot - an LDS
 // histogram per workgroup as in coact.hip, one integer atomic per entry at the end - and either
 // output may be left out (null): the profiling pass wants the counts, not the selections.
@@ -956,7 +973,7 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
         nmax = __builtin_amdgcn_readfirstlane(maxcnt);
     }
 
-    constexpr int EMPTY = (int)0x80000000;  // below every key
+    constexpr int EMPTY = (int)0xff800000;  // minus infinity: below the key of every finite logit
     // A 64-token group is one contiguous run of 64 E floats = E / 4 wave-wide 16-byte loads; lane l's
     // piece of load u holds columns col .. col + 3 of token tok, the same in every group.  Byte offsets
     // into tile_mem: of that piece's first float (the others follow 256 bytes apart), and of this
@@ -974,15 +991,19 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
     };
     // this token's logit of column c (any c, per lane)
     auto logit_of = [&](int c) __attribute__((always_inline)) { return lds_f(lanebase ^ code_of(c)); };
-    auto key_of = [](float v, int c) __attribute__((always_inline)) {
-        const int b = __float_as_int(v);
-        return ((b ^ ((b >> 31) & 0x7fffffff)) & ~63) | (63 - c);
+    auto key_of = [](float v, int c) __attribute__((always_inline)) { return (__float_as_int(v) & ~63) | (63 - c); };
+    // (as instructions: the compiler would first quiet what it takes for possible NaNs)
+    auto max2 = [](int a, int b) __attribute__((always_inline)) {
+        int d;
+        asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+        return d;
     };
     auto med3 = [](int a, int b, int c) __attribute__((always_inline)) {
         int d;
-        asm("v_med3_i32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+        asm("v_med3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
         return d;
     };
+    auto apart = [](int a, int b) __attribute__((always_inline)) { return ((a ^ b) & ~63) != 0; };
 
     // all loads of a 64-token group go out together (a piece past the end of the logits re-reads the start)
     f32x4 q[4 * NV];
@@ -1031,7 +1052,7 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
                 chk = __builtin_fmaf(v, 0.0f, chk);  // NaN once a NaN or an infinity went in
                 const int kk = key_of(v, c);
                 int nk[NKEEP];
-                nk[0] = max(k[0], kk);
+                nk[0] = max2(k[0], kk);
 #pragma unroll
                 for (int u = 1; u < NKEEP; ++u) nk[u] = med3(k[u - 1], k[u], kk);  // (k[0] >= k[1] >= ... throughout)
 #pragma unroll
@@ -1040,7 +1061,7 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
         }
         bool literal = chk != chk;
 #pragma unroll
-        for (int u = 0; u + 1 < NKEEP; ++u) literal = literal || !((k[u] >> 6) > (k[u + 1] >> 6) || k[u] == EMPTY);
+        for (int u = 0; u + 1 < NKEEP; ++u) literal = literal || !(apart(k[u], k[u + 1]) || k[u] == EMPTY);
         int es[4] = {-1, -1, -1, -1};
         float vs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         es[0] = 63 - (k[0] & 63);
@@ -1058,7 +1079,7 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int kk = kq + j < n ? key_of(v[j], (int)(code[j] >> 8)) : EMPTY;
-                    const int n0 = max(m[0], kk), n1 = med3(m[0], m[1], kk), n2 = med3(m[1], m[2], kk),
+                    const int n0 = max2(m[0], kk), n1 = med3(m[0], m[1], kk), n2 = med3(m[1], m[2], kk),
                               n3 = med3(m[2], m[3], kk);
                     m[0] = n0;
                     m[1] = n1;
@@ -1068,7 +1089,7 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
             }
 #pragma unroll
             for (int u = 0; u < 3; ++u) {
-                literal = literal || !((m[u] >> 6) > (m[u + 1] >> 6) || m[u] == EMPTY);
+                literal = literal || !(apart(m[u], m[u + 1]) || m[u] == EMPTY);
                 es[u + 1] = m[u] == EMPTY ? -1 : 63 - (m[u] & 63);
             }
         } else {
@@ -1077,42 +1098,7 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
         }
         float gs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         float den = 1.0f;
-        if (literal) {
-            // the literal scan, slot by slot (a NaN stands if it is the first allowed expert)
-            auto pick_row = [&](uint64_t mm, int &bi, float &bv) {
-                bi = -1;
-                bv = 0.0f;
-                for (int e = 0; e < E; ++e) {
-                    const float v = logit_of(e);
-                    const bool take = ((mm >> e) & 1ull) != 0 && (bi < 0 || v > bv);
-                    bv = take ? v : bv;
-                    bi = take ? e : bi;
-                }
-            };
-            int e0;
-            float v0;
-            pick_row(all, e0, v0);
-            uint64_t mm = all & ~(1ull << e0);
-            if constexpr (LISTS) mm = mask_tab[e0];
-            es[0] = e0;
-            gs[0] = expf(v0 - v0);
-            den = gs[0];
-#pragma unroll
-            for (int s2 = 1; s2 < 4; ++s2) {
-                es[s2] = -1;
-                if (s2 < K) {
-                    int e;
-                    float v;
-                    pick_row(mm, e, v);
-                    if (e >= 0) {
-                        mm &= ~(1ull << e);
-                        gs[s2] = expf(v - v0);
-                    }
-                    es[s2] = e;
-                    den += gs[s2];
-                }
-            }
-        } else {
+        if (!literal) {
 #pragma unroll
             for (int s2 = 1; s2 < 4; ++s2)
                 if (s2 >= K) es[s2] = -1;
@@ -1127,6 +1113,52 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
                         if (es[s2] >= 0) gs[s2] = expf(vs[s2] - vs[0]);
                         den += gs[s2];
                     }
+            }
+        }
+        // The tokens that need the literal scan, one after the other, each by the whole wave (lane = column).  Its rule - first one
+        // standing unless a later one is strictly larger - picks the first allowed column if that holds a NaN, else the largest
+        // number, the lowest column among equals.
+        for (uint64_t todo = __ballot(literal && t < T); todo; todo &= todo - 1) {
+            const int tk = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)todo) - 1);
+            const float v = lds_f((uint32_t)(wave * TILE_BYTES + tk * 4) ^ code_of(lane < E ? lane : 0));
+            const int bits = __float_as_int(v), key = bits ^ ((bits >> 31) & 0x7fffffff);
+            auto pick_row = [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
+                bi = -1;
+                bv = 0.0f;
+                if (mm == 0) return;
+                bi = __ffsll((unsigned long long)mm) - 1;
+                bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
+                if (bv != bv) return;
+                const bool in = ((mm >> lane) & 1ull) != 0 && v == v;
+                const int best = wave_max(in ? key : (int)0x80000000);
+                bi = __ffsll((unsigned long long)__ballot(in && key == best)) - 1;
+                bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
+            };
+            int et[4] = {-1, -1, -1, -1};
+            float gt[4] = {0.0f, 0.0f, 0.0f, 0.0f}, v0;
+            pick_row(all, et[0], v0);
+            uint64_t mm = all & ~(1ull << et[0]);
+            if constexpr (LISTS) mm = mask_tab[et[0]];
+            gt[0] = expf(v0 - v0);
+            float dt = gt[0];
+#pragma unroll
+            for (int s2 = 1; s2 < 4; ++s2)
+                if (s2 < K) {
+                    float vt;
+                    pick_row(mm, et[s2], vt);
+                    if (et[s2] >= 0) {
+                        mm &= ~(1ull << et[s2]);
+                        gt[s2] = expf(vt - v0);
+                    }
+                    dt += gt[s2];
+                }
+            if (lane == tk) {
+                den = dt;
+#pragma unroll
+                for (int s2 = 0; s2 < 4; ++s2) {
+                    es[s2] = et[s2];
+                    gs[s2] = gt[s2];
+                }
             }
         }
         if (t < T) {
