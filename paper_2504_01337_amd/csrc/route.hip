@@ -565,6 +565,22 @@ __device__ __forceinline__ void merge_lower(int upper, int &bi, float &bv) {
 #endif
 }
 
+// The bitwise or of a row of sixteen lanes' values, in each of them.
+__device__ __forceinline__ uint64_t or_of_sixteen(uint64_t m) {
+    int lo = (int)(uint32_t)m, hi = (int)(uint32_t)(m >> 32);
+#if defined(__HIP_DEVICE_COMPILE__)
+    lo |= __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xf, 0xf, true);   // quad_perm 1,0,3,2
+    hi |= __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xf, 0xf, true);
+    lo |= __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xf, 0xf, true);   // quad_perm 2,3,0,1
+    hi |= __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xf, 0xf, true);
+    lo |= __builtin_amdgcn_mov_dpp(lo, 0x141, 0xf, 0xf, true);  // row_half_mirror
+    hi |= __builtin_amdgcn_mov_dpp(hi, 0x141, 0xf, 0xf, true);
+    lo |= __builtin_amdgcn_mov_dpp(lo, 0x140, 0xf, 0xf, true);  // row_mirror
+    hi |= __builtin_amdgcn_mov_dpp(hi, 0x140, 0xf, 0xf, true);
+#endif
+    return (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32);
+}
+
 // ROWMAJOR (stored logits [T, E]): one wave per 64 tokens.  Otherwise (chunk partials):
 // SEL_WAVES waves per 64 tokens; each sums the chunks of a quarter of the experts (the
 // loads of one wave alone cover the memory latency four times worse) and leaves its
@@ -1371,9 +1387,14 @@ __global__ __launch_bounds__(FIN_WAVES * 64) void route_finish_small_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint64_t all = E >= 64 ? ~0ull : ((1ull << E) - 1ull);
 
-    // (a thread's first list entry is requested ahead of the partial sums: one trip to memory instead of two)
-    const int nlist = collab_idx ? E * Tc : 0;
-    const int32_t listed = collab_idx ? collab_idx[min(tid, nlist - 1)] : 0;
+    // (sixteen threads per expert walk its list; their first entries are requested ahead of the partial sums: one trip to memory instead
+    // of two)
+    const int le = tid >> 4, lq = tid & 15, llast = E * Tc - 1;
+    int32_t listed[2];
+    if (collab_idx) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) listed[u] = collab_idx[min(le * Tc + lq + 16 * u, llast)];
+    }
     // ---- logits: a thread adds up the chunk results (left to right) of one expert and four tokens ----
     {
         const int e = tid >> 4, quad = tid & 15;
@@ -1395,18 +1416,23 @@ __global__ __launch_bounds__(FIN_WAVES * 64) void route_finish_small_kernel(
         }
     }
     // ---- collaborator masks and the slot of every expert ----
+    {
+        uint64_t m = collab_idx ? 0ull : all;
+        if (collab_idx) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (lq + 16 * u < Tc && listed[u] >= 0 && listed[u] < E) m |= 1ull << listed[u];
+            for (int i = lq + 32; i < Tc; i += 16) {
+                const int v = le < E ? collab_idx[le * Tc + i] : -1;
+                if (v >= 0 && v < E) m |= 1ull << v;
+            }
+            m = or_of_sixteen(m);
+        }
+        if (lq == 0) mask_tab[le] = m & ~(1ull << le);
+    }
     if (tid < C2R_MAX_E) {
-        mask_tab[tid] = (!collab_idx && tid < E) ? all & ~(1ull << tid) : 0ull;
         const int s = tid < E ? (local_slot ? local_slot[tid] : tid) : -1;
         slot_tab[tid] = s >= 0 && s < E_local ? s : -1;
-    }
-    if (collab_idx) {
-        __syncthreads();
-        for (int i = tid; i < nlist; i += FIN_WAVES * 64) {
-            const int v = i == tid ? listed : collab_idx[i], e = i / Tc;
-            if (v >= 0 && v < E && v != e)
-                atomicOr(reinterpret_cast<unsigned long long *>(&mask_tab[e]), 1ull << v);
-        }
     }
     __syncthreads();
 
@@ -1445,6 +1471,31 @@ __global__ __launch_bounds__(FIN_WAVES * 64) void route_finish_small_kernel(
     //      order (the stable order of a = t * K + s) ----
     const int A = T * K;
     if (tid < A) gates[tid] = gbuf[tid] / den_of[tid / K];
+    if (A <= 32) {
+        // one wave, lane = assignment and lane = slot at once: every assignment's slot passes all lanes by (1 token of 60 experts: the
+        // kernel 8.4 -> 6.8 us with the masks; at 64 assignments the loops below are the faster ones)
+        if (wave != 0) return;
+        const int slot = lane < A ? slots[lane] : -1, mine = slot >= 0 ? slot : 64 + lane;  // (past every slot, no two alike)
+        int pos = 0, n = 0, before = 0;
+        for (int b0 = 0; b0 < A; b0 += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int s = __builtin_amdgcn_readlane(mine, b0 + u);
+                pos += s < mine || (s == mine && b0 + u < lane);
+                n += s == lane;
+                before += s < lane;
+            }
+        }
+        const int valid = __popcll(__ballot(slot >= 0));
+        if (lane < A) inv_perm[lane] = slot >= 0 ? pos : -1;
+        if (slot >= 0) perm[pos] = lane;
+        if (lane < E_local) {
+            counts[lane] = n;
+            offsets[lane] = before;
+            if (lane == E_local - 1) offsets[E_local] = valid;
+        }
+        return;
+    }
     for (int s = wave; s < E_local; s += FIN_WAVES) {
         int n = 0;
         for (int a0 = 0; a0 < A; a0 += 64) n += __popcll(__ballot(a0 + lane < A && slots[a0 + lane] == s));
