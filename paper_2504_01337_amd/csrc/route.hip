@@ -55,20 +55,23 @@ __global__ __launch_bounds__(256) void pack_router_kernel(const float *__restric
 // 64-expert vector per token (256 bytes) instead of one per chunk (2 KB at d = 2048, written
 // here and read back by the selection).  For batches with at least one wave tile per SIMD of
 // the chip; smaller batches need the chunks as separate workgroups to fill it.
-template <bool BF16, int TE, int NWV, int TQ, bool MFMA, bool ALLCHUNKS = false>
-__global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_partial_kernel(const void *__restrict__ x,
+// HALVES: a token tile's two blocks of 32 experts by a wave each, half the tokens per workgroup.
+template <bool BF16, int TE, int NWV, int TQ, bool MFMA, bool ALLCHUNKS = false, bool HALVES = false>
+__global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) void route_partial_kernel(const void *__restrict__ x,
                                                                 const float *__restrict__ W, int ldw,
                                                                 int ep, int64_t T, int d, int nchunk, int cpw,
                                                                 int64_t ntiles,
                                                                 float *__restrict__ part) {
-    constexpr int EPAD = 8 * TE;         // experts covered by a wave
+    constexpr int EPAD = 8 * TE;         // experts covered by a wave (HALVES: by two)
+    constexpr int NT = HALVES ? NWV / 2 : NWV;  // wave tiles of tokens in a workgroup
+    static_assert(!HALVES || (MFMA && EPAD == 64), "halves of 32 experts");
     constexpr int TOK = 8 * TQ;          // tokens covered by a wave
     constexpr int KS = MFMA && !BF16 ? 16 : 32;  // k per staged sub-tile (64 bytes of a token's row on the matrix pipe)
     constexpr int VEC = BF16 ? 8 : 4;    // elements per 16-byte vector of x
     constexpr int ESZ = BF16 ? 2 : 4;
     constexpr int XV = KS / VEC;         // 16-byte vectors per token per sub-tile
     constexpr int XPITCH = KS * ESZ + 16;  // bytes; token rows 8 apart land on distinct bank groups
-    constexpr int XLOADS = TOK * XV / 64;  // vectors per lane per sub-tile
+    constexpr int XLOADS = TOK * XV / 64 / (NWV / NT);  // vectors per lane per sub-tile
     static_assert(XLOADS >= 1 && 64 % TOK == 0, "a wave loads whole vectors; wave tiles divide the 64-token tile");
     constexpr int WF4 = KS * EPAD / 4;     // float4 per W sub-tile
     constexpr int WLOADS = (WF4 + NWV * 64 - 1) / (NWV * 64);
@@ -84,21 +87,24 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
     // the W rows instead, 32 floats per 64-wide row, changed neither the counter nor the time.)
     constexpr int WPITCH = EPAD;
     __shared__ __attribute__((aligned(16))) float Wl[NBUF][KS][WPITCH];
-    __shared__ __attribute__((aligned(16))) unsigned char Xl[NBUF][NWV][TOK * XPITCH];
+    __shared__ __attribute__((aligned(16))) unsigned char Xl[NBUF][NT][TOK * XPITCH];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tl = lane & 7, el = lane >> 3;
     const int64_t nwt = ntiles * (64 / TOK);       // wave tiles
-    const int64_t ngroups = (nwt + NWV - 1) / NWV;
+    const int64_t ngroups = (nwt + NT - 1) / NT;
     const int64_t tgroup = blockIdx.x % ngroups;  // token tiles fastest: neighbours share W rows in L2
     const int chunk_first = ALLCHUNKS ? 0 : (int)(blockIdx.x / ngroups) * cpw;
     const int chunk_last = ALLCHUNKS ? nchunk - 1 : min(chunk_first + cpw, nchunk) - 1;
-    const int64_t wt = tgroup * NWV + wave;        // may be >= nwt: such a wave only helps load W
+    // this wave's token tile and, with HALVES, its experts; the tile whose x it brings, and the first of its vectors
+    const int tt = HALVES ? wave % NT : wave, eo = HALVES ? wave / NT * 32 : 0, xt = HALVES ? wave / 2 : wave;
+    const int x0 = HALVES ? (wave & 1) * 64 : 0;
+    const int64_t wt = tgroup * NT + tt;           // may be >= nwt: such a wave only helps load W
     const bool live = wt < nwt;
     int chunk = chunk_first, k_begin = chunk * C2R_CANON_CHUNK;
     int k_end = min(d, k_begin + C2R_CANON_CHUNK);
-    const int64_t t0 = wt * TOK;
+    const int64_t t0 = (tgroup * NT + xt) * TOK;   // of the tile whose x this wave brings
     const unsigned char *xb = static_cast<const unsigned char *>(x);
 
     // global loads of a sub-tile are held in registers until its LDS buffer is free; several sets
@@ -127,7 +133,7 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
         }
 #pragma unroll
         for (int i = 0; i < XLOADS; ++i) {
-            const int idx = lane + i * 64;
+            const int idx = x0 + lane + i * 64;
             const int tok = idx / XV, c = idx % XV;
             int64_t t = t0 + tok;
             t = t < T ? t : T - 1;  // rows past the end (and dead waves) re-read a valid token
@@ -148,7 +154,7 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
     const int64_t tb = t0 < T ? t0 : T - 1;  // wave-uniform; dead waves re-read valid tokens
 #pragma unroll
     for (int i = 0; i < XLOADS; ++i) {
-        const int idx = lane + i * 64;
+        const int idx = x0 + lane + i * 64;
         const int64_t room = T - 1 - tb, tok = idx / XV < room ? idx / XV : room;
         xoff[i] = (uint32_t)((tok * d + (idx % XV) * VEC) * ESZ);
     }
@@ -162,13 +168,13 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
         }
 #pragma unroll
         for (int i = 0; i < XLOADS; ++i) {
-            const int idx = lane + i * 64;
-            *reinterpret_cast<u32x4 *>(&Xl[buf][wave][(idx / XV) * XPITCH + (idx % XV) * 16]) = xreg[i];
+            const int idx = x0 + lane + i * 64;
+            *reinterpret_cast<u32x4 *>(&Xl[buf][xt][(idx / XV) * XPITCH + (idx % XV) * 16]) = xreg[i];
         }
     };
 
     typedef float f32x16 __attribute__((ext_vector_type(16)));
-    constexpr int NEB = MFMA ? EPAD / 32 : 1, NTB = MFMA ? TOK / 32 : 1;  // 32-expert / 32-token blocks
+    constexpr int NEB = MFMA ? EPAD / 32 / (NWV / NT) : 1, NTB = MFMA ? TOK / 32 : 1;  // 32-expert / 32-token blocks
     static_assert(!MFMA || (EPAD % 32 == 0 && TOK % 32 == 0), "whole 32 x 32 blocks");
     f32x16 macc[NEB][NTB];
 #pragma unroll
@@ -191,10 +197,10 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
             auto pair = [&](int kp) __attribute__((always_inline)) {
                 float wv[NEB], xv[NTB];
 #pragma unroll
-                for (int a = 0; a < NEB; ++a) wv[a] = Wl[buf][2 * kp + mh][a * 32 + mc];
+                for (int a = 0; a < NEB; ++a) wv[a] = Wl[buf][2 * kp + mh][eo + a * 32 + mc];
 #pragma unroll
                 for (int b = 0; b < NTB; ++b) {
-                    const unsigned char *row = &Xl[buf][wave][(b * 32 + mc) * XPITCH];
+                    const unsigned char *row = &Xl[buf][tt][(b * 32 + mc) * XPITCH];
                     if (BF16) {  // one word holds x[k] (low half) and x[k+1] (high half)
                         const uint32_t word = *reinterpret_cast<const uint32_t *>(row + kp * 4);
                         xv[b] = __uint_as_float(mh ? (word & 0xffff0000u) : (word << 16));
@@ -216,10 +222,10 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
 #pragma unroll
                 for (int kp = 0; kp < KS / 2; ++kp)
 #pragma unroll
-                    for (int a = 0; a < NEB; ++a) wv[kp][a] = Wl[buf][2 * kp + mh][a * 32 + mc];
+                    for (int a = 0; a < NEB; ++a) wv[kp][a] = Wl[buf][2 * kp + mh][eo + a * 32 + mc];
 #pragma unroll
                 for (int b = 0; b < NTB; ++b) {
-                    const unsigned char *row = &Xl[buf][wave][(b * 32 + mc) * XPITCH];
+                    const unsigned char *row = &Xl[buf][tt][(b * 32 + mc) * XPITCH];
 #pragma unroll
                     for (int kp = 0; kp < KS / 2; ++kp) {
                         if (BF16) {
@@ -246,7 +252,7 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
             uint4 xp[TQ];
 #pragma unroll
             for (int q = 0; q < TQ; ++q)
-                xp[q] = *reinterpret_cast<const uint4 *>(&Xl[buf][wave][(tl + 8 * q) * XPITCH + v * 16]);
+                xp[q] = *reinterpret_cast<const uint4 *>(&Xl[buf][tt][(tl + 8 * q) * XPITCH + v * 16]);
 #pragma unroll
             for (int u = 0; u < VEC; ++u) {
                 float wv[TE];
@@ -268,7 +274,7 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
     float *const dst_tile = part + ((size_t)tile * (ALLCHUNKS ? 1 : nchunk) * ep) * 64 + (wt % (64 / TOK)) * TOK;
     auto store_sums = [&](const f32x16 (&v)[NEB][NTB], int c) __attribute__((always_inline)) {
         float *dst = dst_tile + (size_t)c * ep * 64;
-        uint32_t at = (uint32_t)(mh * 256 + mc);  // (opaque: the 32 addresses are not held in registers across the chunks)
+        uint32_t at = (uint32_t)(eo * 64 + mh * 256 + mc);  // (opaque: the 32 addresses are not held in registers across the chunks)
         asm volatile("" : "+v"(at));
         // register i of a 32 x 32 block: expert (i/4)*8 + 4*(lane/32) + i%4, token lane%32
 #pragma unroll
@@ -278,7 +284,7 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int e = a * 32 + (i / 4) * 8 + i % 4;
-                    if (e + mh * 4 < ep) dst[at + (uint32_t)(e * 64 + b * 32)] = v[a][b][i];
+                    if (eo + e + mh * 4 < ep) dst[at + (uint32_t)(e * 64 + b * 32)] = v[a][b][i];
                 }
     };
     // A chunk's sums are complete: out to scratch, or onto the sum of the chunks before it - left to right, plain fp32 adds,
@@ -321,10 +327,10 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
 #pragma unroll
             for (int kp = 0; kp < KS / 2; ++kp)
 #pragma unroll
-                for (int a = 0; a < NEB; ++a) o.w[kp][a] = Wl[buf][2 * kp + mh][a * 32 + mc];
+                for (int a = 0; a < NEB; ++a) o.w[kp][a] = Wl[buf][2 * kp + mh][eo + a * 32 + mc];
 #pragma unroll
             for (int b = 0; b < NTB; ++b) {
-                const unsigned char *row = &Xl[buf][wave][(b * 32 + mc) * XPITCH];
+                const unsigned char *row = &Xl[buf][tt][(b * 32 + mc) * XPITCH];
 #pragma unroll
                 for (int kp = 0; kp < KS / 2; ++kp)  // bf16: the word holds x[k] (low) and x[k+1] (high)
                     o.x[kp][b] = *reinterpret_cast<const uint32_t *>(row + (BF16 ? kp : 2 * kp + mh) * 4);
@@ -368,8 +374,8 @@ __global__ __launch_bounds__(NWV * 64, (MFMA && TQ == 4) ? 2 : 1) void route_par
                 }
 #pragma unroll
                 for (int i = 0; i < XLOADS; ++i) {
-                    const int idx = lane + i * 64;
-                    *reinterpret_cast<u32x4 *>(&Xl[buf][wave][(idx / XV) * XPITCH + (idx % XV) * 16]) = xv[i];
+                    const int idx = x0 + lane + i * 64;
+                    *reinterpret_cast<u32x4 *>(&Xl[buf][xt][(idx / XV) * XPITCH + (idx % XV) * 16]) = xv[i];
                 }
             };
             Ops O[2];
@@ -1679,16 +1685,23 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
     const bool wide = ntiles * L.nchunk >= 2048 && te == 1;
     constexpr int NWV = 4;
     const int64_t nwt = wide ? ntiles : ntiles * 2;
-    // With at least one 32-token wave tile per SIMD of the chip (1024), a workgroup on the matrix
-    // pipe walks all the chunks of its tokens and keeps the running sum in registers: scratch then
-    // holds ONE vector per token instead of one per chunk.  Smaller batches need the chunks as
-    // separate workgroups to fill the chip.
-    const bool all_chunks = !wide && te > 1 && nwt >= 1024 && L.nchunk > 1;
+    // With about one 32-token wave tile per SIMD of the chip (1024), a workgroup on the matrix pipe walks all the chunks of its tokens
+    // and keeps the running sum in registers: scratch then holds ONE vector per token instead of one per chunk.  Smaller
+    // batches need the chunks as separate workgroups to fill the chip.  Microseconds of the stage, chunks apart / together: 60 experts,
+    // d 2048: 24000 tokens 75 / 85, 26000 tokens 92 / 85.5, 30000 tokens 96 / 86.5; d 4096, 26000 tokens 158 / 156; 16 experts, d 4096: 26000
+    // tokens 92 / 103, 30000 tokens 104 / 103.5.
+    const bool all_chunks = !wide && te > 1 && nwt >= (te == 8 ? 784 : 1024) && L.nchunk > 1;
     const int nchunk_out = all_chunks ? 1 : L.nchunk;
     // Chunks a workgroup walks otherwise: two where that still makes a workgroup per CU (16384 tokens of 60 experts, d 2048: the
     // stage 53.9 us with one, 51.6 with two, 53.5 with four; 8192 tokens of 16 experts, d 4096: 32.5 / 31.1 / 33.7).
     const int64_t ngroups = (nwt + NWV - 1) / NWV;
     const int cpw = all_chunks ? L.nchunk : (te > 1 && ngroups * ((L.nchunk + 1) / 2) >= 256) ? 2 : 1;
+    // Workgroups of 128 tokens come in rounds of the chip's CUs, and the first batches past a round (or two) leave most of the last one
+    // empty: workgroups of 64 tokens, their waves 32 experts each, make it one of half the length.  (33000 tokens 147 / 124 us,
+    // 48000 tokens 149 / 126, 72000 tokens 221 / 201, fp32 33000 tokens 152 / 119; full rounds cost 4 to 9 % more that way, x
+    // being read by two waves: 32768 tokens 86.5 / 90, 65536 tokens 154 / 167.)
+    const int64_t half_rounds = (ngroups + 127) / 128;
+    const bool halves = all_chunks && te == 8 && (half_rounds == 3 || half_rounds == 5);
     const int64_t nblk = ngroups * ((L.nchunk + cpw - 1) / cpw);
     if (nblk >= (1ll << 31)) return C2R_ERR_UNSUPPORTED;
     // more than 8 experts: the matrix pipe, a wave covering 32 or 64 experts (columns past the packed
@@ -1699,9 +1712,14 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
 #define C2R_ROUTE_LAUNCH_ALL(BF, TE, NWV, TQ)                                                          \
     route_partial_kernel<BF, TE, NWV, TQ, true, true><<<dim3((unsigned)nblk), dim3(NWV * 64), 0, st>>>(  \
         x, W, ldw, L.EP, T, d, L.nchunk, cpw, ntiles, part)
+#define C2R_ROUTE_LAUNCH_HALVES(BF)                                                                              \
+    route_partial_kernel<BF, 8, NWV, 4, true, true, true>                                                          \
+        <<<dim3((unsigned)((nwt + NWV / 2 - 1) / (NWV / 2))), dim3(NWV * 64), 0, st>>>(x, W, ldw, L.EP, T, d, L.nchunk, cpw, \
+                                                                                       ntiles, part)
 #define C2R_ROUTE_TE(BF, NWV, TQ)                                     \
     if (all_chunks) {                                                 \
-        if (te == 8) { C2R_ROUTE_LAUNCH_ALL(BF, 8, NWV, TQ); }        \
+        if (halves) { C2R_ROUTE_LAUNCH_HALVES(BF); }                  \
+        else if (te == 8) { C2R_ROUTE_LAUNCH_ALL(BF, 8, NWV, TQ); }        \
         else { C2R_ROUTE_LAUNCH_ALL(BF, 4, NWV, TQ); }                \
     } else                                                            \
     switch (te) {                                                     \
@@ -1717,6 +1735,7 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
     }
 #undef C2R_ROUTE_TE
 #undef C2R_ROUTE_LAUNCH_ALL
+#undef C2R_ROUTE_LAUNCH_HALVES
 #undef C2R_ROUTE_LAUNCH
     return launch_select(part, L.EP, nchunk_out, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out, st);
 }
