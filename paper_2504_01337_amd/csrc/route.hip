@@ -918,6 +918,163 @@ __device__ __forceinline__ int wave_max(int v) {
     return v;
 }
 
+// One token's selection by the literal rule - first one standing unless a later one is strictly larger - by the whole wave: lane =
+// column, v its logit, `all` the columns, mask_tab the collaborators of every expert or null.  The rule picks the first allowed column if
+// that holds a NaN, else the largest number, the lowest column among equals.  Every lane must be active; results in every lane.
+__device__ __forceinline__ void literal_scan(float v, int K, uint64_t all, const uint64_t *mask_tab, int (&et)[4], float (&gt)[4],
+                                             float &den) {
+    const int lane = lane_id(), bits = __float_as_int(v), key = bits ^ ((bits >> 31) & 0x7fffffff);
+    auto pick_row = [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
+        bi = -1;
+        bv = 0.0f;
+        if (mm == 0) return;
+        bi = __ffsll((unsigned long long)mm) - 1;
+        bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
+        if (bv != bv) return;
+        const bool in = ((mm >> lane) & 1ull) != 0 && v == v;
+        const int best = wave_max(in ? key : (int)0x80000000);
+        bi = __ffsll((unsigned long long)__ballot(in && key == best)) - 1;
+        bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
+    };
+    float v0;
+    pick_row(all, et[0], v0);
+    uint64_t mm = mask_tab ? mask_tab[et[0]] : all & ~(1ull << et[0]);
+    gt[0] = expf(v0 - v0);
+    den = gt[0];
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+        et[s] = -1;
+        gt[s] = 0.0f;
+        if (s < K) {
+            float vt;
+            pick_row(mm, et[s], vt);
+            if (et[s] >= 0) {
+                mm &= ~(1ull << et[s]);
+                gt[s] = expf(vt - v0);
+            }
+            den += gt[s];
+        }
+    }
+}
+
+// The keys of the selections below: a logit (-0 made +0) whose low 6 bits are replaced by 63 - column, compared as floats (as
+// instructions: the compiler would first quiet what it takes for possible NaNs).
+constexpr int KEY_EMPTY = (int)0xff800000;  // minus infinity: below the key of every finite logit
+__device__ __forceinline__ int key_of(float v, int c) { return (__float_as_int(v) & ~63) | (63 - c); }
+__device__ __forceinline__ int key_max(int a, int b) {
+    int d;
+    asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+__device__ __forceinline__ int key_med3(int a, int b, int c) {
+    int d;
+    asm("v_med3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ bool keys_apart(int a, int b) { return ((a ^ b) & ~63) != 0; }
+
+// Top-K, K <= 4, from ONE chunk result per token ([tile][expert][64 tokens]), without lists: a wave per 64 tokens, lane = token, its
+// logits in registers, chosen by the keyed chain of route_select_rows_kernel below, the literal scan where that cannot decide.
+// Bound by the launch and two trips to memory; the stage with route_select_kernel / with this: 60 experts, d 2048: 32768 tokens 87.0 / 84.0,
+// 65536 tokens 155 / 150; 16 experts, 32768 tokens 103.8 / 102.4.  (With lists, the largest two keys and a second chain over the
+// first one's list, it was no faster: 15.6 against 12.7 us for the kernel at 32768 tokens.)
+template <int EP>
+__global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__restrict__ part, const float *__restrict__ bias, int64_t T,
+                                                               int E, int K, int32_t *__restrict__ topk_idx,
+                                                               float *__restrict__ gates, float *__restrict__ logits_out) {
+    const int lane = threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * 64 + lane;
+    const uint64_t all = E >= 64 ? ~0ull : ((1ull << E) - 1ull);
+    const float *p = part + (size_t)blockIdx.x * EP * 64;
+    float l[EP];
+#pragma unroll
+    for (int e = 0; e < EP; ++e) l[e] = p[e * 64 + lane];
+    if (bias) {
+#pragma unroll
+        for (int e = 0; e < EP; ++e)
+            if (e < E) l[e] = l[e] + bias[e];
+    }
+    if (logits_out && t < T) {
+#pragma unroll
+        for (int e = 0; e < EP; ++e)
+            if (e < E) logits_out[(size_t)t * E + e] = l[e];
+    }
+    auto logit_of = [&](int e) __attribute__((always_inline)) { return bias ? p[e * 64 + lane] + bias[e] : p[e * 64 + lane]; };
+    constexpr int NKEEP = 5;
+    int k[NKEEP];
+#pragma unroll
+    for (int u = 0; u < NKEEP; ++u) k[u] = KEY_EMPTY;
+    float chk = 0.0f;
+#pragma unroll
+    for (int e = 0; e < EP; ++e)
+        if (e < E) {  // (uniform)
+            const float v = l[e] + 0.0f;
+            chk = __builtin_fmaf(v, 0.0f, chk);  // NaN once a NaN or an infinity went in
+            const int kk = key_of(v, e);
+            int nk[NKEEP];
+            nk[0] = key_max(k[0], kk);
+#pragma unroll
+            for (int u = 1; u < NKEEP; ++u) nk[u] = key_med3(k[u - 1], k[u], kk);  // (k[0] >= k[1] >= ... throughout)
+#pragma unroll
+            for (int u = 0; u < NKEEP; ++u) k[u] = nk[u];
+        }
+    bool literal = chk != chk;
+#pragma unroll
+    for (int u = 0; u + 1 < NKEEP; ++u) literal = literal || !(keys_apart(k[u], k[u + 1]) || k[u] == KEY_EMPTY);
+    int es[4] = {63 - (k[0] & 63), -1, -1, -1};
+#pragma unroll
+    for (int u = 1; u < 4; ++u) es[u] = k[u] == KEY_EMPTY ? -1 : 63 - (k[u] & 63);
+    float gs[4] = {0.0f, 0.0f, 0.0f, 0.0f}, den = 1.0f;
+    if (!literal) {
+        float vs[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s >= K) es[s] = -1;
+            vs[s] = logit_of(es[s] < 0 ? 0 : es[s]);
+        }
+        gs[0] = expf(vs[0] - vs[0]);
+        den = gs[0];
+#pragma unroll
+        for (int s = 1; s < 4; ++s)
+            if (s < K) {
+                if (es[s] >= 0) gs[s] = expf(vs[s] - vs[0]);
+                den += gs[s];
+            }
+    }
+    for (uint64_t todo = __ballot(literal && t < T); todo; todo &= todo - 1) {
+        const int tk = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)todo) - 1), col = lane < E ? lane : 0;
+        float v = p[col * 64 + tk];
+        if (bias) v = v + bias[col];
+        int et[4];
+        float gt[4], dt;
+        literal_scan(v + 0.0f, K, all, nullptr, et, gt, dt);
+        if (lane == tk) {
+            den = dt;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                es[s] = et[s];
+                gs[s] = gt[s];
+            }
+        }
+    }
+    if (t >= T) return;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) gs[s] = gs[s] / den;
+    if (K == 4 && ((reinterpret_cast<uintptr_t>(topk_idx) | reinterpret_cast<uintptr_t>(gates)) & 15) == 0) {
+        typedef int i32x4 __attribute__((ext_vector_type(4)));
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        *reinterpret_cast<i32x4 *>(topk_idx + (size_t)t * 4) = i32x4{es[0], es[1], es[2], es[3]};
+        *reinterpret_cast<f32x4 *>(gates + (size_t)t * 4) = f32x4{gs[0], gs[1], gs[2], gs[3]};
+    } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (s < K) {
+                topk_idx[(size_t)t * K + s] = es[s];
+                gates[(size_t)t * K + s] = gs[s];
+            }
+    }
+}
+
 // Selection from stored logits [T, E] (the profiling pass of Sec. 3.2 routes 2^20 tokens of stored
 // router outputs), for E a multiple of 4 and K <= 4.  What the kernel has to do is stream the
 // logits, so the arithmetic per token is kept small:
@@ -995,7 +1152,7 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
         nmax = __builtin_amdgcn_readfirstlane(maxcnt);
     }
 
-    constexpr int EMPTY = (int)0xff800000;  // minus infinity: below the key of every finite logit
+    constexpr int EMPTY = KEY_EMPTY;
     // A 64-token group is one contiguous run of 64 E floats = E / 4 wave-wide 16-byte loads; lane l's
     // piece of load u holds columns col .. col + 3 of token tok, the same in every group.  Byte offsets
     // into tile_mem: of that piece's first float (the others follow 256 bytes apart), and of this
@@ -1013,20 +1170,6 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
     };
     // this token's logit of column c (any c, per lane)
     auto logit_of = [&](int c) __attribute__((always_inline)) { return lds_f(lanebase ^ code_of(c)); };
-    auto key_of = [](float v, int c) __attribute__((always_inline)) { return (__float_as_int(v) & ~63) | (63 - c); };
-    // (as instructions: the compiler would first quiet what it takes for possible NaNs)
-    auto max2 = [](int a, int b) __attribute__((always_inline)) {
-        int d;
-        asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
-        return d;
-    };
-    auto med3 = [](int a, int b, int c) __attribute__((always_inline)) {
-        int d;
-        asm("v_med3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-        return d;
-    };
-    auto apart = [](int a, int b) __attribute__((always_inline)) { return ((a ^ b) & ~63) != 0; };
-
     // all loads of a 64-token group go out together (a piece past the end of the logits re-reads the start)
     f32x4 q[4 * NV];
     auto request = [&](int64_t g) __attribute__((always_inline)) {
@@ -1074,16 +1217,16 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
                 chk = __builtin_fmaf(v, 0.0f, chk);  // NaN once a NaN or an infinity went in
                 const int kk = key_of(v, c);
                 int nk[NKEEP];
-                nk[0] = max2(k[0], kk);
+                nk[0] = key_max(k[0], kk);
 #pragma unroll
-                for (int u = 1; u < NKEEP; ++u) nk[u] = med3(k[u - 1], k[u], kk);  // (k[0] >= k[1] >= ... throughout)
+                for (int u = 1; u < NKEEP; ++u) nk[u] = key_med3(k[u - 1], k[u], kk);  // (k[0] >= k[1] >= ... throughout)
 #pragma unroll
                 for (int u = 0; u < NKEEP; ++u) k[u] = nk[u];
             }
         }
         bool literal = chk != chk;
 #pragma unroll
-        for (int u = 0; u + 1 < NKEEP; ++u) literal = literal || !(apart(k[u], k[u + 1]) || k[u] == EMPTY);
+        for (int u = 0; u + 1 < NKEEP; ++u) literal = literal || !(keys_apart(k[u], k[u + 1]) || k[u] == EMPTY);
         int es[4] = {-1, -1, -1, -1};
         float vs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         es[0] = 63 - (k[0] & 63);
@@ -1101,8 +1244,8 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int kk = kq + j < n ? key_of(v[j], (int)(code[j] >> 8)) : EMPTY;
-                    const int n0 = max2(m[0], kk), n1 = med3(m[0], m[1], kk), n2 = med3(m[1], m[2], kk),
-                              n3 = med3(m[2], m[3], kk);
+                    const int n0 = key_max(m[0], kk), n1 = key_med3(m[0], m[1], kk), n2 = key_med3(m[1], m[2], kk),
+                              n3 = key_med3(m[2], m[3], kk);
                     m[0] = n0;
                     m[1] = n1;
                     m[2] = n2;
@@ -1111,7 +1254,7 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
             }
 #pragma unroll
             for (int u = 0; u < 3; ++u) {
-                literal = literal || !(apart(m[u], m[u + 1]) || m[u] == EMPTY);
+                literal = literal || !(keys_apart(m[u], m[u + 1]) || m[u] == EMPTY);
                 es[u + 1] = m[u] == EMPTY ? -1 : 63 - (m[u] & 63);
             }
         } else {
@@ -1137,43 +1280,13 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
                     }
             }
         }
-        // The tokens that need the literal scan, one after the other, each by the whole wave (lane = column).  Its rule - first one
-        // standing unless a later one is strictly larger - picks the first allowed column if that holds a NaN, else the largest
-        // number, the lowest column among equals.
+        // The tokens that need the literal scan, one after the other, each by the whole wave (lane = column).
         for (uint64_t todo = __ballot(literal && t < T); todo; todo &= todo - 1) {
             const int tk = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)todo) - 1);
             const float v = lds_f((uint32_t)(wave * TILE_BYTES + tk * 4) ^ code_of(lane < E ? lane : 0));
-            const int bits = __float_as_int(v), key = bits ^ ((bits >> 31) & 0x7fffffff);
-            auto pick_row = [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
-                bi = -1;
-                bv = 0.0f;
-                if (mm == 0) return;
-                bi = __ffsll((unsigned long long)mm) - 1;
-                bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
-                if (bv != bv) return;
-                const bool in = ((mm >> lane) & 1ull) != 0 && v == v;
-                const int best = wave_max(in ? key : (int)0x80000000);
-                bi = __ffsll((unsigned long long)__ballot(in && key == best)) - 1;
-                bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
-            };
-            int et[4] = {-1, -1, -1, -1};
-            float gt[4] = {0.0f, 0.0f, 0.0f, 0.0f}, v0;
-            pick_row(all, et[0], v0);
-            uint64_t mm = all & ~(1ull << et[0]);
-            if constexpr (LISTS) mm = mask_tab[et[0]];
-            gt[0] = expf(v0 - v0);
-            float dt = gt[0];
-#pragma unroll
-            for (int s2 = 1; s2 < 4; ++s2)
-                if (s2 < K) {
-                    float vt;
-                    pick_row(mm, et[s2], vt);
-                    if (et[s2] >= 0) {
-                        mm &= ~(1ull << et[s2]);
-                        gt[s2] = expf(vt - v0);
-                    }
-                    dt += gt[s2];
-                }
+            int et[4];
+            float gt[4], dt;
+            literal_scan(v, K, all, LISTS ? mask_tab : nullptr, et, gt, dt);
             if (lane == tk) {
                 den = dt;
 #pragma unroll
@@ -1616,6 +1729,11 @@ static int launch_select(const float *part, int EP_, int nchunk, const float *bi
     if (T <= 8192) {
         route_select_small_kernel<<<dim3((unsigned)((T + SEL16_TOKENS - 1) / SEL16_TOKENS)), dim3(256), 0, st>>>(
             part, EP_, nchunk, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out);
+        return launch_status();
+    }
+    if (nchunk == 1 && K <= 4 && !collab_idx) {
+        C2R_EP_SWITCH(EP_, route_select_keys_kernel<EP><<<dim3((unsigned)((T + 63) / 64)), dim3(64), 0, st>>>(part, bias, T, E, K, topk_idx,
+                                                                                                            gates, logits_out));
         return launch_status();
     }
     C2R_EP_SWITCH(EP_, route_select_kernel<EP, false><<<dim3((unsigned)((T + 63) / 64)), dim3(SEL_WAVES * 64), 0, st>>>(

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2504_01337_amd import workloads as wl
-from helpers import dev, host
+from helpers import GATE_RTOL, dev, host
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +29,29 @@ def test_large_route_logits_bit_exact(orc, T, E, d, dtype):
     ref = orc.logits_canon_f32(x, Wg, bias)
     assert np.array_equal(host(logits), ref)
     assert np.array_equal(host(idx), orc.route(ref, 4)[0])
+
+
+# selection from one chunk result per token, past 8192 tokens: ties and values a few bit patterns apart (small integers and a router
+# whose columns are nearly alike), NaN and infinite logits, lists and none, fewer slots than four, partial tiles of 64 tokens
+@pytest.mark.parametrize("T,E,K,dtype", [(8193, 60, 4, "bf16"), (9000, 64, 4, "f32"), (8200, 17, 3, "bf16"), (8256, 36, 1, "f32"),
+                                         (8300, 12, 2, "bf16"), (8250, 4, 4, "f32")])
+def test_large_selection_from_one_chunk(orc, T, E, K, dtype):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(T + E)
+    x = rng.integers(-2, 3, size=(T, 64)).astype(np.float32)
+    x[::3] = wl.round_bf16(rng.standard_normal((len(x[::3]), 64)).astype(np.float32))
+    Wg = np.repeat(rng.standard_normal((64, 1)), E, axis=1) * (1 + 1e-6 * rng.integers(0, 9, size=(1, E)))
+    Wg[:, ::2] = rng.integers(-2, 3, size=Wg[:, ::2].shape)
+    Wg = Wg.astype(np.float32)
+    x[5], x[77] = np.inf, np.nan
+    for bias in (None, np.where(rng.random(E) < 0.1, np.float32(-np.inf), rng.standard_normal(E)).astype(np.float32)):
+        lists = np.stack([rng.permutation(np.delete(np.arange(E), e))[:max(K, E // 3)] for e in range(E)]).astype(np.int32)
+        if E > 8:
+            lists[3, 0] = lists[3, 1]
+        for cl in (None, lists):
+            gl = None if cl is None else np.concatenate([np.full((E, 1), -1, np.int32), cl, np.full((E, 1), E, np.int32)], axis=1)
+            idx, gates, logits = c2r.route(dev(x, dtype), dev(Wg), None if bias is None else dev(bias), K,
+                                           None if gl is None else dev(gl), want_logits=True)
+            ri, rg = orc.route(host(logits), K, cl)
+            assert np.array_equal(host(idx), ri)
+            np.testing.assert_allclose(host(gates), rg, rtol=114 / 34 * GATE_RTOL, atol=1e-37)
