@@ -11,9 +11,10 @@
 //  4. permute_rows_kernel   one wave per token: the row of x is read once and
 //                           written to each of its (up to K) sorted positions
 //                           with 16-byte accesses
-// Up to 49152 assignments, steps 1-3 are one launch instead (permute_by_slot_kernel: 11 us at
-// 32768 assignments and linear in their number; the three launches take 16-24 us from 65536 to
-// 262144 assignments).
+// Up to 512 blocks every block of step 3 does step 2 for itself, and up to 4096 assignments steps 1-3 are one launch
+// (permute_by_slot_kernel).  Microseconds of the index in a graph of such calls (before -> now: one launch up to 49152 assignments and a
+// rank by one ballot per distinct slot of a wave's lanes, up to 60 -> six ballots): 60 slots, 4096 tokens of 4: 10.4 -> 7.4, 8192 tokens
+// 11.0 -> 8.6, 10000 tokens 22.9 -> 9.0, 32768 tokens 27.9 -> 7.6, 131072 tokens 31.5 -> 11.9; 15 of 60 local, 32768 tokens 13.6 -> 7.7.
 // Everything is deterministic: no atomically assigned slots.
 #include <mutex>
 
@@ -103,11 +104,29 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) void permute_scan_kernel(const int
     }
 }
 
+// OWN_BASE: every block derives the start of its (block, slot) runs itself from the block histograms (block_base is then those), and
+// block 0 writes counts and offsets: step 2 without a launch of its own.
+template <bool OWN_BASE>
 __global__ __launch_bounds__(PB_THREADS) void permute_rank_kernel(
     const int32_t *__restrict__ topk_idx, int64_t A, int E, const int32_t *__restrict__ local_slot,
     int E_local, const int32_t *__restrict__ block_base, int32_t *__restrict__ perm,
-    int32_t *__restrict__ inv_perm) {
+    int32_t *__restrict__ inv_perm, int nblocks, int32_t *__restrict__ counts, int32_t *__restrict__ offsets) {
     __shared__ int32_t step_cnt[PB_STEPS][C2R_MAX_E];
+    __shared__ int32_t part_tot[OWN_BASE ? PB_THREADS / 64 : 1][C2R_MAX_E], part_pre[OWN_BASE ? PB_THREADS / 64 : 1][C2R_MAX_E];
+    if constexpr (OWN_BASE) {
+        const int s = threadIdx.x & 63, part = threadIdx.x >> 6;
+        int32_t tot = 0, pre = 0;
+        if (s < E_local) {
+#pragma unroll 16
+            for (int b = part; b < nblocks; b += PB_THREADS / 64) {
+                const int32_t v = block_base[(size_t)b * E_local + s];
+                tot += v;
+                pre += b < (int)blockIdx.x ? v : 0;
+            }
+        }
+        part_tot[part][s] = tot;
+        part_pre[part][s] = pre;
+    }
     for (int i = threadIdx.x; i < PB_STEPS * C2R_MAX_E; i += PB_THREADS) (&step_cnt[0][0])[i] = 0;
     __syncthreads();
 
@@ -120,25 +139,46 @@ __global__ __launch_bounds__(PB_THREADS) void permute_rank_kernel(
         const int64_t a = base + i * PB_THREADS + threadIdx.x;  // wave step q = i*4 + wave covers
         const int q = i * (PB_THREADS / 64) + wave;             // 64 consecutive assignments
         const int s = a < A ? slot_of(topk_idx[a], E, local_slot, E_local) : -1;
-        int r = 0;
-        uint64_t todo = __ballot(s >= 0);
-        while (todo) {
-            const int leader = __ffsll((unsigned long long)todo) - 1;
-            const int sl = __shfl(s, leader);
-            const uint64_t grp = __ballot(s == sl);
-            if (s == sl) {
-                r = __popcll(grp & lt);
-                if (r == 0) step_cnt[q][sl] = __popcll(grp);
-            }
-            todo &= ~grp;
+        // the lanes that hold this lane's slot, bit by bit of the slot's number
+        uint64_t grp = __ballot(s >= 0);
+#pragma unroll
+        for (int bit = 0; bit < 6; ++bit) {
+            const uint64_t set = __ballot((s >> bit) & 1);
+            grp &= ((s >> bit) & 1) ? set : ~set;
         }
+        const int r = __popcll(grp & lt);
+        if (s >= 0 && r == 0) step_cnt[q][s] = __popcll(grp);
         slot[i] = s;
         rank[i] = r;
     }
     __syncthreads();
     // exclusive prefix over the block's wave steps, per slot, seeded with the block's start
+    int32_t run = 0;
+    if constexpr (OWN_BASE) {
+        if (threadIdx.x < 64) {
+            int32_t total = 0, before = 0;
+#pragma unroll
+            for (int q = 0; q < PB_THREADS / 64; ++q) {
+                total += part_tot[q][threadIdx.x];
+                before += part_pre[q][threadIdx.x];
+            }
+            int32_t incl = total;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int32_t v = __shfl_up(incl, off);
+                if ((int)threadIdx.x >= off) incl += v;
+            }
+            run = incl - total + before;
+            if (blockIdx.x == 0 && (int)threadIdx.x < E_local) {
+                counts[threadIdx.x] = total;
+                offsets[threadIdx.x] = incl - total;
+                if ((int)threadIdx.x == E_local - 1) offsets[E_local] = incl;
+            }
+        }
+    } else if (threadIdx.x < E_local) {
+        run = block_base[(size_t)blockIdx.x * E_local + threadIdx.x];
+    }
     if (threadIdx.x < E_local) {
-        int32_t run = block_base[(size_t)blockIdx.x * E_local + threadIdx.x];
 #pragma unroll
         for (int q = 0; q < PB_STEPS; ++q) {
             const int32_t c = step_cnt[q][threadIdx.x];
@@ -163,19 +203,17 @@ __global__ __launch_bounds__(PB_THREADS) void permute_rank_kernel(
     }
 }
 
-// Small batches (the whole index array is a few hundred KB and sits in L2): one launch, one
-// workgroup per local expert slot.  The workgroup's 16 waves each own a contiguous
-// sixteenth of the assignments; a first sweep counts, per wave, the assignments of this
-// slot and of all lower slots, a second sweep hands out the positions in order (ballot +
+// Small batches: one launch, one workgroup per local expert slot.  The workgroup's 16 waves each own a contiguous
+// sixteenth of the assignments, in registers; they count, per wave, the assignments of this
+// slot and of all lower slots, then hand out the positions in order (ballot +
 // prefix inside a 64-assignment step, running count across steps, wave totals across
 // waves), which is the same stable order as the counting sort above.  Workgroup 0 also
 // marks the assignments that belong to no local slot.
 constexpr int PE_WAVES = 16;
-constexpr int64_t BY_SLOT_MAX = 3 << 14;  // assignments up to which the one-launch form is the faster one
+constexpr int64_t OWN_BASE_BLOCKS = 512;                 // blocks up to which each derives its start itself
+constexpr int64_t BY_SLOT_MAX = PE_WAVES * C2R_WAVE * 4;  // 1000 tokens of 4: 3.9 us against 6.5 in two launches; with 8 steps and more 10
 
-// PE_STEPS: 64-assignment steps a wave holds in registers at a time, a power of two.  The steps are straight-line code, so a
-// small batch takes the smallest form that holds its sixteenth (1024 assignments in 1 step, 4096 in 4).
-// (10.2 -> 4.7 us at 1024 assignments of 8 slots.)
+// PE_STEPS: 64-assignment steps that hold a wave's sixteenth.  They are straight-line code, so a small batch takes the smaller form.
 template <int PE_STEPS>
 __global__ __launch_bounds__(PE_WAVES * 64) void permute_by_slot_kernel(
     const int32_t *__restrict__ topk_idx, int A, int E, const int32_t *__restrict__ local_slot, int E_local,
@@ -186,42 +224,30 @@ __global__ __launch_bounds__(PE_WAVES * 64) void permute_by_slot_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int seg = ((A + PE_WAVES - 1) / PE_WAVES + 63) / 64 * 64;  // assignments per wave, whole steps
     const int a_begin = wave * seg, a_end = min(A, a_begin + seg);
-    // Up to PE_STEPS * 64 assignments per wave (A <= 32768 with 32 steps) the slots are loaded once, all loads in
-    // flight together, and stay in registers for both sweeps; longer segments go in pieces
-    // of that size and are read again by the second sweep.
-    const bool single = seg <= PE_STEPS * 64;
-    int sl[PE_STEPS];
     // (every load is unconditional, on a clamped index, so that all of them are in flight at
     // once: guarded loads end up one branch and one memory round trip each)
-    auto load = [&](int c0) {
+    int sl[PE_STEPS];
 #pragma unroll
-        for (int u = 0; u < PE_STEPS; ++u) sl[u] = topk_idx[min(c0 + u * 64 + lane, A - 1)];
-        if (local_slot) {
-            int ex[PE_STEPS];
+    for (int u = 0; u < PE_STEPS; ++u) sl[u] = topk_idx[min(a_begin + u * 64 + lane, A - 1)];
+    if (local_slot) {
+        int ex[PE_STEPS];
 #pragma unroll
-            for (int u = 0; u < PE_STEPS; ++u) ex[u] = sl[u];
+        for (int u = 0; u < PE_STEPS; ++u) ex[u] = sl[u];
 #pragma unroll
-            for (int u = 0; u < PE_STEPS; ++u) sl[u] = local_slot[min(max(ex[u], 0), E - 1)];
+        for (int u = 0; u < PE_STEPS; ++u) sl[u] = local_slot[min(max(ex[u], 0), E - 1)];
 #pragma unroll
-            for (int u = 0; u < PE_STEPS; ++u) sl[u] = (ex[u] >= 0 && ex[u] < E) ? sl[u] : -1;
-        } else {
+        for (int u = 0; u < PE_STEPS; ++u) sl[u] = (ex[u] >= 0 && ex[u] < E) ? sl[u] : -1;
+    } else {
 #pragma unroll
-            for (int u = 0; u < PE_STEPS; ++u) sl[u] = sl[u] < E ? sl[u] : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < PE_STEPS; ++u) {
-            const bool slot_ok = sl[u] >= 0 && sl[u] < E_local;
-            sl[u] = c0 + u * 64 + lane < a_end ? (slot_ok ? sl[u] : -1) : -2;  // -2: past the end
-        }
-    };
+        for (int u = 0; u < PE_STEPS; ++u) sl[u] = sl[u] < E ? sl[u] : -1;
+    }
     int mine = 0, less = 0;
-    for (int c0 = a_begin; c0 < a_end; c0 += PE_STEPS * 64) {
-        load(c0);
 #pragma unroll
-        for (int u = 0; u < PE_STEPS; ++u) {
-            mine += sl[u] == e;
-            less += sl[u] >= 0 && sl[u] < e;
-        }
+    for (int u = 0; u < PE_STEPS; ++u) {
+        const bool slot_ok = sl[u] >= 0 && sl[u] < E_local;
+        sl[u] = a_begin + u * 64 + lane < a_end ? (slot_ok ? sl[u] : -1) : -2;  // -2: past the end
+        mine += sl[u] == e;
+        less += sl[u] >= 0 && sl[u] < e;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -248,21 +274,18 @@ __global__ __launch_bounds__(PE_WAVES * 64) void permute_by_slot_kernel(
         if (e == E_local - 1) offsets[E_local] = start + total;
     }
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    for (int c0 = a_begin; c0 < a_end; c0 += PE_STEPS * 64) {
-        if (!single) load(c0);
 #pragma unroll
-        for (int u = 0; u < PE_STEPS; ++u) {
-            const int a = c0 + u * 64 + lane;
-            const uint64_t m = __ballot(sl[u] == e);
-            if (sl[u] == e) {
-                const int p = run + __popcll(m & lt);
-                perm[p] = a;
-                inv_perm[a] = p;
-            } else if (e == 0 && sl[u] == -1) {
-                inv_perm[a] = -1;
-            }
-            run += __popcll(m);
+    for (int u = 0; u < PE_STEPS; ++u) {
+        const int a = a_begin + u * 64 + lane;
+        const uint64_t m = __ballot(sl[u] == e);
+        if (sl[u] == e) {
+            const int p = run + __popcll(m & lt);
+            perm[p] = a;
+            inv_perm[a] = p;
+        } else if (e == 0 && sl[u] == -1) {
+            inv_perm[a] = -1;
         }
+        run += __popcll(m);
     }
 }
 
@@ -388,19 +411,22 @@ static int permute_impl(const void *x, c2r_dtype dt, const int32_t *topk_idx, in
         const dim3 g((unsigned)E_local), b(PE_WAVES * 64);
         if (A <= PE_WAVES * 64)
             permute_by_slot_kernel<1><<<g, b, 0, st>>>(topk_idx, (int)A, E, local_slot, E_local, counts, offsets, perm, inv_perm);
-        else if (A <= PE_WAVES * 64 * 4)
-            permute_by_slot_kernel<4><<<g, b, 0, st>>>(topk_idx, (int)A, E, local_slot, E_local, counts, offsets, perm, inv_perm);
         else
-            permute_by_slot_kernel<32><<<g, b, 0, st>>>(topk_idx, (int)A, E, local_slot, E_local, counts, offsets, perm, inv_perm);
+            permute_by_slot_kernel<4><<<g, b, 0, st>>>(topk_idx, (int)A, E, local_slot, E_local, counts, offsets, perm, inv_perm);
     } else {
         if (nblocks > 0)
             permute_hist_kernel<<<dim3((unsigned)nblocks), dim3(PB_THREADS), 0, st>>>(
                 topk_idx, A, E, local_slot, E_local, block_counts);
-        permute_scan_kernel<<<dim3(1), dim3(SCAN_WAVES * 64), 0, st>>>(block_counts, (int)nblocks, E_local,
-                                                                      block_base, counts, offsets);
-        if (nblocks > 0)
-            permute_rank_kernel<<<dim3((unsigned)nblocks), dim3(PB_THREADS), 0, st>>>(
-                topk_idx, A, E, local_slot, E_local, block_base, perm, inv_perm);
+        if (nblocks > 0 && nblocks <= OWN_BASE_BLOCKS) {
+            permute_rank_kernel<true><<<dim3((unsigned)nblocks), dim3(PB_THREADS), 0, st>>>(
+                topk_idx, A, E, local_slot, E_local, block_counts, perm, inv_perm, (int)nblocks, counts, offsets);
+        } else {
+            permute_scan_kernel<<<dim3(1), dim3(SCAN_WAVES * 64), 0, st>>>(block_counts, (int)nblocks, E_local, block_base, counts,
+                                                                          offsets);
+            if (nblocks > 0)
+                permute_rank_kernel<false><<<dim3((unsigned)nblocks), dim3(PB_THREADS), 0, st>>>(
+                    topk_idx, A, E, local_slot, E_local, block_base, perm, inv_perm, (int)nblocks, counts, offsets);
+        }
     }
     if (nblocks > 0 && x_perm) return permute_rows(x, dt, T, d, K, inv_perm, x_perm, st);
     return launch_status();

@@ -70,3 +70,19 @@ def test_dispatch_index_at_every_block_size(c2r, orc, T, K, n_dev):
         n = int(ro[-1])
         assert np.array_equal(host(counts), rc) and np.array_equal(host(offsets), ro)
         assert np.array_equal(host(tok)[:n], rt[:n]) and np.array_equal(host(row).reshape(-1), np.asarray(rr).reshape(-1))
+
+
+# the dispatch index on either side of its rules (4096 and 524288 assignments), blocks of 1024 assignments and their remainders, one slot,
+# all slots, slots shared by experts, empty and out-of-range entries
+@pytest.mark.parametrize("T,E,El,K", [(1024, 60, 60, 4), (1025, 60, 60, 4), (4097, 64, 64, 1), (2050, 64, 33, 2), (700, 8, 1, 6), (12289, 60, 15, 4),
+                                      (65537, 17, 9, 8), (1366, 3, 3, 3)])
+def test_dispatch_index_sizes(orc, T, E, El, K):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(T + E)
+    idx = rng.integers(0, E, size=(T, K)).astype(np.int32)
+    idx[rng.random((T, K)) < 0.01] = -1
+    ls = None if El == E else np.where(np.arange(E) % 3 == 1, -1, np.arange(E) % El).astype(np.int32)
+    counts, offsets, perm, inv, _ = c2r.permute(None, dev(idx), E, None if ls is None else dev(ls), El)
+    rc, ro, rp, ri = orc.permute(idx, E, ls, El)
+    assert np.array_equal(host(counts), rc) and np.array_equal(host(offsets), ro)
+    assert np.array_equal(host(perm)[:ro[-1]], rp) and np.array_equal(host(inv), ri)
