@@ -5,7 +5,7 @@
 // of 1 MB are handed out in one and a quarter rounds, and a narrow single group (a shared expert's down pass: 8 tiles of
 // 88 k-slices) keeps 8 CUs busy for 120 us while the rest of the chip waits.  Here a tile is 64 weight rows (64 output
 // columns, or 32 with their gate and up rows) x up to 32, 64 or 128 rows of one group, and a workgroup of four waves, two
-// of them on a CU, walks a contiguous run of tiles that is its equal share of all the k-slices.  Both operands go through
+// of them on a CU, walks a contiguous run of tiles, an equal share of its problem's (see mid_walk).  Both operands go through
 // a ring of six, four or three LDS stages filled by asynchronous copies, and the ring runs on ACROSS tiles: the next
 // tile's first slices are requested while this one's last are computed, so that a workgroup has its copies in flight from
 // its first slice to its last.  (One workgroup per tile instead, the same tile: 99 against 72 us for the gate/up pass of
@@ -236,10 +236,19 @@ __device__ __forceinline__ int mid_single_share(int chunks, int s_items, int kS,
         const int rest = 8 * (MID_WG_PER_XCD - n), cr = (r_items + rest - 1) / rest * kR;
         cost = min(max(cs, cr), 0xffffff) << 6 | lane_id();
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) cost = min(cost, __shfl_xor(cost, off));
+#if defined(__HIP_DEVICE_COMPILE__)
+    // the least of the 64 lanes' costs, in lane 63 (as wave_inclusive_scan: no LDS round trips at the start of every workgroup)
+    constexpr int MOST = 0x7fffffff;
+    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x111, 0xf, 0xf, false));
+    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x112, 0xf, 0xf, false));
+    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x114, 0xf, 0xf, false));
+    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x118, 0xf, 0xf, false));
+    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x142, 0xa, 0xf, false));
+    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x143, 0xc, 0xf, false));
+    cost = __builtin_amdgcn_readlane(cost, 63);
+#endif
     // (chunks is at most 16 here: a single group of more rows takes the tile kernel)
-    return __builtin_amdgcn_readfirstlane(cost == 0x7fffffff ? 1 : ((cost & 63) + 1) * chunks);
+    return cost == 0x7fffffff ? 1 : ((cost & 63) + 1) * chunks;
 }
 
 // ARR, ARS: rows of the ragged problem's and of the single group's tiles.  The two walk on workgroups of their own, the same number in

@@ -1,6 +1,5 @@
-"""Full-precision expert FFN: the two kernels of ffn_f32.hip (few rows: every wave alone; many: LDS tiles) against the oracle
-and against each other.  They add in the same order, and which one runs follows from the rows allotted, so a larger
-allotment has to give the same bits."""
+"""Full-precision expert FFN: the tile shapes of ffn_f32.hip against the oracle and against each other.  They add in the same
+order, and which one runs follows from the rows allotted, so a larger allotment has to give the same bits."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 # contraction lengths that end inside a 16-, 32- and 64-wide group of k (8, 24, 40, 72, 136, 520) and that do not; widths that end
 # inside a 16-, 32-, 64- and 128-wide column block; groups of 1, 15 to 17, 31 to 33, 127 to 129 and no rows.  The last two: some 4000
-# rows and a contraction of 512 and more, where the direct kernel's waves take 32 x 32 in the down pass
+# rows and a contraction of 512 and more
 @pytest.mark.parametrize("d,F,sizes,spare", [
     (8, 8, [1], 0), (24, 40, [15, 16, 17, 0, 1], 3), (72, 136, [31, 32, 33, 127, 128, 129], 0), (64, 512, [40] * 8, 0),
     (520, 264, [300, 0, 2, 61], 0), (256, 512, [128] * 8, 0), (1032, 72, [600, 700], 0), (256, 512, [900, 33, 0, 1000, 511, 513, 1, 1042], 0),
@@ -27,7 +26,7 @@ def test_f32_rows_against_oracle_and_between_kernels(orc, d, F, sizes, spare):
     w = [(rng.standard_normal(s) * 0.1).astype(np.float32) for s in ((E, F, d), (E, F, d), (E, d, F))]
     wd = [dev(a) for a in w]
     got = []
-    for cap in (n + spare, 256 * 128 + n):                  # the second allotment is 256 tiles and more in both passes
+    for cap in (n + spare, 256 * 128 + n):                  # (64-row tiles wherever the width holds three column blocks)
         xa = torch.full((cap, d), float("nan"), device="cuda")
         xa[:n] = dev(x)
         h = torch.full((cap, F), 77.0, device="cuda")
