@@ -44,7 +44,7 @@ def _case(c2r, seed, T, K, E, d, local):
 
 
 def test_permute_noalloc_two_calls_second_smaller(c2r):
-    # both sizes are above the one-launch switch point (49152 assignments), so both calls go
+    # both sizes are above the one-launch switch point (4096 assignments), so both calls go
     # through the block histograms in the static array; the second reuses it with fewer blocks
     _case(c2r, 1, T=70000, K=4, E=60, d=64, local=False)
     _case(c2r, 2, T=20000, K=4, E=60, d=64, local=True)
