@@ -918,11 +918,36 @@ __device__ __forceinline__ int wave_max(int v) {
     return v;
 }
 
-// One token's selection by the literal rule - first one standing unless a later one is strictly larger - by the whole wave: lane =
-// column, v its logit, `all` the columns, mask_tab the collaborators of every expert or null.  The rule picks the first allowed column if
-// that holds a NaN, else the largest number, the lowest column among equals.  Every lane must be active; results in every lane.
-__device__ __forceinline__ void literal_scan(float v, int K, uint64_t all, const uint64_t *mask_tab, int (&et)[4], float (&gt)[4],
+// One token's selection by the literal rule, for K <= 4: first one standing unless a later one is strictly larger.  pick(m, e, v) finds
+// the expert e of the columns m, and its logit; mask_tab: the collaborators of every expert, or null.
+template <typename Pick>
+__device__ __forceinline__ void literal_scan(Pick pick, int K, uint64_t all, const uint64_t *mask_tab, int (&es)[4], float (&gs)[4],
                                              float &den) {
+    float v0;
+    pick(all, es[0], v0);
+    uint64_t mm = mask_tab ? mask_tab[es[0]] : all & ~(1ull << es[0]);
+    gs[0] = expf(v0 - v0);
+    den = gs[0];
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+        es[s] = -1;
+        gs[s] = 0.0f;
+        if (s < K) {
+            float v;
+            pick(mm, es[s], v);
+            if (es[s] >= 0) {
+                mm &= ~(1ull << es[s]);
+                gs[s] = expf(v - v0);
+            }
+            den += gs[s];
+        }
+    }
+}
+
+// The same by the whole wave: lane = column, v its logit.  The rule picks the first allowed column if that holds a NaN, else the largest
+// number, the lowest column among equals.  Every lane must be active; results in every lane.
+__device__ __forceinline__ void literal_scan_by_wave(float v, int K, uint64_t all, const uint64_t *mask_tab, int (&es)[4], float (&gs)[4],
+                                                     float &den) {
     const int lane = lane_id(), bits = __float_as_int(v), key = bits ^ ((bits >> 31) & 0x7fffffff);
     auto pick_row = [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
         bi = -1;
@@ -936,25 +961,7 @@ __device__ __forceinline__ void literal_scan(float v, int K, uint64_t all, const
         bi = __ffsll((unsigned long long)__ballot(in && key == best)) - 1;
         bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
     };
-    float v0;
-    pick_row(all, et[0], v0);
-    uint64_t mm = mask_tab ? mask_tab[et[0]] : all & ~(1ull << et[0]);
-    gt[0] = expf(v0 - v0);
-    den = gt[0];
-#pragma unroll
-    for (int s = 1; s < 4; ++s) {
-        et[s] = -1;
-        gt[s] = 0.0f;
-        if (s < K) {
-            float vt;
-            pick_row(mm, et[s], vt);
-            if (et[s] >= 0) {
-                mm &= ~(1ull << et[s]);
-                gt[s] = expf(vt - v0);
-            }
-            den += gt[s];
-        }
-    }
+    literal_scan(pick_row, K, all, mask_tab, es, gs, den);
 }
 
 // The keys of the selections below: a logit (-0 made +0) whose low 6 bits are replaced by 63 - column, compared as floats (as
@@ -1047,7 +1054,7 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
         if (bias) v = v + bias[col];
         int et[4];
         float gt[4], dt;
-        literal_scan(v + 0.0f, K, all, nullptr, et, gt, dt);
+        literal_scan_by_wave(v + 0.0f, K, all, nullptr, et, gt, dt);
         if (lane == tk) {
             den = dt;
 #pragma unroll
@@ -1075,6 +1082,13 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
     }
 }
 
+// Undecided tokens of a 64-token group that the wave scans together, one after the other: up to E / SCAN_TOGETHER; more are scanned by
+// their own lanes, all at once.  The one takes 0.9 us a token (four slots), the other 0.2 us a column whatever the number of tokens.
+// Microseconds of the selection with n of every 64 tokens undecided (together / alone): 2^20 tokens, 60 experts, n = 8 104 / 140, n = 12
+// 135 / 134, n = 16 166 / 134, n = 64 549 / 129; 36 experts, n = 6 74 / 87, n = 8 90 / 87; 16 experts, n = 3 32 / 37, n = 4 38 / 37; 8 experts,
+// n = 1 18 / 24, n = 3 29 / 24; 65536 tokens, 60 experts, n = 8 15.1 / 24.8, n = 12 18.9 / 19.6, n = 16 22.6 / 19.6.
+constexpr int SCAN_TOGETHER = 5;
+
 // Selection from stored logits [T, E] (the profiling pass of Sec. 3.2 routes 2^20 tokens of stored
 // router outputs), for E a multiple of 4 and K <= 4.  What the kernel has to do is stream the
 // logits, so the arithmetic per token is kept small:
@@ -1094,7 +1108,8 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
 //    literal scan (first one standing unless a later one is strictly larger) for every slot.  Of 2^20 tokens of 60 normal logits some
 //    300 do, one lane's scan is 15 us of LDS reads one after the other, and a launch ends with its last wave: the whole wave
 //    scans such a token, a lane per column (2^20 tokens 60 -> 51.6 us, 65536 tokens 20 -> 14.6; with the keys compared as floats instead
-//    of made order-preserving integers first, three instructions of ten per logit, 48.8 and 13.7; the stream alone 40).
+//    of made order-preserving integers first, three instructions of ten per logit, 48.8 and 13.7; the stream alone 40).  A wave that
+//    holds many of them (ties of rounded logits, an expert masked by -infinity) lets every lane scan its own: see SCAN_TOGETHER.
 // COUNT: the token's expert pairs are added to the co-activation matrix (Eq. 2) on the spot - an LDS
 // histogram per workgroup as in coact.hip, one integer atomic per entry at the end - and either
 // output may be left out (null): the profiling pass wants the counts, not the selections.
@@ -1280,13 +1295,32 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
                     }
             }
         }
-        // The tokens that need the literal scan, one after the other, each by the whole wave (lane = column).
-        for (uint64_t todo = __ballot(literal && t < T); todo; todo &= todo - 1) {
+        // The tokens that need the literal scan: a few one after the other, each by the whole wave (lane = column); more, every one
+        // by its own lane.
+        const bool scan = literal && t < T;
+        uint64_t todo = __ballot(scan);
+        if (__popcll(todo) * SCAN_TOGETHER > E) {
+            todo = 0;
+            if (scan)
+                literal_scan(
+                    [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
+                        bi = -1;
+                        bv = 0.0f;
+                        for (int e = 0; e < E; ++e) {
+                            const float v = logit_of(e);
+                            const bool take = ((mm >> e) & 1ull) != 0 && (bi < 0 || v > bv);
+                            bv = take ? v : bv;
+                            bi = take ? e : bi;
+                        }
+                    },
+                    K, all, LISTS ? mask_tab : nullptr, es, gs, den);
+        }
+        for (; todo; todo &= todo - 1) {
             const int tk = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)todo) - 1);
             const float v = lds_f((uint32_t)(wave * TILE_BYTES + tk * 4) ^ code_of(lane < E ? lane : 0));
             int et[4];
             float gt[4], dt;
-            literal_scan(v, K, all, LISTS ? mask_tab : nullptr, et, gt, dt);
+            literal_scan_by_wave(v, K, all, LISTS ? mask_tab : nullptr, et, gt, dt);
             if (lane == tk) {
                 den = dt;
 #pragma unroll

@@ -36,3 +36,55 @@ def test_close_tied_special_and_subnormal_logits(orc, T, E, K, lists):
         C = dev(np.zeros((E, E), dtype=np.int32))
         c2r.profile_from_logits(dev(l), K, C, None if ci is None else dev(ci))
         assert np.array_equal(host(C), orc.coactivation(ri, E))
+
+
+# undecided tokens in every group of 64: none, one, as many as are scanned by the whole wave and one more, all; with lists and without, a partial
+# last group, special values among them
+@pytest.mark.parametrize("E,K", [(60, 4), (64, 3), (36, 4), (16, 2), (8, 4), (4, 4)])
+def test_groups_with_few_and_many_undecided_tokens(orc, E, K):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(E * K)
+    counts = [0, 1, E // 5 - 1, E // 5, E // 5 + 1, 63, 64, 20]
+    T = 64 * len(counts) - 30
+    l = rng.standard_normal((T, E)).astype(np.float32)
+    for g, n in enumerate(counts):
+        for t in g * 64 + rng.permutation(64)[:max(n, 0)]:
+            if t < T:
+                kind = rng.integers(0, 5)
+                l[t] = (np.float32(0.25) * rng.integers(-1, 3, size=E) if kind < 2 else np.float32(-1.5) if kind == 2 else
+                        np.where(rng.random(E) < 0.3, [np.nan, -np.inf][kind - 3], l[t]))
+    lists = np.stack([rng.permutation(np.delete(np.arange(E), e))[:max(K - 1, E // 3)] for e in range(E)]).astype(np.int32)
+    for ci in (None, lists):
+        idx, gates = c2r.route_from_logits(dev(l), K, None if ci is None else dev(ci))
+        ri, rg = orc.route(l, K, ci)
+        assert np.array_equal(host(idx), ri)
+        np.testing.assert_allclose(host(gates), rg, rtol=GATE_RTOL, atol=1e-37)
+        C = dev(np.zeros((E, E), dtype=np.int32))
+        c2r.profile_from_logits(dev(l), K, C, None if ci is None else dev(ci))
+        assert np.array_equal(host(C), orc.coactivation(ri, E))
+
+
+# an expert masked by -infinity leaves every token undecided: 1.5 times the time of ordinary logits (33 us against 21 on an MI355X, 37 against
+# 24 with lists); one token after the other by the whole wave it was 16 times
+@pytest.mark.parametrize("lists", [False, True])
+def test_undecided_tokens_cost_no_multiple(lists):
+    import torch
+    from paper_2504_01337_amd import c2r
+    T, E, K = 1 << 20, 16, 4
+    l = torch.randn((T, E), device="cuda")
+    masked = l.clone()
+    masked[:, 3] = float("-inf")
+    ci = torch.stack([torch.randperm(E)[:8] for _ in range(E)]).int().cuda() if lists else None
+    best = []
+    for a in (l, masked):
+        times = []
+        for _ in range(12):
+            beg, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            beg.record()
+            for _ in range(4):
+                c2r.route_from_logits(a, K, ci)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(beg.elapsed_time(end))
+        best.append(min(times))
+    assert best[1] < 5 * best[0]
