@@ -964,6 +964,13 @@ __device__ __forceinline__ void literal_scan_by_wave(float v, int K, uint64_t al
     literal_scan(pick_row, K, all, mask_tab, es, gs, den);
 }
 
+// Undecided tokens of a 64-token group that the wave scans together, one after the other: up to E / SCAN_TOGETHER; more are scanned by
+// their own lanes, all at once.  The one takes 0.9 us a token (four slots), the other 0.2 us a column whatever the number of tokens.
+// Microseconds of the selection with n of every 64 tokens undecided (together / alone): 2^20 tokens, 60 experts, n = 8 104 / 140, n = 12
+// 135 / 134, n = 16 166 / 134, n = 64 549 / 129; 36 experts, n = 6 74 / 87, n = 8 90 / 87; 16 experts, n = 3 32 / 37, n = 4 38 / 37; 8 experts,
+// n = 1 18 / 24, n = 3 29 / 24; 65536 tokens, 60 experts, n = 8 15.1 / 24.8, n = 12 18.9 / 19.6, n = 16 22.6 / 19.6.
+constexpr int SCAN_TOGETHER = 5;
+
 // The keys of the selections below: a logit (-0 made +0) whose low 6 bits are replaced by 63 - column, compared as floats (as
 // instructions: the compiler would first quiet what it takes for possible NaNs).
 constexpr int KEY_EMPTY = (int)0xff800000;  // minus infinity: below the key of every finite logit
@@ -985,6 +992,8 @@ __device__ __forceinline__ bool keys_apart(int a, int b) { return ((a ^ b) & ~63
 // Bound by the launch and two trips to memory; the stage with route_select_kernel / with this: 60 experts, d 2048: 32768 tokens 87.0 / 84.0,
 // 65536 tokens 155 / 150; 16 experts, 32768 tokens 103.8 / 102.4.  (With lists, the largest two keys and a second chain over the
 // first one's list, it was no faster: 15.6 against 12.7 us for the kernel at 32768 tokens.)
+constexpr int KEYS_SCAN_TOGETHER = 8;  // as SCAN_TOGETHER; here a token scanned by the wave also waits for its logits out of L2
+
 template <int EP>
 __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__restrict__ part, const float *__restrict__ bias, int64_t T,
                                                                int E, int K, int32_t *__restrict__ topk_idx,
@@ -1015,9 +1024,9 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
 #pragma unroll
     for (int e = 0; e < EP; ++e)
         if (e < E) {  // (uniform)
-            const float v = l[e] + 0.0f;
-            chk = __builtin_fmaf(v, 0.0f, chk);  // NaN once a NaN or an infinity went in
-            const int kk = key_of(v, e);
+            l[e] = l[e] + 0.0f;
+            chk = __builtin_fmaf(l[e], 0.0f, chk);  // NaN once a NaN or an infinity went in
+            const int kk = key_of(l[e], e);
             int nk[NKEEP];
             nk[0] = key_max(k[0], kk);
 #pragma unroll
@@ -1028,6 +1037,19 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
     bool literal = chk != chk;
 #pragma unroll
     for (int u = 0; u + 1 < NKEEP; ++u) literal = literal || !(keys_apart(k[u], k[u + 1]) || k[u] == KEY_EMPTY);
+    // Undecided tokens come in numbers where rows of zeros pad a batch (their logits are all +0) or an expert is masked by -infinity.
+    // Where the replaced bits were all zero and the keys kept are not negative, equal logits lie in ascending columns and the chain
+    // is right as it stands; what is left is scanned as in route_select_rows_kernel.
+    uint64_t todo = __ballot(literal && t < T);
+    if (todo & (todo - 1)) {
+        int low = 0;
+#pragma unroll
+        for (int e = 0; e < EP; ++e)
+            if (e < E) low |= __float_as_int(l[e]) & 63;
+        literal = literal && !(chk == chk && low == 0 && k[NKEEP - 1] >= 0);
+        todo = __ballot(literal && t < T);
+    }
+    const bool alone = __popcll(todo) * KEYS_SCAN_TOGETHER > E;
     int es[4] = {63 - (k[0] & 63), -1, -1, -1};
 #pragma unroll
     for (int u = 1; u < 4; ++u) es[u] = k[u] == KEY_EMPTY ? -1 : 63 - (k[u] & 63);
@@ -1048,7 +1070,10 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
                 den += gs[s];
             }
     }
-    for (uint64_t todo = __ballot(literal && t < T); todo; todo &= todo - 1) {
+    if (alone && literal && t < T)
+        literal_scan([&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) { pick<EP>(l, mm, bi, bv); }, K, all, nullptr, es,
+                     gs, den);
+    for (todo = alone ? 0 : todo; todo; todo &= todo - 1) {
         const int tk = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)todo) - 1), col = lane < E ? lane : 0;
         float v = p[col * 64 + tk];
         if (bias) v = v + bias[col];
@@ -1081,13 +1106,6 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
             }
     }
 }
-
-// Undecided tokens of a 64-token group that the wave scans together, one after the other: up to E / SCAN_TOGETHER; more are scanned by
-// their own lanes, all at once.  The one takes 0.9 us a token (four slots), the other 0.2 us a column whatever the number of tokens.
-// Microseconds of the selection with n of every 64 tokens undecided (together / alone): 2^20 tokens, 60 experts, n = 8 104 / 140, n = 12
-// 135 / 134, n = 16 166 / 134, n = 64 549 / 129; 36 experts, n = 6 74 / 87, n = 8 90 / 87; 16 experts, n = 3 32 / 37, n = 4 38 / 37; 8 experts,
-// n = 1 18 / 24, n = 3 29 / 24; 65536 tokens, 60 experts, n = 8 15.1 / 24.8, n = 12 18.9 / 19.6, n = 16 22.6 / 19.6.
-constexpr int SCAN_TOGETHER = 5;
 
 // Selection from stored logits [T, E] (the profiling pass of Sec. 3.2 routes 2^20 tokens of stored
 // router outputs), for E a multiple of 4 and K <= 4.  What the kernel has to do is stream the

@@ -55,3 +55,54 @@ def test_large_selection_from_one_chunk(orc, T, E, K, dtype):
             ri, rg = orc.route(host(logits), K, cl)
             assert np.array_equal(host(idx), ri)
             np.testing.assert_allclose(host(gates), rg, rtol=114 / 34 * GATE_RTOL, atol=1e-37)
+
+
+# undecided tokens in groups of 64 (none, a few that the wave scans together, one more, all): rows of zeros, rows with equal logits of either sign,
+# an expert masked by -infinity, NaN; a partial last group
+@pytest.mark.parametrize("E,K", [(60, 4), (64, 4), (36, 3), (16, 2), (8, 4), (5, 4)])
+def test_large_selection_of_undecided_tokens(orc, E, K):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(E * K)
+    T, d = 64 * 130 - 17, 64
+    x = rng.standard_normal((T, d)).astype(np.float32)
+    Wg = (0.25 * rng.standard_normal((d, E))).astype(np.float32)  # (logits of deviation 2: kept ones differ by less than GATE_RTOL's 24)
+    Wg[0] = 1.0
+    few = [0, 1, 2, E // 8, E // 8 + 1, 20, 64]
+    for g in range(130):
+        for t in g * 64 + rng.permutation(64)[:few[g % len(few)]]:
+            if t < T:
+                x[t] = 0.0
+                if g % 3:
+                    x[t, 0] = [1.5, -2.25, 1.1, np.nan][rng.integers(0, 4)]   # (1.1: its low bits are not zero)
+    masked = np.zeros(E, dtype=np.float32)
+    masked[E // 2] = -np.inf
+    for bias in (None, masked):
+        idx, gates, logits = c2r.route(dev(x), dev(Wg), None if bias is None else dev(bias), K, want_logits=True)
+        ri, rg = orc.route(host(logits), K)
+        assert np.array_equal(host(idx), ri)
+        np.testing.assert_allclose(host(gates), rg, rtol=GATE_RTOL, atol=1e-37)
+
+
+# a batch of padding (rows of zeros) takes the time of any other (3.5 times it with one undecided token after the other), and so does a router
+# with an expert masked by -infinity
+def test_large_selection_of_padding_costs_no_multiple():
+    import torch
+    from paper_2504_01337_amd import c2r
+    T, E, d = 65536, 60, 64
+    x, Wg = torch.randn((T, d), device="cuda"), torch.randn((d, E), device="cuda")
+    bias = torch.zeros(E, device="cuda")
+    masked = bias.clone()
+    masked[7] = float("-inf")
+    best = []
+    for a, b in ((x, bias), (torch.zeros_like(x), bias), (x, masked)):
+        times = []
+        for _ in range(12):
+            beg, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            beg.record()
+            for _ in range(8):
+                c2r.route(a, Wg, b, 4)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(beg.elapsed_time(end))
+        best.append(min(times))
+    assert max(best[1:]) < 2 * best[0]
