@@ -40,15 +40,26 @@ __device__ __forceinline__ void mid_row_table(const FfnProblem &P, uint16_t *row
     __syncthreads();
 }
 
-// Workgroup w of the nwg that walk one problem, its groups in gm (chunks of AR rows).  Items = (chunk of at most AR rows of one
-// group, column block); the workgroup takes a contiguous run of them, an equal share (they all have the same k-slices).  A group's
-// items are numbered in blocks of `run` columns - the length of a workgroup's run - chunk after chunk inside a block, so that the
+// The workgroups that walk one problem: in all, those of the XCDs before this one, this XCD's, and this one's rank among them.
+struct MidShare {
+    int all, before, here, rank;
+    int room;  // ranks from 0 on that have a CU without each other
+};
+
+// Walks one problem, its groups in gm (chunks of AR rows).  Items = (chunk of at most AR rows of one
+// group, column block); a workgroup takes a contiguous run of them, an equal share (they all have the same k-slices).  Where the shares
+// cannot be equal, the first ranks take an item more: workgroups `slot` and `slot` + 32 of an XCD share a CU, and two longer walks on
+// one are what a launch then waits for.  More of them than there is room for are spread evenly instead (beyond it the pairs are there
+// anyway, and a mixture of pairs and others finishes later than pairs throughout).  Microseconds of the gate/up pass, always spread / the
+// first ranks: 60 groups (2640 items for the 512 workgroups) 151 / 134, 15 groups (660) 33.6 / 29.7, 2 groups (128) 14.0 / 12.4; 8 groups of d
+// 4096 (352, room for 256) 30.4 / 33.9.
+// A group's items are numbered in blocks of `run` columns - the length of a workgroup's run - chunk after chunk inside a block, so that the
 // chunks of a column block, which read the same weights, are walked by neighbouring workgroups at the same time and the weights come
 // into that XCD's L2 once.  (Chunks of a column block one after the other in one workgroup: by the second the weights were gone; the
 // gate/up pass of 131 tokens fetched 1.37 times its weights.)
 template <int MODE, int AR>
 __device__ __forceinline__ void mid_walk(const FfnProblem &P, const GroupMap &gm, unsigned char *smem, const uint16_t *row_of,
-                                         int w, int nwg) {
+                                         const MidShare &share) {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     constexpr int NSTAGE = mid_stages(AR), ROWB = 128, A_BYTES = AR * ROWB, STAGE_BYTES = (AR + MID_BR) * ROWB;
     constexpr int GA = AR / 32, GB = 2, NCOPY = GA + GB;  // 8-row copies per wave and slice
@@ -57,8 +68,15 @@ __device__ __forceinline__ void mid_walk(const FfnProblem &P, const GroupMap &gm
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ntn = P.ntn, N = P.N, Kdim = P.Kdim, nk = (Kdim + 63) / 64;
     const int n_items = __builtin_amdgcn_readfirstlane(gm.total_mtiles) * ntn;
-    const int run = max(1, min(ntn, n_items / nwg));
-    const int first = (int)((int64_t)n_items * w / nwg), last = (int)((int64_t)n_items * (w + 1) / nwg);
+    const int each = n_items / share.all, run = max(1, min(ntn, each));
+    const uint32_t over = n_items - each * share.all;  // (items past an equal share of whole ones, fewer than the workgroups)
+    const int over_before = over * (uint32_t)share.before / (uint32_t)share.all;
+    const int more = (int)(over * (uint32_t)(share.before + share.here) / (uint32_t)share.all) - over_before;  // this XCD's of them
+    const auto start_of = [&](int rank) __attribute__((always_inline)) {
+        return (share.before + rank) * each + over_before +
+               (more <= share.room ? min(rank, more) : (int)((uint32_t)more * (uint32_t)rank / (uint32_t)share.here));
+    };
+    const int first = start_of(share.rank), last = start_of(share.rank + 1);
     if (first >= last) return;
     const int total = (last - first) * nk;  // slices
 
@@ -226,16 +244,15 @@ __device__ __forceinline__ GroupMap mid_single_map(const FfnProblem &S) {
     return m;
 }
 
-// How many of an XCD's workgroups walk the single group when there are ragged items as well: a multiple of its chunks (see mid_walk)
-// that leaves the longest walk, in slices, as short as possible.  Lane l tries (l + 1) * chunks.
-__device__ __forceinline__ int mid_single_share(int chunks, int s_items, int kS, int r_items, int kR) {
-    const int n = (lane_id() + 1) * chunks;
+// How many column blocks of the single group a workgroup walks when there are ragged items as well: what leaves the longest walk, in
+// slices, as short as possible.  ceil(ntn / that) teams of a workgroup per chunk then walk the group, the other workgroups the ragged
+// items.  Lane l tries l + 1; 0: none fits.  (Whole teams per XCD only, as many in each, left 448 or 456 workgroups where 453 make the
+// longest walk an item shorter.)
+__device__ __forceinline__ int mid_single_run(int chunks, int ntn, int kS, int r_items, int kR) {
+    const int c = lane_id() + 1, teams = (ntn + c - 1) / c, rest = 8 * MID_WG_PER_XCD - teams * chunks;
     int cost = 0x7fffffff;
-    if (n < MID_WG_PER_XCD) {
-        const int cs = (s_items + 8 * n - 1) / (8 * n) * kS;
-        const int rest = 8 * (MID_WG_PER_XCD - n), cr = (r_items + rest - 1) / rest * kR;
-        cost = min(max(cs, cr), 0xffffff) << 6 | lane_id();
-    }
+    if ((teams + 7) / 8 * chunks < MID_WG_PER_XCD)
+        cost = min(max(c * kS, (r_items + rest - 1) / rest * kR), 0xffffff) << 6 | (63 - lane_id());  // (the longer run among equals)
 #if defined(__HIP_DEVICE_COMPILE__)
     // the least of the 64 lanes' costs, in lane 63 (as wave_inclusive_scan: no LDS round trips at the start of every workgroup)
     constexpr int MOST = 0x7fffffff;
@@ -247,36 +264,53 @@ __device__ __forceinline__ int mid_single_share(int chunks, int s_items, int kS,
     cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x143, 0xc, 0xf, false));
     cost = __builtin_amdgcn_readlane(cost, 63);
 #endif
-    // (chunks is at most 16 here: a single group of more rows takes the tile kernel)
-    return cost == 0x7fffffff ? 1 : ((cost & 63) + 1) * chunks;
+    return cost == 0x7fffffff ? 0 : 64 - (cost & 63);
 }
 
-// ARR, ARS: rows of the ragged problem's and of the single group's tiles.  The two walk on workgroups of their own, the same number in
-// every XCD (all of the single group's in one XCD made that one finish last: the down pass of 64 tokens 52 against 42 us).
+// ARR, ARS: rows of the ragged problem's and of the single group's tiles.  The two walk on workgroups of their own, the single group's
+// teams spread evenly over the XCDs (all of them in one XCD made that one finish last: the down pass of 64 tokens 52 against 42 us) and on
+// the first workgroups of each, which have a CU each.  Microseconds, 60 experts and a shared one, eight batches each (one list of items
+// for both / workgroups apart, longer walks wherever they fell / these): gate/up, 16 tokens 52.8 / 54.6 / 53.8, 32 tokens 62.0 / 63.6 / 60.1, 131
+// tokens 93.8 / 90.2 / 87.9; down, 64 tokens 51.0 / 42.3 / 40.6, 131 tokens 53.1 / 52.0 / 49.1.
 template <int MODE, int ARR, int ARS>
 __global__ __launch_bounds__(256, 2) void ffn_mid_kernel(const FfnLaunch L) {
     constexpr int LDS = mid_lds_bytes(ARR) > mid_lds_bytes(ARS) ? mid_lds_bytes(ARR) : mid_lds_bytes(ARS);
     __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS];
     __shared__ uint16_t row_of[MODE == 0 ? MID_ROW_TABLE : 1];
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const GroupMap gm = build_group_map<ARR>(L.p[0].offsets, L.has_ragged ? L.p[0].E_local : 0, L.p[0].A_cap);
-    int ns = 0;  // workgroups of an XCD that walk the single group
+    GroupMap gm = {};
+    if (L.has_ragged) gm = build_group_map<ARR>(L.p[0].offsets, L.p[0].E_local, L.p[0].A_cap);
+    int ns = 0, ns_before = 0, ns_all = 0;  // workgroups that walk the single group: in this XCD, in those before it, in all
+    bool long_single = false;               // their walks are longer than the others
     if (L.has_single) {
-        const GroupMap sm = mid_single_map<ARS>(L.p[1]);
+        const FfnProblem &S = L.p[1];
+        const GroupMap sm = mid_single_map<ARS>(S);
         const int chunks = __builtin_amdgcn_readfirstlane(sm.total_mtiles);
-        const int r_items = L.has_ragged ? __builtin_amdgcn_readfirstlane(gm.total_mtiles) * L.p[0].ntn : 0;
-        if (chunks > 0)
-            ns = r_items == 0 ? MID_WG_PER_XCD
-                              : mid_single_share(chunks, chunks * L.p[1].ntn, (L.p[1].Kdim + 63) / 64, r_items, (L.p[0].Kdim + 63) / 64);
+        const int r_items = __builtin_amdgcn_readfirstlane(gm.total_mtiles) * L.p[0].ntn;
+        if (chunks > 0) {
+            const int kS = (S.Kdim + 63) / 64, kR = (L.p[0].Kdim + 63) / 64;
+            const int run = r_items > 0 ? mid_single_run(chunks, S.ntn, kS, r_items, kR) : 0;
+            const int teams = run ? (S.ntn + run - 1) / run : 8;
+            const int size = run ? chunks : r_items > 0 ? 1 : MID_WG_PER_XCD;  // (nothing beside it: all of them)
+            ns_before = xcd * teams / 8 * size;
+            ns = (xcd + 1) * teams / 8 * size - ns_before;
+            ns_all = teams * size;
+            long_single = ns <= CUS_PER_XCD && r_items > 0 && run * kS > (r_items / (8 * MID_WG_PER_XCD - ns_all) + 1) * kR;
+        }
         if (slot < ns) {
-            if (MODE == 0 && L.p[1].gather) mid_row_table(L.p[1], row_of);  // (one routed group)
-            mid_walk<MODE, ARS>(L.p[1], sm, smem, row_of, xcd * ns + slot, 8 * ns);
+            if (MODE == 0 && S.gather) mid_row_table(S, row_of);  // (one routed group)
+            mid_walk<MODE, ARS>(S, sm, smem, row_of, MidShare{ns_all, ns_before, ns, slot, CUS_PER_XCD});
             return;
         }
     }
     if (!L.has_ragged) return;
     if (MODE == 0 && L.p[0].gather) mid_row_table(L.p[0], row_of);
-    mid_walk<MODE, ARR>(L.p[0], gm, smem, row_of, xcd * (MID_WG_PER_XCD - ns) + slot - ns, 8 * (MID_WG_PER_XCD - ns));
+    // (the workgroups beside a longer walk of the single group's come last)
+    const int beside = slot - CUS_PER_XCD;
+    const int rank = !long_single || beside < 0 ? slot - ns : beside < ns ? MID_WG_PER_XCD - 2 * ns + beside : slot - 2 * ns;
+    mid_walk<MODE, ARR>(L.p[0], gm, smem, row_of,
+                        MidShare{8 * MID_WG_PER_XCD - ns_all, xcd * MID_WG_PER_XCD - ns_before, MID_WG_PER_XCD - ns, rank,
+                                 long_single ? MID_WG_PER_XCD : CUS_PER_XCD - ns});
 }
 
 template <int MODE>
