@@ -186,9 +186,9 @@ int c2r_permute(const void *x, c2r_dtype dt, const int32_t *topk_idx, int64_t T,
  * the library holds on every GPU it runs on until the process ends.  The call allocates
  * nothing and frees nothing.
  * Limit: T*K <= 4194304 assignments; beyond it C2R_ERR_UNSUPPORTED (use c2r_permute).
- * Every call on a GPU shares that GPU's array: calls that overlap in time on one GPU (two
- * streams, two host threads) race on it and must be serialised by the caller; calls on one
- * stream, or on different GPUs, are safe.  Nothing in the array needs clearing between calls
+ * Calls of more than 49152 assignments on a GPU share that GPU's array: those that overlap in time
+ * on one GPU (two streams, two host threads) race on it and must be serialised by the caller;
+ * calls on one stream, on different GPUs, or of up to 49152 assignments are safe.  Nothing in the array needs clearing between calls
  * (each call overwrites the part it reads).
  */
 int c2r_permute_noalloc(const void *x, c2r_dtype dt, const int32_t *topk_idx, int64_t T, int d, int E,

@@ -212,9 +212,12 @@ __global__ __launch_bounds__(PB_THREADS) void permute_rank_kernel(
 constexpr int PE_WAVES = 16;
 constexpr int64_t OWN_BASE_BLOCKS = 512;                 // blocks up to which each derives its start itself
 constexpr int64_t BY_SLOT_MAX = PE_WAVES * C2R_WAVE * 4;  // 1000 tokens of 4: 3.9 us against 6.5 in two launches; with 8 steps and more 10
+// Without a workspace, up to here: the block histograms would be in an array that calls on other streams share.
+constexpr int64_t BY_SLOT_NOALLOC_MAX = 3 << 14;
 
 // PE_STEPS: 64-assignment steps that hold a wave's sixteenth.  They are straight-line code, so a small batch takes the smaller form.
-template <int PE_STEPS>
+// PIECES: the sixteenth is longer; it goes in pieces of that size and is read again to hand out the positions.
+template <int PE_STEPS, bool PIECES = false>
 __global__ __launch_bounds__(PE_WAVES * 64) void permute_by_slot_kernel(
     const int32_t *__restrict__ topk_idx, int A, int E, const int32_t *__restrict__ local_slot, int E_local,
     int32_t *__restrict__ counts, int32_t *__restrict__ offsets, int32_t *__restrict__ perm,
@@ -227,28 +230,37 @@ __global__ __launch_bounds__(PE_WAVES * 64) void permute_by_slot_kernel(
     // (every load is unconditional, on a clamped index, so that all of them are in flight at
     // once: guarded loads end up one branch and one memory round trip each)
     int sl[PE_STEPS];
+    auto load = [&](int c0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < PE_STEPS; ++u) sl[u] = topk_idx[min(a_begin + u * 64 + lane, A - 1)];
-    if (local_slot) {
-        int ex[PE_STEPS];
+        for (int u = 0; u < PE_STEPS; ++u) sl[u] = topk_idx[min(c0 + u * 64 + lane, A - 1)];
+        if (local_slot) {
+            int ex[PE_STEPS];
 #pragma unroll
-        for (int u = 0; u < PE_STEPS; ++u) ex[u] = sl[u];
+            for (int u = 0; u < PE_STEPS; ++u) ex[u] = sl[u];
 #pragma unroll
-        for (int u = 0; u < PE_STEPS; ++u) sl[u] = local_slot[min(max(ex[u], 0), E - 1)];
+            for (int u = 0; u < PE_STEPS; ++u) sl[u] = local_slot[min(max(ex[u], 0), E - 1)];
 #pragma unroll
-        for (int u = 0; u < PE_STEPS; ++u) sl[u] = (ex[u] >= 0 && ex[u] < E) ? sl[u] : -1;
-    } else {
+            for (int u = 0; u < PE_STEPS; ++u) sl[u] = (ex[u] >= 0 && ex[u] < E) ? sl[u] : -1;
+        } else {
 #pragma unroll
-        for (int u = 0; u < PE_STEPS; ++u) sl[u] = sl[u] < E ? sl[u] : -1;
-    }
-    int mine = 0, less = 0;
+            for (int u = 0; u < PE_STEPS; ++u) sl[u] = sl[u] < E ? sl[u] : -1;
+        }
 #pragma unroll
-    for (int u = 0; u < PE_STEPS; ++u) {
-        const bool slot_ok = sl[u] >= 0 && sl[u] < E_local;
-        sl[u] = a_begin + u * 64 + lane < a_end ? (slot_ok ? sl[u] : -1) : -2;  // -2: past the end
-        mine += sl[u] == e;
-        less += sl[u] >= 0 && sl[u] < e;
-    }
+        for (int u = 0; u < PE_STEPS; ++u) {
+            const bool slot_ok = sl[u] >= 0 && sl[u] < E_local;
+            sl[u] = c0 + u * 64 + lane < a_end ? (slot_ok ? sl[u] : -1) : -2;  // -2: past the end
+        }
+    };
+    int mine = 0, less = 0, c0 = a_begin;
+    do {
+        load(c0);
+#pragma unroll
+        for (int u = 0; u < PE_STEPS; ++u) {
+            mine += sl[u] == e;
+            less += sl[u] >= 0 && sl[u] < e;
+        }
+        c0 += PE_STEPS * 64;
+    } while (PIECES && c0 < a_end);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         mine += __shfl_xor(mine, off);
@@ -274,19 +286,24 @@ __global__ __launch_bounds__(PE_WAVES * 64) void permute_by_slot_kernel(
         if (e == E_local - 1) offsets[E_local] = start + total;
     }
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    c0 = a_begin;
+    do {
+        if (PIECES) load(c0);
 #pragma unroll
-    for (int u = 0; u < PE_STEPS; ++u) {
-        const int a = a_begin + u * 64 + lane;
-        const uint64_t m = __ballot(sl[u] == e);
-        if (sl[u] == e) {
-            const int p = run + __popcll(m & lt);
-            perm[p] = a;
-            inv_perm[a] = p;
-        } else if (e == 0 && sl[u] == -1) {
-            inv_perm[a] = -1;
+        for (int u = 0; u < PE_STEPS; ++u) {
+            const int a = c0 + u * 64 + lane;
+            const uint64_t m = __ballot(sl[u] == e);
+            if (sl[u] == e) {
+                const int p = run + __popcll(m & lt);
+                perm[p] = a;
+                inv_perm[a] = p;
+            } else if (e == 0 && sl[u] == -1) {
+                inv_perm[a] = -1;
+            }
+            run += __popcll(m);
         }
-        run += __popcll(m);
-    }
+        c0 += PE_STEPS * 64;
+    } while (PIECES && c0 < a_end);
 }
 
 // One wave per token; row bytes must be a multiple of 16.  The token's K positions are fetched
@@ -396,7 +413,7 @@ int c2r::permute_rows(const void *x, c2r_dtype dt, int64_t T, int d, int K, cons
 static int permute_impl(const void *x, c2r_dtype dt, const int32_t *topk_idx, int64_t T, int d,
                         int E, int K, const int32_t *local_slot, int E_local, int32_t *counts,
                         int32_t *offsets, int32_t *perm, int32_t *inv_perm, void *x_perm,
-                        void *ws, size_t ws_bytes, void *stream) {
+                        void *ws, size_t ws_bytes, int64_t by_slot_max, void *stream) {
     drop_stale_error();
     const int rc = permute_check(x, dt, topk_idx, T, d, E, K, local_slot, E_local, counts, offsets, perm, inv_perm, x_perm, ws,
                                  ws_bytes);
@@ -406,13 +423,20 @@ static int permute_impl(const void *x, c2r_dtype dt, const int32_t *topk_idx, in
     int32_t *block_counts = static_cast<int32_t *>(ws);
     int32_t *block_base = reinterpret_cast<int32_t *>(static_cast<char *>(ws) +
                                                       round_up((size_t)nblocks * E_local * sizeof(int32_t), 256));
-    if (A > 0 && A <= BY_SLOT_MAX) {
+    if (A > 0 && A <= by_slot_max) {
         // the index array is swept once per slot out of L2, in one launch
         const dim3 g((unsigned)E_local), b(PE_WAVES * 64);
-        if (A <= PE_WAVES * 64)
-            permute_by_slot_kernel<1><<<g, b, 0, st>>>(topk_idx, (int)A, E, local_slot, E_local, counts, offsets, perm, inv_perm);
+#define C2R_BY_SLOT(...) \
+    permute_by_slot_kernel<__VA_ARGS__><<<g, b, 0, st>>>(topk_idx, (int)A, E, local_slot, E_local, counts, offsets, perm, inv_perm)
+        if (A <= PE_WAVES * C2R_WAVE)
+            C2R_BY_SLOT(1);
+        else if (A <= PE_WAVES * C2R_WAVE * 4)
+            C2R_BY_SLOT(4);
+        else if (A <= PE_WAVES * C2R_WAVE * 16)
+            C2R_BY_SLOT(16);
         else
-            permute_by_slot_kernel<4><<<g, b, 0, st>>>(topk_idx, (int)A, E, local_slot, E_local, counts, offsets, perm, inv_perm);
+            C2R_BY_SLOT(16, true);
+#undef C2R_BY_SLOT
     } else {
         if (nblocks > 0)
             permute_hist_kernel<<<dim3((unsigned)nblocks), dim3(PB_THREADS), 0, st>>>(
@@ -437,7 +461,7 @@ extern "C" int c2r_permute(const void *x, c2r_dtype dt, const int32_t *topk_idx,
                            int32_t *offsets, int32_t *perm, int32_t *inv_perm, void *x_perm,
                            void *ws, size_t ws_bytes, void *stream) {
     return permute_impl(x, dt, topk_idx, T, d, E, K, local_slot, E_local, counts, offsets, perm, inv_perm, x_perm,
-                        ws, ws_bytes, stream);
+                        ws, ws_bytes, BY_SLOT_MAX, stream);
 }
 
 // ---- c2r_permute for callers that cannot allocate: the block histograms live in a static
@@ -477,5 +501,5 @@ extern "C" int c2r_permute_noalloc(const void *x, c2r_dtype dt, const int32_t *t
     const int rc = noalloc_scratch(&ws);
     if (rc != C2R_OK) return rc;
     return permute_impl(x, dt, topk_idx, T, d, E, K, local_slot, E_local, counts, offsets, perm, inv_perm, x_perm,
-                        ws, NOALLOC_SCRATCH_BYTES, stream);
+                        ws, NOALLOC_SCRATCH_BYTES, BY_SLOT_NOALLOC_MAX, stream);
 }

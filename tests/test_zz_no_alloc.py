@@ -44,12 +44,35 @@ def _case(c2r, seed, T, K, E, d, local):
 
 
 def test_permute_noalloc_two_calls_second_smaller(c2r):
-    # both sizes are above the one-launch switch point (4096 assignments), so both calls go
+    # both sizes are above the one-launch switch point (49152 assignments), so both calls go
     # through the block histograms in the static array; the second reuses it with fewer blocks
     _case(c2r, 1, T=70000, K=4, E=60, d=64, local=False)
     _case(c2r, 2, T=20000, K=4, E=60, d=64, local=True)
     # and one below the switch point (no scratch is read)
     _case(c2r, 3, T=1000, K=2, E=8, d=64, local=False)
+
+
+# up to 49152 assignments a call touches nothing that another one shares: many of them on two streams at once
+@pytest.mark.parametrize("T,K,E,local", [(1025, 4, 60, False), (4096, 4, 60, True), (4097, 4, 64, False), (12288, 4, 60, False),
+                                         (49152, 1, 16, True), (16384, 3, 7, True)])
+def test_permute_noalloc_overlapping_calls(c2r, T, K, E, local):
+    _case(c2r, 4, T, K, E, 8, local)
+    _case(c2r, 5, T - 1, K, E, 8, not local)
+    rng = np.random.default_rng(T)
+    idx = [torch.from_numpy(rng.integers(0, E, size=(T - n, K)).astype(np.int32)).cuda() for n in (0, 700)]
+    ref = [c2r.permute(None, i, E, rows=False) for i in idx]
+    out = [[_outputs(T - n, K, E, 8, torch.bfloat16)[:4] + (None,) for _ in range(20)] for n in (0, 700)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in idx]
+    for j in range(20):
+        for s, i, o in zip(streams, idx, out):
+            with torch.cuda.stream(s):
+                c2r.permute_noalloc(None, i, E, None, E, out=o[j])
+    torch.cuda.synchronize()
+    for r, o in zip(ref, out):
+        for got in o:
+            for a, b in zip(got[:4], r[:4]):
+                assert torch.equal(a, b)
 
 
 def test_permute_noalloc_rejects_sizes_beyond_its_array(c2r):
