@@ -45,16 +45,19 @@ __global__ __launch_bounds__(256) void pack_router_kernel(const float *__restric
 // identical, denormal and overflow ranges included), so a chain of them over ascending k IS
 // the declared order, at twice the rate the vector pipe reaches without packed instructions.
 // Lanes 0-31 feed k, lanes 32-63 k+1: one W value and one x value per lane and instruction.
-// With 32-token wave tiles the chunks of a workgroup are one software-pipelined stream of sub-tiles (see PIPE below).  What
-// bounds it is the matrix pipe, at the clock the power limit leaves (about 2.0 GHz: 131 TFLOP/s of the nominal 157), and with
-// one wave per SIMD (32768 tokens) the trips to memory that nothing else hides.  Microseconds of the stage, 60 experts, d 2048,
-// a pipeline per chunk (filled and drained at every 256 k) / one stream: 32768 tokens 102 / 86.6, fp32 117 / 90; 65536 tokens
-// 162 / 153.5 (116 TFLOP/s on 64 columns); 16384 tokens 55.4 / 51.6.
+// With 32-token wave tiles the sub-tiles of a workgroup's chunks are software-pipelined (see PIPE below), in one stream across the
+// chunks (STREAM).  What bounds it is the matrix pipe, at the clock the power limit leaves (about 2.0 GHz: 131 TFLOP/s of the nominal
+// 157), and with one wave per SIMD (32768 tokens) the trips to memory that nothing else hides.  Microseconds of the stage, 60 experts, d
+// 2048, a pipeline per chunk (filled and drained at every 256 k) / one stream: 32768 tokens 102 / 86.6, fp32 117 / 90; 65536 tokens
+// 162 / 153.5 (116 TFLOP/s on 64 columns); 16384 tokens 56.2 / 53.0.  Where a chunk is a workgroup of its own and the tile 32 experts
+// wide, a pipeline per chunk is the faster one: its three smaller buffers leave room for three workgroups on a CU instead of two.  (16
+// experts, d 4096: 9000 tokens 35.3 / 38.4, 26000 tokens 75.0 / 83.5; 32 experts, d 2048: 12000 tokens 27.7 / 30.0; 12 experts, d 8192: 16384
+// tokens 93.5 / 107.8.  With sub-tiles of half the length the stream takes 36.3, 77.0, 28.2 and 104.4.)
 // ALLCHUNKS (matrix pipe only): the workgroup walks ALL the chunks of its tokens and adds the
 // chunk results up in registers, left to right - the declared order - so that scratch holds one
 // 64-expert vector per token (256 bytes) instead of one per chunk (2 KB at d = 2048, written
-// here and read back by the selection).  For batches with at least one wave tile per SIMD of
-// the chip; smaller batches need the chunks as separate workgroups to fill it.
+// here and read back by the selection).  For batches with about a wave tile per SIMD of the chip (the rule: route_impl);
+// smaller batches need the chunks as separate workgroups to fill it.
 // HALVES: a token tile's two blocks of 32 experts by a wave each, half the tokens per workgroup.
 template <bool BF16, int TE, int NWV, int TQ, bool MFMA, bool ALLCHUNKS = false, bool HALVES = false>
 __global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) void route_partial_kernel(const void *__restrict__ x,
@@ -66,7 +69,8 @@ __global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) v
     constexpr int NT = HALVES ? NWV / 2 : NWV;  // wave tiles of tokens in a workgroup
     static_assert(!HALVES || (MFMA && EPAD == 64), "halves of 32 experts");
     constexpr int TOK = 8 * TQ;          // tokens covered by a wave
-    constexpr int KS = MFMA && !BF16 ? 16 : 32;  // k per staged sub-tile (64 bytes of a token's row on the matrix pipe)
+    constexpr bool PIPE = MFMA && TOK == 32, STREAM = PIPE && (EPAD == 64 || ALLCHUNKS);
+    constexpr int KS = STREAM && !BF16 ? 16 : 32;  // k per staged sub-tile
     constexpr int VEC = BF16 ? 8 : 4;    // elements per 16-byte vector of x
     constexpr int ESZ = BF16 ? 2 : 4;
     constexpr int XV = KS / VEC;         // 16-byte vectors per token per sub-tile
@@ -76,10 +80,9 @@ __global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) v
     constexpr int WF4 = KS * EPAD / 4;     // float4 per W sub-tile
     constexpr int WLOADS = (WF4 + NWV * 64 - 1) / (NWV * 64);
     // One wave's matrix instructions of a sub-tile overlap its own operand reads of the next one
-    // (PIPE): that takes a third LDS buffer and two operand register sets, which fit 32-token
-    // wave tiles only.
-    constexpr bool PIPE = MFMA && TOK == 32;
-    constexpr int NBUF = PIPE ? 4 : 2;
+    // (PIPE): that takes a third LDS buffer - the stream a fourth - and two operand register sets,
+    // which fit 32-token wave tiles only.
+    constexpr int NBUF = STREAM ? 4 : PIPE ? 3 : 2;
     // (Counted on the matrix-pipe form at E = 60: SQ_LDS_BANK_CONFLICT = 128 cycles per wave task of
     // 8 sub-tiles, i.e. 16 per sub-tile - one per x operand read: 32 token rows 80 bytes apart fall
     // on 16 banks, a 2-way conflict that any row pitch that keeps the 16-byte staging stores
@@ -107,10 +110,9 @@ __global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) v
     const int64_t t0 = (tgroup * NT + xt) * TOK;   // of the tile whose x this wave brings
     const unsigned char *xb = static_cast<const unsigned char *>(x);
 
-    // global loads of a sub-tile are held in registers until its LDS buffer is free; several sets
-    // (two in the plain loop, three in the pipelined one), so that a sub-tile is fetched two or
-    // three sub-tiles ahead (on the matrix pipe one sub-tile of compute is shorter than the
-    // memory latency)
+    // global loads of a sub-tile are held in registers until its LDS buffer is free; several sets (two in the plain loop, three
+    // in the pipeline of a chunk, two of W and four of x in the stream), so that a sub-tile is fetched several sub-tiles
+    // ahead (on the matrix pipe one sub-tile of compute is shorter than the memory latency)
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     struct Staged {
@@ -315,10 +317,7 @@ __global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) v
                 for (int i = 0; i < 16; ++i) mtot[a][b][i] = -0.0f;
     }
     if constexpr (PIPE) {
-        // The whole chunks, as ONE stream of sub-tiles that runs on across chunk ends.  At step j: operands of sub-tile j in
-        // registers (set j % 2), sub-tiles j+1 and j+2 in LDS (buffer j % 4), sub-tile j+3 on its way there from its staging
-        // registers, W of j+4 and x of j+4 to j+6 (which comes from memory, W from L2) in flight.  (Past the last sub-tile that one
-        // again, never used.)  The chain of every accumulator still takes k in ascending order, two per instruction.
+        // The whole chunks.  The chain of every accumulator still takes k in ascending order, two per instruction.
         struct Ops {
             float w[KS / 2][NEB];
             uint32_t x[KS / 2][NTB];
@@ -349,93 +348,142 @@ __global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) v
                 }
         };
         constexpr int NSUB = C2R_CANON_CHUNK / KS;
-        static_assert(NSUB % 4 == 0, "buffers and register sets take their turns inside a chunk");
-        const int nwhole = min(chunk_last + 1, d / C2R_CANON_CHUNK) - chunk_first;
-        if (nwhole > 0) {
-            const int klast = (chunk_first + nwhole) * C2R_CANON_CHUNK - KS;
-            f32x4 SW[2][WLOADS];
-            u32x4 SX[4][XLOADS];
-            auto load_w = [&](f32x4 (&r)[WLOADS], int k0) __attribute__((always_inline)) {
-                const unsigned char *wb = reinterpret_cast<const unsigned char *>(W + (size_t)min(k0, klast) * ldw);
+        if constexpr (STREAM) {
+            // ONE stream of sub-tiles that runs on across chunk ends.  At step j: operands of sub-tile j in
+            // registers (set j % 2), sub-tiles j+1 and j+2 in LDS (buffer j % 4), sub-tile j+3 on its way there from its staging
+            // registers, W of j+4 and x of j+4 to j+6 (which comes from memory, W from L2) in flight.  (Past the last sub-tile that one
+            // again, never used.)
+            static_assert(NSUB % 4 == 0, "buffers and register sets take their turns inside a chunk");
+            const int nwhole = min(chunk_last + 1, d / C2R_CANON_CHUNK) - chunk_first;
+            if (nwhole > 0) {
+                const int klast = (chunk_first + nwhole) * C2R_CANON_CHUNK - KS;
+                f32x4 SW[2][WLOADS];
+                u32x4 SX[4][XLOADS];
+                auto load_w = [&](f32x4 (&r)[WLOADS], int k0) __attribute__((always_inline)) {
+                    const unsigned char *wb = reinterpret_cast<const unsigned char *>(W + (size_t)min(k0, klast) * ldw);
 #pragma unroll
-                for (int i = 0; i < WLOADS; ++i) r[i] = *reinterpret_cast<const f32x4 *>(wb + woff[i]);
-            };
-            auto load_x = [&](u32x4 (&r)[XLOADS], int k0) __attribute__((always_inline)) {
-                const unsigned char *xs = xb + ((size_t)tb * d + min(k0, klast)) * ESZ;
+                    for (int i = 0; i < WLOADS; ++i) r[i] = *reinterpret_cast<const f32x4 *>(wb + woff[i]);
+                };
+                auto load_x = [&](u32x4 (&r)[XLOADS], int k0) __attribute__((always_inline)) {
+                    const unsigned char *xs = xb + ((size_t)tb * d + min(k0, klast)) * ESZ;
 #pragma unroll
-                for (int i = 0; i < XLOADS; ++i) r[i] = *reinterpret_cast<const u32x4 *>(xs + xoff[i]);
-            };
-            auto to_lds = [&](const f32x4 (&w)[WLOADS], const u32x4 (&xv)[XLOADS], int buf) __attribute__((always_inline)) {
+                    for (int i = 0; i < XLOADS; ++i) r[i] = *reinterpret_cast<const u32x4 *>(xs + xoff[i]);
+                };
+                auto to_lds = [&](const f32x4 (&w)[WLOADS], const u32x4 (&xv)[XLOADS], int buf) __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < WLOADS; ++i) {
-                    const int idx = tid + i * NWV * 64;
-                    if (WF4 % (NWV * 64) == 0 || idx < WF4)
-                        *reinterpret_cast<f32x4 *>(&Wl[buf][idx / (EPAD / 4)][(idx % (EPAD / 4)) * 4]) = w[i];
-                }
-#pragma unroll
-                for (int i = 0; i < XLOADS; ++i) {
-                    const int idx = x0 + lane + i * 64;
-                    *reinterpret_cast<u32x4 *>(&Xl[buf][xt][(idx / XV) * XPITCH + (idx % XV) * 16]) = xv[i];
-                }
-            };
-            Ops O[2];
-            int k0 = chunk_first * C2R_CANON_CHUNK;
-            load_w(SW[0], k0);
-            load_x(SX[0], k0);
-            load_w(SW[1], k0 + KS);
-            load_x(SX[1], k0 + KS);
-            load_x(SX[2], k0 + 2 * KS);
-            load_x(SX[3], k0 + 3 * KS);
-            to_lds(SW[0], SX[0], 0);
-            load_w(SW[0], k0 + 2 * KS);
-            load_x(SX[0], k0 + 4 * KS);
-            to_lds(SW[1], SX[1], 1);
-            load_w(SW[1], k0 + 3 * KS);
-            load_x(SX[1], k0 + 5 * KS);
-            to_lds(SW[0], SX[2], 2);
-            load_w(SW[0], k0 + 4 * KS);
-            load_x(SX[2], k0 + 6 * KS);
-            lds_hand_over();
-            read_ops(O[0], 0);
-            lds_hand_over();
-            for (int c = 0; c < nwhole; ++c, k0 += C2R_CANON_CHUNK) {
-#pragma unroll
-                for (int i = 0; i < NSUB; ++i) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    read_ops(O[(i + 1) & 1], (i + 1) & 3);
-                    to_lds(SW[(i + 3) & 1], SX[(i + 3) & 3], (i + 3) & 3);
-                    load_w(SW[(i + 3) & 1], k0 + (i + 5) * KS);
-                    load_x(SX[(i + 3) & 3], k0 + (i + 7) * KS);
-                    mma(O[i & 1]);
-                    // the step's memory instructions go between its matrix instructions, as a rule one each:
-                    // the wave issues them while the matrix pipe works
-                    constexpr int NMMA = NEB * NTB * KS / 2;
-                    constexpr int NRD = KS / 4 * NEB + (BF16 ? KS / 8 : KS / 4) * NTB, NST = WLOADS + XLOADS;
-                    constexpr int PER = (NRD + 2 * NST + NMMA - 1) / NMMA;
-#pragma unroll
-                    for (int m = 0; m < NMMA; ++m) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a matrix instruction
-#pragma unroll
-                        for (int n = m * PER; n < (m + 1) * PER; ++n) {
-                            if (n < NRD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // an LDS read
-                            else if (n < NRD + NST) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // an LDS write
-                            else if (n < NRD + 2 * NST) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // a global load
-                        }
+                    for (int i = 0; i < WLOADS; ++i) {
+                        const int idx = tid + i * NWV * 64;
+                        if (WF4 % (NWV * 64) == 0 || idx < WF4)
+                            *reinterpret_cast<f32x4 *>(&Wl[buf][idx / (EPAD / 4)][(idx % (EPAD / 4)) * 4]) = w[i];
                     }
-                    __builtin_amdgcn_sched_barrier(0);
-                    // A buffer is written two steps before it is read and two steps after it was: one barrier per two steps.
-                    if (i & 1) lds_hand_over();
+#pragma unroll
+                    for (int i = 0; i < XLOADS; ++i) {
+                        const int idx = x0 + lane + i * 64;
+                        *reinterpret_cast<u32x4 *>(&Xl[buf][xt][(idx / XV) * XPITCH + (idx % XV) * 16]) = xv[i];
+                    }
+                };
+                Ops O[2];
+                int k0 = chunk_first * C2R_CANON_CHUNK;
+                load_w(SW[0], k0);
+                load_x(SX[0], k0);
+                load_w(SW[1], k0 + KS);
+                load_x(SX[1], k0 + KS);
+                load_x(SX[2], k0 + 2 * KS);
+                load_x(SX[3], k0 + 3 * KS);
+                to_lds(SW[0], SX[0], 0);
+                load_w(SW[0], k0 + 2 * KS);
+                load_x(SX[0], k0 + 4 * KS);
+                to_lds(SW[1], SX[1], 1);
+                load_w(SW[1], k0 + 3 * KS);
+                load_x(SX[1], k0 + 5 * KS);
+                to_lds(SW[0], SX[2], 2);
+                load_w(SW[0], k0 + 4 * KS);
+                load_x(SX[2], k0 + 6 * KS);
+                lds_hand_over();
+                read_ops(O[0], 0);
+                lds_hand_over();
+                for (int c = 0; c < nwhole; ++c, k0 += C2R_CANON_CHUNK) {
+#pragma unroll
+                    for (int i = 0; i < NSUB; ++i) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        read_ops(O[(i + 1) & 1], (i + 1) & 3);
+                        to_lds(SW[(i + 3) & 1], SX[(i + 3) & 3], (i + 3) & 3);
+                        load_w(SW[(i + 3) & 1], k0 + (i + 5) * KS);
+                        load_x(SX[(i + 3) & 3], k0 + (i + 7) * KS);
+                        mma(O[i & 1]);
+                        // the step's memory instructions go between its matrix instructions, as a rule one each:
+                        // the wave issues them while the matrix pipe works
+                        constexpr int NMMA = NEB * NTB * KS / 2;
+                        constexpr int NRD = KS / 4 * NEB + (BF16 ? KS / 8 : KS / 4) * NTB, NST = WLOADS + XLOADS;
+                        constexpr int PER = (NRD + 2 * NST + NMMA - 1) / NMMA;
+#pragma unroll
+                        for (int m = 0; m < NMMA; ++m) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a matrix instruction
+#pragma unroll
+                            for (int n = m * PER; n < (m + 1) * PER; ++n) {
+                                if (n < NRD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // an LDS read
+                                else if (n < NRD + NST) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // an LDS write
+                                else if (n < NRD + 2 * NST) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // a global load
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        // A buffer is written two steps before it is read and two steps after it was: one barrier per two steps.
+                        if (i & 1) lds_hand_over();
+                    }
+                    finish_chunk(chunk_first + c);
                 }
-                finish_chunk(chunk_first + c);
+                chunk += nwhole;
+                lds_hand_over();  // (a ragged last chunk starts on the same buffers)
             }
-            chunk += nwhole;
-            lds_hand_over();  // (a ragged last chunk starts on the same buffers)
+        } else if (k_end - k_begin == C2R_CANON_CHUNK) {
+            // A workgroup's one chunk.  At step j: operands of sub-tile j in registers (set j % 2), sub-tile j+1 in LDS (buffer
+            // j % 3), sub-tile j+2 on its way there from its staging registers (set j % 3), j+3 and j+4 in flight.  Straight-line
+            // code, the loads of a whole sub-tile unclamped: only there are the waits for the oldest set alone.
+            static_assert(STREAM || NSUB >= 5, "the prologue fetches sub-tiles 0 to 4");
+            auto load = [&](Staged &r, int k0) __attribute__((always_inline)) {
+                const unsigned char *wb = reinterpret_cast<const unsigned char *>(W + (size_t)k0 * ldw);
+                const unsigned char *xs = xb + ((size_t)tb * d + k0) * ESZ;
+#pragma unroll
+                for (int i = 0; i < WLOADS; ++i) r.w[i] = *reinterpret_cast<const f32x4 *>(wb + woff[i]);
+#pragma unroll
+                for (int i = 0; i < XLOADS; ++i) r.x[i] = *reinterpret_cast<const u32x4 *>(xs + xoff[i]);
+            };
+            Staged R[3];
+            Ops O[2];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) load(R[i], k_begin + i * KS);
+            lstore(R[0], 0);
+            load(R[0], k_begin + 3 * KS);
+            __syncthreads();
+            read_ops(O[0], 0);
+            lstore(R[1], 1);
+            load(R[1], k_begin + 4 * KS);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NSUB; ++i) {
+                if (i + 1 < NSUB) read_ops(O[(i + 1) & 1], (i + 1) % 3);
+                if (i + 2 < NSUB) lstore(R[(i + 2) % 3], (i + 2) % 3);
+                if (i + 5 < NSUB) load(R[(i + 2) % 3], k_begin + (i + 5) * KS);
+                mma(O[i & 1]);
+                // an LDS read after each matrix instruction: the wave issues them while the matrix pipe works
+#pragma unroll
+                for (int m = 0; m < NEB * NTB * KS / 2; ++m) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + 1 < NSUB) __syncthreads();
+            }
+            finish_chunk(chunk);
+            ++chunk;
         }
     }
-    for (; chunk <= chunk_last; ++chunk) {
-    k_begin = chunk * C2R_CANON_CHUNK;
-    k_end = min(d, k_begin + C2R_CANON_CHUNK);
-    {
+    static_assert(STREAM || !ALLCHUNKS, "otherwise a workgroup has one chunk");
+    if (chunk <= chunk_last) {  // the one chunk that is left: a ragged last one, or the only one
+    if constexpr (STREAM) {
+        k_begin = chunk * C2R_CANON_CHUNK;
+        k_end = min(d, k_begin + C2R_CANON_CHUNK);
+    }
     Staged r0, r1;
     gload(r0, k_begin);
     lstore(r0, 0);
@@ -452,7 +500,6 @@ __global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) v
         if (k0 + 2 * KS < k_end) lstore(r0, 0);
         gload(r0, k0 + 4 * KS);
         __syncthreads();
-    }
     }
     finish_chunk(chunk);
     }
@@ -1862,10 +1909,12 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
     // tokens 92 / 103, 30000 tokens 104 / 103.5.
     const bool all_chunks = !wide && te > 1 && nwt >= (te == 8 ? 784 : 1024) && L.nchunk > 1;
     const int nchunk_out = all_chunks ? 1 : L.nchunk;
-    // Chunks a workgroup walks otherwise: two where that still makes a workgroup per CU (16384 tokens of 60 experts, d 2048: the
-    // stage 53.9 us with one, 51.6 with two, 53.5 with four; 8192 tokens of 16 experts, d 4096: 32.5 / 31.1 / 33.7).
-    const int64_t ngroups = (nwt + NWV - 1) / NWV;
-    const int cpw = all_chunks ? L.nchunk : (te > 1 && ngroups * ((L.nchunk + 1) / 2) >= 256) ? 2 : 1;
+    // Chunks a workgroup walks otherwise: two with more than 32 experts where that makes a workgroup per CU and the busiest CU has no
+    // more chunks for it (E 60, d 2048: 8192 tokens, fp32, 35.2 us with one, 32.9 with two; 16384 tokens 55.2 / 53.0; but 8193 tokens,
+    // 260 workgroups of two, 41.8 / 49.0, 20000 tokens 65.1 / 71.2; three or four are never ahead of both by more than 5 %).
+    const int64_t ngroups = (nwt + NWV - 1) / NWV, ntwo = ngroups * ((L.nchunk + 1) / 2);
+    const bool two = te == 8 && ntwo >= 256 && (ntwo + 255) / 256 * 2 <= (ngroups * L.nchunk + 255) / 256;
+    const int cpw = all_chunks ? L.nchunk : two ? 2 : 1;
     // Workgroups of 128 tokens come in rounds of the chip's CUs, and the first batches past a round (or two) leave most of the last one
     // empty: workgroups of 64 tokens, their waves 32 experts each, make it one of half the length.  (33000 tokens 147 / 124 us,
     // 48000 tokens 149 / 126, 72000 tokens 221 / 201, fp32 33000 tokens 152 / 119; full rounds cost 4 to 9 % more that way, x
