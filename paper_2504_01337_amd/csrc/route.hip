@@ -1822,10 +1822,12 @@ extern "C" int c2r_route_chunk(void) { return C2R_CANON_CHUNK; }
 // Selection from chunk results.
 static int launch_select(const float *part, int EP_, int nchunk, const float *bias, int64_t T, int E, int K,
                          const int32_t *collab_idx, int Tc, int32_t *topk_idx, float *gates, float *logits_out, hipStream_t st) {
-    // Up to 8192 tokens the 64-token workgroups are at most half as many as the CUs.  Microseconds of the kernel (64 / 16 tokens per
-    // workgroup), 60 experts, d 2048: 131 tokens 10.5 / 5.4, 1000 tokens 11.9 / 6.2, 8192 tokens 11.9 / 9.3; 16 experts, d 4096, 4096 tokens
-    // 7.2 / 6.5.  Beyond, with every CU at work, the shorter scans count (the stage: 16384 tokens 52.7 / 54.2, 65536 tokens 155 / 157).
-    if (T <= 8192) {
+    // Up to 8192 tokens the 64-token workgroups are at most half as many as the CUs; sixteen lanes per token pay with many experts or
+    // slots.  Microseconds of the kernel (64 / 16 tokens per workgroup), 60 experts, d 2048: 131 tokens 10.5 / 5.4, 1000 tokens 11.9 / 6.2,
+    // 8192 tokens 11.9 / 9.3; of the stage, 32 experts 300 tokens 12 % less, 4096 tokens 1 % more; 16 experts, d 4096, 4096 tokens 17.5 / 18.3, but
+    // 16 slots 29 / 27; 8 experts, d 1024, 300 tokens 8.8 / 9.4; 60 experts, 1 slot, 6000 tokens 29.6 / 31.1.  Beyond, with every CU at work, the shorter scans count (the stage, 60
+    // experts: 16384 tokens 52.7 / 54.2, 65536 tokens 155 / 157).
+    if (T <= (K > 8 ? 8192 : EP_ > 32 ? (K > 2 ? 8192 : 4096) : EP_ > 16 ? 2048 : 0)) {
         route_select_small_kernel<<<dim3((unsigned)((T + SEL16_TOKENS - 1) / SEL16_TOKENS)), dim3(256), 0, st>>>(
             part, EP_, nchunk, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out);
         return launch_status();

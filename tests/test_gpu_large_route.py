@@ -59,6 +59,35 @@ def test_large_selection_from_one_chunk(orc, T, E, K, dtype):
             np.testing.assert_allclose(host(gates), rg, rtol=114 / 34 * GATE_RTOL, atol=1e-37)
 
 
+# selection from several chunk results, by sixteen lanes per token and by four (the sizes on either side of the rule: 16 and 32 experts; 2048, 4096
+# and 8192 tokens; 2 and 8 slots), few slots, five to eight and more; lists of more than sixteen entries with the expert itself, duplicates and
+# entries out of range; ties, NaN and infinite logits
+@pytest.mark.parametrize("T,E,K,d", [
+    (65, 8, 8, 1032), (300, 16, 5, 776), (300, 16, 16, 520), (2048, 20, 4, 520), (2049, 20, 4, 520), (2050, 32, 8, 264), (2050, 32, 9, 264),
+    (4096, 60, 2, 776), (4097, 60, 2, 776), (4100, 33, 1, 264), (8192, 40, 3, 520), (8192, 17, 13, 264), (8193, 12, 9, 264), (8193, 60, 4, 776),
+    (8200, 64, 17, 520), (8256, 61, 6, 520), (9000, 60, 8, 776), (9000, 36, 5, 264), (16400, 60, 4, 776)])
+def test_selection_from_several_chunks(orc, T, E, K, d):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(T + E + K)
+    x = rng.integers(-2, 3, size=(T, d)).astype(np.float32)
+    x[::3] = rng.standard_normal((len(x[::3]), d)).astype(np.float32)
+    x[::7, 8:] = 0.0
+    x[5], x[44] = np.inf, np.nan
+    Wg = rng.integers(-2, 3, size=(d, E)).astype(np.float32)
+    Wg[::5] = 0.03 * rng.standard_normal(Wg[::5].shape)
+    bias = np.where(rng.random(E) < 0.1, np.float32(-np.inf), rng.integers(-2, 3, size=E)).astype(np.float32)
+    cl = np.stack([rng.permutation(np.delete(np.arange(E), e))[:max(K, min(E - 1, 18))] for e in range(E)]).astype(np.int32)
+    gl = np.concatenate([np.full((E, 1), -1), cl[:, :1], cl, np.arange(E)[:, None], np.full((E, 1), E)], axis=1).astype(np.int32)
+    for b in (None, bias):
+        for c, g in ((None, None), (cl, gl)):
+            idx, gates, logits = c2r.route(dev(x), dev(Wg), None if b is None else dev(b), K, None if g is None else dev(g), want_logits=True)
+            ri, rg = orc.route(host(logits), K, c)
+            assert np.array_equal(host(idx), ri)
+            # logits of up to some hundred apart: the bound of GATE_RTOL with |a_s| up to 104, where a gate is flushed to zero (and, for K up to
+            # 17, nine more roundings of the sum)
+            np.testing.assert_allclose(host(gates), rg, rtol=123 / 34 * GATE_RTOL, atol=1e-37)
+
+
 # undecided tokens in groups of 64 (none, a few that the wave scans together, one more, all): rows of zeros, rows with equal logits of either sign,
 # an expert masked by -infinity, NaN; a partial last group
 @pytest.mark.parametrize("E,K", [(60, 4), (64, 4), (36, 3), (16, 2), (8, 4), (5, 4)])
