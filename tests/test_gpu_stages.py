@@ -270,7 +270,9 @@ def test_collaborators(c2r, orc, E):
     # more than 4096 assignments: the histogram and rank launches instead of the one-launch sweep, whole blocks of 1024 and
     # remainders (the sizes at the switch: test_gpu_row_kernels.py)
     (60, 4, 70001, 8, "bf16", None), (16, 4, 65536, 8, "bf16", 5), (16, 4, 65537, 8, "bf16", None),
-    (60, 3, 16384, 8, "bf16", None), (16, 1, 49153, 8, "bf16", 5), (33, 1, 32769, 8, "bf16", None)])
+    (60, 3, 16384, 8, "bf16", None), (16, 1, 49153, 8, "bf16", 5), (33, 1, 32769, 8, "bf16", None),
+    # up to four slots: two ballots instead of six
+    (16, 4, 70000, 8, "bf16", 4), (8, 2, 5000, 8, "bf16", 1), (3, 1, 9000, 8, "f32", None), (2, 2, 300000, 8, "bf16", None)])
 def test_permute(c2r, orc, E, K, T, d, dtype, local):
     rng = np.random.default_rng(E * 7 + T)
     logits = rng.standard_normal((T, E)).astype(np.float32)
