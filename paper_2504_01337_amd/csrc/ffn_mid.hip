@@ -317,11 +317,11 @@ template <int MODE>
 static void mid_launch(int ragged_rows, int single_rows, const FfnLaunch &L, hipStream_t st) {
     const dim3 g(8 * MID_WG_PER_XCD), b(256);
 #define C2R_MID(ARR, ARS) ffn_mid_kernel<MODE, ARR, ARS><<<g, b, 0, st>>>(L)
-#define C2R_MID_S(ARR)                                             \
-    switch (single_rows) {                                         \
-        case 128: C2R_MID(ARR, 128); break;                        \
-        case 64: C2R_MID(ARR, 64); break;                          \
-        default: C2R_MID(ARR, 32);                                 \
+#define C2R_MID_S(ARR)                    \
+    if (single_rows == 64) {              \
+        C2R_MID(ARR, 64);                 \
+    } else {                              \
+        C2R_MID(ARR, 32);                 \
     }
     switch (ragged_rows) {
         case 128: C2R_MID_S(128) break;
@@ -340,25 +340,32 @@ static void mid_launch(int ragged_rows, int single_rows, const FfnLaunch &L, hip
 //     108 / 104, r = 88: 150 / 132 / 115, r = 125: 167 / 146 / 131 (tile kernel 143; down pass r = 100: 118 / 116 / 113 with it);
 //   beside a shared expert, ragged and shared tiles of 32+32 / 64+32 / 32+64 / 64+64 rows: n = 24: 107 / 106 / 108 / 108, n = 64: 133 / 134 / 145 /
 //     147, n = 90: 145 / 142 / 147 / 141, n = 131: 163 / 159 / 160 / 161, n = 178: 187 / 190 / 181 / 174; down pass alone n = 300: 197 / 197 /
-//     195 / 187, n = 500: 236 / 228 / 234 / 210 (64+128 216, the tile kernel 212 at 511).  (The skewed groups beside it hold up to eight
-//     times the mean: 64 rows from a mean of 5.)
+//     195 / 187, n = 500: 236 / 228 / 234 / 210 (64+128 216, the tile kernel 212 at 511): no shared tiles of 128.  (The skewed groups beside it
+//     hold up to eight times the mean: 64 rows from a mean of 5; measured on this one model.)
 // (r counts the rows allotted.  A device that holds a quarter of the experts has a quarter of them in use: its tiles are higher
 // than its rows would ask for, 15 of 60 experts at 300 tokens 67.0 / 65.0 / 71.9.)
 constexpr int MID_LOW_BESIDE = 4;
 
+// most rows (per group / in the single group), for 32-, 64- and 128-row tiles of gate/up and of down
+constexpr int MID_RAGGED_UP_TO[2][3] = {{20, 64, 150}, {20, 45, 90}}, MID_SINGLE_UP_TO[2][2] = {{64, 179}, {100, 511}};
+
 bool ffn_mid_rows(int pass, const FfnLaunch &L, int (&rows)[2]) {
+    for (int q = 0; q < 2; ++q)
+        if ((q == 0 ? L.has_ragged : L.has_single) && L.p[q].gather && (L.p[q].A_cap > MID_ROW_TABLE || L.p[q].gather_rows > 65536))
+            return false;
     rows[0] = rows[1] = 0;
-    for (int q = 0; q < 2; ++q) {
-        const FfnProblem &P = L.p[q];
-        if (!(q == 0 ? L.has_ragged : L.has_single)) continue;
-        if (P.gather && (P.A_cap > MID_ROW_TABLE || P.gather_rows > 65536)) return false;
-        static constexpr int up_to[2][2][3] = {{{20, 64, 150}, {64, 179, 179}}, {{20, 45, 90}, {100, 511, 511}}};
-        const int mean = q == 0 ? P.A_cap / P.E_local : P.A_cap, *most = up_to[pass][q];
+    if (L.has_ragged) {
+        const int mean = L.p[0].A_cap / L.p[0].E_local, *most = MID_RAGGED_UP_TO[pass];
         if (mean > most[2]) return false;
-        rows[q] = mean <= (q == 0 && L.has_single ? MID_LOW_BESIDE : most[0]) ? 32 : (mean <= most[1] ? 64 : 128);
+        rows[0] = mean <= (L.has_single ? MID_LOW_BESIDE : most[0]) ? 32 : (mean <= most[1] ? 64 : 128);
     }
-    if (!rows[0]) rows[0] = rows[1];
-    if (!rows[1]) rows[1] = rows[0];
+    if (L.has_single) {
+        const int n = L.p[1].A_cap, *most = MID_SINGLE_UP_TO[pass];
+        if (n > most[1]) return false;
+        rows[1] = n <= most[0] ? 32 : 64;
+    }
+    if (!rows[0]) rows[0] = rows[1];  // (a side that is not there walks nothing)
+    if (!rows[1]) rows[1] = rows[0] < 64 ? rows[0] : 64;
     return true;
 }
 

@@ -111,6 +111,28 @@ def ffn_kernel(which, E, A_cap, N):
         few = A_cap <= lim["DOWN_ROWS"] and (A_cap <= E or tiles < 1024) and (A_cap <= 16 * E or tiles <= 128)
     if few:
         return "few"
-    table = re.search(r"up_to\[2\]\[2\]\[3\] = ([{}\d, ]+);", _csrc("ffn_mid.hip")).group(1)
-    most = [int(v) for v in re.findall(r"\d+", table)][which * 6 + (3 if E == 1 else 0) + 2]
-    return "mid" if A_cap // E <= most else "tile"
+    most = _mid_limits("SINGLE" if E == 1 else "RAGGED")[which]
+    return "mid" if (A_cap if E == 1 else A_cap // E) <= most[-1] else "tile"
+
+
+def _mid_limits(side):
+    """Most rows of every tile height of ffn_mid.hip, per pass (side: RAGGED, per group, or SINGLE)."""
+    table = re.search(r"\bMID_%s_UP_TO\[2\]\[\d\] = \{([{}\d, ]+)\}" % side, _csrc("ffn_mid.hip")).group(1)
+    return [[int(v) for v in re.findall(r"\d+", t)] for t in re.findall(r"\{([\d, ]+)\}", table + "}")]
+
+
+def ffn_two_problems(which, E, A_cap, T):
+    """The same for a pass over E routed groups and a shared expert's T rows: the kernel, or, for ffn_mid.hip, the rows of the routed
+    and of the shared tiles."""
+    src, mid = _csrc("ffn_skinny.hip"), _csrc("ffn_mid.hip")
+    lim = {k: int(re.search(r"\bSKINNY_%s = (\d+)" % k, src).group(1))
+           for k in ("UP_ROWS", "UP_PER_GROUP", "UP_SINGLE", "DOWN_BESIDE", "DOWN_SINGLE")}
+    if which == 0 and T <= lim["UP_SINGLE"] and A_cap <= min(lim["UP_ROWS"], lim["UP_PER_GROUP"] * E):
+        return "few"
+    if which == 1 and T <= lim["DOWN_SINGLE"] and A_cap <= lim["DOWN_BESIDE"]:
+        return "few"
+    ragged, single, mean = _mid_limits("RAGGED")[which], _mid_limits("SINGLE")[which], A_cap // E
+    if mean > ragged[2] or T > single[1]:
+        return "tile"
+    low = int(re.search(r"\bMID_LOW_BESIDE = (\d+)", mid).group(1))
+    return 32 if mean <= low else 64 if mean <= ragged[1] else 128, 32 if T <= single[0] else 64

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2504_01337_amd import workloads as wl
-from helpers import TOL, dev, ffn_kernel, host, max_rel_err
+from helpers import TOL, dev, ffn_kernel, ffn_two_problems, host, max_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -106,11 +106,17 @@ def test_lower_tiles_of_a_single_group_change_no_bits(c2r, T):
 
 
 # two problems in one launch, tiles of their own heights and workgroups of their own: routed groups even, skewed, one holding all and
-# none holding any; single groups of one to eight chunks, short and long beside the routed ones
-@pytest.mark.parametrize("T,E,d,F,Fs,sizes", [
-    (20, 10, 128, 64, 1024, [8] * 10), (131, 60, 192, 128, 64, [100, 70] + [6] * 58), (179, 30, 64, 704, 320, [0] * 29 + [716]),
-    (70, 12, 704, 64, 64, [0] * 12), (500, 60, 64, 192, 1408, [400, 129, 65] + [24] * 57), (65, 40, 256, 320, 64, [65, 0, 33, 1] * 10)])
-def test_mid_two_problems_against_each_alone(c2r, T, E, d, F, Fs, sizes):
+# none holding any; single groups of one to eight chunks, short and long beside the routed ones.  up, down: the rows of the routed and of the
+# shared tiles of that pass, or the other kernel that takes it
+@pytest.mark.parametrize("T,E,d,F,Fs,sizes,cap,up,down", [
+    (20, 10, 128, 64, 1024, [8] * 10, 80, (64, 32), "few"), (131, 60, 192, 128, 64, [100, 70] + [6] * 58, 524, (64, 64), (64, 64)),
+    (179, 30, 64, 704, 320, [0] * 29 + [716], 716, (64, 64), (64, 64)), (70, 12, 704, 64, 64, [0] * 12, 280, (64, 64), (64, 32)),
+    (500, 60, 64, 192, 1408, [400, 129, 65] + [24] * 57, 2000, "tile", (64, 64)), (65, 40, 256, 320, 64, [65, 0, 33, 1] * 10, 990, (64, 64), (64, 32)),
+    (16, 60, 128, 1408, 320, [3, 0, 1] * 16 + [0] * 12, 64, (32, 32), "few"), (100, 60, 192, 320, 704, [2] * 60, 240, (32, 64), (32, 32)),
+    (150, 60, 704, 64, 320, [33, 0, 1] + [3] * 57, 240, (32, 64), (32, 64)), (179, 8, 128, 192, 320, [140, 0, 129, 1, 260, 100, 86, 0], 716, (128, 64), (128, 64)),
+    (200, 8, 256, 64, 704, [129, 70, 0, 1, 48, 60, 60, 32], 400, "tile", (128, 64)), (64, 4, 64, 320, 128, [200, 129, 0, 183], 512, (128, 32), "tile")])
+def test_mid_two_problems_against_each_alone(c2r, T, E, d, F, Fs, sizes, cap, up, down):
+    assert (ffn_two_problems(0, E, cap, T), ffn_two_problems(1, E, cap, T)) == (up, down)
     rng = np.random.default_rng(T * E)
     n = sum(sizes)
     r = lambda *s: dev((rng.standard_normal(s) * 0.1).astype(np.float32), "bf16")
@@ -118,8 +124,6 @@ def test_mid_two_problems_against_each_alone(c2r, T, E, d, F, Fs, sizes):
     offsets = dev(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
     x, wg, wu, wd, sg, su, sd = r(T, d), r(E, F, d), r(E, F, d), r(E, d, F), r(1, Fs, d), r(1, Fs, d), r(1, d, Fs)
     perm = dev(rng.integers(0, T * 4, size=max(n, 1)).astype(np.int32))
-    cap = max(n, T * 4)
-    assert ffn_kernel(1, 1, T, d) == "mid" or T <= 32
     h, y, hs, ys = z(cap, F), z(cap, d), z(T, Fs), z(T, d)
     full = torch.zeros(cap, dtype=torch.int32, device="cuda")
     full[:n] = perm[:n]
@@ -149,7 +153,7 @@ def test_mid_walks_of_a_few_more_experts():
     x, wg, wu, sg, su = r(T, d), r(E, F, d), r(E, F, d), r(1, Fs, d), r(1, Fs, d)
     h, hs = r(T * K, F), r(T, Fs)
     perm = torch.arange(T * K, dtype=torch.int32, device="cuda")
-    assert ffn_kernel(0, E, T * K, F) == "mid" and ffn_kernel(0, 1, T, Fs) == "mid"
+    assert ffn_two_problems(0, E, T * K, T) == (32, 32)
 
     def offsets(used, first):  # 96 rows of `used` experts from `first` on
         n = np.zeros(E, dtype=np.int64)
