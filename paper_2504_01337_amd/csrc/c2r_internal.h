@@ -54,4 +54,19 @@ int route_and_permute(const void *x, c2r_dtype dt, const float *Wg, const float 
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (C2R_WAVE - 1); }
 
+// The largest of the 64 lanes' values, in every lane, without LDS round trips.  Every lane must be active.
+__device__ __forceinline__ int wave_max(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int LOWEST = (int)0x80000000;
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1, 3
+    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2, 3
+    v = __builtin_amdgcn_readlane(v, 63);
+#endif
+    return v;
+}
+
 }  // namespace c2r

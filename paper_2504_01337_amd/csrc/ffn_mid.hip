@@ -253,17 +253,7 @@ __device__ __forceinline__ int mid_single_run(int chunks, int ntn, int kS, int r
     int cost = 0x7fffffff;
     if ((teams + 7) / 8 * chunks < MID_WG_PER_XCD)
         cost = min(max(c * kS, (r_items + rest - 1) / rest * kR), 0xffffff) << 6 | (63 - lane_id());  // (the longer run among equals)
-#if defined(__HIP_DEVICE_COMPILE__)
-    // the least of the 64 lanes' costs, in lane 63 (as wave_inclusive_scan: no LDS round trips at the start of every workgroup)
-    constexpr int MOST = 0x7fffffff;
-    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x111, 0xf, 0xf, false));
-    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x112, 0xf, 0xf, false));
-    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x114, 0xf, 0xf, false));
-    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x118, 0xf, 0xf, false));
-    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x142, 0xa, 0xf, false));
-    cost = min(cost, __builtin_amdgcn_update_dpp(MOST, cost, 0x143, 0xc, 0xf, false));
-    cost = __builtin_amdgcn_readlane(cost, 63);
-#endif
+    cost = -wave_max(-cost);
     return cost == 0x7fffffff ? 0 : 64 - (cost & 63);
 }
 

@@ -1,17 +1,20 @@
 // Router logits (Eq. 1) and collaboration-constrained selection (Sec. 3.3, step 2).
 //
-// Two kernels (small batches have forms of their own: route_partial_small_kernel, route_select_small_kernel, and
-// route_finish_small_kernel, which also builds the dispatch index).
+// Partial sums, then a selection:
 //  route_partial_kernel: an fp32 GEMM over one 256-long k-chunk in which every (token,
 //    expert) sum is built with one fused multiply-add per k in ascending k - exactly the
 //    ABI's declared order - either by one thread on the vector pipe (up to 8 experts) or by
 //    a chain of v_mfma_f32_32x32x2_f32 on the matrix pipe, whose two products per
 //    instruction are added in that same order.  Chunk results go to scratch as
 //    part[tile][chunk][expert][64] (token fastest, one tile's partials contiguous).
+//    Small batches: route_partial_small_kernel, the same sums on 16 x 16 x 4 matrix instructions.
 //  route_select_kernel: adds the chunk results left to right (four tokens per lane), adds the
 //    bias, then does arg max / masked top-(K-1) in registers with one 64-bit collaborator
 //    mask per expert held in LDS: four lanes per token over a quarter of the experts each
 //    (chunk partials), or one lane per token over all of them (stored logits).
+//    Others for its work: route_select_small_kernel (sixteen lanes per token, up to 8192 tokens), route_finish_small_kernel
+//    (up to 64 tokens, with the dispatch index), route_select_keys_kernel (top-K of K <= 4 from one chunk result, more than 8192
+//    tokens) and route_select_rows_kernel (stored logits, K <= 4).
 #include "c2r_internal.h"
 #include "ffn_copy.h"
 
@@ -618,20 +621,22 @@ __device__ __forceinline__ void merge_lower(int upper, int &bi, float &bv) {
 #endif
 }
 
-// The bitwise or of a row of sixteen lanes' values, in each of them.
-__device__ __forceinline__ uint64_t or_of_sixteen(uint64_t m) {
-    int lo = (int)(uint32_t)m, hi = (int)(uint32_t)(m >> 32);
+// The bitwise or of the values of a quad of lanes (N 4) or of a row of sixteen, in each of them.
+template <int N>
+__device__ __forceinline__ uint64_t or_of_lanes(uint64_t m) {
+    int half[2] = {(int)(uint32_t)m, (int)(uint32_t)(m >> 32)};
 #if defined(__HIP_DEVICE_COMPILE__)
-    lo |= __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xf, 0xf, true);   // quad_perm 1,0,3,2
-    hi |= __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xf, 0xf, true);
-    lo |= __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xf, 0xf, true);   // quad_perm 2,3,0,1
-    hi |= __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xf, 0xf, true);
-    lo |= __builtin_amdgcn_mov_dpp(lo, 0x141, 0xf, 0xf, true);  // row_half_mirror
-    hi |= __builtin_amdgcn_mov_dpp(hi, 0x141, 0xf, 0xf, true);
-    lo |= __builtin_amdgcn_mov_dpp(lo, 0x140, 0xf, 0xf, true);  // row_mirror
-    hi |= __builtin_amdgcn_mov_dpp(hi, 0x140, 0xf, 0xf, true);
+#pragma unroll
+    for (int &h : half) {
+        h |= __builtin_amdgcn_mov_dpp(h, 0xB1, 0xf, 0xf, true);  // quad_perm 1,0,3,2
+        h |= __builtin_amdgcn_mov_dpp(h, 0x4E, 0xf, 0xf, true);  // quad_perm 2,3,0,1
+        if (N == 16) {
+            h |= __builtin_amdgcn_mov_dpp(h, 0x141, 0xf, 0xf, true);  // row_half_mirror
+            h |= __builtin_amdgcn_mov_dpp(h, 0x140, 0xf, 0xf, true);  // row_mirror
+        }
+    }
 #endif
-    return (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32);
+    return (uint64_t)(uint32_t)half[0] | ((uint64_t)(uint32_t)half[1] << 32);
 }
 
 // ROWMAJOR (stored logits [T, E]): one wave per 64 tokens.  Otherwise (chunk partials):
@@ -948,21 +953,6 @@ __global__ __launch_bounds__(ROWMAJOR ? 64 : SEL_WAVES * 64) void route_select_k
         gates[(size_t)t * K + s] = g;
     }
     for (int s = 0; s < K; ++s) gates[(size_t)t * K + s] = gates[(size_t)t * K + s] / den;
-}
-
-// The largest of the 64 lanes' values, in every lane.  Every lane must be active.
-__device__ __forceinline__ int wave_max(int v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int LOWEST = (int)0x80000000;
-    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
-    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x112, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x114, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x118, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1, 3
-    v = max(v, __builtin_amdgcn_update_dpp(LOWEST, v, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2, 3
-    v = __builtin_amdgcn_readlane(v, 63);
-#endif
-    return v;
 }
 
 // One token's selection by the literal rule, for K <= 4: first one standing unless a later one is strictly larger.  pick(m, e, v) finds
@@ -1528,14 +1518,7 @@ __global__ __launch_bounds__(256) void route_select_small_kernel(
                 const int v = e < E ? collab_idx[e * Tc + i] : -1;
                 if (v >= 0 && v < E) m |= 1ull << v;
             }
-#if defined(__HIP_DEVICE_COMPILE__)
-            int lo = (int)(uint32_t)m, hi = (int)(uint32_t)(m >> 32);
-            lo |= __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xf, 0xf, true);
-            hi |= __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xf, 0xf, true);
-            lo |= __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xf, 0xf, true);
-            hi |= __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xf, 0xf, true);
-            m = (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32);
-#endif
+            m = or_of_lanes<4>(m);
         }
         if (quad == 0) mask_tab[e] = m & ~(1ull << e);
     }
@@ -1644,7 +1627,7 @@ __global__ __launch_bounds__(FIN_WAVES * 64) void route_finish_small_kernel(
                 const int v = le < E ? collab_idx[le * Tc + i] : -1;
                 if (v >= 0 && v < E) m |= 1ull << v;
             }
-            m = or_of_sixteen(m);
+            m = or_of_lanes<16>(m);
         }
         if (lq == 0) mask_tab[le] = m & ~(1ull << le);
     }
@@ -1920,7 +1903,8 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
     // Workgroups of 128 tokens come in rounds of the chip's CUs, and the first batches past a round (or two) leave most of the last one
     // empty: workgroups of 64 tokens, their waves 32 experts each, make it one of half the length.  (33000 tokens 147 / 124 us,
     // 48000 tokens 149 / 126, 72000 tokens 221 / 201, fp32 33000 tokens 152 / 119; full rounds cost 4 to 9 % more that way, x
-    // being read by two waves: 32768 tokens 86.5 / 90, 65536 tokens 154 / 167.)
+    // being read by two waves: 32768 tokens 86.5 / 90, 65536 tokens 154 / 167.  Past the third round it is all but even: 106000 tokens
+    // 281 / 272, fp32 299 / 298, 140000 tokens 350 / 345, fp32 386 / 387.)
     const int64_t half_rounds = (ngroups + 127) / 128;
     const bool halves = all_chunks && te == 8 && (half_rounds == 3 || half_rounds == 5);
     const int64_t nblk = ngroups * ((L.nchunk + cpw - 1) / cpw);

@@ -9,7 +9,7 @@ from helpers import GATE_RTOL, dev, host
 pytestmark = pytest.mark.gpu
 
 
-# summed in registers (from 25057 tokens on, 32737 with up to 32 experts): whole chunks, a ragged last one, one expert block and two; stored: one
+# summed in registers (from 25025 tokens on, 32705 with up to 32 experts): whole chunks, a ragged last one, one expert block and two; stored: one
 # chunk per workgroup and two (an even and an odd number of chunks, a ragged last one), the remainders of tokens and experts
 @pytest.mark.parametrize("T,E,d,dtype", [
     (32768, 60, 512, "bf16"), (32705, 33, 520, "bf16"), (32769, 20, 768, "f32"), (40001, 64, 264, "f32"),
@@ -17,9 +17,11 @@ pytestmark = pytest.mark.gpu
     (12289, 17, 256, "bf16"),
     # stored, tiles of 32 experts: a pipeline per chunk, whole chunks and a ragged last one
     (12290, 16, 776, "bf16"), (8193, 31, 1032, "f32"), (6200, 24, 2048, "bf16"),
-    # 64-token workgroups of half the experts per wave (the third and the fifth half round), and the first batches on either side of
-    # the rules
-    (33001, 60, 776, "bf16"), (49153, 36, 512, "bf16"), (65700, 34, 512, "bf16"), (36000, 61, 520, "f32"), (25089, 60, 520, "bf16"), (25000, 60, 520, "bf16")])
+    # 64-token workgroups of half the experts per wave (the third and the fifth half round)
+    (33001, 60, 776, "bf16"), (65700, 34, 512, "bf16"), (36000, 61, 520, "f32"),
+    # the last and the first batches of the rules: chunks stored / summed, workgroups of 128 / 64 tokens
+    (25024, 60, 520, "bf16"), (25025, 60, 520, "bf16"), (32704, 20, 520, "bf16"), (32705, 20, 520, "bf16"),
+    (32768, 33, 512, "bf16"), (32769, 33, 512, "bf16"), (49152, 36, 512, "bf16"), (49153, 36, 512, "bf16")])
 def test_large_route_logits_bit_exact(orc, T, E, d, dtype):
     from paper_2504_01337_amd import c2r
     rng = np.random.default_rng(T + E + d)
@@ -56,6 +58,7 @@ def test_large_selection_from_one_chunk(orc, T, E, K, dtype):
                                            None if gl is None else dev(gl), want_logits=True)
             ri, rg = orc.route(host(logits), K, cl)
             assert np.array_equal(host(idx), ri)
+            # logits of up to some hundred apart: the bound of GATE_RTOL with |a_s| up to 104, where a gate is flushed to zero
             np.testing.assert_allclose(host(gates), rg, rtol=114 / 34 * GATE_RTOL, atol=1e-37)
 
 
