@@ -12,9 +12,9 @@
 //
 // Microseconds gate/up + down of each pass, three sets of weights in turn (register-direct waves for few rows and tiles of 128 x 128
 // for many before -> now): 8 experts, d 256, F 512: 1024 rows 21.3 + 18.0 -> 10.2 + 8.8, 4096 rows 42.9 + 35.3 -> 25.5 + 14.5, 16384
-// rows 101 + 80 -> 81 + 41; d 1024, F 1376: 8 rows, a row
-// per group, gate/up 21.3 -> 22.7 (344 tiles for 256 CUs: the one size that lost), 64 rows 24.3 + 20.3 -> 21.1 + 11.7, 4096 rows 293 + 201 -> 193 + 108, 16384 rows 869 + 493
-// -> 714 + 358 (129 TFLOP/s); 16 experts, d 2048, F 1408: 64 rows 134 + 61 -> 69 + 32, 2048 rows 297 + 207 -> 226 + 115.
+// rows 101 + 80 -> 81 + 41; d 1024, F 1376: 64 rows 24.3 + 20.3 -> 21.1 + 11.7, 4096 rows 293 + 201 -> 193 + 108, 16384 rows 869 + 493
+// -> 714 + 358 (129 TFLOP/s); 16 experts, d 2048, F 1408: 64 rows 134 + 61 -> 69 + 32, 2048 rows 297 + 207 -> 226 + 115.  A row per group
+// is what lost, with a tile or two per CU: 8 experts, d 1024, 8 rows 21.3 -> 22.7 in gate/up; 16 experts, d 2048, 37.1 + 17.4 -> 39.0 + 18.4.
 #include <type_traits>
 
 #include "ffn_common.h"
