@@ -1,7 +1,7 @@
 // Un-permute and gate-weighted sum (last sentence of Sec. 3.1): every thread owns
 // one 16-byte vector of an output row, gathers the matching vector of each of the
 // token's K expert rows, accumulates in fp32 in slot order and rounds once.
-#include "c2r_internal.h"
+#include "row_sum.h"
 
 namespace c2r {
 
@@ -62,42 +62,17 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4 *__restrict__ 
 // of the bytes in flight.  15 of 60 experts local, d 2048, 32768 tokens: 63 -> 37.6 us (5.7 TB/s); all 60 experts + shared,
 // 8192 tokens: 42.5 -> 39.8 us; 16 experts, d 4096, 4096 tokens: 32.2 -> 29.8 us.  Pieces of 1 and 4 KB: 50 and 36.5 us for
 // the first, 40 and 41.3 us for the second.
-constexpr int ROW_NV = 2;
-
 template <bool BF16>
 __global__ __launch_bounds__(256) void combine_rows_kernel(const uint4 *__restrict__ y_perm, const float *__restrict__ gates,
                                                            const int32_t *__restrict__ inv_perm, int64_t T, int row_vecs,
                                                            int K, const uint4 *__restrict__ y_shared,
                                                            uint4 *__restrict__ y) {
-    constexpr int N = BF16 ? 8 : 4, NV = ROW_NV;
-    const int lane = threadIdx.x & 63, pieces = row_vecs / (64 * NV);
+    const int lane = threadIdx.x & 63, pieces = row_vecs / (64 * ROW_NV);
     const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t = w / pieces;
     if (t >= T) return;
-    const int v = (int)(w - t * pieces) * (64 * NV) + lane;
-    float acc[NV][N];
-#pragma unroll
-    for (int i = 0; i < NV; ++i)
-#pragma unroll
-        for (int j = 0; j < N; ++j) acc[i][j] = 0.0f;
-    auto add = [&](const uint4 *row, float g) __attribute__((always_inline)) {
-        uint4 q[NV];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) q[i] = row[i * 64];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const uint32_t u[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if constexpr (BF16) {
-                    acc[i][2 * j] = __builtin_fmaf(g, __uint_as_float(u[j] << 16), acc[i][2 * j]);
-                    acc[i][2 * j + 1] = __builtin_fmaf(g, __uint_as_float(u[j] & 0xffff0000u), acc[i][2 * j + 1]);
-                } else {
-                    acc[i][j] = __builtin_fmaf(g, __uint_as_float(u[j]), acc[i][j]);
-                }
-            }
-        }
-    };
+    const int v = (int)(w - t * pieces) * (64 * ROW_NV) + lane;
+    RowSum<BF16> sum;
     const int pl = lane < K ? inv_perm[t * K + lane] : -1;
     const float gl = lane < K ? gates[t * K + lane] : 0.0f;
     uint64_t have = __ballot(pl >= 0);
@@ -105,20 +80,10 @@ __global__ __launch_bounds__(256) void combine_rows_kernel(const uint4 *__restri
         const int s = __ffsll((unsigned long long)have) - 1;
         have &= have - 1;
         const int p = __builtin_amdgcn_readlane(pl, s);
-        add(y_perm + (int64_t)p * row_vecs + v, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(gl), s)));
+        sum.add(y_perm + (int64_t)p * row_vecs + v, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(gl), s)));
     }
-    if (y_shared) add(y_shared + t * row_vecs + v, 1.0f);
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        uint4 out;
-        if constexpr (BF16)
-            out = make_uint4(pack_bf16x2(acc[i][0], acc[i][1]), pack_bf16x2(acc[i][2], acc[i][3]),
-                             pack_bf16x2(acc[i][4], acc[i][5]), pack_bf16x2(acc[i][6], acc[i][7]));
-        else
-            out = make_uint4(__float_as_uint(acc[i][0]), __float_as_uint(acc[i][1]), __float_as_uint(acc[i][2]),
-                             __float_as_uint(acc[i][3]));
-        y[t * row_vecs + v + i * 64] = out;
-    }
+    if (y_shared) sum.add(y_shared + t * row_vecs + v, 1.0f);
+    sum.store(y + t * row_vecs + v);
 }
 
 }  // namespace c2r
@@ -141,7 +106,7 @@ extern "C" int c2r_combine(const void *y_perm, c2r_dtype dt, const float *gates,
     const int64_t n = T * row_vecs;
     const int64_t nblk = (n + 255) / 256;
     if (nblk >= (1ll << 31)) return C2R_ERR_UNSUPPORTED;
-    if (row_vecs % (64 * ROW_NV) == 0 && K <= 64) {
+    if (row_pieces(row_vecs, K)) {
         const int64_t nw = T * (row_vecs / (64 * ROW_NV));
         const dim3 g((unsigned)((nw + 3) / 4)), b(256);
         const uint4 *yp = static_cast<const uint4 *>(y_perm), *ys = static_cast<const uint4 *>(y_shared);

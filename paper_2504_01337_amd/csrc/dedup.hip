@@ -10,7 +10,7 @@
 //       gate-weighted fp32 sum of the outputs of ITS experts for that token, rounded once;
 //   combine_copies_kernel  : what the token's home device does - add the partial rows of the
 //       token's copies (+ the shared expert) in fp32, round once.
-#include "c2r_internal.h"
+#include "row_sum.h"
 
 namespace c2r {
 
@@ -201,6 +201,104 @@ __global__ __launch_bounds__(DB_THREADS) void dedup_rank_kernel(
     }
 }
 
+// The same index in one launch, for few tokens of up to four slots: one workgroup per device, its 16 waves each with a contiguous
+// sixteenth of the tokens in registers.  They count, per wave, the tokens of this device and the copies for all lower ones, then hand
+// out the rows in order (see permute_by_slot_kernel).  The device 0 workgroup also marks the slots without a device.  A few hundred tokens
+// cost a launch and two trips to memory; beyond, the scattered stores of the rows are what a CU spends its time on, so a device's
+// workgroups share them, every `parts`-th 64-token step each (all of them count all tokens).  Microseconds, 60 experts, top-4, random
+// routing, two launches / this: 4 devices, 64 tokens 6.5 / 3.4, 1000 tokens 7.4 / 3.7, 3000 tokens 7.9 / 5.5, 4096 tokens 8.0 / 5.8, 8192
+// tokens 8.0 / 8.4 (one workgroup per device 10.9); 8 devices, 8192 tokens 15.3 / 8.5, 60 devices 59.6 / 10.6; top-2, 2 devices, 4096
+// tokens 6.8 / 6.5, 8192 tokens 6.7 / 9.9.
+constexpr int DD_WAVES = 16, DD_PARTS = 8, DD_STEPS = 8;
+constexpr int64_t DD_MAX_TOKENS = DD_WAVES * C2R_WAVE * DD_STEPS;
+static inline bool dedup_in_one_launch(int64_t T, int K, int n_dev) {
+    return T > 0 && K <= 4 && T <= (n_dev > 4 ? DD_MAX_TOKENS : DD_MAX_TOKENS / 2);
+}
+
+template <int STEPS>
+__global__ __launch_bounds__(DD_WAVES * 64) void dedup_by_device_kernel(
+    const int32_t *__restrict__ topk_idx, int T, int K, int E, const int32_t *__restrict__ expert_device, int n_dev,
+    int32_t *__restrict__ send_counts, int32_t *__restrict__ send_offsets, int32_t *__restrict__ send_token,
+    int32_t *__restrict__ send_row) {
+    __shared__ int32_t dev_tab[C2R_MAX_E], w_mine[DD_WAVES], w_less[DD_WAVES];
+    const int g = blockIdx.x % n_dev, part = blockIdx.x / n_dev, parts = gridDim.x / n_dev;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int seg = ((T + DD_WAVES - 1) / DD_WAVES + 63) / 64 * 64, t_begin = wave * seg;  // (seg <= 64 * STEPS)
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    i32x4 e[STEPS];
+    if (K == 4 && (reinterpret_cast<uintptr_t>(topk_idx) & 15) == 0) {
+#pragma unroll
+        for (int u = 0; u < STEPS; ++u) e[u] = reinterpret_cast<const i32x4 *>(topk_idx)[min(t_begin + u * 64 + lane, T - 1)];
+    } else {
+#pragma unroll
+        for (int u = 0; u < STEPS; ++u)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) e[u][s] = topk_idx[(size_t)min(t_begin + u * 64 + lane, T - 1) * K + min(s, K - 1)];
+    }
+    load_device_table(dev_tab, E, expert_device, n_dev);
+    const uint64_t below = (1ull << g) - 1ull;
+    int slots[STEPS];  // bits 0..3: the token's slots on this device, 4..7: those without a device
+    int mine = 0, less = 0;
+#pragma unroll
+    for (int u = 0; u < STEPS; ++u) {
+        const bool have = u * 64 < seg && t_begin + u * 64 + lane < T;
+        uint64_t set = 0;
+        slots[u] = 0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int dev = (uint32_t)e[u][s] < (uint32_t)E ? dev_tab[e[u][s]] : -1;
+            if (have && s < K) {
+                set |= dev >= 0 ? 1ull << dev : 0ull;
+                slots[u] |= dev == g ? 1 << s : dev < 0 ? 16 << s : 0;
+            }
+        }
+        mine += (slots[u] & 15) != 0;
+        less += __popcll(set & below);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        mine += __shfl_xor(mine, off);
+        less += __shfl_xor(less, off);
+    }
+    if (lane == 0) {
+        w_mine[wave] = mine;
+        w_less[wave] = less;
+    }
+    __syncthreads();
+    int start = 0, total = 0, run = 0;  // this device's first row and its rows; those of the waves before this one
+#pragma unroll
+    for (int w = 0; w < DD_WAVES; ++w) {
+        start += w_less[w];
+        total += w_mine[w];
+        run += w < wave ? w_mine[w] : 0;
+    }
+    run += start;
+    if (threadIdx.x == 0 && part == 0) {
+        send_counts[g] = total;
+        send_offsets[g] = start;
+        if (g == n_dev - 1) send_offsets[n_dev] = start + total;
+    }
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+    for (int u = 0; u < STEPS; ++u) {
+        const int t = t_begin + u * 64 + lane;
+        const bool on = (slots[u] & 15) != 0;
+        const uint64_t m = __ballot(on);
+        if (u % parts != part) {
+            run += __popcll(m);
+            continue;
+        }
+        const int pos = run + __popcll(m & lt);
+        if (on) send_token[pos] = t;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if ((slots[u] >> s) & 1) send_row[(size_t)t * K + s] = pos;
+            if (g == 0 && ((slots[u] >> s) & 16)) send_row[(size_t)t * K + s] = -1;
+        }
+        run += __popcll(m);
+    }
+}
+
 template <bool BF16>
 struct VecAcc {
     static constexpr int N = BF16 ? 8 : 4;
@@ -265,6 +363,38 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(
     y_part[i] = a.rounded();
 }
 
+// The same sums for rows of whole 2 KB pieces (see combine_rows_kernel): a wave owns one piece of one copy, and the token's rows, positions
+// and gates come in one load each, a lane per slot.  Bound by memory; microseconds, top-4 of 60, d 2048, per vector / per piece: 8192
+// tokens on 4 devices 39.2 / 36.2 (1.2 copies per token), 30 devices (2.1 copies) 59.4 / 42.8, 500 tokens 4.8 / 4.2.  combine_copies_rows_kernel
+// below: 28.2 / 20.6, 40.8 / 33.7, 3.7 / 3.0.
+template <bool BF16>
+__global__ __launch_bounds__(256) void combine_partial_rows_kernel(
+    const uint4 *__restrict__ y_perm, const float *__restrict__ gates, const int32_t *__restrict__ inv_perm,
+    const int32_t *__restrict__ send_token, const int32_t *__restrict__ send_row,
+    const int32_t *__restrict__ n_send_ptr, int64_t T, int64_t cap_rows, int row_vecs, int K,
+    uint4 *__restrict__ y_part) {
+    const int lane = threadIdx.x & 63, pieces = row_vecs / (64 * ROW_NV);
+    const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r = w / pieces, n_send = *n_send_ptr;
+    if (r >= n_send || r >= cap_rows) return;
+    const int v = (int)(w - r * pieces) * (64 * ROW_NV) + lane;
+    const int64_t t = send_token[r];
+    RowSum<BF16> sum;
+    if (t >= 0 && t < T) {
+        const int64_t a = t * K + (lane < K ? lane : 0);
+        const int row = send_row[a], pl = inv_perm[a];
+        const float gl = gates[a];
+        uint64_t have = __ballot(lane < K && row == (int32_t)r && pl >= 0);
+        while (have) {
+            const int s = __ffsll((unsigned long long)have) - 1;
+            have &= have - 1;
+            sum.add(y_perm + (int64_t)__builtin_amdgcn_readlane(pl, s) * row_vecs + v,
+                    __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(gl), s)));
+        }
+    }
+    sum.store(y_part + r * row_vecs + v);
+}
+
 // One thread per 16-byte vector of an output row: the token's copies in order of first use.
 template <bool BF16>
 __global__ __launch_bounds__(256) void combine_copies_kernel(
@@ -283,6 +413,28 @@ __global__ __launch_bounds__(256) void combine_copies_kernel(
     }
     if (y_shared) a.add(y_shared[i], 1.0f);
     y[i] = a.rounded();
+}
+
+// The same for rows of whole 2 KB pieces, a wave per piece.
+template <bool BF16>
+__global__ __launch_bounds__(256) void combine_copies_rows_kernel(
+    const uint4 *__restrict__ y_part, const int32_t *__restrict__ send_row, int64_t T, int64_t cap_rows,
+    int row_vecs, int K, const uint4 *__restrict__ y_shared, uint4 *__restrict__ y) {
+    const int lane = threadIdx.x & 63, pieces = row_vecs / (64 * ROW_NV);
+    const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t t = w / pieces;
+    if (t >= T) return;
+    const int v = (int)(w - t * pieces) * (64 * ROW_NV) + lane;
+    const int rl = lane < K ? send_row[t * K + lane] : -1;
+    RowSum<BF16> sum;
+    uint64_t have = __ballot(rl >= 0 && rl < cap_rows);
+    while (have) {
+        const int r = __builtin_amdgcn_readlane(rl, __ffsll((unsigned long long)have) - 1);
+        have &= ~__ballot(rl == r);  // (the first slot that uses the copy stands for all that do)
+        sum.add(y_part + (int64_t)r * row_vecs + v, 1.0f);
+    }
+    if (y_shared) sum.add(y_shared + t * row_vecs + v, 1.0f);
+    sum.store(y + t * row_vecs + v);
 }
 
 size_t dedup_workspace_bytes(int64_t T, int n_dev) {
@@ -307,6 +459,22 @@ extern "C" int c2r_dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int
     const size_t need = dedup_workspace_bytes(T > 0 ? T : 1, n_dev);
     if (!ws || ws_bytes < need || !aligned(ws, 256)) return C2R_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (dedup_in_one_launch(T, K, n_dev)) {
+        int parts = 1;
+        while (parts < DD_PARTS && parts * (DD_MAX_TOKENS / DD_STEPS) < T && 2 * parts * n_dev <= 64) parts *= 2;
+        const dim3 g((unsigned)(n_dev * parts)), b(DD_WAVES * 64);
+#define C2R_BY_DEVICE(STEPS)                                                                                             \
+    dedup_by_device_kernel<STEPS><<<g, b, 0, st>>>(topk_idx, (int)T, K, E, expert_device, n_dev, send_counts, send_offsets, \
+                                                   send_token, send_row)
+        if (T <= DD_MAX_TOKENS / DD_STEPS)
+            C2R_BY_DEVICE(1);
+        else if (T <= DD_MAX_TOKENS / 2)
+            C2R_BY_DEVICE(4);
+        else
+            C2R_BY_DEVICE(DD_STEPS);
+#undef C2R_BY_DEVICE
+        return launch_status();
+    }
     // Few tokens: one per thread, or two, so that more than a handful of CUs work (8192 tokens, 4 devices: 7.4 + 11.9 us with
     // four per thread, 3.8 + 5.4 with one).  The block counts are 16 bits wide: those of half-size blocks take what the scratch has
     // always had to hold at least, those of quarter-size blocks go where there is room.
@@ -343,6 +511,18 @@ extern "C" int c2r_combine_partial(const void *y_perm, c2r_dtype dt, const float
     const int64_t nblk = (cap_rows * row_vecs + 255) / 256;
     if (nblk >= (1ll << 31)) return C2R_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (row_pieces(row_vecs, K)) {
+        const int64_t waves = cap_rows * (row_vecs / (64 * ROW_NV));
+        const dim3 g((unsigned)((waves + 3) / 4)), b(256);
+        const uint4 *yp = static_cast<const uint4 *>(y_perm);
+        if (dt == C2R_BF16)
+            combine_partial_rows_kernel<true><<<g, b, 0, st>>>(yp, gates, inv_perm, send_token, send_row, n_send, T, cap_rows, row_vecs,
+                                                               K, static_cast<uint4 *>(y_part));
+        else
+            combine_partial_rows_kernel<false><<<g, b, 0, st>>>(yp, gates, inv_perm, send_token, send_row, n_send, T, cap_rows, row_vecs,
+                                                                K, static_cast<uint4 *>(y_part));
+        return launch_status();
+    }
     if (dt == C2R_BF16)
         combine_partial_kernel<true><<<dim3((unsigned)nblk), dim3(256), 0, st>>>(
             static_cast<const uint4 *>(y_perm), gates, inv_perm, send_token, send_row, n_send, T, cap_rows, row_vecs, K,
@@ -367,6 +547,16 @@ extern "C" int c2r_combine_copies(const void *y_part, c2r_dtype dt, const int32_
     const int64_t nblk = (T * row_vecs + 255) / 256;
     if (nblk >= (1ll << 31)) return C2R_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (row_pieces(row_vecs, K)) {
+        const int64_t waves = T * (row_vecs / (64 * ROW_NV));
+        const dim3 g((unsigned)((waves + 3) / 4)), b(256);
+        const uint4 *yp = static_cast<const uint4 *>(y_part), *ys = static_cast<const uint4 *>(y_shared);
+        if (dt == C2R_BF16)
+            combine_copies_rows_kernel<true><<<g, b, 0, st>>>(yp, send_row, T, cap_rows, row_vecs, K, ys, static_cast<uint4 *>(y));
+        else
+            combine_copies_rows_kernel<false><<<g, b, 0, st>>>(yp, send_row, T, cap_rows, row_vecs, K, ys, static_cast<uint4 *>(y));
+        return launch_status();
+    }
     if (dt == C2R_BF16)
         combine_copies_kernel<true><<<dim3((unsigned)nblk), dim3(256), 0, st>>>(
             static_cast<const uint4 *>(y_part), send_row, T, cap_rows, row_vecs, K, static_cast<const uint4 *>(y_shared),

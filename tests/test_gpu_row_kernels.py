@@ -86,3 +86,58 @@ def test_dispatch_index_sizes(orc, T, E, El, K):
     rc, ro, rp, ri = orc.permute(idx, E, ls, El)
     assert np.array_equal(host(counts), rc) and np.array_equal(host(offsets), ro)
     assert np.array_equal(host(perm)[:ro[-1]], rp) and np.array_equal(host(inv), ri)
+
+
+# the dispatch index in one launch, on either side of its rules (1024, 4096 and 8192 tokens, four devices, four slots) and of its 64-token steps;
+# indices that are not 16-byte aligned
+@pytest.mark.parametrize("T", [1, 63, 65, 1024, 1025, 2049, 4096, 4097, 8191, 8192, 8193])
+@pytest.mark.parametrize("K,n_dev", [(4, 4), (4, 5), (3, 64), (1, 1), (5, 6)])
+def test_dedup_index_in_one_launch(c2r, orc, T, K, n_dev):
+    rng = np.random.default_rng(T * 7 + K)
+    E = 64
+    idx = np.argsort(rng.random((T, E)), axis=1)[:, :K].astype(np.int32)
+    idx[rng.random((T, K)) < 0.1] = -1
+    idx[T // 3] = E
+    devmap = rng.integers(-1, n_dev, size=E).astype(np.int32)
+    rc, ro, rt, rr = orc.dedup_dispatch(np.where(idx < E, idx, -1), E, devmap, n_dev)
+    n = int(ro[-1])
+    for shift in (0, 1):
+        i = torch.empty(T * K + shift, dtype=torch.int32, device="cuda")[shift:].view(T, K)
+        i.copy_(dev(idx))
+        counts, offsets, tok, row = c2r.dedup_dispatch(i, E, dev(devmap), n_dev)
+        assert np.array_equal(host(counts), rc) and np.array_equal(host(offsets), ro)
+        assert np.array_equal(host(tok)[:n], rt[:n]) and np.all(host(tok)[n:] == -1)
+        assert np.array_equal(host(row).reshape(-1), np.asarray(rr).reshape(-1))
+
+
+# the two-level combine by whole row pieces: one, two and three of them, 1 to 64 slots and one more (the other kernels); tokens without
+# a copy, an expert that is not computed here
+@pytest.mark.parametrize("dtype,T,K,d", [("bf16", 1, 1, 1024), ("bf16", 37, 4, 2048), ("bf16", 9, 3, 3072), ("bf16", 3, 64, 1024), ("f32", 33, 7, 512),
+                                         ("f32", 5, 2, 1536), ("bf16", 70, 4, 1536)])
+def test_two_level_combine_by_row_pieces(c2r, orc, dtype, T, K, d):
+    rng = np.random.default_rng(T + K + d)
+    store = wl.round_bf16 if dtype == "bf16" else (lambda a: a)
+    E, n_dev = 64, 5
+    idx = np.argsort(rng.random((T, E)), axis=1)[:, :K].astype(np.int32)
+    idx[T // 2] = -1
+    devmap = rng.integers(-1, n_dev, size=E).astype(np.int32)
+    inv = rng.permutation(T * K).astype(np.int32)
+    inv[rng.random(T * K) < 0.2] = -1
+    g = rng.random((T, K)).astype(np.float32)
+    yp, ys = (store(rng.standard_normal((n, d)).astype(np.float32)) for n in (T * K, T))
+    _, offsets, tok, row = c2r.dedup_dispatch(dev(idx), E, dev(devmap), n_dev)
+    _, ro, _, rr = orc.dedup_dispatch(idx, E, devmap, n_dev)
+    n = int(ro[-1])
+    part = torch.full((T * K, d), float("nan"), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+    c2r.combine_partial(dev(yp, dtype), dev(g), dev(inv), tok, row, offsets, part)
+    ref = orc.combine_partial(yp, g, inv, rr, T, K, n)
+    # one rounding of the result, and K + 1 of the fp32 sum
+    tol = 2.0 ** -8 if dtype == "bf16" else (K + 1) * 2.0 ** -24
+    bound = lambda r, terms: tol * (max(np.abs(r).max(initial=0.0), 1.0) if dtype == "bf16" else terms)
+    assert np.isnan(host(part)[n:]).all()
+    if n:
+        assert np.abs(host(part)[:n] - ref).max() <= bound(ref, K * np.abs(yp).max())
+    for shared in (None, ys):
+        y = c2r.combine_copies(part, row, T, K, None if shared is None else dev(shared, dtype))
+        ref2 = orc.combine_copies(host(part)[:n], rr, T, K, shared)
+        assert np.abs(host(y) - ref2).max() <= bound(ref2, K * max(np.abs(host(part)[:n]).max(initial=0.0), np.abs(ys).max()))
