@@ -22,6 +22,7 @@ FfnProblem ffn_bf16_dma_problem(int pass, const uint16_t *a, int lda, const int3
                                 int64_t A_cap, int d, int F, const uint16_t *b0, const uint16_t *b1, uint16_t *out,
                                 int ldo, const int32_t *gather, int gather_div, int gather_rows);
 int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, hipStream_t st);
+int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *const (&second)[2], hipStream_t st);
 }  // namespace c2r
 
 using namespace c2r;
@@ -92,6 +93,20 @@ static int ffn_pass(int pass, c2r_dtype dt, const void *a, const int32_t *offset
                                static_cast<float *>(out), st);
 }
 
+// Both passes of routed groups on the copy-engine kernel: h of pitch ldh in between; gather: rows of x by perm.
+static int ffn_both_passes(const void *a, const int32_t *offsets, int E_local, int64_t A_cap, int d, int F, int ldh,
+                           const void *w_gate, const void *w_up, const void *w_down, void *h, void *y_perm,
+                           const int32_t *gather, int gather_div, int gather_rows, void *stream) {
+    uint16_t *const hb = static_cast<uint16_t *>(h);
+    const FfnProblem p[2] = {
+        ffn_bf16_dma_problem(0, static_cast<const uint16_t *>(a), d, offsets, E_local, A_cap, d, F,
+                             static_cast<const uint16_t *>(w_gate), static_cast<const uint16_t *>(w_up), hb, ldh, gather,
+                             gather_div, gather_rows),
+        ffn_bf16_dma_problem(1, hb, ldh, offsets, E_local, A_cap, d, F, static_cast<const uint16_t *>(w_down), nullptr,
+                             static_cast<uint16_t *>(y_perm), d, nullptr, 1, 1)};
+    return launch_ffn_bf16_dma_both(p, {nullptr, nullptr}, static_cast<hipStream_t>(stream));
+}
+
 extern "C" int c2r_expert_ffn_gate_up(const void *x_perm, c2r_dtype dt, const int32_t *offsets, int E_local,
                                       int64_t A_cap, int d, int F, const void *w_gate, const void *w_up,
                                       void *h, void *stream) {
@@ -104,9 +119,8 @@ extern "C" int c2r_expert_ffn_gate_up(const void *x_perm, c2r_dtype dt, const in
     return ffn_pass(0, dt, x_perm, offsets, E_local, A_cap, d, F, F, w_gate, w_up, h, stream);
 }
 
-extern "C" int c2r_expert_ffn_gate_up_gather(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K,
-                                             const int32_t *offsets, int E_local, int64_t A_cap, int d, int F,
-                                             const void *w_gate, const void *w_up, void *h, void *stream) {
+static int check_gate_up_gather(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K, const int32_t *offsets,
+                                int E_local, int64_t A_cap, int d, int F, const void *w_gate, const void *w_up, const void *h) {
     const int rc = check_ffn(dt, E_local, A_cap, d, F);
     if (rc != C2R_OK) return rc;
     if (T < 1 || K < 1) return C2R_ERR_INVALID_ARG;
@@ -116,19 +130,34 @@ extern "C" int c2r_expert_ffn_gate_up_gather(const void *x, c2r_dtype dt, const 
         return C2R_ERR_INVALID_ARG;
     // only the copy-engine kernel folds the gather into its addresses (32-bit row offsets into x)
     if (!fast_bf16(dt, d, F) || F % 64 != 0 || (uint64_t)T * d * 2 >= (1ull << 32)) return C2R_ERR_UNSUPPORTED;
+    return C2R_OK;
+}
+
+extern "C" int c2r_expert_ffn_gate_up_gather(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K,
+                                             const int32_t *offsets, int E_local, int64_t A_cap, int d, int F,
+                                             const void *w_gate, const void *w_up, void *h, void *stream) {
+    const int rc = check_gate_up_gather(x, dt, perm, T, K, offsets, E_local, A_cap, d, F, w_gate, w_up, h);
+    if (rc != C2R_OK || A_cap == 0) return rc;
     return launch_ffn_bf16_dma_pass(0, static_cast<const uint16_t *>(x), d, offsets, E_local, A_cap, d, F,
                                     static_cast<const uint16_t *>(w_gate), static_cast<const uint16_t *>(w_up),
                                     static_cast<uint16_t *>(h), F, perm, K, (int)T, static_cast<hipStream_t>(stream));
 }
 
-extern "C" int c2r_expert_ffn_down(const void *h, c2r_dtype dt, const int32_t *offsets, int E_local,
-                                   int64_t A_cap, int d, int F, const void *w_down, void *y_perm,
-                                   void *stream) {
+static int check_down(const void *h, c2r_dtype dt, const int32_t *offsets, int E_local, int64_t A_cap, int d, int F,
+                      const void *w_down, const void *y_perm) {
     const int rc = check_ffn(dt, E_local, A_cap, d, F);
     if (rc != C2R_OK) return rc;
     if (A_cap == 0) return C2R_OK;
     if (!h || !offsets || !w_down || !y_perm) return C2R_ERR_INVALID_ARG;
     if (!aligned(h, 16) || !aligned(w_down, 16) || !aligned(y_perm, 16)) return C2R_ERR_INVALID_ARG;
+    return C2R_OK;
+}
+
+extern "C" int c2r_expert_ffn_down(const void *h, c2r_dtype dt, const int32_t *offsets, int E_local,
+                                   int64_t A_cap, int d, int F, const void *w_down, void *y_perm,
+                                   void *stream) {
+    const int rc = check_down(h, dt, offsets, E_local, A_cap, d, F, w_down, y_perm);
+    if (rc != C2R_OK || A_cap == 0) return rc;
     return ffn_pass(1, dt, h, offsets, E_local, A_cap, d, F, F, w_down, nullptr, y_perm, stream);
 }
 
@@ -146,6 +175,8 @@ extern "C" int c2r_expert_ffn(const void *x_perm, c2r_dtype dt, const int32_t *o
     const int ldh = h_pitch(dt, d, F);
     const size_t need = round_up((size_t)A_cap * ldh * (dt == C2R_BF16 ? 2 : 4), 256);
     if (!ws || ws_bytes < need || !aligned(ws, 256)) return C2R_ERR_WORKSPACE;
+    if (fast_bf16(dt, d, F))
+        return ffn_both_passes(x_perm, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, w_down, ws, y_perm, nullptr, 1, 1, stream);
     rc = ffn_pass(0, dt, x_perm, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, ws, stream);
     if (rc != C2R_OK) return rc;
     return ffn_pass(1, dt, ws, offsets, E_local, A_cap, d, F, ldh, w_down, nullptr, y_perm, stream);
@@ -167,11 +198,7 @@ extern "C" int c2r_expert_ffn_gather(const void *x, c2r_dtype dt, const int32_t 
     const int ldh = h_pitch(dt, d, F);
     const size_t need = round_up((size_t)A_cap * ldh * 2, 256);
     if (!ws || ws_bytes < need || !aligned(ws, 256)) return C2R_ERR_WORKSPACE;
-    rc = launch_ffn_bf16_dma_pass(0, static_cast<const uint16_t *>(x), d, offsets, E_local, A_cap, d, F,
-                                  static_cast<const uint16_t *>(w_gate), static_cast<const uint16_t *>(w_up),
-                                  static_cast<uint16_t *>(ws), ldh, perm, K, (int)T, static_cast<hipStream_t>(stream));
-    if (rc != C2R_OK) return rc;
-    return ffn_pass(1, dt, ws, offsets, E_local, A_cap, d, F, ldh, w_down, nullptr, y_perm, stream);
+    return ffn_both_passes(x, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, w_down, ws, y_perm, perm, K, (int)T, stream);
 }
 
 // ---- routed groups and an always-on shared expert in ONE launch per pass ----
@@ -186,11 +213,10 @@ static int check_with_shared(c2r_dtype dt, int64_t T, int E_local, int64_t A_cap
     return C2R_OK;
 }
 
-extern "C" int c2r_expert_ffn_gate_up_with_shared(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K,
-                                                  const int32_t *offsets, int E_local, int64_t A_cap, int d, int F,
-                                                  const void *w_gate, const void *w_up, void *h, int F_shared,
-                                                  const void *ws_gate, const void *ws_up, void *h_shared,
-                                                  void *stream) {
+static int gate_up_with_shared_problems(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K, const int32_t *offsets,
+                                        int E_local, int64_t A_cap, int d, int F, const void *w_gate, const void *w_up, void *h,
+                                        int F_shared, const void *ws_gate, const void *ws_up, void *h_shared,
+                                        FfnProblem &routed, FfnProblem &shared) {
     const int rc = check_with_shared(dt, T, E_local, A_cap, d, F, F_shared);
     if (rc != C2R_OK) return rc;
     if (K < 1) return C2R_ERR_INVALID_ARG;
@@ -200,23 +226,16 @@ extern "C" int c2r_expert_ffn_gate_up_with_shared(const void *x, c2r_dtype dt, c
         !aligned(ws_up, 16) || !aligned(h_shared, 16))
         return C2R_ERR_INVALID_ARG;
     const uint16_t *xs = static_cast<const uint16_t *>(x);
-    const FfnProblem shared = ffn_bf16_dma_problem(0, xs, d, nullptr, 1, T, d, F_shared,
-                                                   static_cast<const uint16_t *>(ws_gate),
-                                                   static_cast<const uint16_t *>(ws_up),
-                                                   static_cast<uint16_t *>(h_shared), F_shared, nullptr, 1, 1);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (A_cap == 0) return launch_ffn_bf16_dma(0, shared, nullptr, st);
-    const FfnProblem routed = ffn_bf16_dma_problem(0, xs, d, offsets, E_local, A_cap, d, F,
-                                                   static_cast<const uint16_t *>(w_gate),
-                                                   static_cast<const uint16_t *>(w_up), static_cast<uint16_t *>(h), F,
-                                                   perm, K, (int)T);
-    return launch_ffn_bf16_dma(0, routed, &shared, st);
+    shared = ffn_bf16_dma_problem(0, xs, d, nullptr, 1, T, d, F_shared, static_cast<const uint16_t *>(ws_gate),
+                                  static_cast<const uint16_t *>(ws_up), static_cast<uint16_t *>(h_shared), F_shared, nullptr, 1, 1);
+    routed = ffn_bf16_dma_problem(0, xs, d, offsets, E_local, A_cap, d, F, static_cast<const uint16_t *>(w_gate),
+                                  static_cast<const uint16_t *>(w_up), static_cast<uint16_t *>(h), F, perm, K, (int)T);
+    return C2R_OK;
 }
 
-extern "C" int c2r_expert_ffn_down_with_shared(const void *h, c2r_dtype dt, const int32_t *offsets, int E_local,
-                                               int64_t A_cap, int d, int F, const void *w_down, void *y_perm,
-                                               int64_t T, int F_shared, const void *h_shared, const void *ws_down,
-                                               void *y_shared, void *stream) {
+static int down_with_shared_problems(const void *h, c2r_dtype dt, const int32_t *offsets, int E_local, int64_t A_cap, int d, int F,
+                                     const void *w_down, void *y_perm, int64_t T, int F_shared, const void *h_shared,
+                                     const void *ws_down, void *y_shared, FfnProblem &routed, FfnProblem &shared) {
     const int rc = check_with_shared(dt, T, E_local, A_cap, d, F, F_shared);
     if (rc != C2R_OK) return rc;
     if (!h_shared || !ws_down || !y_shared) return C2R_ERR_INVALID_ARG;
@@ -224,15 +243,36 @@ extern "C" int c2r_expert_ffn_down_with_shared(const void *h, c2r_dtype dt, cons
     if (!aligned(h, 16) || !aligned(w_down, 16) || !aligned(y_perm, 16) || !aligned(h_shared, 16) ||
         !aligned(ws_down, 16) || !aligned(y_shared, 16))
         return C2R_ERR_INVALID_ARG;
-    const FfnProblem shared = ffn_bf16_dma_problem(1, static_cast<const uint16_t *>(h_shared), F_shared, nullptr, 1, T, d,
-                                                   F_shared, static_cast<const uint16_t *>(ws_down), nullptr,
-                                                   static_cast<uint16_t *>(y_shared), d, nullptr, 1, 1);
+    shared = ffn_bf16_dma_problem(1, static_cast<const uint16_t *>(h_shared), F_shared, nullptr, 1, T, d, F_shared,
+                                  static_cast<const uint16_t *>(ws_down), nullptr, static_cast<uint16_t *>(y_shared), d, nullptr, 1, 1);
+    routed = ffn_bf16_dma_problem(1, static_cast<const uint16_t *>(h), F, offsets, E_local, A_cap, d, F,
+                                  static_cast<const uint16_t *>(w_down), nullptr, static_cast<uint16_t *>(y_perm), d, nullptr, 1, 1);
+    return C2R_OK;
+}
+
+extern "C" int c2r_expert_ffn_gate_up_with_shared(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K,
+                                                  const int32_t *offsets, int E_local, int64_t A_cap, int d, int F,
+                                                  const void *w_gate, const void *w_up, void *h, int F_shared,
+                                                  const void *ws_gate, const void *ws_up, void *h_shared,
+                                                  void *stream) {
+    FfnProblem routed, shared;
+    const int rc = gate_up_with_shared_problems(x, dt, perm, T, K, offsets, E_local, A_cap, d, F, w_gate, w_up, h, F_shared,
+                                                ws_gate, ws_up, h_shared, routed, shared);
+    if (rc != C2R_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (A_cap == 0) return launch_ffn_bf16_dma(1, shared, nullptr, st);
-    const FfnProblem routed = ffn_bf16_dma_problem(1, static_cast<const uint16_t *>(h), F, offsets, E_local, A_cap, d, F,
-                                                   static_cast<const uint16_t *>(w_down), nullptr,
-                                                   static_cast<uint16_t *>(y_perm), d, nullptr, 1, 1);
-    return launch_ffn_bf16_dma(1, routed, &shared, st);
+    return A_cap == 0 ? launch_ffn_bf16_dma(0, shared, nullptr, st) : launch_ffn_bf16_dma(0, routed, &shared, st);
+}
+
+extern "C" int c2r_expert_ffn_down_with_shared(const void *h, c2r_dtype dt, const int32_t *offsets, int E_local,
+                                               int64_t A_cap, int d, int F, const void *w_down, void *y_perm,
+                                               int64_t T, int F_shared, const void *h_shared, const void *ws_down,
+                                               void *y_shared, void *stream) {
+    FfnProblem routed, shared;
+    const int rc = down_with_shared_problems(h, dt, offsets, E_local, A_cap, d, F, w_down, y_perm, T, F_shared, h_shared, ws_down,
+                                             y_shared, routed, shared);
+    if (rc != C2R_OK) return rc;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    return A_cap == 0 ? launch_ffn_bf16_dma(1, shared, nullptr, st) : launch_ffn_bf16_dma(1, routed, &shared, st);
 }
 
 // ---- the layer in one host call ----
@@ -261,12 +301,21 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
                                (size_t)L.ws_route_bytes, L.local_slot, El, L.counts, L.offsets, L.perm, L.inv_perm, L.x_perm,
                                L.ws_permute, (size_t)L.ws_permute_bytes, stream);
     if (rc != C2R_OK) return rc;
-    if (L.h) {
-        if (rides)
-            rc = c2r_expert_ffn_gate_up_with_shared(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, Fs,
-                                                    L.ws_gate, L.ws_up, L.h_shared, stream);
-        else
-            rc = c2r_expert_ffn_gate_up_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, stream);
+    if (rides) {
+        FfnProblem routed[2], with[2];
+        rc = gate_up_with_shared_problems(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, Fs, L.ws_gate, L.ws_up,
+                                          L.h_shared, routed[0], with[0]);
+        if (rc == C2R_OK)
+            rc = down_with_shared_problems(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, T, Fs, L.h_shared, L.ws_down, L.y_shared,
+                                           routed[1], with[1]);
+        if (rc == C2R_OK) rc = launch_ffn_bf16_dma_both(routed, {&with[0], &with[1]}, static_cast<hipStream_t>(stream));
+    } else if (L.h && !shared) {
+        rc = check_gate_up_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h);
+        if (rc == C2R_OK) rc = check_down(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm);
+        if (rc == C2R_OK && A > 0)
+            rc = ffn_both_passes(x, L.offsets, El, A, d, F, F, L.w_gate, L.w_up, L.w_down, L.h, L.y_perm, L.perm, K, (int)T, stream);
+    } else if (L.h) {
+        rc = c2r_expert_ffn_gate_up_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, stream);
     } else if (L.x_perm) {
         rc = c2r_expert_ffn(L.x_perm, dt, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.w_down, L.y_perm, L.ws_ffn,
                             (size_t)L.ws_ffn_bytes, stream);
@@ -279,12 +328,8 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
         rc = c2r_expert_ffn_down(L.h_shared, dt, L.off_shared, 1, T, d, Fs, L.ws_down, L.y_shared, stream);
         if (rc != C2R_OK) return rc;
     }
-    if (L.h) {
-        if (rides)
-            rc = c2r_expert_ffn_down_with_shared(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, T, Fs, L.h_shared,
-                                                 L.ws_down, L.y_shared, stream);
-        else
-            rc = c2r_expert_ffn_down(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, stream);
+    if (L.h && shared && !rides) {
+        rc = c2r_expert_ffn_down(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, stream);
         if (rc != C2R_OK) return rc;
     }
     return c2r_combine(L.y_perm, dt, L.gates, L.inv_perm, T, d, K, shared ? L.y_shared : nullptr, L.y, stream);

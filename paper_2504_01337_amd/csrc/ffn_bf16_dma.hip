@@ -34,6 +34,19 @@ typedef const __attribute__((address_space(4))) FfnLaunch FfnLaunchConst;
 typedef const __attribute__((address_space(4))) FfnProblem FfnProblemConst;
 typedef FfnLaunchConst *FfnLaunchArgs;
 
+// Both passes of an FFN in one launch (see ffn_bf16_dma_both_kernel).
+struct FfnBothLaunch {
+    FfnLaunch pass[2];
+};
+// What a tile is to the other pass.  Gate/up: the M-tile that it is a part of and its rows.  Down: the launch's counters of finished
+// gate/up rows per M-tile, whether all are known to be finished, and the columns of the gate/up pass in tiles, {routed, single}.
+struct FfnTileLink {
+    int mt, rows, n_mtiles;
+    bool ready;
+    int up_ntn[2];
+    const int *rows_done;
+};
+
 // Shapes shared by the per-tile function and the kernel around it.
 template <int WM, int WN>
 struct FfnShape {
@@ -44,9 +57,20 @@ struct FfnShape {
     static constexpr int SMEM_BYTES = LONG_BYTES > SHORT_BYTES ? LONG_BYTES : SHORT_BYTES;
 };
 
+// A store that is complete only once the memory that all XCDs share has it (the policy of an atomic store at device scope).
+__device__ __forceinline__ void store16_through(void *p, uint4 v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 q = {v.x, v.y, v.z, v.w};
+    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(q) : "memory");
+#endif
+}
+
 // Length of XCD x's list (tiles, with the last round cut into parts): what its queue hands out.
+template <bool SPLIT>
 __device__ __forceinline__ int xcd_list_slots(int n_tiles) {
     if (n_tiles <= 0) return 0;
+    if (!SPLIT) return n_tiles;
     const int full = n_tiles / CUS_PER_XCD * CUS_PER_XCD, r = n_tiles - full;
     const int s = r == 0 ? 1 : (r * 4 <= CUS_PER_XCD ? 4 : (r * 2 <= CUS_PER_XCD ? 2 : 1));
     return full + r * s;
@@ -59,10 +83,12 @@ __device__ __forceinline__ int xcd_list_slots(int n_tiles) {
 // before_epilogue(): called once by every wave after the tile's last k-step (the kernel draws
 // the next ticket there, so that the trip to the counter overlaps the epilogue); not called on
 // the early returns.
-template <int MODE, int WM, int WN, class BeforeEpilogue>
+// BOTH: the launch carries both passes; `link` ties the tile to the other one and under_way() is called once by every wave after a
+// barrier behind which this wave's and every other wave's memory operations from before the call are complete.
+template <int MODE, int WM, int WN, bool BOTH, class UnderWay, class BeforeEpilogue>
 __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *smem, const int xcd, const int slot,
                                          const int grp_lo, const int grp_hi, const int sg_lo, const int sg_hi,
-                                         BeforeEpilogue &&before_epilogue) {
+                                         FfnTileLink &link, UnderWay &&under_way, BeforeEpilogue &&before_epilogue) {
     const FfnLaunchConst &L = *Lp;
     constexpr int BM = 256, BN = 256, BK = 64;
     constexpr int NW = WM * WN;                // waves
@@ -126,7 +152,9 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
         ra = equal_range(rmap.totalA * L.p[0].ntn, xcd);
         rb = equal_range(rmap.totalB * L.p[0].ntn, xcd);
     }
-    TailSplit ts = split_last_round(rs.cnt + ra.cnt + rb.cnt, slot);
+    // (beside the other pass there is no last round to cut: a CU that finds no gate/up tile takes a down tile)
+    constexpr bool SPLIT = !(BOTH && MODE == 0);
+    TailSplit ts = split_last_round<SPLIT>(rs.cnt + ra.cnt + rb.cnt, slot);
     if (!ts.valid) return;
     // (the same in every lane, but derived from cross-lane moves: say so, so that everything
     // picked by them - the problem's arguments above all - stays in scalar registers)
@@ -144,7 +172,7 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
     // of full tiles first take them while the others finish their last full tile, which fills
     // part of the idle tail of the launch with work that would otherwise sit in the middle of
     // it (few enough of them that they do not have to share HBM: FILL_TAIL per XCD).
-    constexpr int FILL_TAIL = 12;
+    constexpr int FILL_TAIL = SPLIT ? 12 : 0;
     const int n_b = __builtin_amdgcn_readfirstlane(rb.cnt);
     const int n_tail = n_b < FILL_TAIL ? n_b : FILL_TAIL, n_bi = n_b - n_tail, n_main = n_s + n_a + n_bi;
     const bool in_tail = ts.idx >= n_main;
@@ -162,10 +190,30 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
         g.expert = 0;
         g.row_begin = slo + mt * sbm + ts.sub * (sbm / ts.nsub);  // of this workgroup's part of the tile
         g.row_end = shi;
+        if constexpr (BOTH) {
+            const int b = mt * sbm / BM;
+            link.mt = (ragged0 ? rmap.totalA + rmap.totalB : 0) + b;
+            link.rows = shi - slo - b * BM;
+        }
     } else {
+        int a_rank = o_rank - n_s;
+        if constexpr (BOTH && MODE == 1) {
+            // The chunk of M-tiles that this XCD's share of the gate/up pass began inside of is finished by the XCD before, and
+            // late: it comes last here, the first chunk that is all this XCD's own comes first.
+            if (!is_b) {
+                const int up_first = equal_range(rmap.totalA * link.up_ntn[0], xcd).first;
+                const int skip = ragged_next_chunk(rmap, link.up_ntn[0], up_first) * L.p[0].ntn - ra.first;
+                a_rank += skip > 0 && skip < ra.cnt ? skip : 0;
+                if (a_rank >= ra.cnt) a_rank -= ra.cnt;
+            }
+        }
         const RaggedTile tr = is_b ? ragged_short_tile_at<BM>(rmap, L.p[0].ntn, rb.first + b_before)
-                                   : ragged_full_tile_at<BM>(rmap, L.p[0].ntn, ra.first + o_rank - n_s);
+                                   : ragged_full_tile_at<BM>(rmap, L.p[0].ntn, ra.first + a_rank);
         if (!tr.valid) return;
+        if constexpr (BOTH) {
+            link.mt = tr.mt;
+            link.rows = tr.row_end - tr.row_begin;
+        }
         g.expert = tr.expert;
         g.row_begin = tr.row_begin + ts.sub * (BM / ts.nsub);
         g.row_end = tr.row_end;
@@ -187,6 +235,23 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
     if (part < BM && rows > part) rows = part;
     const bool short_tile = rows <= LM;        // workgroup-uniform
     const bool tiny_tile = rows <= TM_T;
+    if constexpr (BOTH) link.mt = link.mt < link.n_mtiles ? link.mt : link.n_mtiles - 1;  // (overlapping groups of a corrupt array)
+    if constexpr (BOTH && MODE == 0) link.rows = rows < part ? rows : part;
+    if constexpr (BOTH && MODE == 1) {
+        if (!link.ready) {
+            // Rows of h that another workgroup may still be writing.  Its gate/up tiles have all been handed out by now, each to a workgroup
+            // that is running and waits for nothing, so this ends.  The fence empties this CU's L1 and this XCD's L2 of what they may
+            // hold of h; the other waves' loads come after the barrier.
+            if (wave == 0) {
+                const int need = (link.rows < BM ? link.rows : BM) * link.up_ntn[second ? 1 : 0];
+                while (__builtin_amdgcn_readfirstlane(
+                           __hip_atomic_load(&link.rows_done[link.mt], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < need)
+                    __builtin_amdgcn_s_sleep(16);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            }
+            lds_barrier();
+        }
+    }
 
     // ---- copy roles: one copy instruction fills 8 tile rows (1024 bytes); lane l lands on
     //      row l/8, chunk position l%8 and therefore fetches chunk (l%8) ^ key(row) ----
@@ -450,6 +515,7 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
             else
                 wait_copies_but_and_lds<0>();
             lds_barrier();  // every wave's reads of slice kt-1 have returned: its stage is free
+            if (kt == 0) under_way();
             if (kt + 3 < nk) tiny_copy(kt + 3);
             if (wm == 0 && cols_exist) {
                 const unsigned char *stage = smem + (kt & (T_NSTAGE - 1)) * T_STAGE_BYTES;
@@ -494,6 +560,7 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
             else
                 wait_copies_but_and_lds<0>();
             lds_barrier();
+            if (kt == 0) under_way();
             if (kt + 2 < nk) short_copy(kt + 2);
             if (wm == 0 && cols_exist) {
                 const unsigned char *stage = smem + (kt % L_NSTAGE) * L_STAGE_BYTES;
@@ -539,6 +606,7 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
             wait_copies_but<0>();
         }
         lds_barrier();
+        under_way();
         if (active) {
             read_a(st0, 0, 0, 0);
             read_b(bcur, 0, 0);
@@ -601,8 +669,13 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
         uint16_t *o = out + ((size_t)g.row_begin + wm * TM + srow) * ldo + col0 + chunk * 8;
 #pragma unroll
         for (int r0 = 0; r0 < TM; r0 += RPI) {
-            if (r0 + srow < rlim)
-                *reinterpret_cast<uint4 *>(o) = *reinterpret_cast<const uint4 *>(stg + (r0 + srow) * PITCH + chunk * 16);
+            if (r0 + srow < rlim) {
+                const uint4 q = *reinterpret_cast<const uint4 *>(stg + (r0 + srow) * PITCH + chunk * 16);
+                if constexpr (BOTH && MODE == 0)
+                    store16_through(o, q);
+                else
+                    *reinterpret_cast<uint4 *>(o) = q;
+            }
             o += (size_t)RPI * ldo;
         }
         return;
@@ -616,9 +689,17 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
         for (int j = 0; j < FJ; ++j) {
             const int col = col0 + j * 16 + fq * 4;
             uint2 pk = make_uint2(0, 0);
+            auto store = [&]() __attribute__((always_inline)) {
+                uint16_t *o = outb + (size_t)r * ldo + col;
+                if constexpr (BOTH && MODE == 0)
+                    __hip_atomic_store(reinterpret_cast<uint64_t *>(o), (uint64_t)pk.x | ((uint64_t)pk.y << 32), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                else
+                    *reinterpret_cast<uint2 *>(o) = pk;
+            };
             if (col >= N) {
                 // pass 0 keeps the padding columns of h at zero for pass 1's k tail
-                if (col < zero_to) *reinterpret_cast<uint2 *>(outb + (size_t)r * ldo + col) = pk;
+                if (col < zero_to) store();
                 continue;
             }
             float v4[4];
@@ -627,7 +708,7 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
                 v4[u] = MODE == 0 ? silu_mul(acc[i][j][u], acc[i][j + FN16 / 2][u]) : acc[i][j][u];
             pk.x = pack_bf16x2(v4[0], v4[1]);
             pk.y = pack_bf16x2(v4[2], v4[3]);
-            *reinterpret_cast<uint2 *>(outb + (size_t)r * ldo + col) = pk;
+            store();
         }
     }
 }
@@ -636,62 +717,97 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
 // and a count of the workgroups that have left.  All zero between launches: the last workgroup
 // to leave a launch clears the set it used.  The host hands the sets out round-robin, so up to
 // FFN_QUEUE_SETS launches of this kernel may be in flight on a GPU at once (on any streams).
-constexpr int FFN_QUEUE_SETS = 64, FFN_QUEUE_INTS = 16;
+// A launch of both passes has 8 more ticket counters for the second, the number of gate/up tiles that are finished, and per M-tile
+// the rows of h that are, summed over its N-tiles.
+constexpr int FFN_MTILES = 1024;
+constexpr int FFN_LEFT = 8, FFN_FINISHED = 9, FFN_DOWN = 16, FFN_ROWS_DONE = 32;
+constexpr int FFN_QUEUE_SETS = 64, FFN_QUEUE_INTS = FFN_ROWS_DONE + FFN_MTILES;
 __device__ int ffn_queues[FFN_QUEUE_SETS * FFN_QUEUE_INTS];
 
-// The kernel: one workgroup per CU, each pulling tiles until none are left.  The hardware hands
-// workgroups out strictly in order, the k-th of an XCD to shader engine k mod 4 - measured: a CU
-// freed early by a short tile stayed empty for 100 us behind a workgroup that waited for a CU
-// of ANOTHER engine - so with one workgroup per tile every tile shorter than its neighbours
-// left a bubble, and the ragged groups' tiles differ by a factor of six.  Here the list of an
-// XCD (ffn_common.h) is a queue: a ticket counter in device memory that the workgroups of that
-// XCD draw from (the L2 locality of the list is kept), and a workgroup whose own XCD has
-// nothing left draws from the others'.
-template <int MODE, int WM, int WN>
-__global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_kernel(const FfnLaunch L, int *__restrict__ queues) {
+// What stays the same for a workgroup while it walks the lists of one pass, or of both.
+struct FfnWalk {
+    unsigned char *smem;
+    int *queues;
+    // every wave keeps the row range of "its lane's" expert of the ragged problem (the tile
+    // lookup is wave-wide arithmetic on them; they do not change during the launch)
+    int grp_lo, grp_hi;
+    int sg_lo, sg_hi;  // the single group's row range (two scalars)
+    int up_slots;      // both passes: positions of all the lists of the first
+    int ticket;        // and (lane 0 of the first wave) the first ticket of the second's list
+    int n_mtiles;      // and the M-tiles that there are counters for
+};
+
+__device__ __forceinline__ void ffn_walk_init(FfnWalk &w, const FfnLaunch &L) {
+    w.grp_lo = w.grp_hi = w.sg_lo = w.sg_hi = w.up_slots = 0;
+    if (L.has_ragged) load_group_range(L.p[0].offsets, L.p[0].E_local, L.p[0].A_cap, w.grp_lo, w.grp_hi);
+    if (L.has_single) {
+        int lo = L.p[1].offsets ? L.p[1].offsets[0] : L.p[1].row_lo;
+        int hi = L.p[1].offsets ? L.p[1].offsets[1] : L.p[1].row_hi;
+        lo = lo < 0 ? 0 : (lo > L.p[1].A_cap ? L.p[1].A_cap : lo);
+        hi = hi < lo ? lo : (hi > L.p[1].A_cap ? L.p[1].A_cap : hi);
+        w.sg_lo = __builtin_amdgcn_readfirstlane(lo);
+        w.sg_hi = __builtin_amdgcn_readfirstlane(hi);
+    }
+}
+
+// One workgroup's way through the lists of a pass: tiles until none are left.
+// KERNARG: where the pass's FfnLaunch lies in the kernel-argument segment.
+template <int MODE, int WM, int WN, bool BOTH, int KERNARG>
+__device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, const int up_ntn_ragged, const int up_ntn_single) {
     typedef FfnShape<WM, WN> S;
-    static_assert(S::SMEM_BYTES <= 160 * 1024, "one workgroup per CU owns all of its LDS");
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[S::SMEM_BYTES];
+    constexpr bool SPLIT = !(BOTH && MODE == 0);
+    int *const queues = W.queues + (BOTH && MODE == 1 ? FFN_DOWN : 0);
     // The claimed position (XCD of the list, slot; -1: nothing left) is handed to the waves in
     // the last bytes of the stage memory, which is all of the CU's LDS: every layout of a tile
     // writes them only after its first hand-over barrier (the third weight stage of a full
     // tile, the fourth ring stage of a tiny one; a short tile never does), and no wave gets
     // there before every wave has read the claim.
-    int *const claim = reinterpret_cast<int *>(smem + S::SMEM_BYTES - 64);
+    int *const claim = reinterpret_cast<int *>(W.smem + S::SMEM_BYTES - 64);
     const int tid = threadIdx.x, lane = tid & 63;
     const int home = (int)(blockIdx.x & 7);
-    // every wave keeps the row range of "its lane's" expert of the ragged problem (the tile
-    // lookup is wave-wide arithmetic on them; they do not change during the launch)
-    int grp_lo = 0, grp_hi = 0;
-    if (L.has_ragged) load_group_range(L.p[0].offsets, L.p[0].E_local, L.p[0].A_cap, grp_lo, grp_hi);
-    // ... and the single group's row range (two scalars)
-    int sg_lo = 0, sg_hi = 0;
-    if (L.has_single) {
-        sg_lo = L.p[1].offsets ? L.p[1].offsets[0] : L.p[1].row_lo;
-        sg_hi = L.p[1].offsets ? L.p[1].offsets[1] : L.p[1].row_hi;
-        sg_lo = sg_lo < 0 ? 0 : (sg_lo > L.p[1].A_cap ? L.p[1].A_cap : sg_lo);
-        sg_hi = sg_hi < sg_lo ? sg_lo : (sg_hi > L.p[1].A_cap ? L.p[1].A_cap : sg_hi);
-        sg_lo = __builtin_amdgcn_readfirstlane(sg_lo);
-        sg_hi = __builtin_amdgcn_readfirstlane(sg_hi);
-    }
     // the first wave works the queues; its lane x < 8 keeps the number of slots of XCD x's list
     int my_len = 0;
     if (tid < 64) {
-        const int n_s = (sg_hi - sg_lo + L.single_rows - 1) / L.single_rows * (L.has_single ? L.p[1].ntn : 0);
+        const int n_s = (W.sg_hi - W.sg_lo + L.single_rows - 1) / L.single_rows * (L.has_single ? L.p[1].ntn : 0);
         int totA = 0, totB = 0;
         if (L.has_ragged) {
-            const RaggedMap m = ragged_map_of<S::BM>(grp_lo, grp_hi);
+            const RaggedMap m = ragged_map_of<S::BM>(W.grp_lo, W.grp_hi);
             totA = m.totalA * L.p[0].ntn;
             totB = m.totalB * L.p[0].ntn;
         }
         const int x = lane & 7;
-        my_len = xcd_list_slots(equal_range(n_s, x).cnt + equal_range(totA, x).cnt + equal_range(totB, x).cnt);
+        my_len = xcd_list_slots<SPLIT>(equal_range(n_s, x).cnt + equal_range(totA, x).cnt + equal_range(totB, x).cnt);
+        if (BOTH && MODE == 0)
+            for (int i = 0; i < 8; ++i) W.up_slots += __builtin_amdgcn_readlane(my_len, i);
     }
-    int q = home;        // the queue this workgroup draws from: its own XCD's until that is empty
     // The first position of every workgroup is its own number in its XCD (no trip to the counter
-    // before the first tile); the counters hand out what lies beyond those.
-    int ticket = (int)(blockIdx.x >> 3);  // (lane 0 of the first wave) a ticket of queue q drawn ahead
-    bool drawn = true;                    // such a ticket is at hand
+    // before the first tile); the counters hand out what lies beyond those.  (Not so in a second pass: its workgroups
+    // come one by one, and draw the first ticket while the last stores of the other pass are under way.)
+    constexpr bool OWN_FIRST = !(BOTH && MODE == 1);
+    auto beyond = [](int x) { return OWN_FIRST ? ((int)gridDim.x - x + 7) >> 3 : 0; };
+    int q = home;        // the queue this workgroup draws from: its own XCD's until that is empty
+    int ticket = OWN_FIRST ? (int)(blockIdx.x >> 3) : W.ticket;  // (lane 0 of the first wave) a ticket of queue q drawn ahead
+    bool drawn = true;                                           // such a ticket is at hand
+    bool first = true;
+    FfnTileLink link;
+    link.ready = false;
+    link.up_ntn[0] = up_ntn_ragged;
+    link.up_ntn[1] = up_ntn_single;
+    link.n_mtiles = W.n_mtiles;
+    link.rows_done = W.queues + FFN_ROWS_DONE;
+    // gate/up beside down: the tile whose stores are under way, and the positions that are done with since the last post
+    int done_mt = -1, done_rows = 0, done_slots = 0;
+    auto post = [&]() {
+        if constexpr (BOTH && MODE == 0) {
+            asm volatile("" ::: "memory");
+            if (tid == 0 && done_slots > 0) {
+                if (done_mt >= 0) atomicAdd(&W.queues[FFN_ROWS_DONE + done_mt], done_rows);
+                atomicAdd(&W.queues[FFN_FINISHED], done_slots);
+            }
+            done_mt = -1;
+            done_slots = 0;
+        }
+    };
     for (;;) {
         if (tid < 64) {
             // Every trip ends by checking the ticket it holds, so no valid ticket is ever dropped.
@@ -707,41 +823,61 @@ __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_kernel(const FfnLaun
                     // that finds them all empty leaves at once - drawing from eight empty queues one
                     // after the other cost 15 us at the end of every launch.
                     const int x = lane & 7;
-                    const int seen = __hip_atomic_load(&queues[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
-                                     (((int)gridDim.x - x + 7) >> 3);
+                    const int seen = __hip_atomic_load(&queues[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + beyond(x);
                     const uint32_t avail = (uint32_t)__ballot(lane < 8 && seen < my_len) & 0xffu;
                     if (avail == 0) break;  // (t is -1)
                     // own XCD's list first, then the next one (cyclically) that holds something
                     const uint32_t rot = ((avail >> q) | (avail << (8 - q))) & 0xffu;
                     q = (q + __builtin_ctz(rot)) & 7;
-                    if (lane == 0) ticket = atomicAdd(&queues[q], 1) + (((int)gridDim.x - q + 7) >> 3);
+                    if (lane == 0) ticket = atomicAdd(&queues[q], 1) + beyond(q);
                 }
                 have = false;
                 t = __builtin_amdgcn_readfirstlane(ticket);
                 if (t < __builtin_amdgcn_readlane(my_len, q)) break;
                 t = -1;
             }
+            if (BOTH && MODE == 1 && !link.ready && !first && t >= 0) {  // (it seldom is at the first: one trip less)
+                const int n = __hip_atomic_load(&W.queues[FFN_FINISHED], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                link.ready = __builtin_amdgcn_readfirstlane(n) >= W.up_slots;
+                if (link.ready) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            }
+            first = false;
             if (lane == 0) {
                 claim[0] = q;
                 claim[1] = t;
+                if (BOTH && MODE == 1) claim[2] = link.ready ? 1 : 0;
             }
         }
         wait_lds_only();
         lds_barrier();  // the claim is visible
         q = __builtin_amdgcn_readfirstlane(claim[0]);
         const int slot = __builtin_amdgcn_readfirstlane(claim[1]);
-        if (slot < 0) break;  // every queue is empty
+        if (slot < 0) {  // every queue is empty
+            if (BOTH && MODE == 0 && tid == 0) W.ticket = atomicAdd(&W.queues[FFN_DOWN + home], 1);
+            break;
+        }
+        if (BOTH && MODE == 1) link.ready = __builtin_amdgcn_readfirstlane(claim[2]) != 0;
         // The launch arguments are re-read per tile through a pointer the compiler cannot see
         // through: held in registers across the tile they are ~50 scalars too many.
-        // (L is the kernel's first argument: it sits at the start of the kernel-argument segment)
-        FfnLaunchArgs Lp = (FfnLaunchArgs)__builtin_amdgcn_kernarg_segment_ptr();
+        FfnLaunchArgs Lp = (FfnLaunchArgs)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + KERNARG);
         asm volatile("" : "+s"(Lp));
         drawn = false;
-        ffn_tile<MODE, WM, WN>(Lp, smem, q, slot, grp_lo, grp_hi, sg_lo, sg_hi, [&]() {
-            // the next ticket of the same queue, drawn while the epilogue runs
-            if (tid == 0) ticket = atomicAdd(&queues[q], 1) + (((int)gridDim.x - q + 7) >> 3);
-            drawn = true;
-        });
+        link.mt = -1;
+        bool begun = false;
+        ffn_tile<MODE, WM, WN, BOTH>(
+            Lp, W.smem, q, slot, W.grp_lo, W.grp_hi, W.sg_lo, W.sg_hi, link, post,
+            [&]() {
+                // the next ticket of the same queue, drawn while the epilogue runs
+                if (tid == 0) ticket = atomicAdd(&queues[q], 1) + beyond(q);
+                drawn = begun = true;
+            });
+        if (BOTH && MODE == 0) {
+            if (begun) {  // (else the position held nothing, and what was to be posted still is)
+                done_mt = link.mt;
+                done_rows = link.rows;
+            }
+            ++done_slots;
+        }
         // This wave's LDS reads have returned; then every wave's: the next claim and the next tile's
         // copies may overwrite the stages.  The epilogue's stores are NOT waited for (a workgroup
         // that ends does not wait for its stores either): they drain while the next tile is looked
@@ -751,13 +887,71 @@ __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_kernel(const FfnLaun
         wait_lds_only();
         lds_barrier();
     }
-    // the last workgroup to leave clears the set for the launch that gets it next
-    // (this workgroup's draws have all returned - their values were used - so they precede the
-    // count below; no fence: a device-scope release would write the XCD's whole L2 back)
-    if (tid == 0) {
-        if (atomicAdd(&queues[8], 1) == (int)gridDim.x - 1) {
-            for (int i = 0; i < 9; ++i) atomicExch(&queues[i], 0);
-        }
+    if (BOTH && MODE == 0) {  // no tile follows whose first slice the last stores could be posted behind
+        wait_copies_but<0>();
+        lds_barrier();
+        post();
+    }
+}
+
+// The last workgroup to leave clears the set for the launch that gets it next
+// (this workgroup's draws have all returned - their values were used - so they precede the
+// count below; no fence: a device-scope release would write the XCD's whole L2 back)
+__device__ __forceinline__ bool ffn_last_to_leave(int *queues) {
+    return atomicAdd(&queues[FFN_LEFT], 1) == (int)gridDim.x - 1;
+}
+
+// The kernel: one workgroup per CU, each pulling tiles until none are left.  The hardware hands
+// workgroups out strictly in order, the k-th of an XCD to shader engine k mod 4 - measured: a CU
+// freed early by a short tile stayed empty for 100 us behind a workgroup that waited for a CU
+// of ANOTHER engine - so with one workgroup per tile every tile shorter than its neighbours
+// left a bubble, and the ragged groups' tiles differ by a factor of six.  Here the list of an
+// XCD (ffn_common.h) is a queue: a ticket counter in device memory that the workgroups of that
+// XCD draw from (the L2 locality of the list is kept), and a workgroup whose own XCD has
+// nothing left draws from the others'.
+template <int MODE, int WM, int WN>
+__global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_kernel(const FfnLaunch L, int *__restrict__ queues) {
+    typedef FfnShape<WM, WN> S;
+    static_assert(S::SMEM_BYTES <= 160 * 1024, "one workgroup per CU owns all of its LDS");
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[S::SMEM_BYTES];
+    FfnWalk W;
+    W.smem = smem;
+    W.queues = queues;
+    W.n_mtiles = 0;
+    ffn_walk_init(W, L);
+    ffn_walk_lists<MODE, WM, WN, false, 0>(W, L, 0, 0);
+    if (threadIdx.x == 0 && ffn_last_to_leave(queues))
+        for (int i = 0; i <= FFN_LEFT; ++i) atomicExch(&queues[i], 0);
+}
+
+// Both passes in one launch: a workgroup that finds no gate/up tile left goes on with the down pass instead of idling until the
+// last one is finished.  With tiles as long as a third of a pass the workgroups of a pass end up to a tile apart (idle per CU at the end of the
+// gate/up pass, microseconds: 60 experts + shared, 1000 tokens 21 of 129, 16 experts of d 4096, 4096 tokens 28 of 170, 15 of 60 experts, 32768
+// tokens 21 of 202), and a launch begins with all of them at once.  A down tile waits until all the gate/up tiles of its rows are
+// finished; the order of the lists makes that rare (1 to 5 us per CU).  h is written through to the memory that all XCDs share (store16_through),
+// counted per M-tile once a barrier behind the stores' completion has been passed, and read after the reader's caches are emptied.
+// Layer call of the three, two launches / this: 254 / 231, 360 / 331, 469 / 439; 8192 tokens of the first, which the power limit bounds,
+// 1043 / 1036.  Starting the down lists where the share begins instead of at the XCD's first own
+// chunk: 230.3
+// against 228.2, 336 against 330.5, 446 against 435; short gate/up tiles last, as in a launch of their own: 334.9 against 330.5 for the second.
+template <int WM, int WN>
+__global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_both_kernel(const FfnBothLaunch L, int *__restrict__ queues, int n_mtiles) {
+    typedef FfnShape<WM, WN> S;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[S::SMEM_BYTES];
+    FfnWalk W;
+    W.smem = smem;
+    W.queues = queues;
+    W.n_mtiles = n_mtiles;
+    ffn_walk_init(W, L.pass[0]);
+    ffn_walk_lists<0, WM, WN, true, 0>(W, L.pass[0], 0, 0);
+    ffn_walk_lists<1, WM, WN, true, (int)sizeof(FfnLaunch)>(W, L.pass[1], L.pass[0].p[0].ntn, L.pass[0].p[1].ntn);
+    if (threadIdx.x < 64) {
+        wait_copies_but<0>();  // (what this workgroup posted has arrived)
+        int last = 0;
+        if (threadIdx.x == 0) last = ffn_last_to_leave(queues) ? 1 : 0;
+        if (__builtin_amdgcn_readfirstlane(last))
+            for (int i = threadIdx.x; i < FFN_ROWS_DONE + n_mtiles; i += 64)
+                __hip_atomic_store(&queues[i], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -813,17 +1007,8 @@ static int single_tile_rows(const FfnProblem *ragged, const FfnProblem *single) 
     return tiles <= 40 ? BM / 4 : (tiles < 64 ? BM / 2 : BM);
 }
 
-// Launches one pass over one problem (second == nullptr) or over two: the second must be a single
-// group (E_local == 1).  Two go into ONE grid unless the first is a single group as well.
-int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, hipStream_t st) {
-    drop_stale_error();
-    constexpr int BM = 256, WM = 2, WN = 4;
-    if (second && second->E_local != 1) return C2R_ERR_INVALID_ARG;
-    if (second && first.E_local == 1) {  // (a launch holds one single group)
-        const int rc = launch_ffn_bf16_dma(pass, first, nullptr, st);
-        return rc != C2R_OK ? rc : launch_ffn_bf16_dma(pass, *second, nullptr, st);
-    }
-    // the kernel expects the ragged problem (more than one group) in p[0], a single group in p[1]
+// The kernel expects the ragged problem (more than one group) in p[0], a single group in p[1].
+static FfnLaunch ffn_launch_of(const FfnProblem &first, const FfnProblem *second) {
     FfnLaunch L;
     const FfnProblem *single = second ? second : (first.E_local == 1 ? &first : nullptr);
     const FfnProblem *ragged = first.E_local != 1 ? &first : nullptr;
@@ -831,38 +1016,98 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     L.p[1] = single ? *single : *ragged;
     L.has_ragged = ragged ? 1 : 0;
     L.has_single = single ? 1 : 0;
+    L.single_rows = single_tile_rows(ragged, single);
+    return L;
+}
+
+// One workgroup per CU (fewer if the bound on the tiles is smaller), whatever the number of tiles.
+static int64_t ffn_grid_of(const FfnLaunch &L) {
+    constexpr int BM = 256;
+    int64_t tiles = 0;
+    if (L.has_ragged)
+        tiles += 8 * ragged_per_xcd_bound(((int64_t)L.p[0].A_cap + BM - 1) / BM + L.p[0].E_local, L.p[0].E_local, L.p[0].ntn);
+    if (L.has_single)
+        tiles += 8 * single_per_xcd_bound(((int64_t)L.p[1].A_cap + L.single_rows - 1) / L.single_rows + 1, L.p[1].ntn);
+    tiles += 8 * CUS_PER_XCD;  // (row parts of the last rounds)
+    return tiles < 8 * CUS_PER_XCD ? tiles : 8 * CUS_PER_XCD;
+}
+
+// A set of queues for one launch; nullptr: none to be had.
+static int *ffn_next_queues() {
+    static std::atomic<unsigned> next_set{0};
+    static std::atomic<int *> queue_base[64];  // per device: the address of that device's copy of ffn_queues
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+    int *base = queue_base[dev].load();
+    if (!base) {  // (in host code the array's name is only a handle for this query)
+        void *p = nullptr;
+        if (hipGetSymbolAddress(&p, HIP_SYMBOL(ffn_queues)) != hipSuccess || !p) return nullptr;
+        base = static_cast<int *>(p);
+        queue_base[dev].store(base);
+    }
+    return base + (next_set.fetch_add(1) % FFN_QUEUE_SETS) * FFN_QUEUE_INTS;
+}
+
+// Launches one pass over one problem (second == nullptr) or over two: the second must be a single
+// group (E_local == 1).  Two go into ONE grid unless the first is a single group as well.
+int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, hipStream_t st) {
+    drop_stale_error();
+    constexpr int WM = 2, WN = 4;
+    if (second && second->E_local != 1) return C2R_ERR_INVALID_ARG;
+    if (second && first.E_local == 1) {  // (a launch holds one single group)
+        const int rc = launch_ffn_bf16_dma(pass, first, nullptr, st);
+        return rc != C2R_OK ? rc : launch_ffn_bf16_dma(pass, *second, nullptr, st);
+    }
+    const FfnLaunch L = ffn_launch_of(first, second);
     // Few rows: the kernel of ffn_skinny.hip.  More, but not enough to fill the chip with 256 x 256 tiles: that of ffn_mid.hip.
     // Every output is the same chain of the same matrix instructions in all three, so a row's bits do not depend on the choice.
     if (ffn_skinny_takes(pass, L)) return launch_ffn_skinny(pass, L, st);
     int tile_rows[2];
     if (ffn_mid_rows(pass, L, tile_rows)) return launch_ffn_mid(pass, tile_rows, L, st);
-    // one workgroup per CU (fewer if the bound on the tiles is smaller), whatever the number of tiles
-    int64_t tiles = 0;
-    if (ragged)
-        tiles += 8 * ragged_per_xcd_bound(((int64_t)ragged->A_cap + BM - 1) / BM + ragged->E_local, ragged->E_local,
-                                          ragged->ntn);
-    L.single_rows = single_tile_rows(ragged, single);
-    if (single) tiles += 8 * single_per_xcd_bound(((int64_t)single->A_cap + L.single_rows - 1) / L.single_rows + 1, single->ntn);
-    tiles += 8 * CUS_PER_XCD;  // (row parts of the last rounds)
-    const int64_t grid = tiles < 8 * CUS_PER_XCD ? tiles : 8 * CUS_PER_XCD;
-    static std::atomic<unsigned> next_set{0};
-    static std::atomic<int *> queue_base[64];  // per device: the address of that device's copy of ffn_queues
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return C2R_ERR_LAUNCH;
-    int *base = queue_base[dev].load();
-    if (!base) {  // (in host code the array's name is only a handle for this query)
-        void *p = nullptr;
-        if (hipGetSymbolAddress(&p, HIP_SYMBOL(ffn_queues)) != hipSuccess || !p) return C2R_ERR_LAUNCH;
-        base = static_cast<int *>(p);
-        queue_base[dev].store(base);
-    }
-    int *queues = base + (next_set.fetch_add(1) % FFN_QUEUE_SETS) * FFN_QUEUE_INTS;
-    const dim3 g((unsigned)grid), b(WM * WN * 64);
+    int *queues = ffn_next_queues();
+    if (!queues) return C2R_ERR_LAUNCH;
+    const dim3 g((unsigned)ffn_grid_of(L)), b(WM * WN * 64);
     if (pass == 0)
         ffn_bf16_dma_kernel<0, WM, WN><<<g, b, 0, st>>>(L, queues);
     else
         ffn_bf16_dma_kernel<1, WM, WN><<<g, b, 0, st>>>(L, queues);
     return launch_status();
+}
+
+// Both passes over one problem or two (first[pass], second[pass] as above; pass 1 reads the rows that pass 0 writes): one launch where
+// the tile kernel takes both, h has whole 128-byte lines and there are counters for all M-tiles (260000 rows: the idle end of a pass is
+// under 1 % of it there).
+int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *const (&second)[2], hipStream_t st) {
+    constexpr int BM = 256, WM = 2, WN = 4;
+    const bool two_single = second[0] && first[0].E_local == 1;
+    if (!two_single && (!second[0] || second[0]->E_local == 1)) {
+        FfnBothLaunch L;
+        int64_t mtiles = 0;
+        bool tiles = true;
+        for (int pass = 0; pass < 2; ++pass) {
+            L.pass[pass] = ffn_launch_of(first[pass], second[pass]);
+            int rows[2];
+            tiles = tiles && !ffn_skinny_takes(pass, L.pass[pass]) && !ffn_mid_rows(pass, L.pass[pass], rows);
+        }
+        // An XCD writes whole lines of h: no line is in two XCDs' L2.
+        for (int q = 0; q < 2; ++q) {
+            const FfnProblem &P = L.pass[0].p[q];
+            if (!(q == 0 ? L.pass[0].has_ragged : L.pass[0].has_single)) continue;
+            tiles = tiles && aligned(P.out, 128) && P.ldo % 64 == 0;
+            mtiles += P.A_cap / BM + P.E_local;
+        }
+        if (tiles && mtiles <= FFN_MTILES) {
+            drop_stale_error();
+            int *queues = ffn_next_queues();
+            if (!queues) return C2R_ERR_LAUNCH;
+            const int64_t g0 = ffn_grid_of(L.pass[0]), g1 = ffn_grid_of(L.pass[1]);
+            const dim3 g((unsigned)(g0 > g1 ? g0 : g1)), b(WM * WN * 64);
+            ffn_bf16_dma_both_kernel<WM, WN><<<g, b, 0, st>>>(L, queues, (int)mtiles);
+            return launch_status();
+        }
+    }
+    const int rc = launch_ffn_bf16_dma(0, first[0], second[0], st);
+    return rc != C2R_OK ? rc : launch_ffn_bf16_dma(1, first[1], second[1], st);
 }
 
 int launch_ffn_bf16_dma_pass(int pass, const uint16_t *a, int lda, const int32_t *offsets, int E_local,

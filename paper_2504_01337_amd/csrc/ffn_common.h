@@ -214,6 +214,7 @@ __device__ __forceinline__ void load_group_range(const int32_t *__restrict__ off
 struct RaggedTile {
     int expert, row_begin, row_end;  // row_begin: first row of the tile; row_end: the expert's end
     int nt;
+    int mt;                          // M-tile number, full tiles before short ones
     bool valid;
 };
 
@@ -223,7 +224,7 @@ __device__ __forceinline__ RaggedTile ragged_full_tile_at(const RaggedMap &m, in
     RaggedTile t;
     t.valid = false;
     t.expert = -1;
-    t.row_begin = t.row_end = t.nt = 0;
+    t.row_begin = t.row_end = t.nt = t.mt = 0;
     const int tlo = m.firstA * ntn;
     const uint64_t hit = __ballot(m.full > 0 && tile >= tlo && tile < tlo + m.full * ntn);
     if (hit == 0) return t;
@@ -235,11 +236,23 @@ __device__ __forceinline__ RaggedTile ragged_full_tile_at(const RaggedMap &m, in
     const int rem = tp - c * TILE_GM * ntn;
     const int mloc = c * TILE_GM + rem % gsz;
     t.nt = rem / gsz;
+    t.mt = first + mloc;
     t.expert = e;
     t.row_begin = __builtin_amdgcn_readlane(m.lo, e) + mloc * BM;
     t.row_end = __builtin_amdgcn_readlane(m.hi, e);
     t.valid = true;
     return t;
+}
+
+// The first M-tile of the chunk that begins at or after class A tile number `tile` (tile < totalA * ntn).
+__device__ __forceinline__ int ragged_next_chunk(const RaggedMap &m, int ntn, int tile) {
+    const int tlo = m.firstA * ntn;
+    const uint64_t hit = __ballot(m.full > 0 && tile >= tlo && tile < tlo + m.full * ntn);
+    if (hit == 0) return 0;
+    const int e = __ffsll((unsigned long long)hit) - 1;
+    const int full = __builtin_amdgcn_readlane(m.full, e), first = __builtin_amdgcn_readlane(m.firstA, e);
+    const int c = (tile - first * ntn + TILE_GM * ntn - 1) / (TILE_GM * ntn) * TILE_GM;
+    return first + (c < full ? c : full);
 }
 
 // Class B tile number -> tile.
@@ -248,12 +261,14 @@ __device__ __forceinline__ RaggedTile ragged_short_tile_at(const RaggedMap &m, i
     RaggedTile t;
     t.valid = false;
     t.expert = -1;
-    t.row_begin = t.row_end = t.nt = 0;
+    t.row_begin = t.row_end = t.nt = t.mt = 0;
     const int tlo = m.firstB * ntn;
     const uint64_t hit = __ballot(m.shortt > 0 && tile >= tlo && tile < tlo + ntn);
     if (hit == 0) return t;
     const int e = __ffsll((unsigned long long)hit) - 1;
-    t.nt = tile - __builtin_amdgcn_readlane(m.firstB, e) * ntn;
+    const int first = __builtin_amdgcn_readlane(m.firstB, e);
+    t.nt = tile - first * ntn;
+    t.mt = m.totalA + first;
     t.expert = e;
     t.row_begin = __builtin_amdgcn_readlane(m.lo, e) + __builtin_amdgcn_readlane(m.full, e) * BM;
     t.row_end = __builtin_amdgcn_readlane(m.hi, e);
@@ -300,13 +315,14 @@ struct TailSplit {
     bool valid;
 };
 
+template <bool SPLIT>
 __device__ __forceinline__ TailSplit split_last_round(int cnt, int slot) {
     TailSplit t;
     t.idx = slot;
     t.sub = 0;
     t.nsub = 1;
-    t.valid = false;
-    if (cnt <= 0) return t;
+    t.valid = SPLIT ? false : slot < cnt;
+    if (cnt <= 0 || !SPLIT) return t;
     const int full = cnt / CUS_PER_XCD * CUS_PER_XCD, r = cnt - full;
     const int s = r == 0 ? 1 : (r * 4 <= CUS_PER_XCD ? 4 : (r * 2 <= CUS_PER_XCD ? 2 : 1));
     if (slot >= full) {

@@ -1,0 +1,66 @@
+"""The expert FFN's two passes in one launch (ffn_bf16_dma.hip) against the same passes in a launch each: the same tiles, so the same
+bits.  Several times over the same buffers: the launch's counters have to be clear again, and h is rewritten while it is in caches."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import dev, ffn_kernel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def c2r():
+    from paper_2504_01337_amd import c2r as m
+    m.lib()
+    return m
+
+
+def _weights(rng, *shapes):
+    return [dev((rng.standard_normal(s) * 0.05).astype(np.float32), "bf16") for s in shapes]
+
+
+# full, short and tiny tiles and empty groups; one group; fewer M-tiles than XCDs; rows not all in use; a column tail (192, 320); one
+# slice (64); as many M-tiles as there are counters (1024) and one more (two launches)
+@pytest.mark.parametrize("d,F,sizes,cap", [
+    (128, 192, [256, 257, 511, 129, 128, 64, 65, 1, 0, 1000], 2600), (64, 64, [3000, 0, 1], 3001), (192, 704, [700], 800), (512, 128, [300, 299], 599),
+    (2048, 1408, [796, 624, 464, 341, 136, 63, 7, 0], 3200), (128, 320, [900] * 15, 13500), (64, 64, [131000, 130000], 1022 * 256),
+    (64, 64, [131000, 130500], 1023 * 256)])
+def test_routed_groups(c2r, d, F, sizes, cap):
+    rng = np.random.default_rng(d + F)
+    E, n, K = len(sizes), sum(sizes), 2
+    assert ffn_kernel(0, E, cap, F) == ffn_kernel(1, E, cap, d) == "tile"
+    T = (cap + K - 1) // K
+    x = dev(rng.standard_normal((T, d)).astype(np.float32), "bf16")
+    perm = dev(np.concatenate([rng.permutation(T * K)[:n], np.full(cap - n, -1)]).astype(np.int32))
+    offsets = dev(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
+    wg, wu, wd = _weights(rng, (E, F, d), (E, F, d), (E, d, F))
+    h, y = (torch.full((cap, c), 7.0, dtype=torch.bfloat16, device="cuda") for c in (F, d))
+    c2r.expert_ffn_gate_up_gather(x, perm, K, offsets, wg, wu, h)
+    c2r.expert_ffn_down(h, offsets, wd, y)
+    ws = torch.full((c2r.workspace_bytes(c2r.STAGE_EXPERT_FFN, cap, d, E, 1, F, c2r.BF16),), 255, dtype=torch.uint8, device="cuda")
+    for _ in range(4):
+        got = torch.full((cap, d), 7.0, dtype=torch.bfloat16, device="cuda")
+        ws.fill_(255)  # (NaNs: a row of h that is read before it is there shows)
+        c2r.expert_ffn_gather(x, perm, K, offsets, wg, wu, wd, ws=ws, out=got)
+        assert torch.equal(got, y)
+
+
+# a shared expert beside the routed groups, through the layer call: every row of it and of the routed experts
+@pytest.mark.parametrize("T,d,F,Fs", [(1300, 128, 64, 192), (2500, 256, 192, 1024), (5000, 64, 128, 64)])
+def test_layer_with_shared_expert(c2r, T, d, F, Fs):
+    rng = np.random.default_rng(T)
+    E, K = 16, 4
+    x = dev(rng.standard_normal((T, d)).astype(np.float32), "bf16")
+    Wg = dev((rng.standard_normal((d, E)) * 0.05 + np.linspace(0, 0.1, E)).astype(np.float32))
+    collab = dev(np.stack([np.delete(np.arange(E), e) for e in range(E)]).astype(np.int32))
+    weights = _weights(rng, (E, F, d), (E, F, d), (E, d, F))
+    shared = _weights(rng, (1, Fs, d), (1, Fs, d), (1, d, Fs))
+    a, b = (c2r.C2RLayer(T, d, E, K, F, torch.bfloat16, Wg, None, collab, *weights, shared=tuple(shared), fuse_shared=f) for f in (True, False))
+    assert a.fuse_shared and not b.fuse_shared
+    ref = b.forward(x).clone()
+    for _ in range(4):
+        a.h.fill_(float("nan"))
+        a.h_shared.fill_(float("nan"))
+        assert torch.equal(a.forward(x), ref)
+        assert torch.equal(a.y_perm, b.y_perm) and torch.equal(a.y_shared, b.y_shared)
