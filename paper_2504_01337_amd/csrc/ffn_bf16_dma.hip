@@ -239,7 +239,7 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
     if constexpr (BOTH && MODE == 0) link.rows = rows < part ? rows : part;
     if constexpr (BOTH && MODE == 1) {
         if (!link.ready) {
-            // Rows of h that another workgroup may still be writing.  Its gate/up tiles have all been handed out by now, each to a workgroup
+            // Rows of h that another workgroup may still be writing.  The gate/up tiles have all been drawn by now, each by a workgroup
             // that is running and waits for nothing, so this ends.  The fence empties this CU's L1 and this XCD's L2 of what they may
             // hold of h; the other waves' loads come after the barrier.
             if (wave == 0) {
@@ -733,7 +733,7 @@ struct FfnWalk {
     int grp_lo, grp_hi;
     int sg_lo, sg_hi;  // the single group's row range (two scalars)
     int up_slots;      // both passes: positions of all the lists of the first
-    int ticket;        // and (lane 0 of the first wave) the first ticket of the second's list
+    int ticket;        // and (lane 0 of the first wave) the first ticket of the workgroup's own list of the pass
     int n_mtiles;      // and the M-tiles that there are counters for
 };
 
@@ -781,9 +781,11 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
             for (int i = 0; i < 8; ++i) W.up_slots += __builtin_amdgcn_readlane(my_len, i);
     }
     // The first position of every workgroup is its own number in its XCD (no trip to the counter
-    // before the first tile); the counters hand out what lies beyond those.  (Not so in a second pass: its workgroups
-    // come one by one, and draw the first ticket while the last stores of the other pass are under way.)
-    constexpr bool OWN_FIRST = !(BOTH && MODE == 1);
+    // before the first tile); the counters hand out what lies beyond those.  Not so where a pass waits for the other:
+    // there a position must never be one's whose workgroup has not started (two such launches on two streams, each holding the
+    // CUs that the other's last workgroups need, would wait for ever).  Its first tickets are drawn while the groups' ranges
+    // are loaded, and while the last stores of the gate/up pass are under way.
+    constexpr bool OWN_FIRST = !BOTH;
     auto beyond = [](int x) { return OWN_FIRST ? ((int)gridDim.x - x + 7) >> 3 : 0; };
     int q = home;        // the queue this workgroup draws from: its own XCD's until that is empty
     int ticket = OWN_FIRST ? (int)(blockIdx.x >> 3) : W.ticket;  // (lane 0 of the first wave) a ticket of queue q drawn ahead
@@ -917,7 +919,7 @@ __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_kernel(const FfnLaun
     FfnWalk W;
     W.smem = smem;
     W.queues = queues;
-    W.n_mtiles = 0;
+    W.n_mtiles = W.ticket = 0;
     ffn_walk_init(W, L);
     ffn_walk_lists<MODE, WM, WN, false, 0>(W, L, 0, 0);
     if (threadIdx.x == 0 && ffn_last_to_leave(queues))
@@ -942,6 +944,8 @@ __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_both_kernel(const Ff
     W.smem = smem;
     W.queues = queues;
     W.n_mtiles = n_mtiles;
+    W.ticket = 0;
+    if (threadIdx.x == 0) W.ticket = atomicAdd(&queues[blockIdx.x & 7], 1);
     ffn_walk_init(W, L.pass[0]);
     ffn_walk_lists<0, WM, WN, true, 0>(W, L.pass[0], 0, 0);
     ffn_walk_lists<1, WM, WN, true, (int)sizeof(FfnLaunch)>(W, L.pass[1], L.pass[0].p[0].ntn, L.pass[0].p[1].ntn);
