@@ -17,12 +17,15 @@ int launch_ffn_bf16_dma_pass(int pass, const uint16_t *a, int lda, const int32_t
 struct FfnProblem;
 }  // namespace c2r
 #include "ffn_common.h"
+#include "route_few.h"
 namespace c2r {
 FfnProblem ffn_bf16_dma_problem(int pass, const uint16_t *a, int lda, const int32_t *offsets, int E_local,
                                 int64_t A_cap, int d, int F, const uint16_t *b0, const uint16_t *b1, uint16_t *out,
                                 int ldo, const int32_t *gather, int gather_div, int gather_rows);
 int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, hipStream_t st);
 int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *const (&second)[2], hipStream_t st);
+bool ffn_few_takes(const FfnProblem &routed, const FfnProblem *shared);
+int launch_ffn_few(const FfnProblem &routed, const FfnProblem *shared, const FewRoute &few, hipStream_t st);
 }  // namespace c2r
 
 using namespace c2r;
@@ -94,17 +97,15 @@ static int ffn_pass(int pass, c2r_dtype dt, const void *a, const int32_t *offset
 }
 
 // Both passes of routed groups on the copy-engine kernel: h of pitch ldh in between; gather: rows of x by perm.
-static int ffn_both_passes(const void *a, const int32_t *offsets, int E_local, int64_t A_cap, int d, int F, int ldh,
-                           const void *w_gate, const void *w_up, const void *w_down, void *h, void *y_perm,
-                           const int32_t *gather, int gather_div, int gather_rows, void *stream) {
+static void both_problems(const void *a, const int32_t *offsets, int E_local, int64_t A_cap, int d, int F, int ldh,
+                          const void *w_gate, const void *w_up, const void *w_down, void *h, void *y_perm, const int32_t *gather,
+                          int gather_div, int gather_rows, FfnProblem (&p)[2]) {
     uint16_t *const hb = static_cast<uint16_t *>(h);
-    const FfnProblem p[2] = {
-        ffn_bf16_dma_problem(0, static_cast<const uint16_t *>(a), d, offsets, E_local, A_cap, d, F,
-                             static_cast<const uint16_t *>(w_gate), static_cast<const uint16_t *>(w_up), hb, ldh, gather,
-                             gather_div, gather_rows),
-        ffn_bf16_dma_problem(1, hb, ldh, offsets, E_local, A_cap, d, F, static_cast<const uint16_t *>(w_down), nullptr,
-                             static_cast<uint16_t *>(y_perm), d, nullptr, 1, 1)};
-    return launch_ffn_bf16_dma_both(p, {nullptr, nullptr}, static_cast<hipStream_t>(stream));
+    p[0] = ffn_bf16_dma_problem(0, static_cast<const uint16_t *>(a), d, offsets, E_local, A_cap, d, F,
+                                static_cast<const uint16_t *>(w_gate), static_cast<const uint16_t *>(w_up), hb, ldh, gather,
+                                gather_div, gather_rows);
+    p[1] = ffn_bf16_dma_problem(1, hb, ldh, offsets, E_local, A_cap, d, F, static_cast<const uint16_t *>(w_down), nullptr,
+                                static_cast<uint16_t *>(y_perm), d, nullptr, 1, 1);
 }
 
 extern "C" int c2r_expert_ffn_gate_up(const void *x_perm, c2r_dtype dt, const int32_t *offsets, int E_local,
@@ -175,18 +176,21 @@ extern "C" int c2r_expert_ffn(const void *x_perm, c2r_dtype dt, const int32_t *o
     const int ldh = h_pitch(dt, d, F);
     const size_t need = round_up((size_t)A_cap * ldh * (dt == C2R_BF16 ? 2 : 4), 256);
     if (!ws || ws_bytes < need || !aligned(ws, 256)) return C2R_ERR_WORKSPACE;
-    if (fast_bf16(dt, d, F))
-        return ffn_both_passes(x_perm, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, w_down, ws, y_perm, nullptr, 1, 1, stream);
+    if (fast_bf16(dt, d, F)) {
+        FfnProblem p[2];
+        both_problems(x_perm, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, w_down, ws, y_perm, nullptr, 1, 1, p);
+        return launch_ffn_bf16_dma_both(p, {nullptr, nullptr}, static_cast<hipStream_t>(stream));
+    }
     rc = ffn_pass(0, dt, x_perm, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, ws, stream);
     if (rc != C2R_OK) return rc;
     return ffn_pass(1, dt, ws, offsets, E_local, A_cap, d, F, ldh, w_down, nullptr, y_perm, stream);
 }
 
-extern "C" int c2r_expert_ffn_gather(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K,
-                                     const int32_t *offsets, int E_local, int64_t A_cap, int d, int F,
-                                     const void *w_gate, const void *w_up, const void *w_down, void *y_perm,
-                                     void *ws, size_t ws_bytes, void *stream) {
-    int rc = check_ffn(dt, E_local, A_cap, d, F);
+// The arguments of c2r_expert_ffn_gather, checked; p: its two passes (A_cap > 0).
+static int gather_problems(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K, const int32_t *offsets, int E_local,
+                           int64_t A_cap, int d, int F, const void *w_gate, const void *w_up, const void *w_down, void *y_perm,
+                           void *ws, size_t ws_bytes, FfnProblem (&p)[2]) {
+    const int rc = check_ffn(dt, E_local, A_cap, d, F);
     if (rc != C2R_OK) return rc;
     if (T < 1 || K < 1) return C2R_ERR_INVALID_ARG;
     if (A_cap == 0) return C2R_OK;
@@ -198,7 +202,18 @@ extern "C" int c2r_expert_ffn_gather(const void *x, c2r_dtype dt, const int32_t 
     const int ldh = h_pitch(dt, d, F);
     const size_t need = round_up((size_t)A_cap * ldh * 2, 256);
     if (!ws || ws_bytes < need || !aligned(ws, 256)) return C2R_ERR_WORKSPACE;
-    return ffn_both_passes(x, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, w_down, ws, y_perm, perm, K, (int)T, stream);
+    both_problems(x, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, w_down, ws, y_perm, perm, K, (int)T, p);
+    return C2R_OK;
+}
+
+extern "C" int c2r_expert_ffn_gather(const void *x, c2r_dtype dt, const int32_t *perm, int64_t T, int K,
+                                     const int32_t *offsets, int E_local, int64_t A_cap, int d, int F,
+                                     const void *w_gate, const void *w_up, const void *w_down, void *y_perm,
+                                     void *ws, size_t ws_bytes, void *stream) {
+    FfnProblem p[2];
+    const int rc = gather_problems(x, dt, perm, T, K, offsets, E_local, A_cap, d, F, w_gate, w_up, w_down, y_perm, ws, ws_bytes, p);
+    if (rc != C2R_OK || A_cap == 0) return rc;
+    return launch_ffn_bf16_dma_both(p, {nullptr, nullptr}, static_cast<hipStream_t>(stream));
 }
 
 // ---- routed groups and an always-on shared expert in ONE launch per pass ----
@@ -297,38 +312,54 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
                                 (size_t)L.ws_shared_bytes, stream);
         if (rc != C2R_OK) return rc;
     }
+    // The forms whose first pass reads rows of x: the passes' arguments first, so that the gate/up launch of a few tokens can finish the
+    // routing (an error in them is still reported after one in the routing's).
+    const bool own_h = L.h && !shared, gathers = rides || own_h || (!L.h && !L.x_perm);
+    FfnProblem routed[2], with[2];
+    int ffn_rc = C2R_OK;
+    if (rides) {
+        ffn_rc = gate_up_with_shared_problems(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, Fs, L.ws_gate, L.ws_up,
+                                              L.h_shared, routed[0], with[0]);
+        if (ffn_rc == C2R_OK)
+            ffn_rc = down_with_shared_problems(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, T, Fs, L.h_shared, L.ws_down,
+                                               L.y_shared, routed[1], with[1]);
+    } else if (own_h) {
+        ffn_rc = check_gate_up_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h);
+        if (ffn_rc == C2R_OK) ffn_rc = check_down(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm);
+        if (ffn_rc == C2R_OK && A > 0)
+            both_problems(x, L.offsets, El, A, d, F, F, L.w_gate, L.w_up, L.w_down, L.h, L.y_perm, L.perm, K, (int)T, routed);
+    } else if (gathers) {
+        ffn_rc = gather_problems(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.w_down, L.y_perm, L.ws_ffn,
+                                 (size_t)L.ws_ffn_bytes, routed);
+    }
+    const FfnProblem *const beside[2] = {rides ? &with[0] : nullptr, rides ? &with[1] : nullptr};
+    FewRoute few;
+    const bool later = gathers && ffn_rc == C2R_OK && A > 0 && route_may_finish_later(T, d, E, K) && ffn_few_takes(routed[0], beside[0]);
     int rc = route_and_permute(x, dt, L.Wg, L.bias, T, d, E, K, L.collab_idx, (int)L.Tc, L.topk_idx, L.gates, L.ws_route,
                                (size_t)L.ws_route_bytes, L.local_slot, El, L.counts, L.offsets, L.perm, L.inv_perm, L.x_perm,
-                               L.ws_permute, (size_t)L.ws_permute_bytes, stream);
+                               L.ws_permute, (size_t)L.ws_permute_bytes, later ? &few : nullptr, stream);
     if (rc != C2R_OK) return rc;
-    if (rides) {
-        FfnProblem routed[2], with[2];
-        rc = gate_up_with_shared_problems(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, Fs, L.ws_gate, L.ws_up,
-                                          L.h_shared, routed[0], with[0]);
-        if (rc == C2R_OK)
-            rc = down_with_shared_problems(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, T, Fs, L.h_shared, L.ws_down, L.y_shared,
-                                           routed[1], with[1]);
-        if (rc == C2R_OK) rc = launch_ffn_bf16_dma_both(routed, {&with[0], &with[1]}, static_cast<hipStream_t>(stream));
-    } else if (L.h && !shared) {
-        rc = check_gate_up_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h);
-        if (rc == C2R_OK) rc = check_down(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm);
-        if (rc == C2R_OK && A > 0)
-            rc = ffn_both_passes(x, L.offsets, El, A, d, F, F, L.w_gate, L.w_up, L.w_down, L.h, L.y_perm, L.perm, K, (int)T, stream);
+    if (gathers) {
+        hipStream_t st = static_cast<hipStream_t>(stream);
+        rc = ffn_rc;
+        if (later) {
+            rc = launch_ffn_few(routed[0], beside[0], few, st);
+            if (rc == C2R_OK) rc = launch_ffn_bf16_dma(1, routed[1], beside[1], st);
+        } else if (rc == C2R_OK && A > 0) {
+            rc = launch_ffn_bf16_dma_both(routed, beside, st);
+        }
     } else if (L.h) {
         rc = c2r_expert_ffn_gate_up_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, stream);
-    } else if (L.x_perm) {
+    } else {
         rc = c2r_expert_ffn(L.x_perm, dt, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.w_down, L.y_perm, L.ws_ffn,
                             (size_t)L.ws_ffn_bytes, stream);
-    } else {
-        rc = c2r_expert_ffn_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.w_down, L.y_perm,
-                                   L.ws_ffn, (size_t)L.ws_ffn_bytes, stream);
     }
     if (rc != C2R_OK) return rc;
     if (shared && !rides && L.h_shared) {
         rc = c2r_expert_ffn_down(L.h_shared, dt, L.off_shared, 1, T, d, Fs, L.ws_down, L.y_shared, stream);
         if (rc != C2R_OK) return rc;
     }
-    if (L.h && shared && !rides) {
+    if (L.h && !gathers) {
         rc = c2r_expert_ffn_down(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, stream);
         if (rc != C2R_OK) return rc;
     }

@@ -45,14 +45,33 @@ int permute_check(const void *x, c2r_dtype dt, const int32_t *topk_idx, int64_t 
                   int32_t *inv_perm, void *x_perm, void *ws, size_t ws_bytes);
 int permute_rows(const void *x, c2r_dtype dt, int64_t T, int d, int K, const int32_t *inv_perm, void *x_perm,
                  hipStream_t st);
-// route.hip
+// route.hip.  later: not null only where route_may_finish_later; then the chunk results are all that is enqueued, and the next launch has
+// to do the rest (route_few.h).
+struct FewRoute;
+constexpr int FEW_TOKENS = 16, FEW_ASSIGNMENTS = 32;
+bool route_may_finish_later(int64_t T, int d, int E, int K);
 int route_and_permute(const void *x, c2r_dtype dt, const float *Wg, const float *bias, int64_t T, int d, int E, int K,
                       const int32_t *collab_idx, int Tc, int32_t *topk_idx, float *gates, void *ws_route,
                       size_t ws_route_bytes, const int32_t *local_slot, int E_local, int32_t *counts, int32_t *offsets,
                       int32_t *perm, int32_t *inv_perm, void *x_perm, void *ws_permute, size_t ws_permute_bytes,
-                      void *stream);
+                      FewRoute *later, void *stream);
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (C2R_WAVE - 1); }
+
+// Inclusive prefix sum over the 64 lanes of a wave with data-parallel-primitive moves (no
+// LDS round trips): shifts by 1, 2, 4, 8 inside each row of 16 lanes, then the row totals
+// are passed on with the two row broadcasts.  Every lane must be active.
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
+#endif
+    return v;
+}
 
 // The largest of the 64 lanes' values, in every lane, without LDS round trips.  Every lane must be active.
 __device__ __forceinline__ int wave_max(int v) {

@@ -989,7 +989,8 @@ FfnProblem ffn_bf16_dma_problem(int pass, const uint16_t *a, int lda, const int3
 }
 
 bool ffn_skinny_takes(int pass, const FfnLaunch &L);
-int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st);
+bool ffn_skinny_takes_few(FfnLaunch L);
+int launch_ffn_skinny(int pass, const FfnLaunch &L, const FewRoute *few, hipStream_t st);
 bool ffn_mid_rows(int pass, const FfnLaunch &L, int (&rows)[2]);
 int launch_ffn_mid(int pass, const int (&tile_rows)[2], FfnLaunch L, hipStream_t st);
 
@@ -1065,7 +1066,7 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     const FfnLaunch L = ffn_launch_of(first, second);
     // Few rows: the kernel of ffn_skinny.hip.  More, but not enough to fill the chip with 256 x 256 tiles: that of ffn_mid.hip.
     // Every output is the same chain of the same matrix instructions in all three, so a row's bits do not depend on the choice.
-    if (ffn_skinny_takes(pass, L)) return launch_ffn_skinny(pass, L, st);
+    if (ffn_skinny_takes(pass, L)) return launch_ffn_skinny(pass, L, nullptr, st);
     int tile_rows[2];
     if (ffn_mid_rows(pass, L, tile_rows)) return launch_ffn_mid(pass, tile_rows, L, st);
     int *queues = ffn_next_queues();
@@ -1112,6 +1113,16 @@ int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *con
     }
     const int rc = launch_ffn_bf16_dma(0, first[0], second[0], st);
     return rc != C2R_OK ? rc : launch_ffn_bf16_dma(1, first[1], second[1], st);
+}
+
+// Whether the gate/up pass of a few tokens does their selection and index at its start.
+bool ffn_few_takes(const FfnProblem &routed, const FfnProblem *shared) {
+    return routed.E_local != 1 && ffn_skinny_takes_few(ffn_launch_of(routed, shared));
+}
+
+// The gate/up pass that does so.
+int launch_ffn_few(const FfnProblem &routed, const FfnProblem *shared, const FewRoute &few, hipStream_t st) {
+    return launch_ffn_skinny(0, ffn_launch_of(routed, shared), &few, st);
 }
 
 int launch_ffn_bf16_dma_pass(int pass, const uint16_t *a, int lda, const int32_t *offsets, int E_local,

@@ -4,21 +4,6 @@
 
 namespace c2r {
 
-// Inclusive prefix sum over the 64 lanes of a wave with data-parallel-primitive moves (no
-// LDS round trips): shifts by 1, 2, 4, 8 inside each row of 16 lanes, then the row totals
-// are passed on with the two row broadcasts.  Every lane must be active.
-__device__ __forceinline__ int wave_inclusive_scan(int v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);  // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
-#endif
-    return v;
-}
-
 struct GroupTile {
     int expert;        // local expert slot, -1: no such tile
     int row_begin;     // first row of the tile in x_perm
@@ -36,27 +21,33 @@ struct GroupMap {
     int total_mtiles;  // M-tiles over all experts
 };
 
-// Every wave calls this with all 64 lanes active; E_local <= 64.  Offsets are clamped so
-// that a corrupt array cannot send a load out of bounds.
+// From the row range held by each lane (empty past the last group).  Every wave calls this with all 64 lanes active.
 template <int BM>
-__device__ __forceinline__ GroupMap build_group_map(const int32_t *__restrict__ offsets, int E_local,
-                                                     int A_cap) {
-    const int lane = lane_id();
+__device__ __forceinline__ GroupMap group_map_of(int lo, int hi) {
     GroupMap m;
-    m.lo = m.hi = 0;
-    if (lane < E_local) {
-        int lo = offsets[lane], hi = offsets[lane + 1];
-        lo = lo < 0 ? 0 : (lo > A_cap ? A_cap : lo);
-        hi = hi < lo ? lo : (hi > A_cap ? A_cap : hi);
-        m.lo = lo;
-        m.hi = hi;
-    }
+    m.lo = lo;
+    m.hi = hi;
     const int cnt = m.hi - m.lo;
     m.tiles = (cnt + BM - 1) / BM;
     const int incl = wave_inclusive_scan(m.tiles);
     m.first = incl - m.tiles;
     m.total_mtiles = __shfl(incl, 63);
     return m;
+}
+
+// Every wave calls this with all 64 lanes active; E_local <= 64.  Offsets are clamped so
+// that a corrupt array cannot send a load out of bounds.
+template <int BM>
+__device__ __forceinline__ GroupMap build_group_map(const int32_t *__restrict__ offsets, int E_local,
+                                                     int A_cap) {
+    const int lane = lane_id();
+    int lo = 0, hi = 0;
+    if (lane < E_local) {
+        lo = offsets[lane], hi = offsets[lane + 1];
+        lo = lo < 0 ? 0 : (lo > A_cap ? A_cap : lo);
+        hi = hi < lo ? lo : (hi > A_cap ? A_cap : hi);
+    }
+    return group_map_of<BM>(lo, hi);
 }
 
 __device__ __forceinline__ GroupTile locate_group_tile(const GroupMap &m, int mt, int BM) {

@@ -21,6 +21,7 @@
 
 #include "ffn_common.h"
 #include "ffn_copy.h"
+#include "route_few.h"
 
 namespace c2r {
 
@@ -50,7 +51,7 @@ __device__ __forceinline__ void static_for_count(int count, F &&f) {
 // chunk past K is taken from the start of its row and multiplied by those zeros.
 template <int MODE, int WPS, int MF, int NF>
 __device__ __forceinline__ void skinny_tile(const FfnProblem &P, unsigned char *smem, int expert, int row_begin, int rows,
-                                            int n0) {
+                                            int n0, const uint16_t *row_of) {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     constexpr int NB = MODE == 0 ? 2 * NF : NF;  // weight fragments: gate and up rows of the same columns, or down rows
     constexpr int D = skinny_depth(WPS, MF, NB);
@@ -70,7 +71,10 @@ __device__ __forceinline__ void skinny_tile(const FfnProblem &P, unsigned char *
         const int r = i * 16 + fr;
         ra[i] = r < rows ? r : rows - 1;
     }
-    if (P.gather) {
+    if (row_of) {  // (LDS: the source row of every sorted row)
+#pragma unroll
+        for (int i = 0; i < MF; ++i) ra[i] = row_of[row_begin + ra[i]];
+    } else if (P.gather) {
 #pragma unroll
         for (int i = 0; i < MF; ++i) ra[i] = P.gather[row_begin + ra[i]];
 #pragma unroll
@@ -205,24 +209,25 @@ constexpr int SKINNY_BM = 64;
 
 template <int MODE, int WPS, int NF>
 __device__ __forceinline__ void skinny_rows(const FfnProblem &P, unsigned char *smem, int expert, int row_begin, int rows,
-                                            int n0) {
+                                            int n0, const uint16_t *row_of) {
     if (rows <= 16)
-        skinny_tile<MODE, WPS, 1, NF>(P, smem, expert, row_begin, rows, n0);
+        skinny_tile<MODE, WPS, 1, NF>(P, smem, expert, row_begin, rows, n0, row_of);
     else if (MODE == 0 || rows <= 32)  // (the gate/up pass takes no more than 32 rows)
-        skinny_tile<MODE, WPS, 2, NF>(P, smem, expert, row_begin, rows, n0);
+        skinny_tile<MODE, WPS, 2, NF>(P, smem, expert, row_begin, rows, n0, row_of);
     else
-        skinny_tile<MODE, WPS, 4, NF>(P, smem, expert, row_begin, rows, n0);
+        skinny_tile<MODE, WPS, 4, NF>(P, smem, expert, row_begin, rows, n0, row_of);
 }
 
 constexpr int skinny_lds_bytes(int mode, int nf) { return (mode == 0 ? 2 * 2 * nf : 4 * nf) * 1024; }  // the sums of the largest tile
 
-template <int MODE, int WPS, int NFR, int NFS>
-__global__ __launch_bounds__(256, WPS) void ffn_skinny_kernel(const FfnLaunch L) {
-    constexpr int BM = SKINNY_BM, BYTES_R = skinny_lds_bytes(MODE, NFR), BYTES_S = skinny_lds_bytes(MODE, NFS);
-    __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES_R > BYTES_S ? BYTES_R : BYTES_S];
+// FEW: the routed groups are not there yet; their workgroups find them out, each for itself, and one more writes them to memory.
+template <int MODE, int WPS, int NFR, int NFS, bool FEW>
+__device__ __forceinline__ void skinny_item(const FfnLaunch &L, const FewRoute *R, unsigned char *smem) {
+    constexpr int BM = SKINNY_BM;
     const int xcd = blockIdx.x & 7;
     int slot = blockIdx.x >> 3;
-    if (L.has_single) {
+    const bool writer = FEW && blockIdx.x == gridDim.x - 1;
+    if (L.has_single && !writer) {
         const FfnProblem &P = L.p[1];
         int lo = P.offsets ? P.offsets[0] : P.row_lo, hi = P.offsets ? P.offsets[1] : P.row_hi;
         lo = lo < 0 ? 0 : (lo > P.A_cap ? P.A_cap : lo);
@@ -232,14 +237,27 @@ __global__ __launch_bounds__(256, WPS) void ffn_skinny_kernel(const FfnLaunch L)
         if (slot < r.cnt) {
             const int item = r.first + slot, row_begin = lo + item % chunks * BM;
             const int rows = hi - row_begin < BM ? hi - row_begin : BM;
-            skinny_rows<MODE, WPS, NFS>(P, smem, 0, row_begin, rows, item / chunks * (16 * NFS));
+            skinny_rows<MODE, WPS, NFS>(P, smem, 0, row_begin, rows, item / chunks * (16 * NFS), nullptr);
             return;
         }
         slot -= r.cnt;
     }
     if (!L.has_ragged) return;
     const FfnProblem &P = L.p[0];
-    const GroupMap gm = build_group_map<BM>(P.offsets, P.E_local, P.A_cap);
+    GroupMap gm;
+    const uint16_t *row_of = nullptr;
+    if constexpr (FEW) {
+        __shared__ FewScratch<256, FEW_ASSIGNMENTS> S;
+        __shared__ uint16_t rows[FEW_ASSIGNMENTS];
+        int lo, hi;
+        route_few<256>(*R, S, writer, lo, hi, rows);
+        if (writer) return;
+        __syncthreads();
+        gm = group_map_of<BM>(lo, hi);
+        row_of = rows;
+    } else {
+        gm = build_group_map<BM>(P.offsets, P.E_local, P.A_cap);
+    }
     const XcdRange r = equal_range(__builtin_amdgcn_readfirstlane(gm.total_mtiles) * P.ntn, xcd);
     if (slot >= r.cnt) return;
     const int item = r.first + slot;
@@ -251,11 +269,28 @@ __global__ __launch_bounds__(256, WPS) void ffn_skinny_kernel(const FfnLaunch L)
     const int local = item - __builtin_amdgcn_readlane(gm.first, expert) * P.ntn;
     const int row_begin = __builtin_amdgcn_readlane(gm.lo, expert) + local % chunks * BM;
     const int left = __builtin_amdgcn_readlane(gm.hi, expert) - row_begin;
-    skinny_rows<MODE, WPS, NFR>(P, smem, expert, row_begin, left < BM ? left : BM, local / chunks * (16 * NFR));
+    skinny_rows<MODE, WPS, NFR>(P, smem, expert, row_begin, left < BM ? left : BM, local / chunks * (16 * NFR), row_of);
+}
+
+constexpr int skinny_smem_bytes(int mode, int nfr, int nfs) {
+    return skinny_lds_bytes(mode, nfr) > skinny_lds_bytes(mode, nfs) ? skinny_lds_bytes(mode, nfr) : skinny_lds_bytes(mode, nfs);
 }
 
 template <int MODE, int WPS, int NFR, int NFS>
-static void skinny_launch(FfnLaunch L, hipStream_t st) {
+__global__ __launch_bounds__(256, WPS) void ffn_skinny_kernel(const FfnLaunch L) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[skinny_smem_bytes(MODE, NFR, NFS)];
+    skinny_item<MODE, WPS, NFR, NFS, false>(L, nullptr, smem);
+}
+
+template <int WPS, int NFR, int NFS>
+__global__ __launch_bounds__(256, WPS) void ffn_skinny_few_kernel(const FfnLaunch L, const FewRoute R) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[skinny_smem_bytes(0, NFR, NFS)];
+    skinny_item<0, WPS, NFR, NFS, true>(L, &R, smem);
+}
+
+// Sets the column blocks of the launch's problems; its workgroups per XCD.
+template <int NFR, int NFS>
+static int64_t skinny_blocks(FfnLaunch &L) {
     int64_t per_xcd = 0;
     for (int q = 0; q < 2; ++q) {
         FfnProblem &P = L.p[q];
@@ -265,6 +300,18 @@ static void skinny_launch(FfnLaunch L, hipStream_t st) {
         // chunks: one per 64 rows, and one more for every group that can hold a row
         const int64_t groups = P.E_local < P.A_cap ? P.E_local : P.A_cap;
         per_xcd += ((P.A_cap / SKINNY_BM + groups) * P.ntn + 7) / 8;
+    }
+    return per_xcd;
+}
+
+template <int MODE, int WPS, int NFR, int NFS>
+static void skinny_launch(FfnLaunch L, const FewRoute *few, hipStream_t st) {
+    const int64_t per_xcd = skinny_blocks<NFR, NFS>(L);
+    if constexpr (MODE == 0) {
+        if (few) {
+            ffn_skinny_few_kernel<WPS, NFR, NFS><<<dim3((unsigned)(per_xcd * 8 + 1)), dim3(256), 0, st>>>(L, *few);
+            return;
+        }
     }
     ffn_skinny_kernel<MODE, WPS, NFR, NFS><<<dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st>>>(L);
 }
@@ -293,7 +340,15 @@ bool ffn_skinny_takes(int pass, const FfnLaunch &L) {
            (R.A_cap <= 16 * R.E_local || mid_tiles <= 128);
 }
 
-int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st) {
+// Whether the gate/up pass of a few tokens does their selection and index at its start, instead of route_finish_small_kernel before it.  Up
+// to three rounds of workgroups (three share a CU): every round pays for it again.  Microseconds of a layer call, apart / so: 60
+// experts + shared, 1 token (704 workgroups) 50.8 / 46.5, 3 tokens (1408) 68.0 / 63.5, 5 tokens (2112) 73.1 / 71.4, 8 tokens (3168) 78.3 /
+// 83.2; 16 experts of d 4096, 1 token 36.3 / 34.0, 8 tokens (688) 69.0 / 65.7; 15 of 60 experts, 7 tokens 32.0 / 31.0.
+bool ffn_skinny_takes_few(FfnLaunch L) {
+    return L.has_ragged && L.p[0].gather_rows <= FEW_TOKENS && ffn_skinny_takes(0, L) && skinny_blocks<1, 1>(L) * 8 <= 9 * 8 * CUS_PER_XCD;
+}
+
+int launch_ffn_skinny(int pass, const FfnLaunch &L, const FewRoute *few, hipStream_t st) {
     drop_stale_error();
     const FfnProblem &R = L.p[0], &S = L.p[1];
     // Column blocks.  (Figures of a form with a partial sum per wave.)  Wider ones read the activations less often, narrower ones are more numerous: 16 in the gate/up pass (a
@@ -305,11 +360,11 @@ int launch_ffn_skinny(int pass, const FfnLaunch &L, hipStream_t st) {
     // 24 tokens 43.8 / 33.8; 16 experts, 4 tokens 19.0 / 20.5) and in the gate/up pass, which has fewer workgroups (60 experts +
     // shared, 3 tokens 33.5 / 36.1, 8 tokens 43.8 / 44.5; 16 experts, 1 token 22.2 / 18.9, 8 tokens 41.1 / 38.0).
     if (pass == 0)
-        skinny_launch<0, 3, 1, 1>(L, st);
+        skinny_launch<0, 3, 1, 1>(L, few, st);
     else if ((L.has_single && S.A_cap > 16) || (L.has_ragged && R.A_cap > 16 * R.E_local))
-        skinny_launch<1, 3, 2, 1>(L, st);
+        skinny_launch<1, 3, 2, 1>(L, nullptr, st);
     else
-        skinny_launch<1, 4, 2, 1>(L, st);
+        skinny_launch<1, 4, 2, 1>(L, nullptr, st);
     return launch_status();
 }
 

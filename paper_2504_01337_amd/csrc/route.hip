@@ -15,7 +15,7 @@
 //    Others for its work: route_select_small_kernel (sixteen lanes per token, up to 8192 tokens), route_finish_small_kernel
 //    (up to 64 tokens, with the dispatch index), route_select_keys_kernel (top-K of K <= 4 from one chunk result, more than 8192
 //    tokens) and route_select_rows_kernel (stored logits, K <= 4).
-#include "c2r_internal.h"
+#include "route_few.h"
 #include "ffn_copy.h"
 
 #include <type_traits>
@@ -603,40 +603,6 @@ __device__ __forceinline__ void pick(const float (&l)[EP], uint64_t m, int &bi, 
         bv = take ? l[e] : bv;
         bi = take ? e : bi;
     }
-}
-
-// One merge step of a selection spread over neighbouring lanes: the partner's candidate (fetched by a data-parallel-primitive
-// move, a tenth of an LDS shuffle's latency: one token's selection and index 8.6 -> 7.8 us) against this lane's, the part
-// with the lower expert indices first; a later one only if it is strictly larger.  upper: this lane's part is the later one.
-template <int DPP>
-__device__ __forceinline__ void merge_lower(int upper, int &bi, float &bv) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    const int obi = __builtin_amdgcn_mov_dpp(bi, DPP, 0xf, 0xf, true);
-    const float obv = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(bv), DPP, 0xf, 0xf, true));
-    const int abi = upper ? obi : bi, bbi = upper ? bi : obi;
-    const float abv = upper ? obv : bv, bbv = upper ? bv : obv;
-    const bool later = abi < 0 || (bbi >= 0 && bbv > abv);
-    bi = later ? bbi : abi;
-    bv = later ? bbv : abv;
-#endif
-}
-
-// The bitwise or of the values of a quad of lanes (N 4) or of a row of sixteen, in each of them.
-template <int N>
-__device__ __forceinline__ uint64_t or_of_lanes(uint64_t m) {
-    int half[2] = {(int)(uint32_t)m, (int)(uint32_t)(m >> 32)};
-#if defined(__HIP_DEVICE_COMPILE__)
-#pragma unroll
-    for (int &h : half) {
-        h |= __builtin_amdgcn_mov_dpp(h, 0xB1, 0xf, 0xf, true);  // quad_perm 1,0,3,2
-        h |= __builtin_amdgcn_mov_dpp(h, 0x4E, 0xf, 0xf, true);  // quad_perm 2,3,0,1
-        if (N == 16) {
-            h |= __builtin_amdgcn_mov_dpp(h, 0x141, 0xf, 0xf, true);  // row_half_mirror
-            h |= __builtin_amdgcn_mov_dpp(h, 0x140, 0xf, 0xf, true);  // row_mirror
-        }
-    }
-#endif
-    return (uint64_t)(uint32_t)half[0] | ((uint64_t)(uint32_t)half[1] << 32);
 }
 
 // ROWMAJOR (stored logits [T, E]): one wave per 64 tokens.  Otherwise (chunk partials):
@@ -1442,32 +1408,6 @@ __global__ __launch_bounds__(256) void route_select_rows_kernel(const float *__r
     }
 }
 
-// The best allowed expert of one token (see route_select_kernel for the rule), by the token's sixteen lanes: lane sub holds
-// the logits l of experts 4 sub .. 4 sub + 3, row is the token's logits in LDS, m the allowed experts.
-__device__ __forceinline__ void pick_by_sixteen(const float (&l)[4], const float *row, uint64_t m, int sub, int &bi, float &bv) {
-    const uint32_t mloc = (uint32_t)(m >> (sub * 4));
-    bi = -1;
-    bv = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const bool take = ((mloc >> j) & 1u) != 0 && (l[j] > bv || (bi < 0 && l[j] == l[j]));
-        bv = take ? l[j] : bv;
-        bi = take ? sub * 4 + j : bi;
-    }
-    merge_lower<0xB1>(sub & 1, bi, bv);   // quad_perm 1,0,3,2
-    merge_lower<0x4E>(sub & 2, bi, bv);   // quad_perm 2,3,0,1
-    merge_lower<0x141>(sub & 4, bi, bv);  // row_half_mirror: the other quad, whose lanes agree by now
-    merge_lower<0x140>(sub & 8, bi, bv);  // row_mirror: the other eight lanes
-    if (m != 0) {  // a NaN stands only as the first allowed expert
-        const int f = __ffsll((unsigned long long)m) - 1;
-        const float lf = row[f];
-        if (lf != lf) {
-            bi = f;
-            bv = lf;
-        }
-    }
-}
-
 // route_select_kernel for batches that its 64-token workgroups would leave most of the chip idle with: sixteen tokens per
 // workgroup.  What bounds such a selection is the trip of a workgroup's chunk results - 128 KB for 64 tokens of 60 experts and 8 chunks, at
 // the rate one CU pulls from memory - and the length of its scans: a quarter of the one, sixteen lanes per token on the other.
@@ -1569,167 +1509,15 @@ __global__ __launch_bounds__(256) void route_select_small_kernel(
 
 // Selection AND dispatch index of a batch of at most 64 tokens and 1024 assignments, one workgroup: what
 // route_select_kernel and permute_by_slot_kernel (permute.hip) do, in one launch instead of two.
-// A launch costs such a batch as much as its work: 60 experts, 1 token, 9.3 + 6.4 us in two launches, 7.8 in one.  Sixteen waves, so that the chunk
+// (The smallest batches' gate/up pass does the same at its start, ffn_skinny_few_kernel.)  A launch costs such a batch as much as its
+// work: 60 experts, 1 token, 9.3 + 6.4 us in two launches, 6.3 in one.  Sixteen waves, so that the chunk
 // results of a whole batch are one load each in flight per thread, and a token has sixteen lanes to scan its experts.
 constexpr int FIN_WAVES = 16, FIN_TOKENS = 64, FIN_ASSIGNMENTS = 1024;
 
-__global__ __launch_bounds__(FIN_WAVES * 64) void route_finish_small_kernel(
-    const float *__restrict__ part, int ep, int nchunk, const float *__restrict__ bias, int T, int E, int K,
-    const int32_t *__restrict__ collab_idx, int Tc, const int32_t *__restrict__ local_slot, int E_local,
-    int32_t *__restrict__ topk_idx, float *__restrict__ gates, int32_t *__restrict__ counts,
-    int32_t *__restrict__ offsets, int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm) {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    constexpr int LP = C2R_MAX_E + 1;
-    __shared__ float tile[FIN_TOKENS * LP];
-    __shared__ uint64_t mask_tab[C2R_MAX_E];
-    __shared__ int32_t slot_tab[C2R_MAX_E], n_of[C2R_MAX_E];
-    __shared__ int32_t slots[FIN_ASSIGNMENTS];
-    __shared__ float gbuf[FIN_ASSIGNMENTS], den_of[FIN_TOKENS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint64_t all = E >= 64 ? ~0ull : ((1ull << E) - 1ull);
-
-    // (sixteen threads per expert walk its list; their first entries are requested ahead of the partial sums: one trip to memory instead
-    // of two)
-    const int le = tid >> 4, lq = tid & 15, llast = E * Tc - 1;
-    int32_t listed[2];
-    if (collab_idx) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) listed[u] = collab_idx[min(le * Tc + lq + 16 * u, llast)];
-    }
-    // ---- logits: a thread adds up the chunk results (left to right) of one expert and four tokens ----
-    {
-        const int e = tid >> 4, quad = tid & 15;
-        if (e < ep && quad * 4 < T) {
-            const float *p = part + (size_t)e * 64 + quad * 4;
-            f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int c0 = 0; c0 < nchunk; c0 += 8) {
-                f32x4 v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    v[u] = *reinterpret_cast<const f32x4 *>(p + (size_t)min(c0 + u, nchunk - 1) * ep * 64);
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (c0 + u < nchunk) sum = c0 + u == 0 ? v[u] : sum + v[u];
-            }
-            if (bias && e < E) sum = sum + bias[e];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) tile[(quad * 4 + i) * LP + e] = sum[i];
-        }
-    }
-    // ---- collaborator masks and the slot of every expert ----
-    {
-        uint64_t m = collab_idx ? 0ull : all;
-        if (collab_idx) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (lq + 16 * u < Tc && listed[u] >= 0 && listed[u] < E) m |= 1ull << listed[u];
-            for (int i = lq + 32; i < Tc; i += 16) {
-                const int v = le < E ? collab_idx[le * Tc + i] : -1;
-                if (v >= 0 && v < E) m |= 1ull << v;
-            }
-            m = or_of_lanes<16>(m);
-        }
-        if (lq == 0) mask_tab[le] = m & ~(1ull << le);
-    }
-    if (tid < C2R_MAX_E) {
-        const int s = tid < E ? (local_slot ? local_slot[tid] : tid) : -1;
-        slot_tab[tid] = s >= 0 && s < E_local ? s : -1;
-    }
-    __syncthreads();
-
-    // ---- selection: sixteen lanes per token, four experts each; see route_select_kernel for the rule ----
-    const int t = tid >> 4, sub = tid & 15;
-    if (t < T) {  // (the sixteen lanes of a token stay together)
-        float l[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) l[j] = sub * 4 + j < E ? tile[t * LP + sub * 4 + j] : 0.0f;
-        int e;
-        float v, v0 = 0.0f, den = 0.0f;
-        uint64_t m = all;
-        for (int s = 0; s < K; ++s) {
-            pick_by_sixteen(l, &tile[t * LP], m, sub, e, v);
-            float g = 0.0f;
-            if (s == 0) {
-                v0 = v;
-                m = mask_tab[e];
-                g = expf(v0 - v0);  // 1, or NaN when the largest logit is infinite or a NaN
-            } else if (e >= 0) {
-                m &= ~(1ull << e);
-                g = expf(v - v0);
-            }
-            den = s == 0 ? g : den + g;
-            if (sub == 0) {
-                topk_idx[t * K + s] = e;
-                slots[t * K + s] = e >= 0 ? slot_tab[e] : -1;
-                gbuf[t * K + s] = g;
-            }
-        }
-        if (sub == 0) den_of[t] = den;
-    }
-    __syncthreads();
-
-    // ---- dispatch index: a wave counts the assignments of slots wave, wave + 16, ..., then hands out their positions in
-    //      order (the stable order of a = t * K + s) ----
-    const int A = T * K;
-    if (tid < A) gates[tid] = gbuf[tid] / den_of[tid / K];
-    if (A <= 32) {
-        // one wave, lane = assignment and lane = slot at once: every assignment's slot passes all lanes by (1 token of 60 experts: the
-        // kernel 8.4 -> 6.8 us with the masks; at 64 assignments the loops below are the faster ones)
-        if (wave != 0) return;
-        const int slot = lane < A ? slots[lane] : -1, mine = slot >= 0 ? slot : 64 + lane;  // (past every slot, no two alike)
-        int pos = 0, n = 0, before = 0;
-        for (int b0 = 0; b0 < A; b0 += 8) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int s = __builtin_amdgcn_readlane(mine, b0 + u);
-                pos += s < mine || (s == mine && b0 + u < lane);
-                n += s == lane;
-                before += s < lane;
-            }
-        }
-        const int valid = __popcll(__ballot(slot >= 0));
-        if (lane < A) inv_perm[lane] = slot >= 0 ? pos : -1;
-        if (slot >= 0) perm[pos] = lane;
-        if (lane < E_local) {
-            counts[lane] = n;
-            offsets[lane] = before;
-            if (lane == E_local - 1) offsets[E_local] = valid;
-        }
-        return;
-    }
-    for (int s = wave; s < E_local; s += FIN_WAVES) {
-        int n = 0;
-        for (int a0 = 0; a0 < A; a0 += 64) n += __popcll(__ballot(a0 + lane < A && slots[a0 + lane] == s));
-        if (lane == 0) n_of[s] = n;
-    }
-    __syncthreads();
-    const int n = lane < E_local ? n_of[lane] : 0;
-    int incl = n;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(incl, off);
-        if (lane >= off) incl += v;
-    }
-    if (wave == 0 && lane < E_local) {
-        counts[lane] = n;
-        offsets[lane] = incl - n;
-        if (lane == E_local - 1) offsets[E_local] = incl;
-    }
-    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    for (int s = wave; s < E_local; s += FIN_WAVES) {
-        int run = __shfl(incl - n, s);
-        for (int a0 = 0; a0 < A; a0 += 64) {
-            const bool mine = a0 + lane < A && slots[a0 + lane] == s;
-            const uint64_t b = __ballot(mine);
-            if (mine) {
-                const int p = run + __popcll(b & lt);
-                perm[p] = a0 + lane;
-                inv_perm[a0 + lane] = p;
-            }
-            run += __popcll(b);
-        }
-    }
-    if (tid < A && slots[tid] < 0) inv_perm[tid] = -1;
+__global__ __launch_bounds__(FIN_WAVES * 64) void route_finish_small_kernel(const FewRoute R) {
+    __shared__ FewScratch<FIN_WAVES * 64, FIN_ASSIGNMENTS> S;
+    int lo, hi;
+    route_few<FIN_WAVES * 64>(R, S, true, lo, hi, nullptr);
 }
 
 static int check_route_args(int64_t T, int E, int K, const int32_t *collab_idx, int Tc) {
@@ -1830,6 +1618,7 @@ struct DispatchOut {
     const int32_t *local_slot;
     int E_local;
     int32_t *counts, *offsets, *perm, *inv_perm;
+    FewRoute *later;  // not null: the caller's next launch does the work of route_finish_small_kernel, from these arguments
 };
 
 static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const float *bias, int64_t T, int d, int E, int K,
@@ -1864,9 +1653,12 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
         if (x_dt == C2R_BF16) { C2R_SMALL_LAUNCH(true) } else { C2R_SMALL_LAUNCH(false) }
 #undef C2R_SMALL_LAUNCH
         if (dispatch) {
-            route_finish_small_kernel<<<dim3(1), dim3(FIN_WAVES * 64), 0, st>>>(
-                part, L.EP, L.nchunk, bias, (int)T, E, K, collab_idx, Tc, dispatch->local_slot, dispatch->E_local, topk_idx,
-                gates, dispatch->counts, dispatch->offsets, dispatch->perm, dispatch->inv_perm);
+            const FewRoute R = {part, L.EP, L.nchunk, bias, (int)T, E, K, collab_idx, Tc, dispatch->local_slot, dispatch->E_local,
+                                topk_idx, gates, dispatch->counts, dispatch->offsets, dispatch->perm, dispatch->inv_perm};
+            if (dispatch->later)
+                *dispatch->later = R;
+            else
+                route_finish_small_kernel<<<dim3(1), dim3(FIN_WAVES * 64), 0, st>>>(R);
             return launch_status();
         }
         return launch_select(part, L.EP, L.nchunk, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out, st);
@@ -1953,19 +1745,25 @@ extern "C" int c2r_route(const void *x, c2r_dtype x_dt, const float *Wg, const f
                       stream);
 }
 
+// Whether a batch's selection and index are route_few's, and whether the gate/up pass may do them (see ffn_few_takes).
+static bool route_few_takes(int64_t T, int d, int E, int K) {
+    return T >= 1 && T <= FIN_TOKENS && K >= 1 && T * K <= FIN_ASSIGNMENTS && E >= 1 && d >= 1 &&
+           route_small(T, (d + C2R_CANON_CHUNK - 1) / C2R_CANON_CHUNK, ep_of(E));
+}
+bool c2r::route_may_finish_later(int64_t T, int d, int E, int K) { return route_few_takes(T, d, E, K) && T <= FEW_TOKENS && T * K <= FEW_ASSIGNMENTS; }
+
 // c2r_route followed by c2r_permute, for the layer call.
 int c2r::route_and_permute(const void *x, c2r_dtype dt, const float *Wg, const float *bias, int64_t T, int d, int E, int K,
                            const int32_t *collab_idx, int Tc, int32_t *topk_idx, float *gates, void *ws_route,
                            size_t ws_route_bytes, const int32_t *local_slot, int E_local, int32_t *counts, int32_t *offsets,
                            int32_t *perm, int32_t *inv_perm, void *x_perm, void *ws_permute, size_t ws_permute_bytes,
-                           void *stream) {
+                           FewRoute *later, void *stream) {
     int rc;
-    if (T >= 1 && T <= FIN_TOKENS && K >= 1 && T * K <= FIN_ASSIGNMENTS && E >= 1 && d >= 1 &&
-        route_small(T, (d + C2R_CANON_CHUNK - 1) / C2R_CANON_CHUNK, ep_of(E))) {
+    if (route_few_takes(T, d, E, K)) {
         rc = permute_check(x, dt, topk_idx, T, d, E, K, local_slot, E_local, counts, offsets, perm, inv_perm, x_perm,
                            ws_permute, ws_permute_bytes);
         if (rc != C2R_OK) return rc;
-        const DispatchOut out = {local_slot, E_local, counts, offsets, perm, inv_perm};
+        const DispatchOut out = {local_slot, E_local, counts, offsets, perm, inv_perm, later};
         rc = route_impl(x, dt, Wg, bias, T, d, E, K, collab_idx, Tc, topk_idx, gates, nullptr, ws_route, ws_route_bytes, &out,
                         stream);
         if (rc != C2R_OK || !x_perm) return rc;

@@ -43,7 +43,12 @@ def test_small_route_logits_bit_exact(c2r, orc, T, E, d, dtype):
 # one workgroup's selection and index: 1 to 64 tokens, up to 1024 assignments (64 x 16), and the first calls past either limit;
 # lists that cannot fill the slots, NaN and infinite logits, experts that are not local
 @pytest.mark.parametrize("T,E,K,El,dtype", [(1, 60, 4, 60, "bf16"), (64, 60, 4, 15, "bf16"), (65, 60, 4, 15, "bf16"), (64, 64, 16, 64, "bf16"),
-                                            (61, 64, 17, 30, "bf16"), (5, 3, 3, 3, "f32"), (63, 17, 1, 9, "f32"), (37, 8, 2, 8, "f32")])
+                                            (61, 64, 17, 30, "bf16"), (5, 3, 3, 3, "f32"), (63, 17, 1, 9, "f32"), (37, 8, 2, 8, "f32"),
+                                            # at the start of the gate/up pass: up to 16 tokens, 32 assignments, two per expert; the first calls past
+                                            # each; the index of 128 assignments and of one more
+                                            (16, 16, 2, 16, "bf16"), (16, 17, 1, 8, "bf16"), (17, 64, 1, 64, "bf16"), (1, 64, 32, 64, "bf16"),
+                                            (1, 64, 33, 64, "bf16"), (3, 40, 9, 20, "bf16"), (7, 60, 4, 60, "bf16"), (2, 60, 4, 4, "bf16"),
+                                            (4, 5, 3, 2, "bf16"), (32, 60, 4, 60, "bf16"), (43, 60, 3, 31, "bf16")])
 def test_layer_call_of_a_small_batch_routes_like_the_stages(c2r, T, E, K, El, dtype):
     rng = np.random.default_rng(T * E + K)
     d, F = 64, 64
