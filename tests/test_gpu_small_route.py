@@ -50,8 +50,22 @@ def test_small_route_logits_bit_exact(c2r, orc, T, E, d, dtype):
                                             (1, 64, 33, 64, "bf16"), (3, 40, 9, 20, "bf16"), (7, 60, 4, 60, "bf16"), (2, 60, 4, 4, "bf16"),
                                             (4, 5, 3, 2, "bf16"), (32, 60, 4, 60, "bf16"), (43, 60, 3, 31, "bf16")])
 def test_layer_call_of_a_small_batch_routes_like_the_stages(c2r, T, E, K, El, dtype):
+    _layer_call_routes_like_the_stages(c2r, T, E, K, El, dtype, 64)
+
+
+# selection, index and rows in one launch: up to 1024 tokens, 16 experts, 4 slots and 128 KB of chunk results (16 experts, d 4096: 128 tokens), and the
+# first calls past each; one and several chunks, rows of one and several vectors per lane
+@pytest.mark.parametrize("T,E,K,El,dtype,d", [
+    (65, 16, 4, 16, "bf16", 64), (128, 16, 4, 7, "bf16", 4096), (129, 16, 4, 7, "bf16", 4096), (1024, 8, 2, 8, "f32", 256), (1025, 8, 2, 8, "f32", 256),
+    (512, 16, 3, 5, "f32", 520), (513, 5, 5, 5, "f32", 64), (70, 17, 4, 17, "f32", 64), (3, 8, 2, 8, "f32", 2056), (1, 2, 1, 2, "f32", 8), (67, 1, 1, 1, "f32", 24),
+    (999, 13, 4, 2, "bf16", 264)])
+def test_selection_index_and_rows_in_one_launch(c2r, T, E, K, El, dtype, d):
+    _layer_call_routes_like_the_stages(c2r, T, E, K, El, dtype, d)
+
+
+def _layer_call_routes_like_the_stages(c2r, T, E, K, El, dtype, d):
     rng = np.random.default_rng(T * E + K)
-    d, F = 64, 64
+    F = 64
     w = lambda *s: dev((rng.standard_normal(s) * 0.1).astype(np.float32), dtype)
     ls = None
     if El < E:
@@ -67,12 +81,14 @@ def test_layer_call_of_a_small_batch_routes_like_the_stages(c2r, T, E, K, El, dt
     x = w(T, d)
     layer.forward(x)
     idx, gates, _ = c2r.route(x, layer.Wg, layer.bias, K, layer.collab_idx)
-    counts, offsets, perm, inv, _ = c2r.permute(x, idx, E, layer.local_slot, El)
+    counts, offsets, perm, inv, rows = c2r.permute(x, idx, E, layer.local_slot, El)
     torch.cuda.synchronize()
     assert torch.equal(layer.idx, idx) and torch.equal(layer.gates.view(torch.int32), gates.view(torch.int32))
     assert torch.equal(layer.counts, counts) and torch.equal(layer.offsets, offsets) and torch.equal(layer.inv_perm, inv)
     n = int(offsets[-1])
     assert torch.equal(layer.perm[:n], perm[:n]) and bool((layer.perm[n:] == -1).all())
+    if layer.x_perm is not None:
+        assert torch.equal(layer.x_perm[:n], rows[:n])
 
 
 # K = 1 takes lists of no entries (Tc >= K - 1); the array then holds nothing that may be read, also where it is not NULL.  (The pointer
