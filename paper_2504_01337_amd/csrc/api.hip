@@ -332,6 +332,8 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
         ffn_rc = gather_problems(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.w_down, L.y_perm, L.ws_ffn,
                                  (size_t)L.ws_ffn_bytes, routed);
     }
+    if (gathers && ffn_rc == C2R_OK && A > 0 && El <= E)  // (a device that holds a part of the experts)
+        routed[0].rows_hint = routed[1].rows_hint = (int)(A * El / E);
     const FfnProblem *const beside[2] = {rides ? &with[0] : nullptr, rides ? &with[1] : nullptr};
     FewRoute few;
     const bool later = gathers && ffn_rc == C2R_OK && A > 0 && route_may_finish_later(T, d, E, K) && ffn_few_takes(routed[0], beside[0]);

@@ -67,13 +67,11 @@ __device__ __forceinline__ void store16_through(void *p, uint4 v) {
 }
 
 // Length of XCD x's list (tiles, with the last round cut into parts): what its queue hands out.
-template <bool SPLIT>
+template <bool BESIDE>
 __device__ __forceinline__ int xcd_list_slots(int n_tiles) {
     if (n_tiles <= 0) return 0;
-    if (!SPLIT) return n_tiles;
-    const int full = n_tiles / CUS_PER_XCD * CUS_PER_XCD, r = n_tiles - full;
-    const int s = r == 0 ? 1 : (r * 4 <= CUS_PER_XCD ? 4 : (r * 2 <= CUS_PER_XCD ? 2 : 1));
-    return full + r * s;
+    const int full = n_tiles / CUS_PER_XCD * CUS_PER_XCD;
+    return full + (n_tiles - full) * last_round_parts<BESIDE>(n_tiles);
 }
 
 // One output tile: position `slot` of XCD `xcd`'s list.  Every wave of the workgroup calls it
@@ -152,9 +150,8 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
         ra = equal_range(rmap.totalA * L.p[0].ntn, xcd);
         rb = equal_range(rmap.totalB * L.p[0].ntn, xcd);
     }
-    // (beside the other pass there is no last round to cut: a CU that finds no gate/up tile takes a down tile)
-    constexpr bool SPLIT = !(BOTH && MODE == 0);
-    TailSplit ts = split_last_round<SPLIT>(rs.cnt + ra.cnt + rb.cnt, slot);
+    constexpr bool BESIDE = BOTH && MODE == 0;
+    TailSplit ts = split_last_round<BESIDE>(rs.cnt + ra.cnt + rb.cnt, slot);
     if (!ts.valid) return;
     // (the same in every lane, but derived from cross-lane moves: say so, so that everything
     // picked by them - the problem's arguments above all - stays in scalar registers)
@@ -172,7 +169,7 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
     // of full tiles first take them while the others finish their last full tile, which fills
     // part of the idle tail of the launch with work that would otherwise sit in the middle of
     // it (few enough of them that they do not have to share HBM: FILL_TAIL per XCD).
-    constexpr int FILL_TAIL = SPLIT ? 12 : 0;
+    constexpr int FILL_TAIL = BESIDE ? 0 : 12;
     const int n_b = __builtin_amdgcn_readfirstlane(rb.cnt);
     const int n_tail = n_b < FILL_TAIL ? n_b : FILL_TAIL, n_bi = n_b - n_tail, n_main = n_s + n_a + n_bi;
     const bool in_tail = ts.idx >= n_main;
@@ -721,8 +718,8 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
 // the rows of h that are, summed over its N-tiles.
 constexpr int FFN_MTILES = 1024;
 constexpr int FFN_LEFT = 8, FFN_FINISHED = 9, FFN_DOWN = 16, FFN_ROWS_DONE = 32;
-constexpr int FFN_QUEUE_SETS = 64, FFN_QUEUE_INTS = FFN_ROWS_DONE + FFN_MTILES;
-__device__ int ffn_queues[FFN_QUEUE_SETS * FFN_QUEUE_INTS];
+constexpr int FFN_QUEUE_SETS = 64, FFN_QUEUE_INTS = 16, FFN_BOTH_INTS = FFN_ROWS_DONE + FFN_MTILES;
+__device__ int ffn_queues[FFN_QUEUE_SETS * (FFN_QUEUE_INTS + FFN_BOTH_INTS)];  // those of one pass, then those of both
 
 // What stays the same for a workgroup while it walks the lists of one pass, or of both.
 struct FfnWalk {
@@ -755,7 +752,6 @@ __device__ __forceinline__ void ffn_walk_init(FfnWalk &w, const FfnLaunch &L) {
 template <int MODE, int WM, int WN, bool BOTH, int KERNARG>
 __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, const int up_ntn_ragged, const int up_ntn_single) {
     typedef FfnShape<WM, WN> S;
-    constexpr bool SPLIT = !(BOTH && MODE == 0);
     int *const queues = W.queues + (BOTH && MODE == 1 ? FFN_DOWN : 0);
     // The claimed position (XCD of the list, slot; -1: nothing left) is handed to the waves in
     // the last bytes of the stage memory, which is all of the CU's LDS: every layout of a tile
@@ -776,7 +772,7 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
             totB = m.totalB * L.p[0].ntn;
         }
         const int x = lane & 7;
-        my_len = xcd_list_slots<SPLIT>(equal_range(n_s, x).cnt + equal_range(totA, x).cnt + equal_range(totB, x).cnt);
+        my_len = xcd_list_slots<BOTH && MODE == 0>(equal_range(n_s, x).cnt + equal_range(totA, x).cnt + equal_range(totB, x).cnt);
         if (BOTH && MODE == 0)
             for (int i = 0; i < 8; ++i) W.up_slots += __builtin_amdgcn_readlane(my_len, i);
     }
@@ -984,7 +980,7 @@ FfnProblem ffn_bf16_dma_problem(int pass, const uint16_t *a, int lda, const int3
     P.gather_div = pass == 0 ? gather_div : 1;
     P.gather_rows = pass == 0 ? gather_rows : 1;
     P.row_lo = 0;
-    P.row_hi = (int)A_cap;
+    P.row_hi = P.rows_hint = (int)A_cap;
     return P;
 }
 
@@ -1037,9 +1033,9 @@ static int64_t ffn_grid_of(const FfnLaunch &L) {
     return tiles < 8 * CUS_PER_XCD ? tiles : 8 * CUS_PER_XCD;
 }
 
-// A set of queues for one launch; nullptr: none to be had.
-static int *ffn_next_queues() {
-    static std::atomic<unsigned> next_set{0};
+// A set of queues for one launch, of one pass or of both; nullptr: none to be had.
+static int *ffn_next_queues(bool both) {
+    static std::atomic<unsigned> next_set[2];
     static std::atomic<int *> queue_base[64];  // per device: the address of that device's copy of ffn_queues
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
@@ -1050,7 +1046,8 @@ static int *ffn_next_queues() {
         base = static_cast<int *>(p);
         queue_base[dev].store(base);
     }
-    return base + (next_set.fetch_add(1) % FFN_QUEUE_SETS) * FFN_QUEUE_INTS;
+    const unsigned set = next_set[both ? 1 : 0].fetch_add(1) % FFN_QUEUE_SETS;
+    return both ? base + FFN_QUEUE_SETS * FFN_QUEUE_INTS + set * FFN_BOTH_INTS : base + set * FFN_QUEUE_INTS;
 }
 
 // Launches one pass over one problem (second == nullptr) or over two: the second must be a single
@@ -1069,7 +1066,7 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     if (ffn_skinny_takes(pass, L)) return launch_ffn_skinny(pass, L, nullptr, st);
     int tile_rows[2];
     if (ffn_mid_rows(pass, L, tile_rows)) return launch_ffn_mid(pass, tile_rows, L, st);
-    int *queues = ffn_next_queues();
+    int *queues = ffn_next_queues(false);
     if (!queues) return C2R_ERR_LAUNCH;
     const dim3 g((unsigned)ffn_grid_of(L)), b(WM * WN * 64);
     if (pass == 0)
@@ -1077,6 +1074,26 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
     else
         ffn_bf16_dma_kernel<1, WM, WN><<<g, b, 0, st>>>(L, queues);
     return launch_status();
+}
+
+// Whether one launch of the tile kernel takes both passes.  Microseconds of a layer call, a kernel per pass / so:
+//   gate/up in tiles (more than 179 rows of a shared expert), down in ffn_mid: 60 experts + shared, 190 tokens 160 / 191, 250 tokens 176 /
+//     187, 320 tokens 187 / 201, 380 tokens 199 / 203, 400 tokens 198 / 188, 500 tokens 205 / 187;
+//   gate/up in ffn_mid, routed groups alone, r rows per expert: 16 experts of d 4096, r = 92 122.5 / 122.4, r = 125 128.4 / 132.6, r = 130
+//     144.7 / 134.0 (a chunk more per group), r = 147 152.8 / 138.0; 8 experts, r = 100 120 / 128, r = 125 141.7 / 135.2, r = 147 155.2 / 141.9.
+//   both in tiles, n likely gate/up tiles: 16 experts of d 4096, n = 132 155 / 162, n = 188 184 / 179; 8 experts, n = 215 189 / 189; with 15 of
+//     60 experts, whose rows are fewer than that, n = 134 107 / 113, n = 298 148 / 149, n = 426 184 / 183, n = 601 249 / 243: under a round of
+//     tiles there is little to go on with, and what there is waits.
+constexpr int BOTH_BESIDE = 390, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 384;
+static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down) {
+    int rows[2];
+    if (ffn_skinny_takes(0, up) || ffn_skinny_takes(1, down)) return false;
+    const FfnProblem &R = up.p[0], &S = up.p[1];
+    if (ffn_mid_rows(0, up, rows)) return !up.has_single && R.rows_hint / R.E_local > BOTH_PER_GROUP;
+    if (up.has_single && S.A_cap <= BOTH_BESIDE && ffn_mid_rows(1, down, rows)) return false;
+    int64_t tiles = up.has_single ? (int64_t)(S.A_cap + 255) / 256 * S.ntn : 0;
+    if (up.has_ragged) tiles += (int64_t)(R.rows_hint / 256 + (R.E_local < R.rows_hint ? R.E_local : R.rows_hint) / 2) * R.ntn;
+    return tiles >= (up.has_ragged && R.rows_hint < R.A_cap ? BOTH_TILES_OF_PART : BOTH_TILES);
 }
 
 // Both passes over one problem or two (first[pass], second[pass] as above; pass 1 reads the rows that pass 0 writes): one launch where
@@ -1088,12 +1105,8 @@ int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *con
     if (!two_single && (!second[0] || second[0]->E_local == 1)) {
         FfnBothLaunch L;
         int64_t mtiles = 0;
-        bool tiles = true;
-        for (int pass = 0; pass < 2; ++pass) {
-            L.pass[pass] = ffn_launch_of(first[pass], second[pass]);
-            int rows[2];
-            tiles = tiles && !ffn_skinny_takes(pass, L.pass[pass]) && !ffn_mid_rows(pass, L.pass[pass], rows);
-        }
+        for (int pass = 0; pass < 2; ++pass) L.pass[pass] = ffn_launch_of(first[pass], second[pass]);
+        bool tiles = both_in_tiles(L.pass[0], L.pass[1]);
         // An XCD writes whole lines of h: no line is in two XCDs' L2.
         for (int q = 0; q < 2; ++q) {
             const FfnProblem &P = L.pass[0].p[q];
@@ -1103,7 +1116,7 @@ int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *con
         }
         if (tiles && mtiles <= FFN_MTILES) {
             drop_stale_error();
-            int *queues = ffn_next_queues();
+            int *queues = ffn_next_queues(true);
             if (!queues) return C2R_ERR_LAUNCH;
             const int64_t g0 = ffn_grid_of(L.pass[0]), g1 = ffn_grid_of(L.pass[1]);
             const dim3 g((unsigned)(g0 > g1 ? g0 : g1)), b(WM * WN * 64);

@@ -306,16 +306,25 @@ struct TailSplit {
     bool valid;
 };
 
-template <bool SPLIT>
+// BESIDE: the other pass is in the launch and its tiles fill a last round, so that only one of a quarter of the CUs is cut (it ends
+// the round that the other pass waits for; layer call of 3000 tokens, 8 experts of d 4096: never 272 us, so 261), and a list that is no whole
+// round is not (15 of 60 experts, 1200 tokens 113 us, cut 123).
+template <bool BESIDE>
+__device__ __forceinline__ int last_round_parts(int cnt) {
+    const int r = cnt % CUS_PER_XCD;
+    if (r == 0 || (BESIDE && (cnt < CUS_PER_XCD || r * 4 > CUS_PER_XCD))) return 1;
+    return r * 4 <= CUS_PER_XCD ? 4 : (r * 2 <= CUS_PER_XCD ? 2 : 1);
+}
+
+template <bool BESIDE>
 __device__ __forceinline__ TailSplit split_last_round(int cnt, int slot) {
     TailSplit t;
     t.idx = slot;
     t.sub = 0;
     t.nsub = 1;
-    t.valid = SPLIT ? false : slot < cnt;
-    if (cnt <= 0 || !SPLIT) return t;
-    const int full = cnt / CUS_PER_XCD * CUS_PER_XCD, r = cnt - full;
-    const int s = r == 0 ? 1 : (r * 4 <= CUS_PER_XCD ? 4 : (r * 2 <= CUS_PER_XCD ? 2 : 1));
+    t.valid = false;
+    if (cnt <= 0) return t;
+    const int full = cnt / CUS_PER_XCD * CUS_PER_XCD, r = cnt - full, s = last_round_parts<BESIDE>(cnt);
     if (slot >= full) {
         const int q = slot - full;
         if (q >= r * s) return t;
@@ -342,6 +351,7 @@ struct FfnProblem {
     uint16_t *out;            // [rows, ldo]
     const int32_t *gather;    // row p of the sorted order is A[gather[p] / gather_div], or nullptr
     int lda, E_local, A_cap, N, Kdim, ldo, ntn, zero_to, gather_div, gather_rows, row_lo, row_hi;
+    int rows_hint;            // rows that are likely (<= A_cap): what the choice of a kernel goes by, and nothing else
 };
 struct FfnLaunch {
     FfnProblem p[2];            // p[0]: the ragged problem (several groups), p[1]: the single group

@@ -333,10 +333,11 @@ static void mid_launch(int ragged_rows, int single_rows, const FfnLaunch &L, hip
 //     195 / 187, n = 500: 236 / 228 / 234 / 210 (64+128 216, the tile kernel 212 at 511): no shared tiles of 128.  (The skewed groups beside it
 //     hold up to eight times the mean: 64 rows from a mean of 5; measured on this one model.)
 // (r counts the rows allotted.  A device that holds a quarter of the experts has a quarter of them in use: its tiles are higher
-// than its rows would ask for, 15 of 60 experts at 300 tokens 67.0 / 65.0 / 71.9.)
+// than its rows would ask for, 15 of 60 experts at 300 tokens 67.0 / 65.0 / 71.9.  The upper limits go by the rows that are likely: 15
+// of 60 experts, by the rows allotted / so, 400 tokens 81.6 / 75.7, 700 tokens 99.6 / 85.9, 1020 tokens 104.7 / 102.1.)
 constexpr int MID_LOW_BESIDE = 4;
 
-// most rows (per group / in the single group), for 32-, 64- and 128-row tiles of gate/up and of down
+// most rows (likely ones per group / in the single group), for 32-, 64- and 128-row tiles of gate/up and of down
 constexpr int MID_RAGGED_UP_TO[2][3] = {{20, 64, 150}, {20, 45, 90}}, MID_SINGLE_UP_TO[2][2] = {{64, 179}, {100, 511}};
 
 bool ffn_mid_rows(int pass, const FfnLaunch &L, int (&rows)[2]) {
@@ -346,7 +347,7 @@ bool ffn_mid_rows(int pass, const FfnLaunch &L, int (&rows)[2]) {
     rows[0] = rows[1] = 0;
     if (L.has_ragged) {
         const int mean = L.p[0].A_cap / L.p[0].E_local, *most = MID_RAGGED_UP_TO[pass];
-        if (mean > most[2]) return false;
+        if (L.p[0].rows_hint / L.p[0].E_local > most[2]) return false;
         rows[0] = mean <= (L.has_single ? MID_LOW_BESIDE : most[0]) ? 32 : (mean <= most[1] ? 64 : 128);
     }
     if (L.has_single) {

@@ -115,6 +115,15 @@ def ffn_kernel(which, E, A_cap, N):
     return "mid" if (A_cap if E == 1 else A_cap // E) <= most[-1] else "tile"
 
 
+def ffn_tiles(E, rows, F):
+    """Likely gate/up tiles of a problem, by which the launcher decides whether both passes are one launch (ffn_bf16_dma.hip)."""
+    return (-(-rows // 256) if E == 1 else rows // 256 + min(E, rows) // 2) * -(-F // 128)
+
+
+def ffn_tiles_limit():
+    return int(re.search(r"\bBOTH_TILES = (\d+)", _csrc("ffn_bf16_dma.hip")).group(1))
+
+
 def _mid_limits(side):
     """Most rows of every tile height of ffn_mid.hip, per pass (side: RAGGED, per group, or SINGLE)."""
     table = re.search(r"\bMID_%s_UP_TO\[2\]\[\d\] = \{([{}\d, ]+)\}" % side, _csrc("ffn_mid.hip")).group(1)

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import dev, ffn_kernel
+from helpers import dev, ffn_kernel, ffn_tiles, ffn_tiles_limit
 
 pytestmark = pytest.mark.gpu
 
@@ -21,15 +21,15 @@ def _weights(rng, *shapes):
 
 
 # full, short and tiny tiles and empty groups; one group; fewer M-tiles than XCDs; rows not all in use; a column tail (192, 320); one
-# slice (64); as many M-tiles as there are counters (1024) and one more (two launches)
+# slice (64); as many M-tiles as there are counters (1024) and one more (two launches); N-tiles enough for the rule to take one launch
 @pytest.mark.parametrize("d,F,sizes,cap", [
-    (128, 192, [256, 257, 511, 129, 128, 64, 65, 1, 0, 1000], 2600), (64, 64, [3000, 0, 1], 3001), (192, 704, [700], 800), (512, 128, [300, 299], 599),
-    (2048, 1408, [796, 624, 464, 341, 136, 63, 7, 0], 3200), (128, 320, [900] * 15, 13500), (64, 64, [131000, 130000], 1022 * 256),
+    (64, 2560, [256, 257, 511, 129, 128, 64, 65, 1, 0, 1000], 2600), (64, 8192, [3000, 0, 1], 3001), (192, 7744, [700], 800), (512, 8192, [300, 299], 599),
+    (2048, 1408, [796, 624, 464, 341, 136, 63, 7, 0], 3400), (128, 448, [900] * 15, 13500), (64, 64, [131000, 130000], 1022 * 256),
     (64, 64, [131000, 130500], 1023 * 256)])
 def test_routed_groups(c2r, d, F, sizes, cap):
     rng = np.random.default_rng(d + F)
     E, n, K = len(sizes), sum(sizes), 2
-    assert ffn_kernel(0, E, cap, F) == ffn_kernel(1, E, cap, d) == "tile"
+    assert ffn_kernel(0, E, cap, F) == ffn_kernel(1, E, cap, d) == "tile" and ffn_tiles(E, cap, F) >= ffn_tiles_limit()
     T = (cap + K - 1) // K
     x = dev(rng.standard_normal((T, d)).astype(np.float32), "bf16")
     perm = dev(np.concatenate([rng.permutation(T * K)[:n], np.full(cap - n, -1)]).astype(np.int32))
@@ -47,10 +47,11 @@ def test_routed_groups(c2r, d, F, sizes, cap):
 
 
 # a shared expert beside the routed groups, through the layer call: every row of it and of the routed experts
-@pytest.mark.parametrize("T,d,F,Fs", [(1300, 128, 64, 192), (2500, 256, 192, 1024), (5000, 64, 128, 64)])
+@pytest.mark.parametrize("T,d,F,Fs", [(1300, 128, 832, 2560), (2500, 256, 448, 1024), (5000, 64, 192, 64)])
 def test_layer_with_shared_expert(c2r, T, d, F, Fs):
     rng = np.random.default_rng(T)
     E, K = 16, 4
+    assert ffn_tiles(E, T * K, F) + ffn_tiles(1, T, Fs) >= ffn_tiles_limit()
     x = dev(rng.standard_normal((T, d)).astype(np.float32), "bf16")
     Wg = dev((rng.standard_normal((d, E)) * 0.05 + np.linspace(0, 0.1, E)).astype(np.float32))
     collab = dev(np.stack([np.delete(np.arange(E), e) for e in range(E)]).astype(np.int32))
@@ -64,3 +65,26 @@ def test_layer_with_shared_expert(c2r, T, d, F, Fs):
         a.h_shared.fill_(float("nan"))
         assert torch.equal(a.forward(x), ref)
         assert torch.equal(a.y_perm, b.y_perm) and torch.equal(a.y_shared, b.y_shared)
+
+
+# the layer call on either side of the rules that give a pass to this kernel or that: 390 rows of a shared expert, 125 likely rows per expert,
+# 4096 rows allotted to a device with a part of the experts.  The same bits as stage by stage, where every pass chooses by the rows allotted.
+@pytest.mark.parametrize("T,E,El,K,Fs", [(390, 60, 60, 4, 192), (391, 60, 60, 4, 192), (501, 16, 16, 4, 0), (504, 16, 16, 4, 0), (600, 16, 16, 4, 0),
+                                         (1000, 60, 15, 4, 0), (1024, 60, 15, 4, 0), (1025, 60, 15, 4, 0), (2100, 60, 15, 4, 0), (15500, 60, 15, 4, 0), (300, 64, 1, 4, 0)])
+def test_layer_at_the_limits_of_the_kernels(c2r, T, E, El, K, Fs):
+    rng = np.random.default_rng(T + E)
+    d, F = 128, 704
+    x = dev(rng.standard_normal((T, d)).astype(np.float32), "bf16")
+    Wg = dev((rng.standard_normal((d, E)) * 0.05 + np.linspace(0, 0.1, E)).astype(np.float32))
+    slots = None
+    if El < E:
+        slots = np.full(E, -1, dtype=np.int32)
+        slots[rng.permutation(E)[:El]] = np.arange(El)
+        slots = dev(slots)
+    shared = tuple(_weights(rng, (1, Fs, d), (1, Fs, d), (1, d, Fs))) if Fs else None
+    layer = c2r.C2RLayer(T, d, E, K, F, torch.bfloat16, Wg, None, None, *_weights(rng, (El, F, d), (El, F, d), (El, d, F)), local_slot=slots, E_local=El,
+                         shared=shared)
+    ref = layer.forward(x, trace={}).clone()
+    for _ in range(3):
+        layer.h.fill_(float("nan"))
+        assert torch.equal(layer.forward(x), ref)
