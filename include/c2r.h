@@ -216,7 +216,7 @@ int c2r_permute_noalloc(const void *x, c2r_dtype dt, const int32_t *topk_idx, in
  * and x itself as x_perm.
  * Concurrency (this and every other c2r_expert_ffn_* call, bf16 shapes of the fast kernel): a
  * launch hands its tiles out through a set of counters in a static device array; the library
- * holds 64 sets per GPU and gives them to launches in turn, and a set is all zero again when its
+ * holds 64 sets per GPU (and 64 for launches of both passes) and gives them to launches in turn, and a set is all zero again when its
  * launch ends.  Two launches that were given the same set (every 64th call) must not RUN at the
  * same time: on one stream they never do, however many are queued; a caller that spreads these
  * calls over several streams keeps fewer than 64 of them outstanding (enqueued and not finished)
@@ -305,9 +305,9 @@ int c2r_combine(const void *y_perm, c2r_dtype dt, const float *gates, const int3
 
 /*
  * The whole layer (Sec. 3.1, Sec. 3.3) in one host call: c2r_route, c2r_permute, the expert FFN and c2r_combine
- * on the buffers of *layer, enqueued on `stream` in that order.  It does what those calls do one by one - the
- * same kernels, checks and results - and exists because a decoding step's kernels are shorter than a dozen calls
- * through a language binding.  Nothing of *layer is kept.  An error of a later stage is returned after the
+ * on the buffers of *layer, enqueued on `stream` in that order.  It does what those calls do one by one, with the same
+ * checks and results bit for bit, in fewer launches where stages can share one, and exists because a decoding step's
+ * kernels are shorter than a dozen calls through a language binding.  Nothing of *layer is kept.  An error of a later stage is returned after the
  * earlier stages have been enqueued.
  * Sizes and device pointers are those of the entry points of the same names; every field is 64 bits wide.  The
  * pointers that are set choose the form of the expert FFN:
