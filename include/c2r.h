@@ -308,7 +308,8 @@ int c2r_combine(const void *y_perm, c2r_dtype dt, const float *gates, const int3
  * on the buffers of *layer, enqueued on `stream` in that order.  It does what those calls do one by one, with the same
  * checks and results bit for bit, in fewer launches where stages can share one, and exists because a decoding step's
  * kernels are shorter than a dozen calls through a language binding.  Nothing of *layer is kept.  An error of a later stage is returned after the
- * earlier stages have been enqueued.
+ * earlier stages have been enqueued.  Memory that the calls one by one may hand on (one scratch for every ws_*, h where ws_route was, y_shared in
+ * the place of x) may be handed on here: stages share a launch only where nothing that it writes meets anything else of it.
  * Sizes and device pointers are those of the entry points of the same names; every field is 64 bits wide.  The
  * pointers that are set choose the form of the expert FFN:
  *   x_perm          : rows are scattered by c2r_permute and both passes run as c2r_expert_ffn (h in ws_ffn)

@@ -336,7 +336,16 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
         routed[0].rows_hint = routed[1].rows_hint = (int)(A * El / E);
     const FfnProblem *const beside[2] = {rides ? &with[0] : nullptr, rides ? &with[1] : nullptr};
     FewRoute few;
-    const bool later = gathers && ffn_rc == C2R_OK && A > 0 && route_may_finish_later(T, d, E, K) && ffn_few_takes(routed[0], beside[0]);
+    bool later = gathers && ffn_rc == C2R_OK && A > 0 && route_may_finish_later(T, d, E, K) && ffn_few_takes(routed[0], beside[0]);
+    if (later) {
+        // (every workgroup of that launch reads what the selection is made from, while others write h)
+        const size_t a4 = (size_t)A * 4, up = (size_t)El * F * d * 2, up_shared = rides ? (size_t)Fs * d * 2 : 0;
+        later = all_apart({{L.topk_idx, a4}, {L.gates, a4}, {L.counts, (size_t)El * 4}, {L.offsets, (size_t)(El + 1) * 4}, {L.perm, a4},
+                           {L.inv_perm, a4}, {routed[0].out, (size_t)A * routed[0].ldo * 2}, {L.h_shared, rides ? (size_t)T * Fs * 2 : 0}},
+                          {{L.ws_route, route_workspace_bytes(T, d, E)}, {L.bias, (size_t)E * 4}, {L.collab_idx, (size_t)E * L.Tc * 4},
+                           {L.local_slot, (size_t)E * 4}, {x, (size_t)T * d * 2}, {L.w_gate, up}, {L.w_up, up}, {L.ws_gate, up_shared},
+                           {L.ws_up, up_shared}});
+    }
     int rc = route_and_permute(x, dt, L.Wg, L.bias, T, d, E, K, L.collab_idx, (int)L.Tc, L.topk_idx, L.gates, L.ws_route,
                                (size_t)L.ws_route_bytes, L.local_slot, El, L.counts, L.offsets, L.perm, L.inv_perm, L.x_perm,
                                L.ws_permute, (size_t)L.ws_permute_bytes, later ? &few : nullptr, stream);

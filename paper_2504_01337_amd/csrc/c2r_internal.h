@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "../../include/c2r.h"
 
 #define C2R_WAVE 64
@@ -23,6 +25,28 @@ static inline int launch_status() {
 static inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 static inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
+// Memory that a launch reads or writes (no bytes, or a null pointer: none).
+struct MemRange {
+    const void *p;
+    size_t bytes;
+};
+static inline bool apart(const MemRange &a, const MemRange &b) {
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a.p), pb = reinterpret_cast<uintptr_t>(b.p);
+    return !pa || !pb || !a.bytes || !b.bytes || pa + a.bytes <= pb || pb + b.bytes <= pa;
+}
+// Whether nothing that is written meets anything else.  Stages that are enqueued one after the other may hand memory on (one scratch for
+// all of them, a result in the place of an input that is done with); workgroups of ONE launch that does their work run in no order, so
+// it is taken only where this holds.
+static inline bool all_apart(std::initializer_list<MemRange> written, std::initializer_list<MemRange> read) {
+    for (const MemRange *w = written.begin(); w != written.end(); ++w) {
+        for (const MemRange *v = w + 1; v != written.end(); ++v)
+            if (!apart(*w, *v)) return false;
+        for (const MemRange &r : read)
+            if (!apart(*w, r)) return false;
+    }
+    return true;
+}
 
 // bf16 <-> fp32 on raw bits. Storage is uint16_t; conversion to fp32 is exact.
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
