@@ -1917,7 +1917,15 @@ int c2r::route_and_permute(const void *x, c2r_dtype dt, const float *Wg, const f
                            FewRoute *later, void *stream) {
     int rc;
     const int64_t nchunk = d >= 1 ? ((int64_t)d + C2R_CANON_CHUNK - 1) / C2R_CANON_CHUNK : 1;
-    const bool with_rows = E >= 1 && route_small(T, (int)nchunk, ep_of(E)) && select_index_takes(T, E, K, nchunk) && (T > FIN_TOKENS || x_perm);
+    bool with_rows = E >= 1 && route_small(T, (int)nchunk, ep_of(E)) && select_index_takes(T, E, K, nchunk) && (T > FIN_TOKENS || x_perm);
+    if (with_rows) {
+        // (every workgroup of that launch selects for all tokens, while others write the index and the rows)
+        const size_t a4 = (size_t)(T * K) * 4, size = dt == C2R_BF16 ? 2 : 4;
+        with_rows = all_apart({{topk_idx, a4}, {gates, a4}, {counts, (size_t)E_local * 4}, {offsets, (size_t)(E_local + 1) * 4}, {perm, a4},
+                               {inv_perm, a4}, {x_perm, (size_t)(T * K) * d * size}},
+                              {{ws_route, route_workspace_bytes(T, d, E)}, {bias, (size_t)E * 4}, {collab_idx, (size_t)E * Tc * 4},
+                               {local_slot, (size_t)E * 4}, {x, (size_t)T * d * size}});
+    }
     if (with_rows || route_few_takes(T, d, E, K)) {
         rc = permute_check(x, dt, topk_idx, T, d, E, K, local_slot, E_local, counts, offsets, perm, inv_perm, x_perm,
                            ws_permute, ws_permute_bytes);

@@ -58,3 +58,20 @@ def test_scratch_of_the_router_where_h_goes(c2r, T, d, E, K, F, Fs):
         assert torch.equal(_forward(c2r, layer, x, places), ref)
     m = _memory(layer.perm, layer.ws_route).data_ptr()
     assert torch.equal(_forward(c2r, layer, x, {WS_ROUTE: m, PERM: m}), ref)
+
+
+# selection, index and row scatter in one launch (few experts): the chunk results that it reads where the rows or the index go; 65 tokens and up
+# without rows; batches that one workgroup selects for, and the first that no launch does it all for
+@pytest.mark.parametrize("T,d,E,K,F,kw", [(20, 256, 8, 2, 64, {"fuse_gather": False}), (512, 256, 8, 2, 64, {"fuse_gather": False}),
+                                          (1000, 128, 16, 4, 64, {"fuse_gather": False}), (1024, 64, 16, 3, 72, {"fuse_gather": False}),
+                                          (1025, 64, 16, 3, 72, {"fuse_gather": False}), (128, 256, 16, 4, 64, {})])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_scratch_of_the_router_where_the_rows_go(c2r, T, d, E, K, F, kw, dtype):
+    layer, x = _layer(c2r, T, d, E, K, F, dtype, **kw)
+    ref = layer.forward(x).clone()
+    for field, own in ((X_PERM, layer.x_perm), (PERM, layer.perm)):
+        if own is None:
+            continue
+        for _ in range(3):
+            m = _memory(own, layer.ws_route).data_ptr()
+            assert torch.equal(_forward(c2r, layer, x, {WS_ROUTE: m, field: m}), ref)
