@@ -1096,9 +1096,41 @@ static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down) {
     return tiles >= (up.has_ragged && R.rows_hint < R.A_cap ? BOTH_TILES_OF_PART : BOTH_TILES);
 }
 
+// Whether the down pass may write while the gate/up pass still reads: its outputs meet nothing else of the two (but for one in the place of
+// its own problem's rows, not gathered: a tile waits until the gate/up tiles of its rows, the only ones that read them, are finished).
+static bool ffn_both_apart(const FfnBothLaunch &L) {
+    const MemRange none = {nullptr, 0};
+    MemRange y[2], h[2], read[2][6];
+    for (int q = 0; q < 2; ++q) {
+        const FfnProblem &U = L.pass[0].p[q], &D = L.pass[1].p[q];
+        y[q] = h[q] = none;
+        for (MemRange &r : read[q]) r = none;
+        if (!(q == 0 ? L.pass[0].has_ragged : L.pass[0].has_single)) continue;
+        const size_t weights = (size_t)U.E_local * U.N * U.Kdim * 2;
+        y[q] = {D.out, (size_t)D.A_cap * D.ldo * 2};
+        h[q] = {U.out, (size_t)U.A_cap * U.ldo * 2};
+        read[q][0] = {U.A, (size_t)(U.gather ? U.gather_rows : U.A_cap) * U.lda * 2};
+        read[q][1] = {U.B0, weights};
+        read[q][2] = {U.B1, weights};
+        read[q][3] = {D.B0, weights};
+        read[q][4] = {U.gather, (size_t)U.A_cap * 4};
+        read[q][5] = {U.offsets, (size_t)(U.E_local + 1) * 4};
+    }
+    for (int q = 0; q < 2; ++q) {
+        if (!apart(y[q], y[1 - q]) || !apart(y[q], h[0]) || !apart(y[q], h[1])) return false;
+        for (int o = 0; o < 2; ++o)
+            for (int i = 0; i < 6; ++i) {
+                const FfnProblem &U = L.pass[0].p[q], &D = L.pass[1].p[q];
+                const bool in_place = o == q && i == 0 && !U.gather && D.out == U.A && D.ldo == U.lda;
+                if (!in_place && !apart(y[q], read[o][i])) return false;
+            }
+    }
+    return true;
+}
+
 // Both passes over one problem or two (first[pass], second[pass] as above; pass 1 reads the rows that pass 0 writes): one launch where
-// the tile kernel takes both, h has whole 128-byte lines and there are counters for all M-tiles (260000 rows: the idle end of a pass is
-// under 1 % of it there).
+// the tile kernel takes both, their buffers are apart, h has whole 128-byte lines and there are counters for all M-tiles (260000 rows: the
+// idle end of a pass is under 1 % of it there).
 int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *const (&second)[2], hipStream_t st) {
     constexpr int BM = 256, WM = 2, WN = 4;
     const bool two_single = second[0] && first[0].E_local == 1;
@@ -1114,7 +1146,7 @@ int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *con
             tiles = tiles && aligned(P.out, 128) && P.ldo % 64 == 0;
             mtiles += P.A_cap / BM + P.E_local;
         }
-        if (tiles && mtiles <= FFN_MTILES) {
+        if (tiles && mtiles <= FFN_MTILES && ffn_both_apart(L)) {
             drop_stale_error();
             int *queues = ffn_next_queues(true);
             if (!queues) return C2R_ERR_LAUNCH;

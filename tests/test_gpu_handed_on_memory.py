@@ -75,3 +75,53 @@ def test_scratch_of_the_router_where_the_rows_go(c2r, T, d, E, K, F, kw, dtype):
         for _ in range(3):
             m = _memory(own, layer.ws_route).data_ptr()
             assert torch.equal(_forward(c2r, layer, x, {WS_ROUTE: m, field: m}), ref)
+
+
+# both FFN passes in one launch: results in the place of what the first pass reads.  Sizes on either side of the rule for one launch.
+@pytest.mark.parametrize("T,Fs", [(200, 1408), (1300, 2560), (2500, 1024)])
+def test_results_in_the_place_of_x(c2r, T, Fs):
+    layer, x = _layer(c2r, T, 128, 16, 4, 832, Fs=Fs)
+    assert layer.fuse_shared
+    ref, y_perm = layer.forward(x).clone(), layer.y_perm.clone()
+    for _ in range(3):
+        xs = x.clone()
+        assert torch.equal(_forward(c2r, layer, xs, {Y_SHARED: xs.data_ptr()}), ref)
+    m = _memory(layer.y_perm)                          # x at the end of y_perm
+    for _ in range(3):
+        xs = m[m.numel() - x.numel() * 2:].view(torch.bfloat16).view(x.shape)
+        xs.copy_(x)
+        layer.y_perm.fill_(7.0)
+        assert torch.equal(_forward(c2r, layer, xs, {Y_PERM: m.data_ptr()}), ref)
+        assert torch.equal(m.view(torch.bfloat16).view(y_perm.shape), y_perm)
+    # one scratch for every stage that has one
+    n = _memory(layer.ws_route, layer.ws_perm).data_ptr()
+    assert torch.equal(_forward(c2r, layer, x, {WS_ROUTE: n, WS_PERMUTE: n}), ref)
+
+
+# the expert FFN alone: y_perm over x where rows are gathered (partly and whole), in the place of x_perm where they are not, and over a part of it
+@pytest.mark.parametrize("sizes,F", [([30, 0, 70], 448), ([700, 600, 33, 257], 2560), ([1500], 7744)])
+def test_expert_ffn_over_its_input(c2r, sizes, F):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(F)
+    d, E, K, n = 128, len(sizes), 2, sum(sizes)
+    w = [torch.randn(s, generator=gen, device="cuda").mul_(0.05).bfloat16() for s in ((E, F, d), (E, F, d), (E, d, F))]
+    T = (n + K - 1) // K
+    x = torch.randn((T, d), generator=gen, device="cuda").bfloat16()
+    perm = torch.randperm(T * K, generator=gen, device="cuda").to(torch.int32)[:n].contiguous()
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(sizes)]), dtype=torch.int32, device="cuda")
+    ws = torch.empty(c2r.workspace_bytes(c2r.STAGE_EXPERT_FFN, n, d, E, 1, F, c2r.BF16), dtype=torch.uint8, device="cuda")
+    x_perm = x[(perm // K).long()].contiguous()
+    ref = c2r.expert_ffn(x_perm, offsets, *w).clone()
+    for _ in range(3):
+        for shift in (0, 16, n - T):                   # rows of y_perm before x
+            m = torch.full((n + T + 16, d), 7.0, dtype=torch.bfloat16, device="cuda")
+            xs, y = m[shift:shift + T], m[:n]
+            xs.copy_(x)
+            ws.fill_(255)
+            c2r.expert_ffn_gather(xs, perm, K, offsets, *w, ws=ws, out=y)
+            assert torch.equal(y, ref)
+        xs = x_perm.clone()
+        assert torch.equal(c2r.expert_ffn(xs, offsets, *w, ws=ws, out=xs), ref)
+        m = torch.full((n + 300, d), 7.0, dtype=torch.bfloat16, device="cuda")
+        m[300:].copy_(x_perm)
+        assert torch.equal(c2r.expert_ffn(m[300:], offsets, *w, ws=ws, out=m[:n]), ref)
