@@ -459,7 +459,10 @@ extern "C" int c2r_dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int
     const size_t need = dedup_workspace_bytes(T > 0 ? T : 1, n_dev);
     if (!ws || ws_bytes < need || !aligned(ws, 256)) return C2R_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (dedup_in_one_launch(T, K, n_dev)) {
+    // (every workgroup of the one launch reads all of topk_idx and the device map while others write: send_row may stand in topk_idx's place, say)
+    const size_t a4 = (size_t)(T * K) * 4, g4 = (size_t)n_dev * 4;
+    if (dedup_in_one_launch(T, K, n_dev) && all_apart({{send_counts, g4}, {send_offsets, g4 + 4}, {send_token, a4}, {send_row, a4}},
+                                                      {{topk_idx, a4}, {expert_device, (size_t)E * 4}})) {
         int parts = 1;
         while (parts < DD_PARTS && parts * (DD_MAX_TOKENS / DD_STEPS) < T && 2 * parts * n_dev <= 64) parts *= 2;
         const dim3 g((unsigned)(n_dev * parts)), b(DD_WAVES * 64);

@@ -125,3 +125,20 @@ def test_expert_ffn_over_its_input(c2r, sizes, F):
         m = torch.full((n + 300, d), 7.0, dtype=torch.bfloat16, device="cuda")
         m[300:].copy_(x_perm)
         assert torch.equal(c2r.expert_ffn(m[300:], offsets, *w, ws=ws, out=m[:n]), ref)
+
+
+# the dispatch index with send_row in the place of topk_idx, on either side of the rule for one launch
+@pytest.mark.parametrize("T,K,n_dev", [(1, 4, 4), (1000, 4, 4), (1000, 3, 60), (4096, 2, 3), (4097, 2, 3), (8192, 4, 8), (700, 6, 5)])
+def test_dispatch_index_over_its_input(c2r, T, K, n_dev):
+    rng = np.random.default_rng(T)
+    E = 60
+    idx = torch.from_numpy(np.argsort(rng.random((T, E)), axis=1)[:, :K].astype(np.int32)).cuda()
+    devmap = torch.from_numpy(rng.integers(-1, n_dev, size=E).astype(np.int32)).cuda()
+    counts, offsets, token, row = c2r.dedup_dispatch(idx, E, devmap, n_dev)
+    ws = torch.empty(max(256, c2r.workspace_bytes(c2r.STAGE_DEDUP_DISPATCH, T, 0, n_dev, K, 0, c2r.F32)), dtype=torch.uint8, device="cuda")
+    for _ in range(3):
+        both, c, o, t = idx.clone(), torch.empty_like(counts), torch.empty_like(offsets), torch.full_like(token, -1)
+        p = lambda v: v.data_ptr()
+        assert c2r.lib().c2r_dedup_dispatch(p(both), T, K, E, p(devmap), n_dev, p(c), p(o), p(t), p(both), p(ws), ws.numel(),
+                                            torch.cuda.current_stream().cuda_stream) == c2r.OK
+        assert torch.equal(c, counts) and torch.equal(o, offsets) and torch.equal(t, token) and torch.equal(both.view(-1), row.view(-1))
