@@ -313,19 +313,19 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
         if (rc != C2R_OK) return rc;
     }
     // The forms whose first pass reads rows of x: the passes' arguments first, so that the gate/up launch of a few tokens can finish the
-    // routing (an error in them is still reported after one in the routing's).
+    // routing (an error in them is still reported after one in the routing's, and one in the down pass's after the gate/up pass).
     const bool own_h = L.h && !shared, gathers = rides || own_h || (!L.h && !L.x_perm);
     FfnProblem routed[2], with[2];
-    int ffn_rc = C2R_OK;
+    int ffn_rc = C2R_OK, down_rc = C2R_OK;
     if (rides) {
         ffn_rc = gate_up_with_shared_problems(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, Fs, L.ws_gate, L.ws_up,
                                               L.h_shared, routed[0], with[0]);
         if (ffn_rc == C2R_OK)
-            ffn_rc = down_with_shared_problems(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, T, Fs, L.h_shared, L.ws_down,
-                                               L.y_shared, routed[1], with[1]);
+            down_rc = down_with_shared_problems(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm, T, Fs, L.h_shared, L.ws_down,
+                                                L.y_shared, routed[1], with[1]);
     } else if (own_h) {
         ffn_rc = check_gate_up_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h);
-        if (ffn_rc == C2R_OK) ffn_rc = check_down(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm);
+        if (ffn_rc == C2R_OK) down_rc = check_down(L.h, dt, L.offsets, El, A, d, F, L.w_down, L.y_perm);
         if (ffn_rc == C2R_OK && A > 0)
             both_problems(x, L.offsets, El, A, d, F, F, L.w_gate, L.w_up, L.w_down, L.h, L.y_perm, L.perm, K, (int)T, routed);
     } else if (gathers) {
@@ -336,7 +336,7 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
         routed[0].rows_hint = routed[1].rows_hint = (int)(A * El / E);
     const FfnProblem *const beside[2] = {rides ? &with[0] : nullptr, rides ? &with[1] : nullptr};
     FewRoute few;
-    bool later = gathers && ffn_rc == C2R_OK && A > 0 && route_may_finish_later(T, d, E, K) && ffn_few_takes(routed[0], beside[0]);
+    bool later = gathers && ffn_rc == C2R_OK && down_rc == C2R_OK && A > 0 && route_may_finish_later(T, d, E, K) && ffn_few_takes(routed[0], beside[0]);
     if (later) {
         // (every workgroup of that launch reads what the selection is made from, while others write h)
         const size_t a4 = (size_t)A * 4, up = (size_t)El * F * d * 2, up_shared = rides ? (size_t)Fs * d * 2 : 0;
@@ -357,7 +357,8 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
             rc = launch_ffn_few(routed[0], beside[0], few, st);
             if (rc == C2R_OK) rc = launch_ffn_bf16_dma(1, routed[1], beside[1], st);
         } else if (rc == C2R_OK && A > 0) {
-            rc = launch_ffn_bf16_dma_both(routed, beside, st);
+            rc = down_rc == C2R_OK ? launch_ffn_bf16_dma_both(routed, beside, st) : launch_ffn_bf16_dma(0, routed[0], beside[0], st);
+            if (rc == C2R_OK) rc = down_rc;
         }
     } else if (L.h) {
         rc = c2r_expert_ffn_gate_up_gather(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.h, stream);

@@ -1929,7 +1929,10 @@ int c2r::route_and_permute(const void *x, c2r_dtype dt, const float *Wg, const f
     if (with_rows || route_few_takes(T, d, E, K)) {
         rc = permute_check(x, dt, topk_idx, T, d, E, K, local_slot, E_local, counts, offsets, perm, inv_perm, x_perm,
                            ws_permute, ws_permute_bytes);
-        if (rc != C2R_OK) return rc;
+        if (rc != C2R_OK) {  // (as ahead of a c2r_permute that fails)
+            const int rr = c2r_route(x, dt, Wg, bias, T, d, E, K, collab_idx, Tc, topk_idx, gates, nullptr, ws_route, ws_route_bytes, stream);
+            return rr != C2R_OK ? rr : rc;
+        }
         const DispatchOut out = {local_slot, E_local, counts, offsets, perm, inv_perm, later, with_rows ? x_perm : nullptr};
         rc = route_impl(x, dt, Wg, bias, T, d, E, K, collab_idx, Tc, topk_idx, gates, nullptr, ws_route, ws_route_bytes, &out,
                         stream);

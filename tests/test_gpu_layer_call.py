@@ -130,3 +130,38 @@ def test_shared_weights_without_the_leading_dimension():
     assert flat.fuse_shared and full.fuse_shared
     x = w(T, d)
     assert torch.equal(flat.forward(x), full.forward(x)) and torch.equal(flat.forward(x), flat.forward(x, trace={}))
+
+
+# an error of a later stage comes after the earlier stages: the router ahead of a bad index, the gate/up pass ahead of a bad down pass; batches
+# of every form in which stages share a launch
+@pytest.mark.parametrize("T,E,dtype,Fs", [(3, 20, "bf16", 0), (3, 20, "bf16", 64), (20, 20, "bf16", 0), (100, 8, "f32", 0), (100, 8, "bf16", 128), (2000, 8, "bf16", 0)])
+def test_an_error_of_a_later_stage(T, E, dtype, Fs):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(T)
+    d, K, F = 64, 2, 64
+    w = lambda *sh: dev((rng.standard_normal(sh) * 0.05).astype(np.float32), dtype)
+    shared = (w(1, Fs, d), w(1, Fs, d), w(1, d, Fs)) if Fs else None
+    layer = c2r.C2RLayer(T, d, E, K, F, torch.bfloat16 if dtype == "bf16" else torch.float32, w(d, E).float(), None, None,
+                         w(E, F, d), w(E, F, d), w(E, d, F), shared=shared)
+    x = w(T, d)
+    layer.forward(x)
+    idx, gates, inv = layer.idx.clone(), layer.gates.clone(), layer.inv_perm.clone()
+    h = None if layer.h is None else layer.h.clone()
+
+    def call(field, value):
+        fields = list(layer._LAYER.unpack(layer._args()))
+        fields[field] = value
+        for t in (layer.idx, layer.gates, layer.inv_perm, layer.h):
+            if t is not None:
+                t.fill_(-7)
+        rc = c2r.lib().c2r_layer_forward(layer._LAYER.pack(*fields), x.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        return rc
+
+    assert call(37, 0) == c2r.ERR_WORKSPACE            # ws_permute_bytes
+    assert torch.equal(layer.idx, idx) and torch.equal(layer.gates, gates) and bool((layer.inv_perm == -7).all())
+    assert call(36, 0) == c2r.ERR_WORKSPACE            # ws_route_bytes
+    assert bool((layer.idx == -7).all())
+    if h is not None:
+        assert call(16, 0) == c2r.ERR_INVALID_ARG      # w_down
+        assert torch.equal(layer.idx, idx) and torch.equal(layer.inv_perm, inv) and torch.equal(layer.h, h)
