@@ -22,8 +22,8 @@ namespace c2r {
 FfnProblem ffn_bf16_dma_problem(int pass, const uint16_t *a, int lda, const int32_t *offsets, int E_local,
                                 int64_t A_cap, int d, int F, const uint16_t *b0, const uint16_t *b1, uint16_t *out,
                                 int ldo, const int32_t *gather, int gather_div, int gather_rows);
-int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, hipStream_t st);
-int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *const (&second)[2], hipStream_t st);
+int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, int likely, hipStream_t st);
+int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *const (&second)[2], int likely, hipStream_t st);
 bool ffn_few_takes(const FfnProblem &routed, const FfnProblem *shared);
 int launch_ffn_few(const FfnProblem &routed, const FfnProblem *shared, const FewRoute &few, hipStream_t st);
 }  // namespace c2r
@@ -179,7 +179,7 @@ extern "C" int c2r_expert_ffn(const void *x_perm, c2r_dtype dt, const int32_t *o
     if (fast_bf16(dt, d, F)) {
         FfnProblem p[2];
         both_problems(x_perm, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, w_down, ws, y_perm, nullptr, 1, 1, p);
-        return launch_ffn_bf16_dma_both(p, {nullptr, nullptr}, static_cast<hipStream_t>(stream));
+        return launch_ffn_bf16_dma_both(p, {nullptr, nullptr}, (int)A_cap, static_cast<hipStream_t>(stream));
     }
     rc = ffn_pass(0, dt, x_perm, offsets, E_local, A_cap, d, F, ldh, w_gate, w_up, ws, stream);
     if (rc != C2R_OK) return rc;
@@ -213,7 +213,7 @@ extern "C" int c2r_expert_ffn_gather(const void *x, c2r_dtype dt, const int32_t 
     FfnProblem p[2];
     const int rc = gather_problems(x, dt, perm, T, K, offsets, E_local, A_cap, d, F, w_gate, w_up, w_down, y_perm, ws, ws_bytes, p);
     if (rc != C2R_OK || A_cap == 0) return rc;
-    return launch_ffn_bf16_dma_both(p, {nullptr, nullptr}, static_cast<hipStream_t>(stream));
+    return launch_ffn_bf16_dma_both(p, {nullptr, nullptr}, (int)A_cap, static_cast<hipStream_t>(stream));
 }
 
 // ---- routed groups and an always-on shared expert in ONE launch per pass ----
@@ -275,7 +275,7 @@ extern "C" int c2r_expert_ffn_gate_up_with_shared(const void *x, c2r_dtype dt, c
                                                 ws_gate, ws_up, h_shared, routed, shared);
     if (rc != C2R_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return A_cap == 0 ? launch_ffn_bf16_dma(0, shared, nullptr, st) : launch_ffn_bf16_dma(0, routed, &shared, st);
+    return A_cap == 0 ? launch_ffn_bf16_dma(0, shared, nullptr, (int)T, st) : launch_ffn_bf16_dma(0, routed, &shared, (int)A_cap, st);
 }
 
 extern "C" int c2r_expert_ffn_down_with_shared(const void *h, c2r_dtype dt, const int32_t *offsets, int E_local,
@@ -287,7 +287,7 @@ extern "C" int c2r_expert_ffn_down_with_shared(const void *h, c2r_dtype dt, cons
                                              y_shared, routed, shared);
     if (rc != C2R_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return A_cap == 0 ? launch_ffn_bf16_dma(1, shared, nullptr, st) : launch_ffn_bf16_dma(1, routed, &shared, st);
+    return A_cap == 0 ? launch_ffn_bf16_dma(1, shared, nullptr, (int)T, st) : launch_ffn_bf16_dma(1, routed, &shared, (int)A_cap, st);
 }
 
 // ---- the layer in one host call ----
@@ -332,8 +332,8 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
         ffn_rc = gather_problems(x, dt, L.perm, T, K, L.offsets, El, A, d, F, L.w_gate, L.w_up, L.w_down, L.y_perm, L.ws_ffn,
                                  (size_t)L.ws_ffn_bytes, routed);
     }
-    if (gathers && ffn_rc == C2R_OK && A > 0 && El <= E)  // (a device that holds a part of the experts)
-        routed[0].rows_hint = routed[1].rows_hint = (int)(A * El / E);
+    // (a device that holds a part of the experts)
+    const int likely = gathers && ffn_rc == C2R_OK && A > 0 ? (int)(El <= E ? A * El / E : A) : 0;
     const FfnProblem *const beside[2] = {rides ? &with[0] : nullptr, rides ? &with[1] : nullptr};
     FewRoute few;
     bool later = gathers && ffn_rc == C2R_OK && down_rc == C2R_OK && A > 0 && route_may_finish_later(T, d, E, K) && ffn_few_takes(routed[0], beside[0]);
@@ -355,9 +355,10 @@ extern "C" int c2r_layer_forward(const c2r_layer *layer, const void *x, void *st
         rc = ffn_rc;
         if (later) {
             rc = launch_ffn_few(routed[0], beside[0], few, st);
-            if (rc == C2R_OK) rc = launch_ffn_bf16_dma(1, routed[1], beside[1], st);
+            if (rc == C2R_OK) rc = launch_ffn_bf16_dma(1, routed[1], beside[1], likely, st);
         } else if (rc == C2R_OK && A > 0) {
-            rc = down_rc == C2R_OK ? launch_ffn_bf16_dma_both(routed, beside, st) : launch_ffn_bf16_dma(0, routed[0], beside[0], st);
+            rc = down_rc == C2R_OK ? launch_ffn_bf16_dma_both(routed, beside, likely, st)
+                                  : launch_ffn_bf16_dma(0, routed[0], beside[0], likely, st);
             if (rc == C2R_OK) rc = down_rc;
         }
     } else if (L.h) {

@@ -980,14 +980,14 @@ FfnProblem ffn_bf16_dma_problem(int pass, const uint16_t *a, int lda, const int3
     P.gather_div = pass == 0 ? gather_div : 1;
     P.gather_rows = pass == 0 ? gather_rows : 1;
     P.row_lo = 0;
-    P.row_hi = P.rows_hint = (int)A_cap;
+    P.row_hi = (int)A_cap;
     return P;
 }
 
 bool ffn_skinny_takes(int pass, const FfnLaunch &L);
 bool ffn_skinny_takes_few(FfnLaunch L);
 int launch_ffn_skinny(int pass, const FfnLaunch &L, const FewRoute *few, hipStream_t st);
-bool ffn_mid_rows(int pass, const FfnLaunch &L, int (&rows)[2]);
+bool ffn_mid_rows(int pass, const FfnLaunch &L, int likely, int (&rows)[2]);
 int launch_ffn_mid(int pass, const int (&tile_rows)[2], FfnLaunch L, hipStream_t st);
 
 // Rows of the single group's tiles.  Fewer tiles than a quarter of the CUs, each a chain of k-slices much longer than those
@@ -1052,20 +1052,21 @@ static int *ffn_next_queues(bool both) {
 
 // Launches one pass over one problem (second == nullptr) or over two: the second must be a single
 // group (E_local == 1).  Two go into ONE grid unless the first is a single group as well.
-int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, hipStream_t st) {
+// likely: rows of the first that are likely (<= its A_cap): what the choice of a kernel goes by, and nothing else.
+int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *second, int likely, hipStream_t st) {
     drop_stale_error();
     constexpr int WM = 2, WN = 4;
     if (second && second->E_local != 1) return C2R_ERR_INVALID_ARG;
     if (second && first.E_local == 1) {  // (a launch holds one single group)
-        const int rc = launch_ffn_bf16_dma(pass, first, nullptr, st);
-        return rc != C2R_OK ? rc : launch_ffn_bf16_dma(pass, *second, nullptr, st);
+        const int rc = launch_ffn_bf16_dma(pass, first, nullptr, likely, st);
+        return rc != C2R_OK ? rc : launch_ffn_bf16_dma(pass, *second, nullptr, second->A_cap, st);
     }
     const FfnLaunch L = ffn_launch_of(first, second);
     // Few rows: the kernel of ffn_skinny.hip.  More, but not enough to fill the chip with 256 x 256 tiles: that of ffn_mid.hip.
     // Every output is the same chain of the same matrix instructions in all three, so a row's bits do not depend on the choice.
     if (ffn_skinny_takes(pass, L)) return launch_ffn_skinny(pass, L, nullptr, st);
     int tile_rows[2];
-    if (ffn_mid_rows(pass, L, tile_rows)) return launch_ffn_mid(pass, tile_rows, L, st);
+    if (ffn_mid_rows(pass, L, likely, tile_rows)) return launch_ffn_mid(pass, tile_rows, L, st);
     int *queues = ffn_next_queues(false);
     if (!queues) return C2R_ERR_LAUNCH;
     const dim3 g((unsigned)ffn_grid_of(L)), b(WM * WN * 64);
@@ -1085,15 +1086,15 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
 //     60 experts, whose rows are fewer than that, n = 134 107 / 113, n = 298 148 / 149, n = 426 184 / 183, n = 601 249 / 243: under a round of
 //     tiles there is little to go on with, and what there is waits.
 constexpr int BOTH_BESIDE = 390, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 384;
-static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down) {
+static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely) {
     int rows[2];
     if (ffn_skinny_takes(0, up) || ffn_skinny_takes(1, down)) return false;
     const FfnProblem &R = up.p[0], &S = up.p[1];
-    if (ffn_mid_rows(0, up, rows)) return !up.has_single && R.rows_hint / R.E_local > BOTH_PER_GROUP;
-    if (up.has_single && S.A_cap <= BOTH_BESIDE && ffn_mid_rows(1, down, rows)) return false;
+    if (ffn_mid_rows(0, up, likely, rows)) return !up.has_single && likely / R.E_local > BOTH_PER_GROUP;
+    if (up.has_single && S.A_cap <= BOTH_BESIDE && ffn_mid_rows(1, down, likely, rows)) return false;
     int64_t tiles = up.has_single ? (int64_t)(S.A_cap + 255) / 256 * S.ntn : 0;
-    if (up.has_ragged) tiles += (int64_t)(R.rows_hint / 256 + (R.E_local < R.rows_hint ? R.E_local : R.rows_hint) / 2) * R.ntn;
-    return tiles >= (up.has_ragged && R.rows_hint < R.A_cap ? BOTH_TILES_OF_PART : BOTH_TILES);
+    if (up.has_ragged) tiles += (int64_t)(likely / 256 + (R.E_local < likely ? R.E_local : likely) / 2) * R.ntn;
+    return tiles >= (up.has_ragged && likely < R.A_cap ? BOTH_TILES_OF_PART : BOTH_TILES);
 }
 
 // Whether the down pass may write while the gate/up pass still reads: its outputs meet nothing else of the two (but for one in the place of
@@ -1131,14 +1132,14 @@ static bool ffn_both_apart(const FfnBothLaunch &L) {
 // Both passes over one problem or two (first[pass], second[pass] as above; pass 1 reads the rows that pass 0 writes): one launch where
 // the tile kernel takes both, their buffers are apart, h has whole 128-byte lines and there are counters for all M-tiles (260000 rows: the
 // idle end of a pass is under 1 % of it there).
-int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *const (&second)[2], hipStream_t st) {
+int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *const (&second)[2], int likely, hipStream_t st) {
     constexpr int BM = 256, WM = 2, WN = 4;
     const bool two_single = second[0] && first[0].E_local == 1;
     if (!two_single && (!second[0] || second[0]->E_local == 1)) {
         FfnBothLaunch L;
         int64_t mtiles = 0;
         for (int pass = 0; pass < 2; ++pass) L.pass[pass] = ffn_launch_of(first[pass], second[pass]);
-        bool tiles = both_in_tiles(L.pass[0], L.pass[1]);
+        bool tiles = both_in_tiles(L.pass[0], L.pass[1], likely);
         // An XCD writes whole lines of h: no line is in two XCDs' L2.
         for (int q = 0; q < 2; ++q) {
             const FfnProblem &P = L.pass[0].p[q];
@@ -1156,8 +1157,8 @@ int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *con
             return launch_status();
         }
     }
-    const int rc = launch_ffn_bf16_dma(0, first[0], second[0], st);
-    return rc != C2R_OK ? rc : launch_ffn_bf16_dma(1, first[1], second[1], st);
+    const int rc = launch_ffn_bf16_dma(0, first[0], second[0], likely, st);
+    return rc != C2R_OK ? rc : launch_ffn_bf16_dma(1, first[1], second[1], likely, st);
 }
 
 // Whether the gate/up pass of a few tokens does their selection and index at its start.
@@ -1176,7 +1177,7 @@ int launch_ffn_bf16_dma_pass(int pass, const uint16_t *a, int lda, const int32_t
                              hipStream_t st) {
     const FfnProblem P = ffn_bf16_dma_problem(pass, a, lda, offsets, E_local, A_cap, d, F, b0, b1, out, ldo, gather,
                                               gather_div, gather_rows);
-    return launch_ffn_bf16_dma(pass, P, nullptr, st);
+    return launch_ffn_bf16_dma(pass, P, nullptr, P.A_cap, st);
 }
 
 }  // namespace c2r

@@ -351,7 +351,6 @@ struct FfnProblem {
     uint16_t *out;            // [rows, ldo]
     const int32_t *gather;    // row p of the sorted order is A[gather[p] / gather_div], or nullptr
     int lda, E_local, A_cap, N, Kdim, ldo, ntn, zero_to, gather_div, gather_rows, row_lo, row_hi;
-    int rows_hint;            // rows that are likely (<= A_cap): what the choice of a kernel goes by, and nothing else
 };
 struct FfnLaunch {
     FfnProblem p[2];            // p[0]: the ragged problem (several groups), p[1]: the single group

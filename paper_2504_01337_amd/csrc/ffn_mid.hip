@@ -340,14 +340,14 @@ constexpr int MID_LOW_BESIDE = 4;
 // most rows (likely ones per group / in the single group), for 32-, 64- and 128-row tiles of gate/up and of down
 constexpr int MID_RAGGED_UP_TO[2][3] = {{20, 64, 150}, {20, 45, 90}}, MID_SINGLE_UP_TO[2][2] = {{64, 179}, {100, 511}};
 
-bool ffn_mid_rows(int pass, const FfnLaunch &L, int (&rows)[2]) {
+bool ffn_mid_rows(int pass, const FfnLaunch &L, int likely, int (&rows)[2]) {
     for (int q = 0; q < 2; ++q)
         if ((q == 0 ? L.has_ragged : L.has_single) && L.p[q].gather && (L.p[q].A_cap > MID_ROW_TABLE || L.p[q].gather_rows > 65536))
             return false;
     rows[0] = rows[1] = 0;
     if (L.has_ragged) {
         const int mean = L.p[0].A_cap / L.p[0].E_local, *most = MID_RAGGED_UP_TO[pass];
-        if (L.p[0].rows_hint / L.p[0].E_local > most[2]) return false;
+        if (likely / L.p[0].E_local > most[2]) return false;
         rows[0] = mean <= (L.has_single ? MID_LOW_BESIDE : most[0]) ? 32 : (mean <= most[1] ? 64 : 128);
     }
     if (L.has_single) {
