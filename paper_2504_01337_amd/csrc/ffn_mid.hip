@@ -332,12 +332,15 @@ static void mid_launch(int ragged_rows, int single_rows, const FfnLaunch &L, hip
 //     147, n = 90: 145 / 142 / 147 / 141, n = 131: 163 / 159 / 160 / 161, n = 178: 187 / 190 / 181 / 174; down pass alone n = 300: 197 / 197 /
 //     195 / 187, n = 500: 236 / 228 / 234 / 210 (64+128 216, the tile kernel 212 at 511): no shared tiles of 128.  (The skewed groups beside it
 //     hold up to eight times the mean: 64 rows from a mean of 5; measured on this one model.)
-// (r counts the rows allotted.  A device that holds a quarter of the experts has a quarter of them in use: its tiles are higher
-// than its rows would ask for, 15 of 60 experts at 300 tokens 67.0 / 65.0 / 71.9.  The upper limits go by the rows that are likely: 15
-// of 60 experts, by the rows allotted / so, 400 tokens 81.6 / 75.7, 700 tokens 99.6 / 85.9, 1020 tokens 104.7 / 102.1.)
+// (r counts the rows allotted.  A device that holds a quarter of the experts has a quarter of them in use if the load is even; of a skewed
+// model, whose quarters have 0.5 to 2.1 times that, the heaviest is the one that a group waits for.  Its tiles are higher than its rows
+// would ask for, 15 of 60 experts at 300 tokens 67.0 / 65.0 / 71.9.  The limit of the down pass goes by twice the even share.  Microseconds, 15
+// of 60 experts, by the rows allotted / so: the heaviest quarter 400 tokens 88.0 / 82.8, 600 tokens 95.3 / 88.0, 675 tokens 97.7 / 97.9, a
+// light one 400 tokens 79.4 / 73.2, 675 tokens 94.1 / 86.6; 20 of 60, 500 tokens 97.1 / 90.4.  With the limits of both passes by the even share
+// the light one went on gaining, 700 tokens 91.9 / 82.2, but the heaviest lost: 700 tokens 98.3 / 104.4, 850 tokens 101 / 112, 1000 tokens 105 / 116.)
 constexpr int MID_LOW_BESIDE = 4;
 
-// most rows (likely ones per group / in the single group), for 32-, 64- and 128-row tiles of gate/up and of down
+// most rows (per group, in the down pass at most twice the likely ones / in the single group), for 32-, 64- and 128-row tiles of gate/up and of down
 constexpr int MID_RAGGED_UP_TO[2][3] = {{20, 64, 150}, {20, 45, 90}}, MID_SINGLE_UP_TO[2][2] = {{64, 179}, {100, 511}};
 
 bool ffn_mid_rows(int pass, const FfnLaunch &L, int likely, int (&rows)[2]) {
@@ -347,7 +350,8 @@ bool ffn_mid_rows(int pass, const FfnLaunch &L, int likely, int (&rows)[2]) {
     rows[0] = rows[1] = 0;
     if (L.has_ragged) {
         const int mean = L.p[0].A_cap / L.p[0].E_local, *most = MID_RAGGED_UP_TO[pass];
-        if (likely / L.p[0].E_local > most[2]) return false;
+        const int heavy = pass == 0 || 2ll * likely > L.p[0].A_cap ? L.p[0].A_cap : 2 * likely;
+        if (heavy / L.p[0].E_local > most[2]) return false;
         rows[0] = mean <= (L.has_single ? MID_LOW_BESIDE : most[0]) ? 32 : (mean <= most[1] ? 64 : 128);
     }
     if (L.has_single) {
