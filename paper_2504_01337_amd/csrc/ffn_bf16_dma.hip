@@ -1082,10 +1082,13 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
 //     187, 320 tokens 187 / 201, 380 tokens 199 / 203, 400 tokens 198 / 188, 500 tokens 205 / 187;
 //   gate/up in ffn_mid, routed groups alone, r rows per expert: 16 experts of d 4096, r = 92 122.5 / 122.4, r = 125 128.4 / 132.6, r = 130
 //     144.7 / 134.0 (a chunk more per group), r = 147 152.8 / 138.0; 8 experts, r = 100 120 / 128, r = 125 141.7 / 135.2, r = 147 155.2 / 141.9.
-//   both in tiles, n likely gate/up tiles: 16 experts of d 4096, n = 132 155 / 162, n = 188 184 / 179; 8 experts, n = 215 189 / 189; with 15 of
-//     60 experts, whose rows are fewer than that, n = 134 107 / 113, n = 298 148 / 149, n = 426 184 / 183, n = 601 249 / 243: under a round of
-//     tiles there is little to go on with, and what there is waits.
-constexpr int BOTH_BESIDE = 390, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 384;
+//   both in tiles, n gate/up tiles if the load is even: 16 experts of d 4096, n = 132 155 / 162, n = 188 184 / 179; 8 experts, n = 215 189 / 189:
+//     under a round of tiles there is little to go on with, and what there is waits;
+//   so with a part of the experts, whose rows are 0.5 to 2.1 times n's (skewed load): 15 of 60 experts, three light quarters and the heaviest,
+//     n = 385 170 / 173, 166 / 166, 190 / 193, 319 / 294, n = 429 181 / 183, 173 / 175, 205 / 201, 356 / 328, n = 462 201 / 201, 194 / 193, 231 / 225;
+//     30 of 60, the light half n = 385 167 / 172, n = 407 170 / 174, n = 440 174 / 163, the heavy one n = 385 211 / 210, n = 506 269 / 257.
+// (BOTH_BESIDE is measured on that one shape.)
+constexpr int BOTH_BESIDE = 390, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 435;
 static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely) {
     int rows[2];
     if (ffn_skinny_takes(0, up) || ffn_skinny_takes(1, down)) return false;

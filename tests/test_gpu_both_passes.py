@@ -70,7 +70,8 @@ def test_layer_with_shared_expert(c2r, T, d, F, Fs):
 # the layer call on either side of the rules that give a pass to this kernel or that: 390 rows of a shared expert, 125 likely rows per expert,
 # 4096 rows allotted to a device with a part of the experts.  The same bits as stage by stage, where every pass chooses by the rows allotted.
 @pytest.mark.parametrize("T,E,El,K,Fs", [(390, 60, 60, 4, 192), (391, 60, 60, 4, 192), (501, 16, 16, 4, 0), (504, 16, 16, 4, 0), (600, 16, 16, 4, 0),
-                                         (1000, 60, 15, 4, 0), (1024, 60, 15, 4, 0), (1025, 60, 15, 4, 0), (2100, 60, 15, 4, 0), (15500, 60, 15, 4, 0), (300, 64, 1, 4, 0)])
+                                         (1000, 60, 15, 4, 0), (1024, 60, 15, 4, 0), (1025, 60, 15, 4, 0), (2100, 60, 15, 4, 0), (15500, 60, 15, 4, 0),
+                                         (16384, 60, 15, 4, 0), (17000, 60, 15, 4, 0), (300, 64, 1, 4, 0)])
 def test_layer_at_the_limits_of_the_kernels(c2r, T, E, El, K, Fs):
     rng = np.random.default_rng(T + E)
     d, F = 128, 704
