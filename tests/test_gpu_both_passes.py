@@ -20,7 +20,7 @@ def _weights(rng, *shapes):
     return [dev((rng.standard_normal(s) * 0.05).astype(np.float32), "bf16") for s in shapes]
 
 
-# full, short and tiny tiles and empty groups; one group; fewer M-tiles than XCDs; rows not all in use; a column tail (192, 320); one
+# full, short and tiny tiles and empty groups; one group; fewer M-tiles than XCDs; rows not all in use; a column tail (d 192); one
 # slice (64); as many M-tiles as there are counters (1024) and one more (two launches); N-tiles enough for the rule to take one launch
 @pytest.mark.parametrize("d,F,sizes,cap", [
     (64, 2560, [256, 257, 511, 129, 128, 64, 65, 1, 0, 1000], 2600), (64, 8192, [3000, 0, 1], 3001), (192, 7744, [700], 800), (512, 8192, [300, 299], 599),
@@ -89,3 +89,53 @@ def test_layer_at_the_limits_of_the_kernels(c2r, T, E, El, K, Fs):
     for _ in range(3):
         layer.h.fill_(float("nan"))
         assert torch.equal(layer.forward(x), ref)
+
+
+# widths that are no whole slices: the first pass keeps the padding columns of h at zero in its workspace.  Zero weights there in launches of
+# their own give the same sums.
+@pytest.mark.parametrize("d,F,sizes,cap", [(128, 688, [900, 513, 130, 0, 64, 1] * 4, 6500), (64, 2568, [700, 257, 33, 1000], 2000), (192, 7688, [700], 800)])
+def test_padded_widths(c2r, d, F, sizes, cap):
+    rng = np.random.default_rng(d + F)
+    E, n, K, Fp = len(sizes), sum(sizes), 2, -(-F // 64) * 64
+    assert Fp > F and ffn_kernel(0, E, cap, Fp) == ffn_kernel(1, E, cap, d) == "tile" and ffn_tiles(E, cap, Fp) >= ffn_tiles_limit()
+    T = (cap + K - 1) // K
+    x = dev(rng.standard_normal((T, d)).astype(np.float32), "bf16")
+    perm = dev(np.concatenate([rng.permutation(T * K)[:n], np.full(cap - n, -1)]).astype(np.int32))
+    offsets = dev(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
+    wg, wu, wd = _weights(rng, (E, F, d), (E, F, d), (E, d, F))
+    pad = lambda w, dim: torch.cat([w, torch.zeros([Fp - F if i == dim else s for i, s in enumerate(w.shape)], dtype=w.dtype, device="cuda")], dim).contiguous()
+    h, y = (torch.full((cap, c), 7.0, dtype=torch.bfloat16, device="cuda") for c in (Fp, d))
+    c2r.expert_ffn_gate_up_gather(x, perm, K, offsets, pad(wg, 1), pad(wu, 1), h)
+    c2r.expert_ffn_down(h, offsets, pad(wd, 2), y)
+    x_perm = torch.zeros((cap, d), dtype=torch.bfloat16, device="cuda")
+    x_perm[:n] = x[(perm[:n] // K).long()]
+    ws = torch.empty(c2r.workspace_bytes(c2r.STAGE_EXPERT_FFN, cap, d, E, 1, F, c2r.BF16), dtype=torch.uint8, device="cuda")
+    for _ in range(3):
+        for call in (lambda o: c2r.expert_ffn_gather(x, perm, K, offsets, wg, wu, wd, ws=ws, out=o),
+                     lambda o: c2r.expert_ffn(x_perm, offsets, wg, wu, wd, ws=ws, out=o)):
+            got = torch.full((cap, d), 7.0, dtype=torch.bfloat16, device="cuda")
+            ws.fill_(255)
+            assert torch.equal(call(got), y)
+
+
+# two layers on two streams: a tile of either waits only for workgroups of its own launch that run
+def test_beside_another_launch(c2r):
+    layers, xs, refs = [], [], []
+    for seed, (T, d, F, Fs) in enumerate([(1300, 128, 832, 2560), (3000, 256, 448, 1024)]):
+        rng = np.random.default_rng(seed)
+        E, K = 16, 4
+        assert ffn_tiles(E, T * K, F) + ffn_tiles(1, T, Fs) >= ffn_tiles_limit()
+        Wg = dev((rng.standard_normal((d, E)) * 0.05 + np.linspace(0, 0.1, E)).astype(np.float32))
+        layers.append(c2r.C2RLayer(T, d, E, K, F, torch.bfloat16, Wg, None, None, *_weights(rng, (E, F, d), (E, F, d), (E, d, F)),
+                                   shared=tuple(_weights(rng, (1, Fs, d), (1, Fs, d), (1, d, Fs)))))
+        xs.append(dev(rng.standard_normal((T, d)).astype(np.float32), "bf16"))
+        refs.append(layers[-1].forward(xs[-1]).clone())
+    streams = [torch.cuda.Stream() for _ in layers]
+    outs = [[torch.empty_like(r) for _ in range(12)] for r in refs]
+    torch.cuda.synchronize()
+    for i in range(12):
+        for layer, x, stream, out in zip(layers, xs, streams, outs):
+            with torch.cuda.stream(stream):
+                out[i].copy_(layer.forward(x))
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, ref) for out, ref in zip(outs, refs) for o in out)

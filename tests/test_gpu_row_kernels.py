@@ -110,15 +110,16 @@ def test_dedup_index_in_one_launch(c2r, orc, T, K, n_dev):
         assert np.array_equal(host(row).reshape(-1), np.asarray(rr).reshape(-1))
 
 
-# the two-level combine by whole row pieces: one, two and three of them, 1 to 64 slots and one more (the other kernels); tokens without
+# the two-level combine by whole row pieces: one, two and three of them, and rows that are not; 1 to 64 slots and one more (the other kernels); tokens without
 # a copy, an expert that is not computed here
 @pytest.mark.parametrize("dtype,T,K,d", [("bf16", 1, 1, 1024), ("bf16", 37, 4, 2048), ("bf16", 9, 3, 3072), ("bf16", 3, 64, 1024), ("f32", 33, 7, 512),
-                                         ("f32", 5, 2, 1536), ("bf16", 70, 4, 1536)])
+                                         ("f32", 5, 2, 1536), ("bf16", 70, 4, 1536), ("bf16", 6, 65, 1024)])
 def test_two_level_combine_by_row_pieces(c2r, orc, dtype, T, K, d):
     rng = np.random.default_rng(T + K + d)
     store = wl.round_bf16 if dtype == "bf16" else (lambda a: a)
     E, n_dev = 64, 5
     idx = np.argsort(rng.random((T, E)), axis=1)[:, :K].astype(np.int32)
+    idx = np.concatenate([idx, np.full((T, K - idx.shape[1]), -1, dtype=np.int32)], axis=1)  # (no more than E are there)
     idx[T // 2] = -1
     devmap = rng.integers(-1, n_dev, size=E).astype(np.int32)
     inv = rng.permutation(T * K).astype(np.int32)

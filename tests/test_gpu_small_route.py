@@ -91,6 +91,74 @@ def _layer_call_routes_like_the_stages(c2r, T, E, K, El, dtype, d):
         assert torch.equal(layer.x_perm[:n], rows[:n])
 
 
+# the same with lists of distinct experts and logits that spread the tokens over all of them, whose gates are numbers, and with NaNs and
+# infinities in the logits of some tokens only (both forms of the scan in one batch)
+@pytest.mark.parametrize("T,E,K,El,dtype,d", [
+    (1, 60, 4, 60, "bf16", 64), (16, 16, 2, 16, "bf16", 64), (8, 60, 4, 60, "bf16", 64), (10, 40, 3, 20, "bf16", 64), (32, 60, 4, 60, "bf16", 64), (43, 60, 3, 31, "bf16", 64),
+    (64, 60, 4, 15, "bf16", 64), (64, 64, 16, 64, "bf16", 64), (61, 64, 17, 30, "bf16", 64), (63, 17, 2, 9, "f32", 64),
+    (65, 16, 4, 16, "bf16", 64), (128, 16, 4, 7, "bf16", 4096), (1024, 8, 2, 8, "f32", 256), (512, 16, 3, 5, "f32", 520), (999, 13, 4, 2, "bf16", 264)])
+def test_layer_call_routes_like_the_stages_over_all_experts(c2r, T, E, K, El, dtype, d):
+    rng = np.random.default_rng(T * E + K)
+    w = lambda *s: dev((rng.standard_normal(s) * 0.1).astype(np.float32), dtype)
+    ls = None
+    if El < E:
+        ls = np.full(E, -1, dtype=np.int32)
+        ls[rng.permutation(E)[:El]] = rng.permutation(El).astype(np.int32)
+    lists = np.stack([rng.permutation(np.delete(np.arange(E), e))[:min(K + 3, E - 1)] for e in range(E)]).astype(np.int32)
+    layer = c2r.C2RLayer(T, d, E, K, 64, torch.bfloat16 if dtype == "bf16" else torch.float32, dev(rng.standard_normal((d, E)).astype(np.float32)),
+                         dev((rng.standard_normal(E) * 0.1).astype(np.float32)), dev(lists), w(El, 64, d), w(El, 64, d), w(El, d, 64),
+                         local_slot=dev(ls), E_local=El)
+    finite = rng.standard_normal((T, d)).astype(np.float32)
+    mixed = finite.copy()
+    mixed[1::5, 0] = np.inf    # logits of both infinities
+    mixed[3::7, 1] = np.nan    # NaN throughout
+    for x in (finite, mixed):
+        x = dev(x, dtype)
+        layer.perm.fill_(-1)
+        layer.forward(x)
+        idx, gates, _ = c2r.route(x, layer.Wg, layer.bias, K, layer.collab_idx)
+        counts, offsets, perm, inv, rows = c2r.permute(x, idx, E, layer.local_slot, El)
+        assert torch.equal(layer.idx, idx) and torch.equal(layer.gates.view(torch.int32), gates.view(torch.int32))
+        assert torch.equal(layer.counts, counts) and torch.equal(layer.offsets, offsets) and torch.equal(layer.inv_perm, inv)
+        n = int(offsets[-1])
+        assert torch.equal(layer.perm[:n], perm[:n]) and bool((layer.perm[n:] == -1).all())
+        if layer.x_perm is not None:
+            assert torch.equal(layer.x_perm[:n].view(torch.int16 if dtype == "bf16" else torch.int32), rows[:n].view(torch.int16 if dtype == "bf16" else torch.int32))
+        if x.isfinite().all():
+            assert bool(gates.isfinite().all()) and bool((idx >= 0).all())
+            assert len(torch.unique(idx[:, 0])) >= min(T, E) // 2 and int((counts > 0).sum()) >= min(T * K * El // E, El) // 2
+
+
+# the expert FFN of such a batch: every gate/up workgroup selects for itself, and its rows and their places are what it found.  One to 16 tokens,
+# on either side of 2304 workgroups (72 and 76 column blocks of 32 rows), of 32 assignments and of 8 tokens beside a shared expert
+@pytest.mark.parametrize("T,E,K,El,F,Fs", [
+    (1, 60, 4, 60, 704, 0), (1, 60, 4, 60, 704, 1408), (3, 60, 4, 60, 64, 320), (7, 60, 4, 15, 128, 0), (2, 60, 4, 4, 64, 64), (8, 60, 4, 60, 704, 1408), (8, 60, 4, 60, 1152, 0),
+    (8, 60, 4, 60, 1216, 0), (16, 16, 2, 16, 704, 0), (9, 32, 3, 32, 128, 320), (11, 20, 3, 20, 128, 0), (8, 32, 4, 32, 128, 320), (5, 20, 4, 20, 72, 0)])
+def test_expert_ffn_of_the_smallest_batches(c2r, T, E, K, El, F, Fs):
+    rng = np.random.default_rng(T + E + F)
+    d = 128
+    w = lambda *s: dev((rng.standard_normal(s) * 0.1).astype(np.float32), "bf16")
+    ls = None
+    if El < E:
+        ls = np.full(E, -1, dtype=np.int32)
+        ls[rng.permutation(E)[:El]] = rng.permutation(El).astype(np.int32)
+    lists = np.stack([rng.permutation(np.delete(np.arange(E), e))[:K + 3] for e in range(E)]).astype(np.int32)
+    layer = c2r.C2RLayer(T, d, E, K, F, torch.bfloat16, w(d, E).float(), None, dev(lists), w(El, F, d), w(El, F, d), w(El, d, F), local_slot=dev(ls),
+                         E_local=El, shared=(w(1, Fs, d), w(1, Fs, d), w(1, d, Fs)) if Fs else None)
+    assert layer.fuse_shared == bool(Fs) and layer.x_perm is None
+    for _ in range(3):
+        x = w(T, d)
+        results = []
+        for kw in ({"trace": {}}, {}):
+            for t in (layer.y, layer.y_perm, layer.y_shared, layer.h, layer.__dict__.get("h_shared"), layer.__dict__.get("ws_ffn")):
+                if t is not None:
+                    t.view(torch.uint8).fill_(255)
+            y = layer.forward(x, **kw).clone()
+            n = int(layer.offsets[-1])
+            results.append((y, layer.y_perm[:n].clone(), layer.idx.clone()) + ((layer.y_shared.clone(),) if Fs else ()))
+        assert bool(results[0][0].isfinite().all()) and all(torch.equal(a, b) for a, b in zip(*results))
+
+
 # K = 1 takes lists of no entries (Tc >= K - 1); the array then holds nothing that may be read, also where it is not NULL.  (The pointer
 # lies inside an allocation here.)  Batches of the two routers, and the one-launch selection and index of the layer call.
 @pytest.mark.parametrize("T,E,d,dtype", [(1, 60, 256, "bf16"), (70, 8, 64, "f32"), (12289, 5, 264, "f32")])
