@@ -216,9 +216,9 @@ int c2r_permute_noalloc(const void *x, c2r_dtype dt, const int32_t *topk_idx, in
  * and x itself as x_perm.
  * Concurrency (this and every other c2r_expert_ffn_* call, bf16 shapes of the fast kernel): a
  * launch hands its tiles out through a set of counters in a static device array; the library
- * holds 64 sets per GPU (and 64 for launches of both passes) and gives them to launches in turn, and a set is all zero again when its
- * launch ends.  Two launches that were given the same set (every 64th call) must not RUN at the
- * same time: on one stream they never do, however many are queued; a caller that spreads these
+ * holds 64 sets per GPU (and 64 more for launches of both passes) and gives them to launches in turn, and a set is all zero
+ * again when its launch ends.  Two launches that were given the same set (every 64th call) must not RUN at the
+ * same time: tiles would be left out, and two launches of both passes may wait for ever for rows that the other one counted.  On one stream they never do, however many are queued; a caller that spreads these
  * calls over several streams keeps fewer than 64 of them outstanding (enqueued and not finished)
  * per GPU.  A launch recorded into a HIP graph keeps the set it was given at capture: replays of
  * that graph must not overlap each other.

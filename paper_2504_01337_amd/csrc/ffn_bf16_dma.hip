@@ -82,7 +82,11 @@ __device__ __forceinline__ int xcd_list_slots(int n_tiles) {
 // the next ticket there, so that the trip to the counter overlaps the epilogue); not called on
 // the early returns.
 // BOTH: the launch carries both passes; `link` ties the tile to the other one and under_way() is called once by every wave after a
-// barrier behind which this wave's and every other wave's memory operations from before the call are complete.
+// barrier behind which this wave's and every other wave's memory operations from before the call are complete.  Every wave has waited there
+// until no more than its copies of the later slices are outstanding.  That covers the older stores because a wave's loads, stores and copies
+// count down ONE counter in the order of their issue on gfx9 targets, and gfx950 is the only one this is built for (LLVM, "User Guide for AMDGPU
+// Backend", memory model: vector memory operations' completion is reported to a wavefront in execution order).  A store with sc1 is
+// the guide's atomic store at agent scope, whose completion a release at that scope waits for with the same counter.
 template <int MODE, int WM, int WN, bool BOTH, class UnderWay, class BeforeEpilogue>
 __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *smem, const int xcd, const int slot,
                                          const int grp_lo, const int grp_hi, const int sg_lo, const int sg_hi,
@@ -880,8 +884,9 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
         // copies may overwrite the stages.  The epilogue's stores are NOT waited for (a workgroup
         // that ends does not wait for its stores either): they drain while the next tile is looked
         // up and its first slices are requested.  The copy waits of the next tile stay correct with
-        // stores in flight: they ask for "at most N operations outstanding", copies complete in
-        // order among themselves, so older stores still in flight only make a wait longer.
+        // stores in flight: they ask for "at most N operations outstanding", and what is older completes
+        // first, so stores still in flight only make a wait longer.  Beside the down pass more rests on that
+        // order: the first slice's wait is what the stores of h are known to be complete by (see ffn_tile).
         wait_lds_only();
         lds_barrier();
     }
@@ -929,9 +934,8 @@ __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_kernel(const FfnLaun
 // finished; the order of the lists makes that rare (1 to 5 us per CU).  h is written through to the memory that all XCDs share (store16_through),
 // counted per M-tile once a barrier behind the stores' completion has been passed, and read after the reader's caches are emptied.
 // Layer call of the three, two launches / this: 254 / 231, 360 / 331, 469 / 439; 8192 tokens of the first, which the power limit bounds,
-// 1043 / 1036.  Starting the down lists where the share begins instead of at the XCD's first own
-// chunk: 230.3
-// against 228.2, 336 against 330.5, 446 against 435; short gate/up tiles last, as in a launch of their own: 334.9 against 330.5 for the second.
+// are even.  Starting the down lists where the share begins instead of at the XCD's first own chunk: 230.3 against 228.2, 336 against 330.5, 446
+// against 435; short gate/up tiles last, as in a launch of their own: 334.9 against 330.5 for the second.
 template <int WM, int WN>
 __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_both_kernel(const FfnBothLaunch L, int *__restrict__ queues, int n_mtiles) {
     typedef FfnShape<WM, WN> S;
