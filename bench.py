@@ -372,6 +372,8 @@ def main():
     sep_shared = bool(shared) and not L.fuse_shared      # the shared expert has launches of its own
     dom_stages = [s for s in ("ffn_gate_up", "shared_gate_up") if s in stages]   # launches of the dominant kernel
     mk = lambda: torch.cuda.Event(enable_timing=True)
+    # (A step that carries events runs stage by stage, a launch per FFN pass; the others put both passes into
+    # one launch where the library does.)
     # timed region: only the dominant kernel's launches carry events, and only on every fourth
     # step (an event record holds the stream for 5.6 us: fourteen per step were 3 % of the step,
     # the four around the two gate/up launches still 1.9 %)
@@ -614,7 +616,9 @@ def main():
     if sep_shared and not L.split_shared:
         dom_fl += fl_sdn / n_launch
     if not L.fuse_gather:
-        both = " and <1> (both passes of c2r_expert_ffn)"
+        # (bf16: in one launch, ffn_bf16_dma_both_kernel, where the library does so)
+        both = " and <1> (both passes of c2r_expert_ffn)" if w.dtype != "bf16" else \
+            ", <1> or ffn_bf16_dma_both_kernel (both passes of the call)"
         for k_gu, k_dn in (("ffn_gate_up", "ffn_down"), ("shared_gate_up", "shared_down")):
             if k_gu in stage_info and k_dn in stage_info:
                 stage_info[k_gu]["note"] = "both passes (c2r_expert_ffn); flops of gate/up only in TFLOPs"
@@ -627,7 +631,8 @@ def main():
                     "traffic_source": traffic_src,
                     "avg_launch_ms": dom_ms, "launches_per_step": n_launch, "launches_timed": dom_launches_timed,
                     "timed_by": "event pairs on the launch stream around every fourth step's launches, inside the "
-                                "timed region (a pair brackets the marker latency too: a few per cent more than "
+                                "timed region (those steps run stage by stage, the others put both FFN passes into one "
+                                "launch where the library does; a pair brackets the marker latency too: a few per cent more than "
                                 "the kernel's own duration in the rocprofv3 trace)"}
     else:
         # (the fp32 matrix peak is the vector peak)
