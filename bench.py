@@ -389,8 +389,10 @@ def main():
             L.forward(x)
         torch.cuda.synchronize()
         ramp_steps += 8
-    for _ in range(args.warmup):
-        L.forward(x)
+    # (a kernel's first launch loads its code, which takes about a millisecond: the warm-up runs both schedules)
+    ev_warm = {s: (mk(), mk()) for s in dom_stages}
+    for i in range(args.warmup):
+        L.forward(x, trace=ev_warm if i % ev_every == 0 else None)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for i in range(args.steps):
