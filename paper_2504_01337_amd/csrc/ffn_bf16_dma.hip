@@ -89,7 +89,8 @@ __device__ __forceinline__ int xcd_list_slots(int n_tiles) {
 // count down ONE counter in the order of their issue on gfx9 targets, and gfx950 is the only one this is built for (LLVM, "User Guide for AMDGPU
 // Backend", memory model: vector memory operations' completion is reported to a wavefront in execution order).  A store with sc1 is
 // the guide's atomic store at agent scope, whose completion a release at that scope waits for with the same counter.
-template <int MODE, int WM, int WN, bool BOTH, class UnderWay, class BeforeEpilogue>
+// EARLY: the single group's tiles come before all others of their pass (see ffn_bf16_dma_both_kernel).
+template <int MODE, int WM, int WN, bool BOTH, bool EARLY, class UnderWay, class BeforeEpilogue>
 __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *smem, const int xcd, const int slot,
                                          const int grp_lo, const int grp_hi, const int sg_lo, const int sg_hi,
                                          FfnTileLink &link, UnderWay &&under_way, BeforeEpilogue &&before_epilogue) {
@@ -177,11 +178,14 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
     // it (few enough of them that they do not have to share HBM: FILL_TAIL per XCD).
     constexpr int FILL_TAIL = BESIDE ? 0 : 12;
     const int n_b = __builtin_amdgcn_readfirstlane(rb.cnt);
-    const int n_tail = n_b < FILL_TAIL ? n_b : FILL_TAIL, n_bi = n_b - n_tail, n_main = n_s + n_a + n_bi;
-    const bool in_tail = ts.idx >= n_main;
-    const int b_before = in_tail ? n_bi + (ts.idx - n_main)
-                                 : (int)((uint32_t)ts.idx * (uint32_t)n_bi / (uint32_t)(n_main > 0 ? n_main : 1));
-    const bool is_b = in_tail || (int)(((uint32_t)ts.idx + 1u) * (uint32_t)n_bi / (uint32_t)(n_main > 0 ? n_main : 1)) > b_before;
+    const int n_first = EARLY ? n_s : 0;
+    const int n_tail = n_b < FILL_TAIL ? n_b : FILL_TAIL, n_bi = n_b - n_tail, n_main = n_s + n_a + n_bi - n_first, idx = ts.idx - n_first;
+    const bool in_tail = idx >= n_main, first_of_all = EARLY && idx < 0;
+    const int b_before = first_of_all ? 0
+                         : in_tail    ? n_bi + (idx - n_main)
+                                      : (int)((uint32_t)idx * (uint32_t)n_bi / (uint32_t)(n_main > 0 ? n_main : 1));
+    const bool is_b = !first_of_all &&
+                      (in_tail || (int)(((uint32_t)idx + 1u) * (uint32_t)n_bi / (uint32_t)(n_main > 0 ? n_main : 1)) > b_before);
     const int o_rank = ts.idx - b_before;  // rank among the other items
     const bool second = !is_b && o_rank < n_s;  // workgroup-uniform: this tile is the single group's (p[1])
     GroupTile g;
@@ -745,6 +749,8 @@ struct FfnWalk {
     int up_slots;      // both passes: positions of all the lists of the first
     int ticket;        // and (lane 0 of the first wave) the first ticket of the workgroup's own list of the pass
     int n_mtiles;      // and the M-tiles that there are counters for
+    int early;         // EARLY: the position of a down tile that comes before the gate/up tiles that are left; -1: none is left
+    bool holds;        // EARLY: `ticket` is of the second pass already
 };
 
 __device__ __forceinline__ void ffn_walk_init(FfnWalk &w, const FfnLaunch &L) {
@@ -762,8 +768,12 @@ __device__ __forceinline__ void ffn_walk_init(FfnWalk &w, const FfnLaunch &L) {
 
 // One workgroup's way through the lists of a pass: tiles until none are left.
 // KERNARG: where the pass's FfnLaunch lies in the kernel-argument segment.
-template <int MODE, int WM, int WN, bool BOTH, int KERNARG>
-__device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, const int up_ntn_ragged, const int up_ntn_single) {
+// EARLY: the first pass ends (for now) as well where a down tile of the single group comes next, and the second walks that one alone.
+// down_single: the single group's tiles in the down pass; begin: the first pass is entered for the first time.
+constexpr int FFN_NEVER = 0x7fffffff;
+template <int MODE, int WM, int WN, bool BOTH, bool EARLY, int KERNARG>
+__device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, const int up_ntn_ragged, const int up_ntn_single,
+                                               const int down_single, const bool begin) {
     typedef FfnShape<WM, WN> S;
     int *const queues = W.queues + (BOTH && MODE == 1 ? FFN_DOWN : 0);
     // The claimed position (XCD of the list, slot; -1: nothing left) is handed to the waves in
@@ -775,7 +785,10 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
     const int tid = threadIdx.x, lane = tid & 63;
     const int home = (int)(blockIdx.x & 7);
     // the first wave works the queues; its lane x < 8 keeps the number of slots of XCD x's list
-    int my_len = 0;
+    int my_len = 0, my_single = 0;
+    // EARLY: the position of its own list from which on a workgroup takes the single group's down tiles, of which its XCD has n_early:
+    // all positions that start along with the last round of that group's gate/up tiles are handed out then, and those tiles nearly finished
+    int early_from = FFN_NEVER, n_early = 0;
     if (tid < 64) {
         const int n_s = (W.sg_hi - W.sg_lo + L.single_rows - 1) / L.single_rows * (L.has_single ? L.p[1].ntn : 0);
         int totA = 0, totB = 0;
@@ -785,9 +798,20 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
             totB = m.totalB * L.p[0].ntn;
         }
         const int x = lane & 7;
-        my_len = xcd_list_slots<BOTH && MODE == 0>(equal_range(n_s, x).cnt + equal_range(totA, x).cnt + equal_range(totB, x).cnt);
-        if (BOTH && MODE == 0)
+        my_single = equal_range(n_s, x).cnt;
+        const int my_tiles = my_single + equal_range(totA, x).cnt + equal_range(totB, x).cnt;
+        my_len = xcd_list_slots<BOTH && MODE == 0>(my_tiles);
+        if (BOTH && MODE == 0) {
+            W.up_slots = 0;
             for (int i = 0; i < 8; ++i) W.up_slots += __builtin_amdgcn_readlane(my_len, i);
+        }
+        if (EARLY && MODE == 0) {
+            const int n = __builtin_amdgcn_readlane(my_single, home);
+            const int from = 2 * ((n + CUS_PER_XCD - 1) / CUS_PER_XCD * CUS_PER_XCD) - n;
+            n_early = equal_range(down_single, home).cnt;
+            if (n_early > 0 && from < __builtin_amdgcn_readlane(my_len, home)) early_from = from;
+            if (my_single > my_tiles / CUS_PER_XCD * CUS_PER_XCD) my_single = my_len;  // (some of them are cut into parts)
+        }
     }
     // The first position of every workgroup is its own number in its XCD (no trip to the counter
     // before the first tile); the counters hand out what lies beyond those.  Not so where a pass waits for the other:
@@ -797,8 +821,9 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
     constexpr bool OWN_FIRST = !BOTH;
     auto beyond = [](int x) { return OWN_FIRST ? ((int)gridDim.x - x + 7) >> 3 : 0; };
     int q = home;        // the queue this workgroup draws from: its own XCD's until that is empty
-    int ticket = OWN_FIRST ? (int)(blockIdx.x >> 3) : W.ticket;  // (lane 0 of the first wave) a ticket of queue q drawn ahead
-    bool drawn = true;                                           // such a ticket is at hand
+    // (lane 0 of the first wave) a ticket of queue q drawn ahead
+    int ticket = OWN_FIRST ? (int)(blockIdx.x >> 3) : EARLY && MODE == 1 && W.early >= 0 ? W.early : W.ticket;
+    bool drawn = !(EARLY && MODE == 0) || begin;  // such a ticket is at hand
     bool first = true;
     FfnTileLink link;
     link.ready = false;
@@ -824,7 +849,7 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
             // Every trip ends by checking the ticket it holds, so no valid ticket is ever dropped.
             // A ticket that comes back past the end of its list (another workgroup was faster) makes
             // that list look empty from then on, so at most one draw per list fails: 9 trips at most.
-            int t = -1;
+            int t = -1, early = -1;
             bool have = drawn;  // the ticket drawn during the last epilogue, or the static first one
             drawn = false;
             for (int tries = 0; tries < 16; ++tries) {
@@ -834,7 +859,24 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
                     // that finds them all empty leaves at once - drawing from eight empty queues one
                     // after the other cost 15 us at the end of every launch.
                     const int x = lane & 7;
-                    const int seen = __hip_atomic_load(&queues[x * FFN_LINE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + beyond(x);
+                    const int *counter = &queues[x * FFN_LINE];
+                    if (EARLY && MODE == 0 && lane >= 8) counter = &queues[FFN_DOWN + home * FFN_LINE];
+                    const int seen = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + beyond(x);
+                    if (EARLY && MODE == 0 && early_from != FFN_NEVER) {
+                        // A down tile may wait for the single group's gate/up tiles once all of those are drawn, each by a workgroup that
+                        // runs and waits for nothing before it has finished them.
+                        if (__builtin_amdgcn_readlane(seen, 8) >= n_early) {
+                            early_from = FFN_NEVER;
+                        } else if (__builtin_amdgcn_readlane(seen, home) >= early_from && __ballot(lane < 8 && seen < my_single) == 0) {
+                            if (lane == 0) ticket = atomicAdd(&queues[FFN_DOWN + home * FFN_LINE], 1);
+                            early = __builtin_amdgcn_readfirstlane(ticket);
+                            if (early < n_early) break;
+                            W.ticket = early;  // (another workgroup was faster: it is this one's first of the down pass)
+                            W.holds = true;
+                            early = -1;
+                            early_from = FFN_NEVER;
+                        }
+                    }
                     const uint32_t avail = (uint32_t)__ballot(lane < 8 && seen < my_len) & 0xffu;
                     if (avail == 0) break;  // (t is -1)
                     // own XCD's list first, then the next one (cyclically) that holds something
@@ -856,6 +898,7 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
             if (lane == 0) {
                 claim[0] = q;
                 claim[1] = t;
+                if (EARLY && MODE == 0) claim[2] = early;
                 if (BOTH && MODE == 1) claim[2] = link.ready ? 1 : 0;
             }
         }
@@ -863,8 +906,10 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
         lds_barrier();  // the claim is visible
         q = __builtin_amdgcn_readfirstlane(claim[0]);
         const int slot = __builtin_amdgcn_readfirstlane(claim[1]);
-        if (slot < 0) {  // every queue is empty
-            if (BOTH && MODE == 0 && tid == 0) W.ticket = atomicAdd(&W.queues[FFN_DOWN + home * FFN_LINE], 1);
+        if (slot < 0) {  // every queue is empty, or a down tile comes first
+            if (EARLY && MODE == 0) W.early = __builtin_amdgcn_readfirstlane(claim[2]);
+            if (BOTH && MODE == 0 && tid == 0 && !(EARLY && (W.early >= 0 || W.holds)))
+                W.ticket = atomicAdd(&W.queues[FFN_DOWN + home * FFN_LINE], 1);
             break;
         }
         if (BOTH && MODE == 1) link.ready = __builtin_amdgcn_readfirstlane(claim[2]) != 0;
@@ -875,12 +920,13 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
         drawn = false;
         link.mt = -1;
         bool begun = false;
-        ffn_tile<MODE, WM, WN, BOTH>(
+        ffn_tile<MODE, WM, WN, BOTH, EARLY>(
             Lp, W.smem, q, slot, W.grp_lo, W.grp_hi, W.sg_lo, W.sg_hi, link, post,
             [&]() {
-                // the next ticket of the same queue, drawn while the epilogue runs
-                if (tid == 0) ticket = atomicAdd(&queues[q * FFN_LINE], 1) + beyond(q);
-                drawn = begun = true;
+                // the next ticket of the same queue, drawn while the epilogue runs (but none where a down tile may come first)
+                begun = true;
+                drawn = !EARLY || (MODE == 0 ? q != home || slot + CUS_PER_XCD < early_from : W.early < 0);
+                if (tid == 0 && drawn) ticket = atomicAdd(&queues[q * FFN_LINE], 1) + beyond(q);
             });
         if (BOTH && MODE == 0) {
             if (begun) {  // (else the position held nothing, and what was to be posted still is)
@@ -898,6 +944,7 @@ __device__ __forceinline__ void ffn_walk_lists(FfnWalk &W, const FfnLaunch &L, c
         // order: the first slice's wait is what the stores of h are known to be complete by (see ffn_tile).
         wait_lds_only();
         lds_barrier();
+        if (EARLY && MODE == 1 && W.early >= 0) break;
     }
     if (BOTH && MODE == 0) {  // no tile follows whose first slice the last stores could be posted behind
         wait_copies_but<0>();
@@ -930,8 +977,10 @@ __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_kernel(const FfnLaun
     W.smem = smem;
     W.queues = queues;
     W.n_mtiles = W.ticket = 0;
+    W.early = -1;
+    W.holds = false;
     ffn_walk_init(W, L);
-    ffn_walk_lists<MODE, WM, WN, false, 0>(W, L, 0, 0);
+    ffn_walk_lists<MODE, WM, WN, false, false, 0>(W, L, 0, 0, 0, true);
     if (threadIdx.x == 0 && ffn_last_to_leave(queues))
         for (int i = 0; i <= FFN_LEFT; i += FFN_LINE) atomicExch(&queues[i], 0);
 }
@@ -945,7 +994,12 @@ __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_kernel(const FfnLaun
 // Layer call of the three, two launches / this: 254 / 231, 360 / 331, 469 / 439; 8192 tokens of the first, which the power limit bounds,
 // are even.  Starting the down lists where the share begins instead of at the XCD's first own chunk: 230.3 against 228.2, 336 against 330.5, 446
 // against 435; short gate/up tiles last, as in a launch of their own: 334.9 against 330.5 for the second.
-template <int WM, int WN>
+//
+// EARLY: a shared expert's down tiles (88 k-slices, three to five times the others' length) are what the launch ends with if they come after all
+// gate/up tiles.  Here they come after its own gate/up tiles, which are the first of all, and the routed gate/up tiles beside and after them.
+// Traced at 420 tokens of 60 experts + shared: they ran from 64-97 us to 171-174, the workgroups' ends 127 to 174, 144 on average; so from 56-78 to
+// 144-148, the ends 119 to 150, 132 on average.
+template <int WM, int WN, bool EARLY>
 __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_both_kernel(const FfnBothLaunch L, int *__restrict__ queues, int n_mtiles) {
     typedef FfnShape<WM, WN> S;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[S::SMEM_BYTES];
@@ -954,10 +1008,18 @@ __global__ __launch_bounds__(WM *WN * 64) void ffn_bf16_dma_both_kernel(const Ff
     W.queues = queues;
     W.n_mtiles = n_mtiles;
     W.ticket = 0;
+    W.early = -1;
+    W.holds = false;
     if (threadIdx.x == 0) W.ticket = atomicAdd(&queues[(blockIdx.x & 7) * FFN_LINE], 1);
     ffn_walk_init(W, L.pass[0]);
-    ffn_walk_lists<0, WM, WN, true, 0>(W, L.pass[0], 0, 0);
-    ffn_walk_lists<1, WM, WN, true, (int)sizeof(FfnLaunch)>(W, L.pass[1], L.pass[0].p[0].ntn, L.pass[0].p[1].ntn);
+    const FfnLaunch &D = L.pass[1];
+    const int down_single = EARLY && D.has_single ? (W.sg_hi - W.sg_lo + D.single_rows - 1) / D.single_rows * D.p[1].ntn : 0;
+    bool begin = true;
+    do {
+        ffn_walk_lists<0, WM, WN, true, EARLY, 0>(W, L.pass[0], 0, 0, down_single, begin);
+        ffn_walk_lists<1, WM, WN, true, EARLY, (int)sizeof(FfnLaunch)>(W, D, L.pass[0].p[0].ntn, L.pass[0].p[1].ntn, 0, false);
+        begin = false;
+    } while (EARLY && W.early >= 0);
     if (threadIdx.x < 64) {
         wait_copies_but<0>();  // (what this workgroup posted has arrived)
         int last = 0;
@@ -1091,8 +1153,13 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
 }
 
 // Whether one launch of the tile kernel takes both passes.  Microseconds of a layer call, a kernel per pass / so:
-//   gate/up in tiles (more than 179 rows of a shared expert), down in ffn_mid: 60 experts + shared, 190 tokens 160 / 191, 250 tokens 176 /
-//     187, 320 tokens 187 / 201, 380 tokens 199 / 203, 400 tokens 198 / 188, 500 tokens 205 / 187;
+//   gate/up in tiles (more than 179 rows of a shared expert), down in ffn_mid / one launch, the shared expert's down tiles early: 60 experts +
+//     shared, 220 tokens 171.5 / 175.5, 241 tokens 173 / 178 (one M-tile of the shared expert), 260 tokens 182 / 170, 300 tokens 187.5 / 176.8, 350
+//     tokens 194.8 / 172.9, 390 tokens 200 / 174.3;
+//   both passes in one launch, the shared expert's down tiles after all gate/up tiles / early: 420 tokens 193 / 180, 450 tokens 195 / 176, 520 tokens
+//     193.3 / 188.8, 600 tokens 196.4 / 195.4, 640 tokens 201.2 / 199, 700 tokens 198.5 / 205, 1000 tokens 226 / 248: the rows of h that the routed
+//     down tiles then wait for come late, and a tile of 64 rows takes 82 beside gate/up tiles that stream, 75 after them.  (With tiles of 128
+//     rows 390 tokens 186, 600 tokens 194, 1000 tokens 232; of 256 rows 420 tokens 208, 600 tokens 210, 1000 tokens 236.)
 //   gate/up in ffn_mid, routed groups alone, r rows per expert: 16 experts of d 4096, r = 92 122.5 / 122.4, r = 125 128.4 / 132.6, r = 130
 //     144.7 / 134.0 (a chunk more per group), r = 147 152.8 / 138.0; 8 experts, r = 100 120 / 128, r = 125 141.7 / 135.2, r = 147 155.2 / 141.9.
 //   both in tiles, n gate/up tiles if the load is even: 16 experts of d 4096, n = 132 155 / 162, n = 188 184 / 179; 8 experts, n = 215 189 / 189:
@@ -1100,8 +1167,8 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
 //   so with a part of the experts, whose rows are 0.5 to 2.1 times n's (skewed load): 15 of 60 experts, three light quarters and the heaviest,
 //     n = 385 170 / 173, 166 / 166, 190 / 193, 319 / 294, n = 429 181 / 183, 173 / 175, 205 / 201, 356 / 328, n = 462 201 / 201, 194 / 193, 231 / 225;
 //     30 of 60, the light half n = 385 167 / 172, n = 407 170 / 174, n = 440 174 / 163, the heavy one n = 385 211 / 210, n = 506 269 / 257.
-// (BOTH_BESIDE is measured on that one shape.)
-constexpr int BOTH_BESIDE = 390, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 435;
+// (BOTH_BESIDE and BOTH_EARLY_UP_TO are measured on that one shape.)
+constexpr int BOTH_BESIDE = 256, BOTH_EARLY_UP_TO = 640, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 435;
 static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely) {
     int rows[2];
     if (ffn_skinny_takes(0, up) || ffn_skinny_takes(1, down)) return false;
@@ -1169,7 +1236,10 @@ int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *con
             if (!queues) return C2R_ERR_LAUNCH;
             const int64_t g0 = ffn_grid_of(L.pass[0]), g1 = ffn_grid_of(L.pass[1]);
             const dim3 g((unsigned)(g0 > g1 ? g0 : g1)), b(WM * WN * 64);
-            ffn_bf16_dma_both_kernel<WM, WN><<<g, b, 0, st>>>(L, queues, (int)mtiles);
+            if (L.pass[1].has_single && L.pass[1].has_ragged && L.pass[1].p[1].A_cap <= BOTH_EARLY_UP_TO)
+                ffn_bf16_dma_both_kernel<WM, WN, true><<<g, b, 0, st>>>(L, queues, (int)mtiles);
+            else
+                ffn_bf16_dma_both_kernel<WM, WN, false><<<g, b, 0, st>>>(L, queues, (int)mtiles);
             return launch_status();
         }
     }

@@ -139,3 +139,36 @@ def test_beside_another_launch(c2r):
                 out[i].copy_(layer.forward(x))
     torch.cuda.synchronize()
     assert all(torch.equal(o, ref) for out, ref in zip(outs, refs) for o in out)
+
+
+# a shared expert's down tiles ahead of routed gate/up tiles: both ends of the rule's range and one row beyond, a down pass cut to 64 rows (long
+# contraction) and whole, more gate/up tiles than a round and one tile only, nothing but the shared expert's in a list's first round; two such
+# layers on two streams, each of whose waits must end by workgroups of its own launch
+@pytest.mark.parametrize("T,E,d,F,Fs", [(257, 60, 128, 704, 2816), (420, 60, 2048, 320, 5632), (640, 60, 256, 1408, 1024), (641, 60, 256, 1408, 1024),
+                                        (300, 60, 128, 1408, 64), (512, 16, 192, 192, 16448), (257, 2, 64, 11264, 8192)])
+def test_shared_expert_down_tiles_early(c2r, T, E, d, F, Fs):
+    K = min(E, 4)
+    assert ffn_tiles(E, T * K, F) + ffn_tiles(1, T, Fs) >= ffn_tiles_limit() and ffn_kernel(0, 1, T, Fs) == "tile"
+    layers, xs, refs = [], [], []
+    for seed in (T, T + 1):
+        rng = np.random.default_rng(seed)
+        xs.append(dev(rng.standard_normal((T, d)).astype(np.float32), "bf16"))
+        Wg = dev((rng.standard_normal((d, E)) * 0.05 + np.linspace(0, 0.1, E)).astype(np.float32))
+        weights, shared = _weights(rng, (E, F, d), (E, F, d), (E, d, F)), tuple(_weights(rng, (1, Fs, d), (1, Fs, d), (1, d, Fs)))
+        a, b = (c2r.C2RLayer(T, d, E, K, F, torch.bfloat16, Wg, None, None, *weights, shared=shared, fuse_shared=f) for f in (True, False))
+        layers.append(a)
+        refs.append(b.forward(xs[-1]).clone())
+        for _ in range(3):
+            a.h.fill_(float("nan"))
+            a.h_shared.fill_(float("nan"))
+            assert torch.equal(a.forward(xs[-1]), refs[-1])
+            assert torch.equal(a.y_perm, b.y_perm) and torch.equal(a.y_shared, b.y_shared)
+    streams = [torch.cuda.Stream() for _ in layers]
+    outs = [[torch.empty_like(r) for _ in range(8)] for r in refs]
+    torch.cuda.synchronize()
+    for i in range(8):
+        for layer, x, stream, out in zip(layers, xs, streams, outs):
+            with torch.cuda.stream(stream):
+                out[i].copy_(layer.forward(x))
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, ref) for out, ref in zip(outs, refs) for o in out)
