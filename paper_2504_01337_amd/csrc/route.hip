@@ -32,6 +32,245 @@ __global__ __launch_bounds__(256) void pack_router_kernel(const float *__restric
     Wp[i] = j < E ? Wg[(int64_t)k * E + j] : 0.0f;
 }
 
+// What the selection of a batch needs and writes.
+struct SelectArgs {
+    const float *bias;
+    int E, K;
+    const int32_t *collab_idx;
+    int Tc;
+    int32_t *topk_idx;
+    float *gates;
+};
+
+// One token's selection by the literal rule, for K <= 4: first one standing unless a later one is strictly larger.  pick(m, e, v) finds
+// the expert e of the columns m, and its logit; mask_tab: the collaborators of every expert, or null.
+template <typename Pick>
+__device__ __forceinline__ void literal_scan(Pick pick, int K, uint64_t all, const uint64_t *mask_tab, int (&es)[4], float (&gs)[4],
+                                             float &den) {
+    float v0;
+    pick(all, es[0], v0);
+    uint64_t mm = mask_tab ? mask_tab[es[0]] : all & ~(1ull << es[0]);
+    gs[0] = expf(v0 - v0);
+    den = gs[0];
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+        es[s] = -1;
+        gs[s] = 0.0f;
+        if (s < K) {
+            float v;
+            pick(mm, es[s], v);
+            if (es[s] >= 0) {
+                mm &= ~(1ull << es[s]);
+                gs[s] = expf(v - v0);
+            }
+            den += gs[s];
+        }
+    }
+}
+
+// The same by the whole wave: lane = column, v its logit.  The rule picks the first allowed column if that holds a NaN, else the largest
+// number, the lowest column among equals.  Every lane must be active; results in every lane.
+__device__ __forceinline__ void literal_scan_by_wave(float v, int K, uint64_t all, const uint64_t *mask_tab, int (&es)[4], float (&gs)[4],
+                                                     float &den) {
+    const int lane = lane_id(), bits = __float_as_int(v), key = bits ^ ((bits >> 31) & 0x7fffffff);
+    auto pick_row = [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
+        bi = -1;
+        bv = 0.0f;
+        if (mm == 0) return;
+        bi = __ffsll((unsigned long long)mm) - 1;
+        bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
+        if (bv != bv) return;
+        const bool in = ((mm >> lane) & 1ull) != 0 && v == v;
+        const int best = wave_max(in ? key : (int)0x80000000);
+        bi = __ffsll((unsigned long long)__ballot(in && key == best)) - 1;
+        bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
+    };
+    literal_scan(pick_row, K, all, mask_tab, es, gs, den);
+}
+
+// The keys of the selections below: a logit (-0 made +0) whose low 6 bits are replaced by 63 - column, compared as floats (as
+// instructions: the compiler would first quiet what it takes for possible NaNs).
+constexpr int KEY_EMPTY = (int)0xff800000;  // minus infinity: below the key of every finite logit
+__device__ __forceinline__ int key_of(float v, int c) { return (__float_as_int(v) & ~63) | (63 - c); }
+__device__ __forceinline__ int key_max(int a, int b) {
+    int d;
+    asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+__device__ __forceinline__ int key_med3(int a, int b, int c) {
+    int d;
+    asm("v_med3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ bool keys_apart(int a, int b) { return ((a ^ b) & ~63) != 0; }
+
+constexpr int KEYS_SCAN_TOGETHER = 8;  // as SCAN_TOGETHER; here a token scanned by the wave also waits for its logits out of L2
+
+// The collaborators of every expert as a 64-bit mask (without itself; without lists all others).  Every thread of the workgroup calls it.
+__device__ __forceinline__ void build_masks(uint64_t *mask_tab, const int32_t *__restrict__ collab_idx, int E, int Tc, uint64_t all) {
+    if (threadIdx.x < C2R_MAX_E) mask_tab[threadIdx.x] = collab_idx ? 0ull : all & ~(1ull << threadIdx.x);
+    __syncthreads();
+    if (!collab_idx) return;
+    for (int i = threadIdx.x; i < E * Tc; i += blockDim.x) {
+        const int e = i / Tc, v = collab_idx[i];
+        if (v >= 0 && v < E && v != e) atomicOr(reinterpret_cast<unsigned long long *>(&mask_tab[e]), 1ull << v);
+    }
+    __syncthreads();
+}
+
+// The selection of 32 tokens by the wave that has their logits in registers, K <= 4: lane (mh, mc) holds experts 32 a + 8 (i / 4) + 4 mh + i % 4
+// of token mc.  Both lanes of a token run the keyed chain of route_select_rows_kernel over their experts and then over the other's
+// largest; with lists a chain of two keys finds the first expert, one over its collaborators the others.  What the keys cannot
+// decide is scanned by the literal rule (see route_select_keys_kernel).  tile (LDS, this wave's): the logits, [expert][32 tokens].
+template <int NEB, class Acc>
+__device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, const uint64_t *mask_tab, const SelectArgs &S, int64_t t0, int64_t T) {
+    const int lane = lane_id(), mh = lane >> 5, mc = lane & 31, E = S.E, K = S.K;
+    const int64_t t = t0 + mc;
+    const uint64_t all = E >= 64 ? ~0ull : ((1ull << E) - 1ull);
+    const uint64_t *const lists = S.collab_idx ? mask_tab : nullptr;
+    float l[NEB * 16];
+    float chk = 0.0f;
+    int low = 0;
+#pragma unroll
+    for (int n = 0; n < NEB * 16; ++n) {
+        const int e0 = n / 16 * 32 + n % 16 / 4 * 8 + n % 4, e = e0 + mh * 4;
+        float v = sums[n / 16][0][n % 16];
+        if (S.bias) v = v + S.bias[e < E ? e : 0];
+        v = v + 0.0f;
+        l[n] = v;
+        if (e < E) {
+            tile[e * 32 + mc] = v;
+            chk = __builtin_fmaf(v, 0.0f, chk);  // NaN once a NaN or an infinity went in
+            low |= __float_as_int(v) & 63;
+        }
+    }
+    chk += __shfl_xor(chk, 32);
+    low |= __shfl_xor(low, 32);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (the tile is this wave's alone)
+    // the NKEEP largest keys of the token's experts in m, the same in both its lanes
+    auto largest = [&](auto &k, uint64_t m) __attribute__((always_inline)) {
+        constexpr int NKEEP = sizeof(k) / sizeof(k[0]);
+#pragma unroll
+        for (int u = 0; u < NKEEP; ++u) k[u] = KEY_EMPTY;
+        auto insert = [&](int kk) __attribute__((always_inline)) {
+            int nk[NKEEP];
+            nk[0] = key_max(k[0], kk);
+#pragma unroll
+            for (int u = 1; u < NKEEP; ++u) nk[u] = key_med3(k[u - 1], k[u], kk);  // (k[0] >= k[1] >= ... throughout)
+#pragma unroll
+            for (int u = 0; u < NKEEP; ++u) k[u] = nk[u];
+        };
+        const uint32_t mine[2] = {(uint32_t)(m >> (mh * 4)), (uint32_t)(m >> 32 >> (mh * 4))};
+#pragma unroll
+        for (int n = 0; n < NEB * 16; ++n) {
+            const int e0 = n / 16 * 32 + n % 16 / 4 * 8 + n % 4;
+            insert((mine[n / 16] >> (e0 % 32)) & 1u ? (int)((__float_as_uint(l[n]) & ~63u) | (uint32_t)(63 - e0 - mh * 4)) : KEY_EMPTY);
+        }
+        int other[NKEEP];
+#pragma unroll
+        for (int u = 0; u < NKEEP; ++u) other[u] = __shfl_xor(k[u], 32);
+#pragma unroll
+        for (int u = 0; u < NKEEP; ++u) insert(other[u]);
+    };
+    bool literal = chk != chk, nonneg;
+    auto undecided = [&](const auto &k) __attribute__((always_inline)) {
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u + 1 < (int)(sizeof(k) / sizeof(k[0])); ++u) any = any || !(keys_apart(k[u], k[u + 1]) || k[u] == KEY_EMPTY);
+        return any;
+    };
+    int es[4];
+    if (lists) {
+        int k[2], r[4];
+        largest(k, all);
+        literal = literal || undecided(k);
+        es[0] = 63 - (k[0] & 63);
+        largest(r, lists[es[0]]);
+        literal = literal || undecided(r);
+        nonneg = k[1] >= 0 && r[3] >= 0;
+#pragma unroll
+        for (int s = 1; s < 4; ++s) es[s] = r[s - 1] == KEY_EMPTY ? -1 : 63 - (r[s - 1] & 63);
+    } else {
+        int k[5];
+        largest(k, all);
+        literal = literal || undecided(k);
+        nonneg = k[4] >= 0;
+        es[0] = 63 - (k[0] & 63);
+#pragma unroll
+        for (int s = 1; s < 4; ++s) es[s] = k[s] == KEY_EMPTY ? -1 : 63 - (k[s] & 63);
+    }
+    uint64_t todo = __ballot(literal && t < T && mh == 0);
+    if (todo & (todo - 1)) {
+        // (rows of zeros that pad a batch: where the replaced bits were all zero and the keys kept are not negative, equal logits lie in
+        // ascending columns and the chain is right as it stands)
+        literal = literal && !(chk == chk && low == 0 && nonneg);
+        todo = __ballot(literal && t < T && mh == 0);
+    }
+    const bool alone = __popcll(todo) * KEYS_SCAN_TOGETHER > E;
+    float gs[4] = {0.0f, 0.0f, 0.0f, 0.0f}, den = 1.0f;
+    if (!literal) {
+        float vs[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s >= K) es[s] = -1;
+            vs[s] = tile[(es[s] < 0 ? 0 : es[s]) * 32 + mc];
+        }
+        gs[0] = expf(vs[0] - vs[0]);
+        den = gs[0];
+#pragma unroll
+        for (int s = 1; s < 4; ++s)
+            if (s < K) {
+                if (es[s] >= 0) gs[s] = expf(vs[s] - vs[0]);
+                den += gs[s];
+            }
+    } else if (alone && t < T) {
+        literal_scan(
+            [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
+                bi = -1;
+                bv = 0.0f;
+                for (int e = 0; e < E; ++e) {
+                    const float v = tile[e * 32 + mc];
+                    const bool take = ((mm >> e) & 1ull) != 0 && (bi < 0 || v > bv);
+                    bv = take ? v : bv;
+                    bi = take ? e : bi;
+                }
+            },
+            K, all, lists, es, gs, den);
+    }
+    for (todo = alone ? 0 : todo; todo; todo &= todo - 1) {
+        const int tk = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)todo) - 1), col = lane < E ? lane : 0;
+        int et[4];
+        float gt[4], dt;
+        literal_scan_by_wave(tile[col * 32 + tk], K, all, lists, et, gt, dt);
+        if (mc == tk) {
+            den = dt;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                es[s] = et[s];
+                gs[s] = gt[s];
+            }
+        }
+    }
+    if (t >= T || mh != 0) return;
+    int32_t *topk_idx = S.topk_idx;
+    float *gates = S.gates;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) gs[s] = gs[s] / den;
+    if (K == 4 && ((reinterpret_cast<uintptr_t>(topk_idx) | reinterpret_cast<uintptr_t>(gates)) & 15) == 0) {
+        typedef int i32x4 __attribute__((ext_vector_type(4)));
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        *reinterpret_cast<i32x4 *>(topk_idx + (size_t)t * 4) = i32x4{es[0], es[1], es[2], es[3]};
+        *reinterpret_cast<f32x4 *>(gates + (size_t)t * 4) = f32x4{gs[0], gs[1], gs[2], gs[3]};
+    } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (s < K) {
+                topk_idx[(size_t)t * K + s] = es[s];
+                gates[(size_t)t * K + s] = gs[s];
+            }
+    }
+}
+
 // Partial logits of one 256-long k-chunk for NWV token tiles of 8*TQ tokens (one per wave), all
 // experts.  A register-tiled fp32 GEMM: lane = (token lane tl, expert lane el) on an 8 x 8 grid; the
 // thread owns tokens tl + 8q (q < TQ) and experts el*TE + j (j < TE), i.e. TQ*TE accumulators,
@@ -62,12 +301,14 @@ __global__ __launch_bounds__(256) void pack_router_kernel(const float *__restric
 // here and read back by the selection).  For batches with about a wave tile per SIMD of the chip (the rule: route_impl);
 // smaller batches need the chunks as separate workgroups to fill it.
 // HALVES: a token tile's two blocks of 32 experts by a wave each, half the tokens per workgroup.
-template <bool BF16, int TE, int NWV, int TQ, bool MFMA, bool ALLCHUNKS = false, bool HALVES = false>
+// SELECT: the wave that has a token's logits selects as well, and nothing goes to scratch.
+template <bool BF16, int TE, int NWV, int TQ, bool MFMA, bool ALLCHUNKS = false, bool HALVES = false, bool SELECT = false>
 __global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) void route_partial_kernel(const void *__restrict__ x,
                                                                 const float *__restrict__ W, int ldw,
                                                                 int ep, int64_t T, int d, int nchunk, int cpw,
                                                                 int64_t ntiles,
-                                                                float *__restrict__ part) {
+                                                                float *__restrict__ part, const SelectArgs S) {
+    static_assert(!SELECT || (ALLCHUNKS && !HALVES), "a wave has all logits of its tokens");
     constexpr int EPAD = 8 * TE;         // experts covered by a wave (HALVES: by two)
     constexpr int NT = HALVES ? NWV / 2 : NWV;  // wave tiles of tokens in a workgroup
     static_assert(!HALVES || (MFMA && EPAD == 64), "halves of 32 experts");
@@ -506,6 +747,14 @@ __global__ __launch_bounds__(NWV * 64, HALVES ? 4 : (MFMA && TQ == 4) ? 2 : 1) v
     }
     finish_chunk(chunk);
     }
+    if constexpr (SELECT) {
+        // (the operand buffers, which every wave has read for the last time, hold the logits now)
+        __shared__ uint64_t mask_tab[C2R_MAX_E];
+        static_assert(sizeof(Xl) >= (size_t)NWV * EPAD * 32 * sizeof(float), "a tile of logits for every wave");
+        build_masks(mask_tab, S.collab_idx, S.E, S.Tc, S.E >= 64 ? ~0ull : ((1ull << S.E) - 1ull));
+        if (live) select_of_sums<NEB>(mtot, reinterpret_cast<float *>(&Xl[0][0][0]) + wave * (EPAD * 32), mask_tab, S, wt * TOK, T);
+        return;
+    }
     if (!live) return;
     if constexpr (MFMA) {
         if constexpr (ALLCHUNKS) store_sums(mtot, 0);
@@ -921,52 +1170,6 @@ __global__ __launch_bounds__(ROWMAJOR ? 64 : SEL_WAVES * 64) void route_select_k
     for (int s = 0; s < K; ++s) gates[(size_t)t * K + s] = gates[(size_t)t * K + s] / den;
 }
 
-// One token's selection by the literal rule, for K <= 4: first one standing unless a later one is strictly larger.  pick(m, e, v) finds
-// the expert e of the columns m, and its logit; mask_tab: the collaborators of every expert, or null.
-template <typename Pick>
-__device__ __forceinline__ void literal_scan(Pick pick, int K, uint64_t all, const uint64_t *mask_tab, int (&es)[4], float (&gs)[4],
-                                             float &den) {
-    float v0;
-    pick(all, es[0], v0);
-    uint64_t mm = mask_tab ? mask_tab[es[0]] : all & ~(1ull << es[0]);
-    gs[0] = expf(v0 - v0);
-    den = gs[0];
-#pragma unroll
-    for (int s = 1; s < 4; ++s) {
-        es[s] = -1;
-        gs[s] = 0.0f;
-        if (s < K) {
-            float v;
-            pick(mm, es[s], v);
-            if (es[s] >= 0) {
-                mm &= ~(1ull << es[s]);
-                gs[s] = expf(v - v0);
-            }
-            den += gs[s];
-        }
-    }
-}
-
-// The same by the whole wave: lane = column, v its logit.  The rule picks the first allowed column if that holds a NaN, else the largest
-// number, the lowest column among equals.  Every lane must be active; results in every lane.
-__device__ __forceinline__ void literal_scan_by_wave(float v, int K, uint64_t all, const uint64_t *mask_tab, int (&es)[4], float (&gs)[4],
-                                                     float &den) {
-    const int lane = lane_id(), bits = __float_as_int(v), key = bits ^ ((bits >> 31) & 0x7fffffff);
-    auto pick_row = [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
-        bi = -1;
-        bv = 0.0f;
-        if (mm == 0) return;
-        bi = __ffsll((unsigned long long)mm) - 1;
-        bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
-        if (bv != bv) return;
-        const bool in = ((mm >> lane) & 1ull) != 0 && v == v;
-        const int best = wave_max(in ? key : (int)0x80000000);
-        bi = __ffsll((unsigned long long)__ballot(in && key == best)) - 1;
-        bv = __int_as_float(__builtin_amdgcn_readlane(bits, bi));
-    };
-    literal_scan(pick_row, K, all, mask_tab, es, gs, den);
-}
-
 // Undecided tokens of a 64-token group that the wave scans together, one after the other: up to E / SCAN_TOGETHER; more are scanned by
 // their own lanes, all at once.  The one takes 0.9 us a token (four slots), the other 0.2 us a column whatever the number of tokens.
 // Microseconds of the selection with n of every 64 tokens undecided (together / alone): 2^20 tokens, 60 experts, n = 8 104 / 140, n = 12
@@ -974,28 +1177,11 @@ __device__ __forceinline__ void literal_scan_by_wave(float v, int K, uint64_t al
 // n = 1 18 / 24, n = 3 29 / 24; 65536 tokens, 60 experts, n = 8 15.1 / 24.8, n = 12 18.9 / 19.6, n = 16 22.6 / 19.6.
 constexpr int SCAN_TOGETHER = 5;
 
-// The keys of the selections below: a logit (-0 made +0) whose low 6 bits are replaced by 63 - column, compared as floats (as
-// instructions: the compiler would first quiet what it takes for possible NaNs).
-constexpr int KEY_EMPTY = (int)0xff800000;  // minus infinity: below the key of every finite logit
-__device__ __forceinline__ int key_of(float v, int c) { return (__float_as_int(v) & ~63) | (63 - c); }
-__device__ __forceinline__ int key_max(int a, int b) {
-    int d;
-    asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
-    return d;
-}
-__device__ __forceinline__ int key_med3(int a, int b, int c) {
-    int d;
-    asm("v_med3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-    return d;
-}
-__device__ __forceinline__ bool keys_apart(int a, int b) { return ((a ^ b) & ~63) != 0; }
-
 // Top-K, K <= 4, from ONE chunk result per token ([tile][expert][64 tokens]), without lists: a wave per 64 tokens, lane = token, its
 // logits in registers, chosen by the keyed chain of route_select_rows_kernel below, the literal scan where that cannot decide.
 // Bound by the launch and two trips to memory; the stage with route_select_kernel / with this: 60 experts, d 2048: 32768 tokens 87.0 / 84.0,
 // 65536 tokens 155 / 150; 16 experts, 32768 tokens 103.8 / 102.4.  (With lists, the largest two keys and a second chain over the
 // first one's list, it was no faster: 15.6 against 12.7 us for the kernel at 32768 tokens.)
-constexpr int KEYS_SCAN_TOGETHER = 8;  // as SCAN_TOGETHER; here a token scanned by the wave also waits for its logits out of L2
 
 template <int EP>
 __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__restrict__ part, const float *__restrict__ bias, int64_t T,
@@ -1856,20 +2042,35 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
     // 281 / 272, fp32 299 / 298, 140000 tokens 350 / 345, fp32 386 / 387.)
     const int64_t half_rounds = (ngroups + 127) / 128;
     const bool halves = all_chunks && te == 8 && (half_rounds == 3 || half_rounds == 5);
+    const SelectArgs sel = {bias, E, K, collab_idx, Tc, topk_idx, gates};
+    // The waves that have the sums select as well: the logits go neither out (16 MB at 65536 tokens) nor back, and the selection's launch (10 to
+    // 14 us by itself) costs 3 to 5 at the end of this one, whose workgroups all end at once.  Microseconds, in two launches / so: top-K of the
+    // profiling call, 60 experts, d 2048: 26000 tokens 98.1 / 94.2, 32768 tokens 99.4 / 94.7, 65536 tokens 166.8 / 161.8, 16 experts of d 4096, 32768
+    // tokens 112.6 / 110.6; with lists, the layer call of 15 of 60 experts, 26000 tokens 376 / 364, 32768 tokens 430 / 418.  Not with 64-token
+    // workgroups, whose waves have half of a token's logits, nor where logits are asked for.
+    // (In one launch workgroups write selections while others still read.)
+    const size_t a4 = (size_t)(T * K) * 4;
+    const bool select = all_chunks && !halves && K <= 4 && !logits_out &&
+                        all_apart({{topk_idx, a4}, {gates, a4}}, {{x, (size_t)T * d * (x_dt == C2R_BF16 ? 2 : 4)}, {W, (size_t)d * ldw * 4},
+                                                                 {bias, (size_t)E * 4}, {collab_idx, (size_t)E * Tc * 4}});
     const int64_t nblk = ngroups * ((L.nchunk + cpw - 1) / cpw);
     if (nblk >= (1ll << 31)) return C2R_ERR_UNSUPPORTED;
     // more than 8 experts: the matrix pipe, a wave covering 32 or 64 experts (columns past the packed
     // expert count re-read column 0; their sums are never stored)
 #define C2R_ROUTE_LAUNCH(BF, TE, NWV, TQ, MF)                                                     \
     route_partial_kernel<BF, TE, NWV, TQ, MF><<<dim3((unsigned)nblk), dim3(NWV * 64), 0, st>>>(    \
-        x, W, ldw, L.EP, T, d, L.nchunk, cpw, ntiles, part)
+        x, W, ldw, L.EP, T, d, L.nchunk, cpw, ntiles, part, sel)
 #define C2R_ROUTE_LAUNCH_ALL(BF, TE, NWV, TQ)                                                          \
+    if (select) {                                                                                      \
+        route_partial_kernel<BF, TE, NWV, TQ, true, true, false, true><<<dim3((unsigned)nblk), dim3(NWV * 64), 0, st>>>(  \
+            x, W, ldw, L.EP, T, d, L.nchunk, cpw, ntiles, part, sel);                                  \
+    } else                                                                                             \
     route_partial_kernel<BF, TE, NWV, TQ, true, true><<<dim3((unsigned)nblk), dim3(NWV * 64), 0, st>>>(  \
-        x, W, ldw, L.EP, T, d, L.nchunk, cpw, ntiles, part)
+        x, W, ldw, L.EP, T, d, L.nchunk, cpw, ntiles, part, sel)
 #define C2R_ROUTE_LAUNCH_HALVES(BF)                                                                              \
     route_partial_kernel<BF, 8, NWV, 4, true, true, true>                                                          \
         <<<dim3((unsigned)((nwt + NWV / 2 - 1) / (NWV / 2))), dim3(NWV * 64), 0, st>>>(x, W, ldw, L.EP, T, d, L.nchunk, cpw, \
-                                                                                       ntiles, part)
+                                                                                       ntiles, part, sel)
 #define C2R_ROUTE_TE(BF, NWV, TQ)                                     \
     if (all_chunks) {                                                 \
         if (halves) { C2R_ROUTE_LAUNCH_HALVES(BF); }                  \
@@ -1891,6 +2092,7 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
 #undef C2R_ROUTE_LAUNCH_ALL
 #undef C2R_ROUTE_LAUNCH_HALVES
 #undef C2R_ROUTE_LAUNCH
+    if (select) return launch_status();
     return launch_select(part, L.EP, nchunk_out, bias, T, E, K, collab_idx, Tc, topk_idx, gates, logits_out, st);
 }
 

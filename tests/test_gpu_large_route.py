@@ -166,3 +166,44 @@ def test_large_route_of_one_more_token(E, d, most):
             times.append(beg.elapsed_time(end))
         best.append(min(times))
     assert best[1] < most * best[0]
+
+
+# selection by the waves that have the sums in registers (no logits asked for, up to four slots): two blocks of 32 experts and one, the first and a
+# ragged number of tokens, one slot to four; lists with the expert itself, duplicates and entries out of range, short ones and none; ties,
+# logits of equal upper bits, NaN and infinite ones, rows of zeros one by one and in numbers, experts masked by -infinity; outputs that
+# stand in the place of the input's memory or are not aligned, which take the two launches
+@pytest.mark.parametrize("T,E,K,d,dtype", [(25025, 60, 4, 520, "bf16"), (32768, 64, 4, 512, "bf16"), (25100, 33, 3, 264, "f32"), (32705, 20, 4, 512, "bf16"),
+                                           (32721, 32, 2, 264, "f32"), (25030, 61, 1, 512, "bf16"), (50000, 36, 4, 512, "bf16"), (32710, 17, 4, 520, "bf16")])
+def test_selection_beside_the_sums(orc, T, E, K, d, dtype):
+    import torch
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(T + E)
+    x = rng.integers(-2, 3, size=(T, d)).astype(np.float32)
+    x[::3] = wl.round_bf16(rng.standard_normal((len(x[::3]), d)).astype(np.float32))
+    x[::11, 8:] = 0.0
+    x[1000:1040], x[64 * 200 + 5], x[5], x[77], x[T - 1] = 0.0, 0.0, np.inf, np.nan, np.inf
+    Wg = rng.integers(-2, 3, size=(d, E)).astype(np.float32)
+    Wg[::5] = 0.03 * rng.standard_normal(Wg[::5].shape)
+    Wg[:, 1] = Wg[:, 0] * np.float32(1 + 2.0 ** -22)
+    bias = np.where(rng.random(E) < 0.1, np.float32(-np.inf), rng.integers(-2, 3, size=E)).astype(np.float32)
+    cl = np.stack([rng.permutation(np.delete(np.arange(E), e))[:max(K, E // 3)] for e in range(E)]).astype(np.int32)
+    gl = np.concatenate([np.full((E, 1), -1), cl[:, :1], cl, np.arange(E)[:, None], np.full((E, 1), E)], axis=1).astype(np.int32)
+    short = np.full((E, 4), -1, dtype=np.int32)
+    short[:, 0] = (np.arange(E) + 1) % E
+    xd, wd = dev(x, dtype), dev(Wg)
+    for b in (None, bias):
+        bd = None if b is None else dev(b)
+        for c, g in ((None, None), (cl, gl), (None, short)):
+            gd = None if g is None else dev(g)
+            two = c2r.route(xd, wd, bd, K, gd, want_logits=True)  # (the two launches; the oracle takes no lists that are too short)
+            ri, rg = (host(two[0]), host(two[1])) if g is short else orc.route(host(two[2]), K, c)
+            apart = torch.empty(T * K + 1, dtype=torch.int32, device="cuda"), torch.empty(T * K + 1, device="cuda")
+            for out in (None, tuple(a[1:].view(T, K) for a in apart)):
+                idx, gates, _ = c2r.route(xd, wd, bd, K, gd, out=out)
+                assert np.array_equal(host(idx), ri)
+                # (logits up to some hundred apart: the bound of GATE_RTOL with |a_s| up to 104, where a gate is flushed to zero)
+                np.testing.assert_allclose(host(gates), rg, rtol=114 / 34 * GATE_RTOL, atol=1e-37)
+    x2 = xd.clone()
+    idx = x2.view(-1).view(torch.int32)[:T * K].view(T, K)
+    got = c2r.route(x2, wd, None, K, None, out=(idx, torch.empty((T, K), device="cuda")))
+    assert np.array_equal(host(got[0]), orc.route(host(c2r.route(xd, wd, None, K, want_logits=True)[2]), K)[0])
