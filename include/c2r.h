@@ -362,6 +362,14 @@ int c2r_dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int E, const i
                        int32_t *send_row, void *ws, size_t ws_bytes, void *stream);
 
 /*
+ * The same index (Sec. 3.4), and the entries of send_token past n_send become -1: for a caller
+ * whose array is fresh memory, without a launch that fills it first.
+ */
+int c2r_dedup_dispatch_filled(const int32_t *topk_idx, int64_t T, int K, int E, const int32_t *expert_device,
+                              int n_dev, int32_t *send_counts, int32_t *send_offsets, int32_t *send_token,
+                              int32_t *send_row, void *ws, size_t ws_bytes, void *stream);
+
+/*
  * Expert -> device map that co-locates collaborating experts (Sec. 3.4 proposes placing
  * experts that collaborate closely on one device; the paper names the goal
  * and gives no procedure - this is a greedy fill).  Devices 0..n_dev-1 are filled in order

@@ -26,7 +26,7 @@ EXPORTS = ["c2r_version", "c2r_route_chunk", "c2r_workspace_bytes", "c2r_build_c
            "c2r_collaborators", "c2r_route", "c2r_route_from_logits", "c2r_profile_from_logits", "c2r_permute", "c2r_permute_noalloc", "c2r_expert_ffn",
            "c2r_expert_ffn_gate_up", "c2r_expert_ffn_gate_up_gather", "c2r_expert_ffn_gather", "c2r_expert_ffn_down",
            "c2r_expert_ffn_gate_up_with_shared", "c2r_expert_ffn_down_with_shared", "c2r_combine", "c2r_layer_forward",
-           "c2r_place_experts", "c2r_dedup_dispatch", "c2r_combine_partial", "c2r_combine_copies",
+           "c2r_place_experts", "c2r_dedup_dispatch", "c2r_dedup_dispatch_filled", "c2r_combine_partial", "c2r_combine_copies",
            "c2r_collaboration_degree", "c2r_distinct_devices"]
 
 
@@ -71,6 +71,7 @@ def lib():
         L.c2r_layer_forward.argtypes = [C.c_char_p, vp, vp]
         L.c2r_place_experts.argtypes = [vp, i32, i32, vp, vp]
         L.c2r_dedup_dispatch.argtypes = [vp, i64, i32, i32, vp, i32, vp, vp, vp, vp, vp, sz, vp]
+        L.c2r_dedup_dispatch_filled.argtypes = L.c2r_dedup_dispatch.argtypes
         L.c2r_combine_partial.argtypes = [vp, i32, vp, vp, vp, vp, vp, i64, i64, i32, i32, vp, vp]
         L.c2r_combine_copies.argtypes = [vp, i32, vp, i64, i64, i32, i32, vp, vp, vp]
         L.c2r_collaboration_degree.argtypes = [vp, i32, vp, vp]
@@ -354,11 +355,11 @@ def dedup_dispatch(topk_idx, E, expert_device, n_dev, ws=None):
     dev = topk_idx.device
     i32 = dict(dtype=torch.int32, device=dev)
     counts, offsets = torch.empty((n_dev,), **i32), torch.empty((n_dev + 1,), **i32)
-    tok, row = torch.full((T * K,), -1, **i32), torch.empty((T * K,), **i32)
+    tok, row = torch.empty((T * K,), **i32), torch.empty((T * K,), **i32)
     ws = _ws(workspace_bytes(STAGE_DEDUP_DISPATCH, T, 0, n_dev, K, 0, F32), dev, ws)
-    _check("c2r_dedup_dispatch", lib().c2r_dedup_dispatch(_ptr(topk_idx), T, K, E, _ptr(expert_device), n_dev,
-                                                        _ptr(counts), _ptr(offsets), _ptr(tok), _ptr(row),
-                                                        _ptr(ws), ws.numel(), _stream()))
+    _check("c2r_dedup_dispatch_filled", lib().c2r_dedup_dispatch_filled(
+        _ptr(topk_idx), T, K, E, _ptr(expert_device), n_dev, _ptr(counts), _ptr(offsets), _ptr(tok), _ptr(row), _ptr(ws), ws.numel(),
+        _stream()))
     return counts, offsets, tok, row
 
 

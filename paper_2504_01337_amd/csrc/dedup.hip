@@ -65,11 +65,11 @@ __device__ __forceinline__ uint64_t device_set(const int32_t *__restrict__ topk_
     return m;
 }
 
-// DB_ITEMS: tokens per thread.
+// DB_ITEMS: tokens per thread.  fill: not null, T * K entries that become -1 (those that the next launch lists copies in are overwritten).
 template <int DB_ITEMS>
 __global__ __launch_bounds__(DB_THREADS) void dedup_count_kernel(
     const int32_t *__restrict__ topk_idx, int64_t T, int K, int E, const int32_t *__restrict__ expert_device,
-    int n_dev, uint16_t *__restrict__ block_counts) {
+    int n_dev, uint16_t *__restrict__ block_counts, int32_t *__restrict__ fill) {
     __shared__ int32_t hist[C2R_MAX_E], dev_tab[C2R_MAX_E];
     if (threadIdx.x < C2R_MAX_E) hist[threadIdx.x] = 0;
     load_device_table(dev_tab, E, expert_device, n_dev);
@@ -79,6 +79,10 @@ __global__ __launch_bounds__(DB_THREADS) void dedup_count_kernel(
 #pragma unroll
     for (int i = 0; i < DB_ITEMS; ++i)
         sets[i] = device_set(topk_idx, base + i * DB_THREADS + threadIdx.x, T, K, E, dev_tab);
+    if (fill) {
+        const int64_t end = base + DB_THREADS * DB_ITEMS < T ? (base + DB_THREADS * DB_ITEMS) * K : T * K;
+        for (int64_t i = base * K + threadIdx.x; i < end; i += DB_THREADS) fill[i] = -1;
+    }
 #pragma unroll
     for (int i = 0; i < DB_ITEMS; ++i) {
         const uint64_t m = sets[i];
@@ -219,7 +223,7 @@ template <int STEPS>
 __global__ __launch_bounds__(DD_WAVES * 64) void dedup_by_device_kernel(
     const int32_t *__restrict__ topk_idx, int T, int K, int E, const int32_t *__restrict__ expert_device, int n_dev,
     int32_t *__restrict__ send_counts, int32_t *__restrict__ send_offsets, int32_t *__restrict__ send_token,
-    int32_t *__restrict__ send_row) {
+    int32_t *__restrict__ send_row, const bool fill) {
     __shared__ int32_t dev_tab[C2R_MAX_E], w_mine[DD_WAVES], w_less[DD_WAVES];
     const int g = blockIdx.x % n_dev, part = blockIdx.x / n_dev, parts = gridDim.x / n_dev;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -278,6 +282,8 @@ __global__ __launch_bounds__(DD_WAVES * 64) void dedup_by_device_kernel(
         send_offsets[g] = start;
         if (g == n_dev - 1) send_offsets[n_dev] = start + total;
     }
+    if (fill && g == n_dev - 1)  // (no copies past the last device's)
+        for (int i = start + total + part * (int)blockDim.x + threadIdx.x; i < T * K; i += parts * (int)blockDim.x) send_token[i] = -1;
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
     for (int u = 0; u < STEPS; ++u) {
@@ -447,9 +453,10 @@ size_t dedup_workspace_bytes(int64_t T, int n_dev) {
 
 using namespace c2r;
 
-extern "C" int c2r_dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int E, const int32_t *expert_device,
-                                  int n_dev, int32_t *send_counts, int32_t *send_offsets, int32_t *send_token,
-                                  int32_t *send_row, void *ws, size_t ws_bytes, void *stream) {
+// fill: entries of send_token past the copies become -1.  (Dispatch index and two-level combine, a fill launch ahead / so: 8192 tokens of 60
+// experts on 4 devices 62.8 / 60.7 us, 2000 tokens 46.3 / 42.6.)
+static int dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int E, const int32_t *expert_device, int n_dev, int32_t *send_counts,
+                          int32_t *send_offsets, int32_t *send_token, int32_t *send_row, bool fill, void *ws, size_t ws_bytes, void *stream) {
     drop_stale_error();
     if (T < 0 || K < 1 || E < 1 || n_dev < 1) return C2R_ERR_INVALID_ARG;
     if (E > C2R_MAX_E || n_dev > C2R_MAX_E) return C2R_ERR_UNSUPPORTED;
@@ -468,7 +475,7 @@ extern "C" int c2r_dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int
         const dim3 g((unsigned)(n_dev * parts)), b(DD_WAVES * 64);
 #define C2R_BY_DEVICE(STEPS)                                                                                             \
     dedup_by_device_kernel<STEPS><<<g, b, 0, st>>>(topk_idx, (int)T, K, E, expert_device, n_dev, send_counts, send_offsets, \
-                                                   send_token, send_row)
+                                                   send_token, send_row, fill)
         if (T <= DD_MAX_TOKENS / DD_STEPS)
             C2R_BY_DEVICE(1);
         else if (T <= DD_MAX_TOKENS / 2)
@@ -488,7 +495,7 @@ extern "C" int c2r_dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int
     uint16_t *block_counts = static_cast<uint16_t *>(ws);
     const dim3 grid((unsigned)nblocks), block(DB_THREADS);
 #define C2R_DEDUP_LAUNCH(ITEMS)                                                                                      \
-    dedup_count_kernel<ITEMS><<<grid, block, 0, st>>>(topk_idx, T, K, E, expert_device, n_dev, block_counts);        \
+    dedup_count_kernel<ITEMS><<<grid, block, 0, st>>>(topk_idx, T, K, E, expert_device, n_dev, block_counts, fill ? send_token : nullptr); \
     dedup_rank_kernel<ITEMS><<<grid, block, 0, st>>>(topk_idx, T, K, E, expert_device, n_dev, block_counts, (int)nblocks, \
                                                      send_counts, send_offsets, send_token, send_row)
     switch (items) {
@@ -498,6 +505,18 @@ extern "C" int c2r_dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int
     }
 #undef C2R_DEDUP_LAUNCH
     return launch_status();
+}
+
+extern "C" int c2r_dedup_dispatch(const int32_t *topk_idx, int64_t T, int K, int E, const int32_t *expert_device,
+                                  int n_dev, int32_t *send_counts, int32_t *send_offsets, int32_t *send_token,
+                                  int32_t *send_row, void *ws, size_t ws_bytes, void *stream) {
+    return dedup_dispatch(topk_idx, T, K, E, expert_device, n_dev, send_counts, send_offsets, send_token, send_row, false, ws, ws_bytes, stream);
+}
+
+extern "C" int c2r_dedup_dispatch_filled(const int32_t *topk_idx, int64_t T, int K, int E, const int32_t *expert_device,
+                                         int n_dev, int32_t *send_counts, int32_t *send_offsets, int32_t *send_token,
+                                         int32_t *send_row, void *ws, size_t ws_bytes, void *stream) {
+    return dedup_dispatch(topk_idx, T, K, E, expert_device, n_dev, send_counts, send_offsets, send_token, send_row, true, ws, ws_bytes, stream);
 }
 
 extern "C" int c2r_combine_partial(const void *y_perm, c2r_dtype dt, const float *gates, const int32_t *inv_perm,

@@ -2046,7 +2046,7 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
     // The waves that have the sums select as well: the logits go neither out (16 MB at 65536 tokens) nor back, and the selection's launch (10 to
     // 14 us by itself) costs 3 to 5 at the end of this one, whose workgroups all end at once.  Microseconds, in two launches / so: top-K of the
     // profiling call, 60 experts, d 2048: 26000 tokens 98.1 / 94.2, 32768 tokens 99.4 / 94.7, 65536 tokens 166.8 / 161.8, 16 experts of d 4096, 32768
-    // tokens 112.6 / 110.6; with lists, the layer call of 15 of 60 experts, 26000 tokens 376 / 364, 32768 tokens 430 / 418.  Not with 64-token
+    // tokens 112.6 / 110.6; with lists, the layer call of 15 of 60 experts, 26000 tokens 369 / 362, 32768 tokens 425.5 / 418.  Not with 64-token
     // workgroups, whose waves have half of a token's logits, nor where logits are asked for.
     // (In one launch workgroups write selections while others still read.)
     const size_t a4 = (size_t)(T * K) * 4;

@@ -142,3 +142,25 @@ def test_two_level_combine_by_row_pieces(c2r, orc, dtype, T, K, d):
         y = c2r.combine_copies(part, row, T, K, None if shared is None else dev(shared, dtype))
         ref2 = orc.combine_copies(host(part)[:n], rr, T, K, shared)
         assert np.abs(host(y) - ref2).max() <= bound(ref2, K * max(np.abs(host(part)[:n]).max(initial=0.0), np.abs(ys).max()))
+
+
+# entries of the send list past its copies: left as they are, or -1, in one launch and in two (one token, two and four per thread)
+@pytest.mark.parametrize("T,K,n_dev", [(1, 4, 4), (4096, 4, 4), (4097, 4, 4), (5000, 5, 60), (32769, 3, 7), (40000, 9, 2)])
+def test_dedup_list_past_its_copies(c2r, orc, T, K, n_dev):
+    rng = np.random.default_rng(T + K)
+    E = 60
+    idx = np.argsort(rng.random((T, E)), axis=1)[:, :K].astype(np.int32)
+    devmap = rng.integers(0, n_dev, size=E).astype(np.int32)
+    rt = orc.dedup_dispatch(idx, E, devmap, n_dev)[2]
+    i, m, i32 = dev(idx), dev(devmap), dict(dtype=torch.int32, device="cuda")
+    p = lambda t: t.data_ptr()
+    least = c2r.workspace_bytes(c2r.STAGE_DEDUP_DISPATCH, T, 0, n_dev, K, 0, c2r.F32)
+    for call, past in ((c2r.lib().c2r_dedup_dispatch, 123), (c2r.lib().c2r_dedup_dispatch_filled, -1)):
+        for ws in (torch.empty(least, dtype=torch.uint8, device="cuda"), torch.empty(4 * least, dtype=torch.uint8, device="cuda")):
+            tok = torch.full((T * K + 3,), 123, **i32)
+            counts, offsets, row = torch.empty(n_dev, **i32), torch.empty(n_dev + 1, **i32), torch.empty(T * K, **i32)
+            assert call(p(i), T, K, E, p(m), n_dev, p(counts), p(offsets), p(tok), p(row), p(ws), ws.numel(),
+                        torch.cuda.current_stream().cuda_stream) == 0
+            n = int(offsets[-1])
+            got = host(tok)
+            assert np.array_equal(got[:n], rt[:n]) and np.all(got[n:T * K] == past) and np.all(got[T * K:] == 123)
