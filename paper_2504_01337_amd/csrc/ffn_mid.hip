@@ -65,6 +65,12 @@ __device__ __forceinline__ void mid_walk(const FfnProblem &P, const GroupMap &gm
     constexpr int GA = AR / 32, GB = 2, NCOPY = GA + GB;  // 8-row copies per wave and slice
     constexpr int MF = AR / 32;                           // 16-row fragments per wave
     constexpr int BN = MODE == 0 ? MID_BR / 2 : MID_BR;
+    // Tiles of 32 rows have four matrix instructions a slice, and a slice's time is its chain of wait, barrier, fragment reads and those: the reads go
+    // ahead of the slice's copies, which the texture-address unit takes one by one.  Microseconds of a layer call, copies first / reads first:
+    // 60 experts + shared, 16 tokens 99.4 / 98.9, 40 tokens 122.7 / 120.4, 64 tokens 132.9 / 130.9, 80 tokens 133.5 / 131.6; 16 experts of d 4096, 24 tokens
+    // 71.0 / 69.7; 15 of 60 experts, 64 tokens 47.2 / 45.9.  Higher tiles are even or lose: 64-row tiles of gate/up, 8 experts of d 4096, 200
+    // tokens 86.6 / 88.8.
+    constexpr bool READS_FIRST = AR == 32;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ntn = P.ntn, N = P.N, Kdim = P.Kdim, nk = (Kdim + 63) / 64;
     const int n_items = __builtin_amdgcn_readfirstlane(gm.total_mtiles) * ntn;
@@ -171,10 +177,12 @@ __device__ __forceinline__ void mid_walk(const FfnProblem &P, const GroupMap &gm
         else
             wait_copies_but_and_lds<0>();
         lds_barrier();  // every wave's copies have landed and its reads of the slice before have returned: that stage is free
-        if (n + NSTAGE - 1 < total) request(stage == 0 ? NSTAGE - 1 : stage - 1);
+        const bool more = n + NSTAGE - 1 < total;
+        const int into = stage == 0 ? NSTAGE - 1 : stage - 1;
+        if (!READS_FIRST && more) request(into);
         const unsigned char *s = smem + stage * STAGE_BYTES;
+        bf16x8 a[2][MF], b[2][2];
         if (nf > 0) {
-            bf16x8 a[2][MF], b[2][2];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const uint32_t ch = (uint32_t)(((q * 4 + fq) ^ sw) * 16);
@@ -184,6 +192,9 @@ __device__ __forceinline__ void mid_walk(const FfnProblem &P, const GroupMap &gm
                 for (int i = 0; i < MF; ++i)
                     if (i < nf) a[q][i] = *reinterpret_cast<const bf16x8 *>(s + rdA[i] + ch);
             }
+        }
+        if (READS_FIRST && more) request(into);
+        if (nf > 0) {
             // (operands swapped: a lane's four results are consecutive columns of one row)
 #pragma unroll
             for (int q = 0; q < 2; ++q)
