@@ -1063,6 +1063,7 @@ bool ffn_skinny_takes(int pass, const FfnLaunch &L);
 bool ffn_skinny_takes_few(FfnLaunch L);
 int launch_ffn_skinny(int pass, const FfnLaunch &L, const FewRoute *few, hipStream_t st);
 bool ffn_mid_rows(int pass, const FfnLaunch &L, int likely, int (&rows)[2]);
+bool ffn_mid_in_one_round(const FfnProblem &down, int rows);
 int launch_ffn_mid(int pass, const int (&tile_rows)[2], FfnLaunch L, hipStream_t st);
 
 // Rows of the single group's tiles.  Fewer tiles than a quarter of the CUs, each a chain of k-slices much longer than those
@@ -1167,6 +1168,10 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
 //   so with a part of the experts, whose rows are 0.5 to 2.1 times n's (skewed load): 15 of 60 experts, three light quarters and the heaviest,
 //     n = 385 170 / 173, 166 / 166, 190 / 193, 319 / 294, n = 429 181 / 183, 173 / 175, 205 / 201, 356 / 328, n = 462 201 / 201, 194 / 193, 231 / 225;
 //     30 of 60, the light half n = 385 167 / 172, n = 407 170 / 174, n = 440 174 / 163, the heavy one n = 385 211 / 210, n = 506 269 / 257.
+//   one group alone, gate/up in tiles, by the items of ffn_mid's down pass (64 rows x 64 columns) for its 512 workgroups: up to one each, d 2048, F 12288,
+//     300 rows 106.8 / 148.9, 511 rows 108.8 / 152.3; d 4096, F 14336, 300 rows 209 / 235, 511 rows (512 items) 222 / 249; d 5120, F 13824, 384 rows
+//     232 / 254; more: 385 rows (560) 272.7 / 271.5, 511 rows 292 / 278; d 6144, F 12288, 320 rows (480) 241 / 273, 321 rows (576) 283 / 273; d 8192, F
+//     12288, 257 rows (640) 343 / 329.
 // (BOTH_BESIDE and BOTH_EARLY_UP_TO are measured on that one shape.)
 constexpr int BOTH_BESIDE = 256, BOTH_EARLY_UP_TO = 640, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 435;
 static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely) {
@@ -1174,7 +1179,8 @@ static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely
     if (ffn_skinny_takes(0, up) || ffn_skinny_takes(1, down)) return false;
     const FfnProblem &R = up.p[0], &S = up.p[1];
     if (ffn_mid_rows(0, up, likely, rows)) return !up.has_single && likely / R.E_local > BOTH_PER_GROUP;
-    if (up.has_single && S.A_cap <= BOTH_BESIDE && ffn_mid_rows(1, down, likely, rows)) return false;
+    if (up.has_single && ffn_mid_rows(1, down, likely, rows) && (up.has_ragged ? S.A_cap <= BOTH_BESIDE : ffn_mid_in_one_round(down.p[1], rows[1])))
+        return false;
     int64_t tiles = up.has_single ? (int64_t)(S.A_cap + 255) / 256 * S.ntn : 0;
     if (up.has_ragged) tiles += (int64_t)(likely / 256 + (R.E_local < likely ? R.E_local : likely) / 2) * R.ntn;
     return tiles >= (up.has_ragged && likely < R.A_cap ? BOTH_TILES_OF_PART : BOTH_TILES);

@@ -375,6 +375,11 @@ bool ffn_mid_rows(int pass, const FfnLaunch &L, int likely, int (&rows)[2]) {
     return true;
 }
 
+// Whether a down pass over one group alone leaves no workgroup more than one item.
+bool ffn_mid_in_one_round(const FfnProblem &down, int rows) {
+    return (int64_t)((down.A_cap + rows - 1) / rows) * ((down.N + MID_BR - 1) / MID_BR) <= 8 * MID_WG_PER_XCD;
+}
+
 int launch_ffn_mid(int pass, const int (&tile_rows)[2], FfnLaunch L, hipStream_t st) {
     drop_stale_error();
     for (FfnProblem &P : L.p) {

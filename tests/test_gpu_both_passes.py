@@ -172,3 +172,49 @@ def test_shared_expert_down_tiles_early(c2r, T, E, d, F, Fs):
                 out[i].copy_(layer.forward(x))
     torch.cuda.synchronize()
     assert all(torch.equal(o, ref) for out, ref in zip(outs, refs) for o in out)
+
+
+# one group alone: both passes in one launch (more items in ffn_mid's down pass than workgroups: 511 rows of d 4160) and a launch each (as many: d 4096)
+@pytest.mark.parametrize("d", [4096, 4160])
+def test_lone_group_at_the_limit_of_the_down_pass(c2r, d):
+    T, F = 511, 11520
+    assert ffn_kernel(0, 1, T, F) == "tile" and ffn_kernel(1, 1, T, d) == "mid" and ffn_tiles(1, T, F) >= ffn_tiles_limit()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    wg, wu, wd = (torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16).mul_(0.02) for s in ((1, F, d), (1, F, d), (1, d, F)))
+    x = torch.randn((T, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    offsets = dev(np.array([0, T], dtype=np.int32))
+    h = torch.empty((T, F), dtype=torch.bfloat16, device="cuda")
+    y = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+    c2r.expert_ffn_gate_up(x, offsets, wg, wu, h)
+    c2r.expert_ffn_down(h, offsets, wd, y)
+    for _ in range(3):
+        assert torch.equal(c2r.expert_ffn(x, offsets, wg, wu, wd), y)
+
+
+# One call takes no longer than its two passes by themselves where one group's down pass gives every workgroup of ffn_mid one item at most (300
+# rows of d 2048, F 12288: 107 us either way; 149 in one launch of the tile kernel, whose 40 down tiles are a chain of 192 slices each)
+def test_lone_group_costs_no_more_than_its_passes(c2r):
+    T, d, F = 300, 2048, 12288
+    wg, wu, wd = (torch.randn(s, device="cuda", dtype=torch.bfloat16) for s in ((1, F, d), (1, F, d), (1, d, F)))
+    x, y = torch.randn((T, d), device="cuda", dtype=torch.bfloat16), torch.empty((T, d), device="cuda", dtype=torch.bfloat16)
+    h, offsets = torch.empty((T, F), device="cuda", dtype=torch.bfloat16), dev(np.array([0, T], dtype=np.int32))
+    ws = torch.empty(c2r.workspace_bytes(c2r.STAGE_EXPERT_FFN, T, d, 1, 1, F, c2r.BF16), dtype=torch.uint8, device="cuda")
+
+    def passes():
+        c2r.expert_ffn_gate_up(x, offsets, wg, wu, h)
+        c2r.expert_ffn_down(h, offsets, wd, y)
+
+    best = []
+    for call in (passes, lambda: c2r.expert_ffn(x, offsets, wg, wu, wd, ws=ws, out=y)):
+        times = []
+        for _ in range(12):
+            beg, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            beg.record()
+            for _ in range(8):
+                call()
+            end.record()
+            torch.cuda.synchronize()
+            times.append(beg.elapsed_time(end))
+        best.append(min(times))
+    assert best[1] < 1.15 * best[0]
