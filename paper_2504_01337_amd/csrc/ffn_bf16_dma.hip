@@ -1154,13 +1154,10 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
 }
 
 // Whether one launch of the tile kernel takes both passes.  Microseconds of a layer call, a kernel per pass / so:
-//   gate/up in tiles (more than 179 rows of a shared expert), down in ffn_mid / one launch, the shared expert's down tiles early: 60 experts +
-//     shared, 220 tokens 171.5 / 175.5, 241 tokens 173 / 178 (one M-tile of the shared expert), 260 tokens 182 / 170, 300 tokens 187.5 / 176.8, 350
-//     tokens 194.8 / 172.9, 390 tokens 200 / 174.3;
-//   both passes in one launch, the shared expert's down tiles after all gate/up tiles / early: 420 tokens 193 / 180, 450 tokens 195 / 176, 520 tokens
-//     193.3 / 188.8, 600 tokens 196.4 / 195.4, 640 tokens 201.2 / 199, 700 tokens 198.5 / 205, 1000 tokens 226 / 248: the rows of h that the routed
-//     down tiles then wait for come late, and a tile of 64 rows takes 82 beside gate/up tiles that stream, 75 after them.  (With tiles of 128
-//     rows 390 tokens 186, 600 tokens 194, 1000 tokens 232; of 256 rows 420 tokens 208, 600 tokens 210, 1000 tokens 236.)
+//   gate/up in tiles (more than 179 rows of a shared expert), down in ffn_mid / one launch, the shared expert's down tiles early (ffn_down_early): 60
+//     experts + shared, F 1408 / 5632, 220 tokens 171.5 / 175.5, 241 tokens 173 / 178 (one M-tile of the shared expert), 260 tokens 175.9 / 163.8, 320
+//     tokens 172.5 / 165.2, 390 tokens 175.5 / 162.0; shared experts of 704 to 2816, 260 tokens 156.8 / 151.3 to 155.9 / 135.1, 320 tokens 156 / 154 to 175 /
+//     159, 390 tokens 155 / 150 to 182 / 163; 8 experts of d 4096, F 2816 / 8192, 260 tokens 242 / 215, 320 tokens 273 / 220;
 //   gate/up in ffn_mid, routed groups alone, r rows per expert: 16 experts of d 4096, r = 92 122.5 / 122.4, r = 125 128.4 / 132.6, r = 130
 //     144.7 / 134.0 (a chunk more per group), r = 147 152.8 / 138.0; 8 experts, r = 100 120 / 128, r = 125 141.7 / 135.2, r = 147 155.2 / 141.9.
 //   both in tiles, n gate/up tiles if the load is even: 16 experts of d 4096, n = 132 155 / 162, n = 188 184 / 179; 8 experts, n = 215 189 / 189:
@@ -1172,8 +1169,7 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
 //     300 rows 106.8 / 148.9, 511 rows 108.8 / 152.3; d 4096, F 14336, 300 rows 209 / 235, 511 rows (512 items) 222 / 249; d 5120, F 13824, 384 rows
 //     232 / 254; more: 385 rows (560) 272.7 / 271.5, 511 rows 292 / 278; d 6144, F 12288, 320 rows (480) 241 / 273, 321 rows (576) 283 / 273; d 8192, F
 //     12288, 257 rows (640) 343 / 329.
-// (BOTH_BESIDE and BOTH_EARLY_UP_TO are measured on that one shape.)
-constexpr int BOTH_BESIDE = 256, BOTH_EARLY_UP_TO = 640, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 435;
+constexpr int BOTH_BESIDE = 256, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 435;
 static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely) {
     int rows[2];
     if (ffn_skinny_takes(0, up) || ffn_skinny_takes(1, down)) return false;
@@ -1184,6 +1180,24 @@ static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely
     int64_t tiles = up.has_single ? (int64_t)(S.A_cap + 255) / 256 * S.ntn : 0;
     if (up.has_ragged) tiles += (int64_t)(likely / 256 + (R.E_local < likely ? R.E_local : likely) / 2) * R.ntn;
     return tiles >= (up.has_ragged && likely < R.A_cap ? BOTH_TILES_OF_PART : BOTH_TILES);
+}
+
+// Whether a launch of both passes takes the single group's down tiles early.  They gain where they are longer than what else is there to fill the end
+// of the launch with, and few; the rows of h that the routed down tiles wait for come later by it.  Microseconds of a layer call, after all gate/up
+// tiles / early, by the ratio of the two contractions:
+//   4, 60 experts, F 1408 / 5632, four draws of the weights: 420 tokens 185 / 171, 186 / 172, 199 / 181, 190 / 174, 512 tokens 188 / 177, 188 / 176, 204 / 191,
+//     181 / 176, 560 tokens 189 / 192, 190 / 196, 204 / 199, 198 / 192, 600 tokens 196 / 197, 185 / 187, 204 / 202, 640 tokens 186 / 192, 194 / 201, 197 / 199,
+//     195 / 195, 1000 tokens 226 / 248; 32 experts 520 tokens 179 / 172, 560 tokens 176 / 165; 16 of d 4096, F 2048 / 8192, 450 tokens 291 / 285, 520 tokens
+//     314 / 303, 640 tokens 338 / 341;
+//   3 and 2.5, 60 experts, F 1408 / 4224 and 3520: 300 tokens 165 / 157, 155.6 / 154, 390 tokens 159 / 160, 158 / 161, 420 tokens 159 / 161, 152.5 / 157, 512
+//     tokens 163 / 166, 160 / 164;
+//   2 and less: 260 tokens 148 / 145.5 (F 1408 / 2816), 151 / 135 (1408 / 1408), 390 tokens 156 / 158, 153 / 153, 480 tokens 156 / 158, 640 tokens 196 / 200.
+// (Up to 390 rows either way is ahead of a launch per pass, see above.)
+constexpr int BOTH_EARLY_UP_TO = 390, BOTH_EARLY_LONG_UP_TO = 600;
+static bool ffn_down_early(const FfnLaunch &down) {
+    if (!down.has_single || !down.has_ragged) return false;
+    const FfnProblem &R = down.p[0], &S = down.p[1];
+    return S.A_cap <= (S.Kdim > 3 * R.Kdim ? BOTH_EARLY_LONG_UP_TO : BOTH_EARLY_UP_TO);
 }
 
 // Whether the down pass may write while the gate/up pass still reads: its outputs meet nothing else of the two (but for one in the place of
@@ -1242,7 +1256,7 @@ int launch_ffn_bf16_dma_both(const FfnProblem (&first)[2], const FfnProblem *con
             if (!queues) return C2R_ERR_LAUNCH;
             const int64_t g0 = ffn_grid_of(L.pass[0]), g1 = ffn_grid_of(L.pass[1]);
             const dim3 g((unsigned)(g0 > g1 ? g0 : g1)), b(WM * WN * 64);
-            if (L.pass[1].has_single && L.pass[1].has_ragged && L.pass[1].p[1].A_cap <= BOTH_EARLY_UP_TO)
+            if (ffn_down_early(L.pass[1]))
                 ffn_bf16_dma_both_kernel<WM, WN, true><<<g, b, 0, st>>>(L, queues, (int)mtiles);
             else
                 ffn_bf16_dma_both_kernel<WM, WN, false><<<g, b, 0, st>>>(L, queues, (int)mtiles);

@@ -120,8 +120,13 @@ def ffn_tiles(E, rows, F):
     return (-(-rows // 256) if E == 1 else rows // 256 + min(E, rows) // 2) * -(-F // 128)
 
 
+def ffn_both_limit(name):
+    """A limit of the rules by which one launch takes both passes (BOTH_*, ffn_bf16_dma.hip)."""
+    return int(re.search(r"\bBOTH_%s = (\d+)" % name, _csrc("ffn_bf16_dma.hip")).group(1))
+
+
 def ffn_tiles_limit():
-    return int(re.search(r"\bBOTH_TILES = (\d+)", _csrc("ffn_bf16_dma.hip")).group(1))
+    return ffn_both_limit("TILES")
 
 
 def _mid_limits(side):

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import dev, ffn_kernel, ffn_tiles, ffn_tiles_limit
+from helpers import dev, ffn_both_limit, ffn_kernel, ffn_tiles, ffn_tiles_limit
 
 pytestmark = pytest.mark.gpu
 
@@ -67,9 +67,15 @@ def test_layer_with_shared_expert(c2r, T, d, F, Fs):
         assert torch.equal(a.y_perm, b.y_perm) and torch.equal(a.y_shared, b.y_shared)
 
 
-# the layer call on either side of the rules that give a pass to this kernel or that: 390 rows of a shared expert, 125 likely rows per expert,
-# 4096 rows allotted to a device with a part of the experts.  The same bits as stage by stage, where every pass chooses by the rows allotted.
-@pytest.mark.parametrize("T,E,El,K,Fs", [(390, 60, 60, 4, 192), (391, 60, 60, 4, 192), (501, 16, 16, 4, 0), (504, 16, 16, 4, 0), (600, 16, 16, 4, 0),
+BESIDE, EARLY, LONG = ffn_both_limit("BESIDE"), ffn_both_limit("EARLY_UP_TO"), ffn_both_limit("EARLY_LONG_UP_TO")
+
+
+# the layer call on either side of the rules that give a pass to this kernel or that: rows of a shared expert (one launch for both passes, its
+# down tiles early), 125 likely rows per expert, 4096 rows allotted to a device with a part of the experts.  The same bits as stage by stage,
+# where every pass chooses by the rows allotted.
+@pytest.mark.parametrize("T,E,El,K,Fs", [(BESIDE, 60, 60, 4, 192), (BESIDE + 1, 60, 60, 4, 192), (EARLY, 60, 60, 4, 192), (EARLY + 1, 60, 60, 4, 192),
+                                         (LONG, 60, 60, 4, 2176), (LONG + 1, 60, 60, 4, 2176),
+                                         (390, 60, 60, 4, 192), (391, 60, 60, 4, 192), (501, 16, 16, 4, 0), (504, 16, 16, 4, 0), (600, 16, 16, 4, 0),
                                          (1000, 60, 15, 4, 0), (1024, 60, 15, 4, 0), (1025, 60, 15, 4, 0), (2100, 60, 15, 4, 0), (15500, 60, 15, 4, 0),
                                          (16384, 60, 15, 4, 0), (17000, 60, 15, 4, 0), (300, 64, 1, 4, 0)])
 def test_layer_at_the_limits_of_the_kernels(c2r, T, E, El, K, Fs):
@@ -141,10 +147,13 @@ def test_beside_another_launch(c2r):
     assert all(torch.equal(o, ref) for out, ref in zip(outs, refs) for o in out)
 
 
-# a shared expert's down tiles ahead of routed gate/up tiles: both ends of the rule's range and one row beyond, a down pass cut to 64 rows (long
-# contraction) and whole, more gate/up tiles than a round and one tile only, nothing but the shared expert's in a list's first round; two such
-# layers on two streams, each of whose waits must end by workgroups of its own launch
-@pytest.mark.parametrize("T,E,d,F,Fs", [(257, 60, 128, 704, 2816), (420, 60, 2048, 320, 5632), (640, 60, 256, 1408, 1024), (641, 60, 256, 1408, 1024),
+# a shared expert's down tiles ahead of routed gate/up tiles: the last rows on one side of the rules and the first on the other (two launches; a
+# shared contraction of more than three times the routed one and of as much), a down pass cut to 64 rows (long contraction) and whole, more gate/up
+# tiles than a round and one tile only, nothing but the shared expert's in a list's first round; two such layers on two streams, each of whose
+# waits must end by workgroups of its own launch
+@pytest.mark.parametrize("T,E,d,F,Fs", [(BESIDE, 60, 128, 704, 2816), (BESIDE + 1, 60, 128, 704, 2816), (EARLY, 60, 128, 704, 2112), (EARLY + 1, 60, 128, 704, 2112),
+                                        (LONG, 60, 128, 704, 2176), (LONG + 1, 60, 128, 704, 2176),
+                                        (257, 60, 128, 704, 2816), (420, 60, 2048, 320, 5632), (640, 60, 256, 1408, 1024), (641, 60, 256, 1408, 1024),
                                         (300, 60, 128, 1408, 64), (512, 16, 192, 192, 16448), (257, 2, 64, 11264, 8192)])
 def test_shared_expert_down_tiles_early(c2r, T, E, d, F, Fs):
     K = min(E, 4)
