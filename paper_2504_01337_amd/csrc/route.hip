@@ -120,8 +120,9 @@ __device__ __forceinline__ void build_masks(uint64_t *mask_tab, const int32_t *_
 
 // The selection of 32 tokens by the wave that has their logits in registers, K <= 4: lane (mh, mc) holds experts 32 a + 8 (i / 4) + 4 mh + i % 4
 // of token mc.  Both lanes of a token run the keyed chain of route_select_rows_kernel over their experts and then over the other's
-// largest; with lists a chain of two keys finds the first expert, one over its collaborators the others.  What the keys cannot
-// decide is scanned by the literal rule (see route_select_keys_kernel).  tile (LDS, this wave's): the logits, [expert][32 tokens].
+// largest; with lists a chain of two keys finds the first expert, one over its collaborators the others.  Experts masked by -infinity stay
+// out of the chains and are chosen, by the literal rule, where nothing else is left.  What the keys cannot decide is scanned by that
+// rule (see route_select_keys_kernel).  tile (LDS, this wave's): the logits, [expert][32 tokens].
 template <int NEB, class Acc>
 __device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, const uint64_t *mask_tab, const SelectArgs &S, int64_t t0, int64_t T) {
     const int lane = lane_id(), mh = lane >> 5, mc = lane & 31, E = S.E, K = S.K;
@@ -146,6 +147,23 @@ __device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, con
     }
     chk += __shfl_xor(chk, 32);
     low |= __shfl_xor(low, 32);
+    uint64_t masked = 0;  // the token's experts at -infinity
+    if (__ballot(chk != chk)) {  // (one of them makes a NaN of every token's sum)
+        uint32_t mine[2] = {0u, 0u};
+        chk = 0.0f;
+#pragma unroll
+        for (int n = 0; n < NEB * 16; ++n) {
+            const int e0 = n / 16 * 32 + n % 16 / 4 * 8 + n % 4;
+            const bool out = __float_as_int(l[n]) == KEY_EMPTY;
+            if (e0 + mh * 4 < E) {
+                mine[n / 16] |= out ? 1u << (e0 % 32) : 0u;
+                chk = __builtin_fmaf(out ? 0.0f : l[n], 0.0f, chk);
+            }
+        }
+        chk += __shfl_xor(chk, 32);
+        masked = ((uint64_t)mine[1] << 32 | mine[0]) << (mh * 4);
+        masked |= (uint64_t)(uint32_t)__shfl_xor((int)(masked >> 32), 32) << 32 | (uint32_t)__shfl_xor((int)masked, 32);
+    }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (the tile is this wave's alone)
     // the NKEEP largest keys of the token's experts in m, the same in both its lanes
     auto largest = [&](auto &k, uint64_t m) __attribute__((always_inline)) {
@@ -180,25 +198,33 @@ __device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, con
         return any;
     };
     int es[4];
+    bool bare;  // a slot is left empty
     if (lists) {
         int k[2], r[4];
-        largest(k, all);
+        largest(k, all & ~masked);
         literal = literal || undecided(k);
         es[0] = 63 - (k[0] & 63);
-        largest(r, lists[es[0]]);
+        const uint64_t allowed = lists[es[0]];
+        largest(r, allowed & ~masked);
         literal = literal || undecided(r);
+        masked &= k[0] == KEY_EMPTY ? ~0ull : allowed;
         nonneg = k[1] >= 0 && r[3] >= 0;
 #pragma unroll
         for (int s = 1; s < 4; ++s) es[s] = r[s - 1] == KEY_EMPTY ? -1 : 63 - (r[s - 1] & 63);
+        bare = k[0] == KEY_EMPTY;
     } else {
         int k[5];
-        largest(k, all);
+        largest(k, all & ~masked);
         literal = literal || undecided(k);
         nonneg = k[4] >= 0;
         es[0] = 63 - (k[0] & 63);
 #pragma unroll
         for (int s = 1; s < 4; ++s) es[s] = k[s] == KEY_EMPTY ? -1 : 63 - (k[s] & 63);
+        bare = k[0] == KEY_EMPTY;
     }
+#pragma unroll
+    for (int s = 1; s < 4; ++s) bare = bare || (s < K && es[s] < 0);
+    literal = literal || (bare && masked != 0);
     uint64_t todo = __ballot(literal && t < T && mh == 0);
     if (todo & (todo - 1)) {
         // (rows of zeros that pad a batch: where the replaced bits were all zero and the keys kept are not negative, equal logits lie in

@@ -207,3 +207,58 @@ def test_selection_beside_the_sums(orc, T, E, K, d, dtype):
     idx = x2.view(-1).view(torch.int32)[:T * K].view(T, K)
     got = c2r.route(x2, wd, None, K, None, out=(idx, torch.empty((T, K), device="cuda")))
     assert np.array_equal(host(got[0]), orc.route(host(c2r.route(xd, wd, None, K, want_logits=True)[2]), K)[0])
+
+
+# experts masked by -infinity in the same selection: one, every second, all but two, all; by the type's lowest value; lists of any experts and, for half
+# of the experts, of masked ones alone (what is left to choose is then masked itself); rows of zeros among the others, a NaN and an infinity
+@pytest.mark.parametrize("T,E,K,d,dtype", [(25025, 60, 4, 512, "bf16"), (25100, 33, 3, 264, "f32"), (32705, 20, 2, 512, "bf16"), (32721, 32, 4, 264, "f32"),
+                                           (25030, 64, 1, 264, "bf16")])
+def test_masked_experts_beside_the_sums(orc, T, E, K, d, dtype):
+    from paper_2504_01337_amd import c2r
+    rng = np.random.default_rng(T + E)
+    x = wl.round_bf16(rng.standard_normal((T, d)).astype(np.float32))
+    x[1000:1100], x[::97], x[5, 3], x[77, 0] = 0.0, 0.0, np.inf, np.nan
+    Wg = (0.25 * rng.standard_normal((d, E))).astype(np.float32)
+    order = rng.permutation(E)
+    xd, wd = dev(x, dtype), dev(Wg)
+    for out, value in ((order[:1], -np.inf), (order[::2], -np.inf), (order[2:], -np.inf), (order, -np.inf), (order[::2], np.finfo(np.float32).min)):
+        bias = rng.standard_normal(E).astype(np.float32)
+        bias[out] = value
+        lists = np.stack([rng.permutation(np.delete(np.arange(E), e))[:max(K, E // 3)] for e in range(E)]).astype(np.int32)
+        n = max(K - 1, 1)
+        gone = np.stack([rng.permutation(out[out != e] if e % 2 and len(out) > n else np.delete(np.arange(E), e))[:n] for e in range(E)]).astype(np.int32)
+        for cl in (None, lists, gone):
+            bd, cd = dev(bias), None if cl is None else dev(cl)
+            ri, rg = orc.route(host(c2r.route(xd, wd, bd, K, cd, want_logits=True)[2]), K, cl)
+            idx, gates, _ = c2r.route(xd, wd, bd, K, cd)
+            assert np.array_equal(host(idx), ri)
+            # (logits up to some hundred apart: the bound of GATE_RTOL with |a_s| up to 104, where a gate is flushed to zero)
+            np.testing.assert_allclose(host(gates), rg, rtol=114 / 34 * GATE_RTOL, atol=1e-37)
+
+
+# ... which costs what any other batch does (1.3 times it, 8 us of 28, with every token scanned by the literal rule), and so do rows of zeros
+@pytest.mark.parametrize("lists", [False, True])
+def test_masked_experts_beside_the_sums_cost_no_more(lists):
+    import torch
+    from paper_2504_01337_amd import c2r
+    T, E, d = 32768, 60, 512
+    x, Wg = torch.randn((T, d), device="cuda", dtype=torch.bfloat16), torch.randn((d, E), device="cuda")
+    plain = torch.zeros(E, device="cuda")
+    masked = plain.clone()
+    masked[7] = float("-inf")
+    cl = dev(np.stack([np.random.default_rng(e).permutation(np.delete(np.arange(E), e))[:16] for e in range(E)]).astype(np.int32)) if lists else None
+    ws = torch.empty(c2r.workspace_bytes(c2r.STAGE_ROUTE, T, d, E, 4, 0, c2r.BF16), dtype=torch.uint8, device="cuda")
+    out = torch.empty((T, 4), dtype=torch.int32, device="cuda"), torch.empty((T, 4), device="cuda")
+    best = []
+    for a, bias in ((x, plain), (x, masked), (torch.zeros_like(x), plain)):
+        times = []
+        for _ in range(20):
+            beg, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            beg.record()
+            for _ in range(8):
+                c2r.route(a, Wg, bias, 4, cl, ws=ws, out=out)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(beg.elapsed_time(end))
+        best.append(min(times))
+    assert max(best[1:]) < 1.15 * best[0]
