@@ -104,8 +104,6 @@ __device__ __forceinline__ int key_med3(int a, int b, int c) {
 }
 __device__ __forceinline__ bool keys_apart(int a, int b) { return ((a ^ b) & ~63) != 0; }
 
-constexpr int KEYS_SCAN_TOGETHER = 8;  // as SCAN_TOGETHER; here a token scanned by the wave also waits for its logits out of L2
-
 // The collaborators of every expert as a 64-bit mask (without itself; without lists all others).  Every thread of the workgroup calls it.
 __device__ __forceinline__ void build_masks(uint64_t *mask_tab, const int32_t *__restrict__ collab_idx, int E, int Tc, uint64_t all) {
     if (threadIdx.x < C2R_MAX_E) mask_tab[threadIdx.x] = collab_idx ? 0ull : all & ~(1ull << threadIdx.x);
@@ -117,6 +115,11 @@ __device__ __forceinline__ void build_masks(uint64_t *mask_tab, const int32_t *_
     }
     __syncthreads();
 }
+
+// Undecided tokens of the 32 of a wave below: scanned by the wave one after the other, at 0.95 us each, or by their own lanes all at once, at
+// 2 us and 0.1 a column.  Microseconds of the router with n of every 32 tokens undecided (together / alone), 32768 tokens of d 512: 60 experts, n = 6 33.0 /
+// 36.1, n = 8 34.6 / 36.3, n = 10 36.5 / 34.2; 32 experts, n = 5 23.0 / 23.3, n = 6 24.0 / 23.2; 20 experts, n = 4 22.1 / 24.0, n = 5 22.8 / 22.0.
+__device__ __forceinline__ bool scan_alone(int n, int E) { return 9 * n > E + 20; }
 
 // The selection of 32 tokens by the wave that has their logits in registers, K <= 4: lane (mh, mc) holds experts 32 a + 8 (i / 4) + 4 mh + i % 4
 // of token mc.  Both lanes of a token run the keyed chain of route_select_rows_kernel over their experts and then over the other's
@@ -232,7 +235,7 @@ __device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, con
         literal = literal && !(chk == chk && low == 0 && nonneg);
         todo = __ballot(literal && t < T && mh == 0);
     }
-    const bool alone = __popcll(todo) * KEYS_SCAN_TOGETHER > E;
+    const bool alone = scan_alone(__popcll(todo), E);
     float gs[4] = {0.0f, 0.0f, 0.0f, 0.0f}, den = 1.0f;
     if (!literal) {
         float vs[4];
@@ -252,13 +255,19 @@ __device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, con
     } else if (alone && t < T) {
         literal_scan(
             [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
-                bi = -1;
-                bv = 0.0f;
-                for (int e = 0; e < E; ++e) {
-                    const float v = tile[e * 32 + mc];
-                    const bool take = ((mm >> e) & 1ull) != 0 && (bi < 0 || v > bv);
-                    bv = take ? v : bv;
-                    bi = take ? e : bi;
+                bi = __ffsll((unsigned long long)mm) - 1;
+                bv = tile[(bi < 0 ? 0 : bi) * 32 + mc];
+                for (int e0 = 0; e0 < E; e0 += 8) {  // (eight reads at once; columns past E are not in mm)
+                    const uint32_t in = (uint32_t)(mm >> e0);
+                    float v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = tile[(e0 + u) * 32 + mc];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const bool take = (in & (1u << u)) != 0 && v[u] > bv;
+                        bv = take ? v[u] : bv;
+                        bi = take ? e0 + u : bi;
+                    }
                 }
             },
             K, all, lists, es, gs, den);
@@ -1208,6 +1217,7 @@ constexpr int SCAN_TOGETHER = 5;
 // Bound by the launch and two trips to memory; the stage with route_select_kernel / with this: 60 experts, d 2048: 32768 tokens 87.0 / 84.0,
 // 65536 tokens 155 / 150; 16 experts, 32768 tokens 103.8 / 102.4.  (With lists, the largest two keys and a second chain over the
 // first one's list, it was no faster: 15.6 against 12.7 us for the kernel at 32768 tokens.)
+constexpr int KEYS_SCAN_TOGETHER = 8;  // as SCAN_TOGETHER; here a token scanned by the wave also waits for its logits out of L2
 
 template <int EP>
 __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__restrict__ part, const float *__restrict__ bias, int64_t T,
