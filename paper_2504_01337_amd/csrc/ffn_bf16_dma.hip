@@ -402,9 +402,10 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
         copy_piece(CKT, CST, (P0) + (Q), STEADY);   \
         __builtin_amdgcn_sched_barrier(0);          \
     }
-// (odd rows of fragments run through the columns backwards, so that two instructions in a row always share an operand: under the power
-// limit that is clock.  Layer call, every row forwards / so, three runs each in turn: 60 experts + shared, 8192 tokens 1053.6 / 1046.8 us, 15 of 60
-// experts, 32768 tokens 447.9 / 443.4, 16 experts of d 4096, 4096 tokens 331.9 / 330.6.  Columns of fragments instead of rows: as forwards)
+// (odd rows of fragments run through the columns backwards, so that two instructions in a row always share an operand.  It is worth little:
+// layer call, every row forwards / so, 25 times in turn: 60 experts + shared, 8192 tokens 1032.4 / 1028.7 us, 1000 tokens 228.2 / 227.1, 15 of 60 experts,
+// 32768 tokens 431.1 / 430.6, 16 experts of d 4096, 4096 tokens 320.8 / 320.5; the launch of 8192 tokens under counters 909.7 / 907.8, at 1.971 / 1.970 GHz with
+// the matrix pipe busy 0.614 of the time either way.  Columns of fragments instead of rows: as forwards)
 #define C2R_MFMA_HALF(AS, BS, H, I, J0)                  \
     C2R_MFMA(AS, BS, H, I, (J0) + ((I) & 1));            \
     C2R_MFMA(AS, BS, H, I, (J0) + 1 - ((I) & 1))
@@ -730,9 +731,10 @@ __device__ __forceinline__ void ffn_tile(const FfnLaunchArgs Lp, unsigned char *
 // A launch of both passes has 8 more ticket counters for the second, the number of gate/up tiles that are finished, and per M-tile
 // the rows of h that are, summed over its N-tiles.
 // Every counter that the workgroups of one XCD use most has a 128-byte line of its own: atomics of several XCDs on one line wait for each
-// other, and a workgroup's next tile for them.  (M-tiles next to each other are mostly one XCD's: four to a line.)  Layer call, all in one line
-// and its neighbours / so, microseconds: 60 experts + shared, 1000 tokens 232.5 / 225.9; 16 experts of d 4096, 4096 tokens 332.4 / 324.0; 8 experts,
-// 2000 tokens 189.6 / 180.2; 60 experts + shared, 8192 tokens 1038 / 1031.
+// other, and a workgroup's next tile for them.  (M-tiles next to each other are mostly one XCD's: four to a line.)  Microseconds, all in one line
+// and its neighbours / so, one after the other in one process: the joint launch, 60 experts + shared, 420 tokens 166.4 / 161.0, 1000 tokens 210.3 /
+// 203.4; 16 experts of d 4096, 4096 tokens 278.0 / 267.2; 8 experts, 2000 tokens 162.4 / 153.1; the layer call of the four 182.3 / 175.0, 226.1 / 222.0,
+// 325.2 / 318.9, 187.8 / 175.6, 8192 tokens of the first 1045 / 1035.
 constexpr int FFN_MTILES = 1024;
 constexpr int FFN_LEFT = 8 * FFN_LINE, FFN_FINISHED = 9 * FFN_LINE, FFN_DOWN = 10 * FFN_LINE, FFN_ROWS_DONE = 18 * FFN_LINE;
 constexpr int FFN_QUEUE_SETS = 64, FFN_QUEUE_INTS = 9 * FFN_LINE, FFN_BOTH_INTS = FFN_ROWS_DONE + FFN_MTILES * FFN_MTILE_INTS;

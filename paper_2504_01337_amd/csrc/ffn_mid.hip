@@ -66,10 +66,11 @@ __device__ __forceinline__ void mid_walk(const FfnProblem &P, const GroupMap &gm
     constexpr int MF = AR / 32;                           // 16-row fragments per wave
     constexpr int BN = MODE == 0 ? MID_BR / 2 : MID_BR;
     // Tiles of 32 rows have four matrix instructions a slice, and a slice's time is its chain of wait, barrier, fragment reads and those: the reads go
-    // ahead of the slice's copies, which the texture-address unit takes one by one.  Microseconds of a layer call, copies first / reads first:
-    // 60 experts + shared, 16 tokens 99.4 / 98.9, 40 tokens 122.7 / 120.4, 64 tokens 132.9 / 130.9, 80 tokens 133.5 / 131.6; 16 experts of d 4096, 24 tokens
-    // 71.0 / 69.7; 15 of 60 experts, 64 tokens 47.2 / 45.9.  Higher tiles are even or lose: 64-row tiles of gate/up, 8 experts of d 4096, 200
-    // tokens 86.6 / 88.8.
+    // ahead of the slice's copies, which the texture-address unit takes one by one.  Microseconds, copies first / reads first, one after the other in
+    // one process: the kernel, 60 experts + shared, gate/up, 16 tokens 43.5 / 42.7, 24 tokens 47.0 / 45.8, 40 tokens 61.9 / 60.8, down, 40 tokens 38.9 /
+    // 37.1, 64 tokens 39.3 / 38.4; 16 experts of d 4096, 24 tokens 30.5 / 30.1 and 17.5 / 17.2; 15 of 60 experts, 64 tokens 13.5 / 13.0 and 9.3 / 8.3; the
+    // layer call, 16 tokens 79.5 / 78.6, 40 tokens 116.8 / 113.6, 64 tokens 135.0 / 134.0; d 4096, 24 tokens 63.3 / 62.1; 15 of 60 experts, 64 tokens
+    // 41.5 / 40.1.  Higher tiles are even or lose: 64-row tiles of gate/up, 8 experts of d 4096, 200 tokens 86.6 / 88.8.
     constexpr bool READS_FIRST = AR == 32;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ntn = P.ntn, N = P.N, Kdim = P.Kdim, nk = (Kdim + 63) / 64;

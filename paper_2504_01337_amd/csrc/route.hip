@@ -1214,8 +1214,9 @@ constexpr int SCAN_TOGETHER = 5;
 
 // Top-K, K <= 4, from ONE chunk result per token ([tile][expert][64 tokens]), without lists: a wave per 64 tokens, lane = token, its
 // logits in registers, chosen by the keyed chain of route_select_rows_kernel below, the literal scan where that cannot decide.
-// Bound by the launch and two trips to memory; the stage with route_select_kernel / with this: 60 experts, d 2048: 32768 tokens 87.0 / 84.0,
-// 65536 tokens 155 / 150; 16 experts, 32768 tokens 103.8 / 102.4.  (With lists, the largest two keys and a second chain over the
+// Such batches are those of one chunk (d up to 256), those whose sums select_of_sums cannot take: 64-token workgroups, logits asked for,
+// results that meet the inputs.  Bound by the launch and two trips to memory; the stage with route_select_kernel / with this, in batches that
+// now take the other: 60 experts, d 2048: 32768 tokens 87.0 / 84.0, 65536 tokens 155 / 150; 16 experts, 32768 tokens 103.8 / 102.4.  (With lists, the largest two keys and a second chain over the
 // first one's list, it was no faster: 15.6 against 12.7 us for the kernel at 32768 tokens.)
 constexpr int KEYS_SCAN_TOGETHER = 8;  // as SCAN_TOGETHER; here a token scanned by the wave also waits for its logits out of L2
 
