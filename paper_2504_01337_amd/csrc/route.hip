@@ -103,6 +103,55 @@ __device__ __forceinline__ int key_med3(int a, int b, int c) {
     return d;
 }
 __device__ __forceinline__ bool keys_apart(int a, int b) { return ((a ^ b) & ~63) != 0; }
+// The N largest keys so far, k[0] >= k[1] >= ... throughout, and one more.
+template <int N>
+__device__ __forceinline__ void keep_key(int (&k)[N], int kk) {
+    int nk[N];
+    nk[0] = key_max(k[0], kk);
+#pragma unroll
+    for (int u = 1; u < N; ++u) nk[u] = key_med3(k[u - 1], k[u], kk);
+#pragma unroll
+    for (int u = 0; u < N; ++u) k[u] = nk[u];
+}
+// Whether the replaced bits may have decided the order of the keys kept, or what the last one is.
+template <int N>
+__device__ __forceinline__ bool keys_undecided(const int (&k)[N]) {
+    bool any = false;
+#pragma unroll
+    for (int u = 0; u + 1 < N; ++u) any = any | !(keys_apart(k[u], k[u + 1]) | (k[u] == KEY_EMPTY));
+    return any;
+}
+
+// Gates before the division, and the divisor, of the experts es (-1: none) with logits vs.
+__device__ __forceinline__ void gates_of(const float (&vs)[4], const int (&es)[4], int K, float (&gs)[4], float &den) {
+    gs[0] = expf(vs[0] - vs[0]);
+    den = gs[0];
+#pragma unroll
+    for (int s = 1; s < 4; ++s)
+        if (s < K) {
+            if (es[s] >= 0) gs[s] = expf(vs[s] - vs[0]);
+            den += gs[s];
+        }
+}
+
+// A token's selection out, for K <= 4.
+__device__ __forceinline__ void store_selection(int64_t t, int K, const int (&es)[4], float (&gs)[4], float den, int32_t *topk_idx, float *gates) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) gs[s] = gs[s] / den;
+    if (K == 4 && ((reinterpret_cast<uintptr_t>(topk_idx) | reinterpret_cast<uintptr_t>(gates)) & 15) == 0) {
+        typedef int i32x4 __attribute__((ext_vector_type(4)));
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        *reinterpret_cast<i32x4 *>(topk_idx + (size_t)t * 4) = i32x4{es[0], es[1], es[2], es[3]};
+        *reinterpret_cast<f32x4 *>(gates + (size_t)t * 4) = f32x4{gs[0], gs[1], gs[2], gs[3]};
+    } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (s < K) {
+                topk_idx[(size_t)t * K + s] = es[s];
+                gates[(size_t)t * K + s] = gs[s];
+            }
+    }
+}
 
 // The collaborators of every expert as a 64-bit mask (without itself; without lists all others).  Every thread of the workgroup calls it.
 __device__ __forceinline__ void build_masks(uint64_t *mask_tab, const int32_t *__restrict__ collab_idx, int E, int Tc, uint64_t all) {
@@ -173,43 +222,29 @@ __device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, con
         constexpr int NKEEP = sizeof(k) / sizeof(k[0]);
 #pragma unroll
         for (int u = 0; u < NKEEP; ++u) k[u] = KEY_EMPTY;
-        auto insert = [&](int kk) __attribute__((always_inline)) {
-            int nk[NKEEP];
-            nk[0] = key_max(k[0], kk);
-#pragma unroll
-            for (int u = 1; u < NKEEP; ++u) nk[u] = key_med3(k[u - 1], k[u], kk);  // (k[0] >= k[1] >= ... throughout)
-#pragma unroll
-            for (int u = 0; u < NKEEP; ++u) k[u] = nk[u];
-        };
         const uint32_t mine[2] = {(uint32_t)(m >> (mh * 4)), (uint32_t)(m >> 32 >> (mh * 4))};
 #pragma unroll
         for (int n = 0; n < NEB * 16; ++n) {
             const int e0 = n / 16 * 32 + n % 16 / 4 * 8 + n % 4;
-            insert((mine[n / 16] >> (e0 % 32)) & 1u ? (int)((__float_as_uint(l[n]) & ~63u) | (uint32_t)(63 - e0 - mh * 4)) : KEY_EMPTY);
+            keep_key(k, (mine[n / 16] >> (e0 % 32)) & 1u ? (int)((__float_as_uint(l[n]) & ~63u) | (uint32_t)(63 - e0 - mh * 4)) : KEY_EMPTY);
         }
         int other[NKEEP];
 #pragma unroll
         for (int u = 0; u < NKEEP; ++u) other[u] = __shfl_xor(k[u], 32);
 #pragma unroll
-        for (int u = 0; u < NKEEP; ++u) insert(other[u]);
+        for (int u = 0; u < NKEEP; ++u) keep_key(k, other[u]);
     };
     bool literal = chk != chk, nonneg;
-    auto undecided = [&](const auto &k) __attribute__((always_inline)) {
-        bool any = false;
-#pragma unroll
-        for (int u = 0; u + 1 < (int)(sizeof(k) / sizeof(k[0])); ++u) any = any || !(keys_apart(k[u], k[u + 1]) || k[u] == KEY_EMPTY);
-        return any;
-    };
     int es[4];
     bool bare;  // a slot is left empty
     if (lists) {
         int k[2], r[4];
         largest(k, all & ~masked);
-        literal = literal || undecided(k);
+        literal = literal || keys_undecided(k);
         es[0] = 63 - (k[0] & 63);
         const uint64_t allowed = lists[es[0]];
         largest(r, allowed & ~masked);
-        literal = literal || undecided(r);
+        literal = literal || keys_undecided(r);
         masked &= k[0] == KEY_EMPTY ? ~0ull : allowed;
         nonneg = k[1] >= 0 && r[3] >= 0;
 #pragma unroll
@@ -218,7 +253,7 @@ __device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, con
     } else {
         int k[5];
         largest(k, all & ~masked);
-        literal = literal || undecided(k);
+        literal = literal || keys_undecided(k);
         nonneg = k[4] >= 0;
         es[0] = 63 - (k[0] & 63);
 #pragma unroll
@@ -244,14 +279,7 @@ __device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, con
             if (s >= K) es[s] = -1;
             vs[s] = tile[(es[s] < 0 ? 0 : es[s]) * 32 + mc];
         }
-        gs[0] = expf(vs[0] - vs[0]);
-        den = gs[0];
-#pragma unroll
-        for (int s = 1; s < 4; ++s)
-            if (s < K) {
-                if (es[s] >= 0) gs[s] = expf(vs[s] - vs[0]);
-                den += gs[s];
-            }
+        gates_of(vs, es, K, gs, den);
     } else if (alone && t < T) {
         literal_scan(
             [&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) {
@@ -286,24 +314,7 @@ __device__ __forceinline__ void select_of_sums(const Acc &sums, float *tile, con
             }
         }
     }
-    if (t >= T || mh != 0) return;
-    int32_t *topk_idx = S.topk_idx;
-    float *gates = S.gates;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) gs[s] = gs[s] / den;
-    if (K == 4 && ((reinterpret_cast<uintptr_t>(topk_idx) | reinterpret_cast<uintptr_t>(gates)) & 15) == 0) {
-        typedef int i32x4 __attribute__((ext_vector_type(4)));
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        *reinterpret_cast<i32x4 *>(topk_idx + (size_t)t * 4) = i32x4{es[0], es[1], es[2], es[3]};
-        *reinterpret_cast<f32x4 *>(gates + (size_t)t * 4) = f32x4{gs[0], gs[1], gs[2], gs[3]};
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-            if (s < K) {
-                topk_idx[(size_t)t * K + s] = es[s];
-                gates[(size_t)t * K + s] = gs[s];
-            }
-    }
+    if (t < T && mh == 0) store_selection(t, K, es, gs, den, S.topk_idx, S.gates);
 }
 
 // Partial logits of one 256-long k-chunk for NWV token tiles of 8*TQ tokens (one per wave), all
@@ -1252,17 +1263,10 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
         if (e < E) {  // (uniform)
             l[e] = l[e] + 0.0f;
             chk = __builtin_fmaf(l[e], 0.0f, chk);  // NaN once a NaN or an infinity went in
-            const int kk = key_of(l[e], e);
-            int nk[NKEEP];
-            nk[0] = key_max(k[0], kk);
-#pragma unroll
-            for (int u = 1; u < NKEEP; ++u) nk[u] = key_med3(k[u - 1], k[u], kk);  // (k[0] >= k[1] >= ... throughout)
-#pragma unroll
-            for (int u = 0; u < NKEEP; ++u) k[u] = nk[u];
+            keep_key(k, key_of(l[e], e));
         }
     bool literal = chk != chk;
-#pragma unroll
-    for (int u = 0; u + 1 < NKEEP; ++u) literal = literal || !(keys_apart(k[u], k[u + 1]) || k[u] == KEY_EMPTY);
+    literal = literal || keys_undecided(k);
     // Undecided tokens come in numbers where rows of zeros pad a batch (their logits are all +0) or an expert is masked by -infinity.
     // Where the replaced bits were all zero and the keys kept are not negative, equal logits lie in ascending columns and the chain
     // is right as it stands; what is left is scanned as in route_select_rows_kernel.
@@ -1287,14 +1291,7 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
             if (s >= K) es[s] = -1;
             vs[s] = logit_of(es[s] < 0 ? 0 : es[s]);
         }
-        gs[0] = expf(vs[0] - vs[0]);
-        den = gs[0];
-#pragma unroll
-        for (int s = 1; s < 4; ++s)
-            if (s < K) {
-                if (es[s] >= 0) gs[s] = expf(vs[s] - vs[0]);
-                den += gs[s];
-            }
+        gates_of(vs, es, K, gs, den);
     }
     if (alone && literal && t < T)
         literal_scan([&](uint64_t mm, int &bi, float &bv) __attribute__((always_inline)) { pick<EP>(l, mm, bi, bv); }, K, all, nullptr, es,
@@ -1315,22 +1312,7 @@ __global__ __launch_bounds__(64) void route_select_keys_kernel(const float *__re
             }
         }
     }
-    if (t >= T) return;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) gs[s] = gs[s] / den;
-    if (K == 4 && ((reinterpret_cast<uintptr_t>(topk_idx) | reinterpret_cast<uintptr_t>(gates)) & 15) == 0) {
-        typedef int i32x4 __attribute__((ext_vector_type(4)));
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        *reinterpret_cast<i32x4 *>(topk_idx + (size_t)t * 4) = i32x4{es[0], es[1], es[2], es[3]};
-        *reinterpret_cast<f32x4 *>(gates + (size_t)t * 4) = f32x4{gs[0], gs[1], gs[2], gs[3]};
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-            if (s < K) {
-                topk_idx[(size_t)t * K + s] = es[s];
-                gates[(size_t)t * K + s] = gs[s];
-            }
-    }
+    if (t < T) store_selection(t, K, es, gs, den, topk_idx, gates);
 }
 
 // Selection from stored logits [T, E] (the profiling pass of Sec. 3.2 routes 2^20 tokens of stored
