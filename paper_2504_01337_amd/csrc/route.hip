@@ -1973,6 +1973,10 @@ struct DispatchOut {
     void *x_perm;     // where route_select_index_kernel scatters the rows, or null
 };
 
+// Tokens up to which the waves that have the sums select as well (see the rule): without lists, with nearly as many experts as a wave selects from,
+// and with lists where a token's row is short.
+constexpr int64_t SELECT_UP_TO = 65536, SELECT_MOST_UP_TO = 131072, SELECT_NARROW_UP_TO = 262144;
+
 static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const float *bias, int64_t T, int d, int E, int K,
                       const int32_t *collab_idx, int Tc, int32_t *topk_idx, float *gates, float *logits_out, void *ws,
                       size_t ws_bytes, const DispatchOut *dispatch, void *stream) {
@@ -2067,9 +2071,17 @@ static int route_impl(const void *x, c2r_dtype x_dt, const float *Wg, const floa
     // profiling call, 60 experts, d 2048: 26000 tokens 98.1 / 94.2, 32768 tokens 99.4 / 94.7, 65536 tokens 166.8 / 161.8, 16 experts of d 4096, 32768
     // tokens 112.6 / 110.6; with lists, the layer call of 15 of 60 experts, 26000 tokens 369 / 362, 32768 tokens 425.5 / 418.  Not with 64-token
     // workgroups, whose waves have half of a token's logits, nor where logits are asked for.
+    // Every round of the chip's workgroups (32768 tokens) pays for its selection, at the price of 32 or 64 experts, where one launch for all selects at
+    // the memory's pace by what experts there are; from some round on that is ahead.  Microseconds of top-4, in two launches / so, without lists: d 512,
+    // 65536 tokens, 9 experts 32.1 / 31.2, 33 experts 49.8 / 47.0, 100000 tokens, 9 experts 51.5 / 54.2, 20 51.1 / 52.2, 33 83.2 / 85.7, 48 82.8 / 83.5, but 32
+    // 53.1 / 52.5, 60 84.8 / 83.9; 131072 tokens, 32 experts 56.1 / 54.0, 60 88.6 / 85.2; 400000 tokens, 32 experts 163 / 167, 60 260 / 264; d 2048, 400000
+    // tokens, 9 experts 526 / 536.  With lists the other launch costs more: d 512, 400000 tokens, 9 experts 169.7 / 168.6, 60 297 / 281, 10^6 tokens 388 / 386
+    // and 699 / 662; but where little is read, d 264, 400000 tokens, 9 experts 110 / 112, 33 178 / 177, 10^6 tokens 262 / 283 and 421 / 437.
+    const bool most = E * 8 > (te == 8 ? 64 : 32) * 7;  // of the experts that a wave selects from
+    const int64_t select_up_to = collab_idx ? (most || d >= 512 ? T : SELECT_NARROW_UP_TO) : most ? SELECT_MOST_UP_TO : SELECT_UP_TO;
     // (In one launch workgroups write selections while others still read.)
     const size_t a4 = (size_t)(T * K) * 4;
-    const bool select = all_chunks && !halves && K <= 4 && !logits_out &&
+    const bool select = all_chunks && !halves && K <= 4 && !logits_out && T <= select_up_to &&
                         all_apart({{topk_idx, a4}, {gates, a4}}, {{x, (size_t)T * d * (x_dt == C2R_BF16 ? 2 : 4)}, {W, (size_t)d * ldw * 4},
                                                                  {bias, (size_t)E * 4}, {collab_idx, (size_t)E * Tc * 4}});
     const int64_t nblk = ngroups * ((L.nchunk + cpw - 1) / cpw);

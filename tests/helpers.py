@@ -125,6 +125,11 @@ def ffn_both_limit(name):
     return int(re.search(r"\bBOTH_%s = (\d+)" % name, _csrc("ffn_bf16_dma.hip")).group(1))
 
 
+def select_limit(name):
+    """A number of tokens up to which the router's waves of large batches select as well (SELECT_*, route.hip)."""
+    return int(re.search(r"\bSELECT_%s = (\d+)" % name, _csrc("route.hip")).group(1))
+
+
 def ffn_tiles_limit():
     return ffn_both_limit("TILES")
 
