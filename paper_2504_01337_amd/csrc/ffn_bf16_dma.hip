@@ -1158,7 +1158,7 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
 // Whether one launch of the tile kernel takes both passes.  Microseconds of a layer call, a kernel per pass / so:
 //   gate/up in tiles (more than 179 rows of a shared expert), down in ffn_mid / one launch, the shared expert's down tiles early (ffn_down_early): 60
 //     experts + shared, F 1408 / 5632, 220 tokens 171.5 / 175.5, 241 tokens 173 / 178 (one M-tile of the shared expert), 260 tokens 175.9 / 163.8, 320
-//     tokens 172.5 / 165.2, 390 tokens 175.5 / 162.0; shared experts of 704 to 2816, 260 tokens 156.8 / 151.3 to 155.9 / 135.1, 320 tokens 156 / 154 to 175 /
+//     tokens 172.5 / 165.2, 390 tokens 175.5 / 162.0 (see both_fills for the narrow models); shared experts of 704 to 2816, 260 tokens 156.8 / 151.3 to 155.9 / 135.1, 320 tokens 156 / 154 to 175 /
 //     159, 390 tokens 155 / 150 to 182 / 163; 8 experts of d 4096, F 2816 / 8192, 260 tokens 242 / 215, 320 tokens 273 / 220;
 //   gate/up in ffn_mid, routed groups alone, r rows per expert: 16 experts of d 4096, r = 92 122.5 / 122.4, r = 125 128.4 / 132.6, r = 130
 //     144.7 / 134.0 (a chunk more per group), r = 147 152.8 / 138.0; 8 experts, r = 100 120 / 128, r = 125 141.7 / 135.2, r = 147 155.2 / 141.9.
@@ -1172,15 +1172,35 @@ int launch_ffn_bf16_dma(int pass, const FfnProblem &first, const FfnProblem *sec
 //     232 / 254; more: 385 rows (560) 272.7 / 271.5, 511 rows 292 / 278; d 6144, F 12288, 320 rows (480) 241 / 273, 321 rows (576) 283 / 273; d 8192, F
 //     12288, 257 rows (640) 343 / 329.
 constexpr int BOTH_BESIDE = 256, BOTH_PER_GROUP = 125, BOTH_TILES = 180, BOTH_TILES_OF_PART = 435;
+
+// Whether routed groups and a shared expert, of as many rows as ffn_mid takes, give one launch work enough.  Its down tiles are 256
+// columns wide, ffn_mid's items 64: a narrow model has few of them, and chains as long as the rest of the launch leave most CUs idle behind them.  So
+// there have to be down tiles for half of the CUs, and the k-slices of all tiles, per CU, have to be 0.7 of the longest down chain.  Microseconds of a
+// layer call, a launch per pass / one (slices per CU to the longest chain, down tiles): E 8, K 1, d 512, F 4096 / 2048, 363 tokens 62 / 86 (0.14, 14);
+// E 24, K 1, d 1024, F 2048 / 10240, 397 tokens 106 / 145 (0.29, 80); E 16, K 2, d 2048, F 4096 / 20480, 486 tokens 335 / 434 (0.58, 152); E 16, K 4, d 2048,
+// F 1408 / 4224, 288 tokens 120 / 129 (0.66, 136); E 24, K 4, d 2048, F 1408 / 4224, 288 tokens 156 / 144 (0.78, 168); E 24, K 4, d 4096, F 1536 / 7680, 280 tokens
+// 335 / 260 (1.16, 336).  Of 2146 drawn shapes with 257 to 511 tokens (d 512 to 5120, even and skewed loads), by this rule one launch is more than 3 % behind
+// in 71 (nearly all skewed, whose experts in use nobody knows here), a launch per pass in 68; one launch for all would be in 552.
+constexpr int BOTH_DOWN_TILES = 128;
+static bool both_fills(const FfnLaunch &up, const FfnLaunch &down, int routed_mtiles) {
+    const FfnProblem &R = down.p[0], &S = down.p[1];
+    const int64_t cus = 8 * CUS_PER_XCD, up_slices = (up.p[0].Kdim + 63) / 64, routed = (R.Kdim + 63) / 64, shared = (S.Kdim + 63) / 64;
+    const int64_t up_tiles = (int64_t)routed_mtiles * up.p[0].ntn + (int64_t)(up.p[1].A_cap + 255) / 256 * up.p[1].ntn;
+    const int64_t routed_tiles = (int64_t)routed_mtiles * R.ntn, shared_tiles = (int64_t)(S.A_cap + down.single_rows - 1) / down.single_rows * S.ntn;
+    return routed_tiles + shared_tiles >= BOTH_DOWN_TILES &&
+           10 * (up_tiles * up_slices + routed_tiles * routed + shared_tiles * shared) >= 7 * cus * (routed > shared ? routed : shared);
+}
 static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely) {
     int rows[2];
     if (ffn_skinny_takes(0, up) || ffn_skinny_takes(1, down)) return false;
     const FfnProblem &R = up.p[0], &S = up.p[1];
     if (ffn_mid_rows(0, up, likely, rows)) return !up.has_single && likely / R.E_local > BOTH_PER_GROUP;
-    if (up.has_single && ffn_mid_rows(1, down, likely, rows) && (up.has_ragged ? S.A_cap <= BOTH_BESIDE : ffn_mid_in_one_round(down.p[1], rows[1])))
+    const int routed_mtiles = up.has_ragged ? likely / 256 + (R.E_local < likely ? R.E_local : likely) / 2 : 0;
+    if (up.has_single && ffn_mid_rows(1, down, likely, rows) &&
+        (up.has_ragged ? S.A_cap <= BOTH_BESIDE || !both_fills(up, down, routed_mtiles) : ffn_mid_in_one_round(down.p[1], rows[1])))
         return false;
     int64_t tiles = up.has_single ? (int64_t)(S.A_cap + 255) / 256 * S.ntn : 0;
-    if (up.has_ragged) tiles += (int64_t)(likely / 256 + (R.E_local < likely ? R.E_local : likely) / 2) * R.ntn;
+    tiles += (int64_t)routed_mtiles * R.ntn;
     return tiles >= (up.has_ragged && likely < R.A_cap ? BOTH_TILES_OF_PART : BOTH_TILES);
 }
 
@@ -1194,7 +1214,7 @@ static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely
 //   3 and 2.5, 60 experts, F 1408 / 4224 and 3520: 300 tokens 165 / 157, 155.6 / 154, 390 tokens 159 / 160, 158 / 161, 420 tokens 159 / 161, 152.5 / 157, 512
 //     tokens 163 / 166, 160 / 164;
 //   2 and less: 260 tokens 148 / 145.5 (F 1408 / 2816), 151 / 135 (1408 / 1408), 390 tokens 156 / 158, 153 / 153, 480 tokens 156 / 158, 640 tokens 196 / 200.
-// (Up to 390 rows either way is ahead of a launch per pass, see above.)
+// (Where both_fills, either way is ahead of a launch per pass up to 390 rows.)
 constexpr int BOTH_EARLY_UP_TO = 390, BOTH_EARLY_LONG_UP_TO = 600;
 static bool ffn_down_early(const FfnLaunch &down) {
     if (!down.has_single || !down.has_ragged) return false;

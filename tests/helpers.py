@@ -134,6 +134,22 @@ def ffn_tiles_limit():
     return ffn_both_limit("TILES")
 
 
+def ffn_shared_schedule(T, E, K, d, F, Fs):
+    """The FFN of a layer call whose gate/up pass and shared expert the tile kernel takes: "two" launches, or one with the shared expert's
+    down tiles "late" or "early" (both_in_tiles, both_fills and ffn_down_early, ffn_bf16_dma.hip)."""
+    up = lambda a, b: -(-a // b)
+    mtiles, cols = T * K // 256 + min(E, T * K) // 2, up(d, 256)
+    rows = 256 if Fs < 2 * F else {0: 64, 1: 128, 2: 256}[(up(T, 256) * cols > 40) + (up(T, 256) * cols >= 64)]
+    routed, shared = mtiles * cols, up(T, rows) * cols
+    gate_up = mtiles * up(F, 128) + up(T, 256) * up(Fs, 128)
+    slices = gate_up * up(d, 64) + routed * up(F, 64) + shared * up(Fs, 64)
+    fills = routed + shared >= ffn_both_limit("DOWN_TILES") and 10 * slices >= 7 * 256 * up(max(F, Fs), 64)
+    mid = T <= _mid_limits("SINGLE")[1][1] and T * K // E <= _mid_limits("RAGGED")[1][2]
+    if gate_up < ffn_tiles_limit() or mid and (T <= ffn_both_limit("BESIDE") or not fills):
+        return "two"
+    return "early" if T <= ffn_both_limit("EARLY_LONG_UP_TO" if Fs > 3 * F else "EARLY_UP_TO") else "late"
+
+
 def _mid_limits(side):
     """Most rows of every tile height of ffn_mid.hip, per pass (side: RAGGED, per group, or SINGLE)."""
     table = re.search(r"\bMID_%s_UP_TO\[2\]\[\d\] = \{([{}\d, ]+)\}" % side, _csrc("ffn_mid.hip")).group(1)

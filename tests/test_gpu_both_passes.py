@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import dev, ffn_both_limit, ffn_kernel, ffn_tiles, ffn_tiles_limit
+from helpers import dev, ffn_both_limit, ffn_kernel, ffn_shared_schedule, ffn_tiles, ffn_tiles_limit
 
 pytestmark = pytest.mark.gpu
 
@@ -70,11 +70,10 @@ def test_layer_with_shared_expert(c2r, T, d, F, Fs):
 BESIDE, EARLY, LONG = ffn_both_limit("BESIDE"), ffn_both_limit("EARLY_UP_TO"), ffn_both_limit("EARLY_LONG_UP_TO")
 
 
-# the layer call on either side of the rules that give a pass to this kernel or that: rows of a shared expert (one launch for both passes, its
-# down tiles early), 125 likely rows per expert, 4096 rows allotted to a device with a part of the experts.  The same bits as stage by stage,
-# where every pass chooses by the rows allotted.
-@pytest.mark.parametrize("T,E,El,K,Fs", [(BESIDE, 60, 60, 4, 192), (BESIDE + 1, 60, 60, 4, 192), (EARLY, 60, 60, 4, 192), (EARLY + 1, 60, 60, 4, 192),
-                                         (LONG, 60, 60, 4, 2176), (LONG + 1, 60, 60, 4, 2176),
+# the layer call on either side of the rules that give a pass to this kernel or that: rows of a shared expert (its down tiles early), 125 likely
+# rows per expert, 4096 rows allotted to a device with a part of the experts.  The same bits as stage by stage, where every pass chooses by the
+# rows allotted.
+@pytest.mark.parametrize("T,E,El,K,Fs", [(LONG, 60, 60, 4, 2176), (LONG + 1, 60, 60, 4, 2176),
                                          (390, 60, 60, 4, 192), (391, 60, 60, 4, 192), (501, 16, 16, 4, 0), (504, 16, 16, 4, 0), (600, 16, 16, 4, 0),
                                          (1000, 60, 15, 4, 0), (1024, 60, 15, 4, 0), (1025, 60, 15, 4, 0), (2100, 60, 15, 4, 0), (15500, 60, 15, 4, 0),
                                          (16384, 60, 15, 4, 0), (17000, 60, 15, 4, 0), (300, 64, 1, 4, 0)])
@@ -147,12 +146,10 @@ def test_beside_another_launch(c2r):
     assert all(torch.equal(o, ref) for out, ref in zip(outs, refs) for o in out)
 
 
-# a shared expert's down tiles ahead of routed gate/up tiles: the last rows on one side of the rules and the first on the other (two launches; a
-# shared contraction of more than three times the routed one and of as much), a down pass cut to 64 rows (long contraction) and whole, more gate/up
-# tiles than a round and one tile only, nothing but the shared expert's in a list's first round; two such layers on two streams, each of whose
-# waits must end by workgroups of its own launch
-@pytest.mark.parametrize("T,E,d,F,Fs", [(BESIDE, 60, 128, 704, 2816), (BESIDE + 1, 60, 128, 704, 2816), (EARLY, 60, 128, 704, 2112), (EARLY + 1, 60, 128, 704, 2112),
-                                        (LONG, 60, 128, 704, 2176), (LONG + 1, 60, 128, 704, 2176),
+# a shared expert's down tiles ahead of routed gate/up tiles: the last rows of the rule for long contractions and the first beyond it, a down pass cut
+# to 64 rows, nothing but the shared expert's in a list's first round; and such layers as take a launch per pass or the down tiles late; two
+# layers on two streams, each of whose waits must end by workgroups of its own launch
+@pytest.mark.parametrize("T,E,d,F,Fs", [(LONG, 60, 128, 704, 2176), (LONG + 1, 60, 128, 704, 2176), (512, 2, 64, 2048, 16448),
                                         (257, 60, 128, 704, 2816), (420, 60, 2048, 320, 5632), (640, 60, 256, 1408, 1024), (641, 60, 256, 1408, 1024),
                                         (300, 60, 128, 1408, 64), (512, 16, 192, 192, 16448), (257, 2, 64, 11264, 8192)])
 def test_shared_expert_down_tiles_early(c2r, T, E, d, F, Fs):
@@ -181,6 +178,63 @@ def test_shared_expert_down_tiles_early(c2r, T, E, d, F, Fs):
                 out[i].copy_(layer.forward(x))
     torch.cuda.synchronize()
     assert all(torch.equal(o, ref) for out, ref in zip(outs, refs) for o in out)
+
+
+# the rules for as many rows of a shared expert as ffn_mid's down pass takes: the last rows and the first (a launch per pass or one; the down tiles
+# early or late, for a shared contraction of three times the routed one and of more), one expert and one step of the shared contraction more or
+# less (down tiles, k-slices), a narrow model; 64-row down tiles and whole ones, one column tile of gate/up.  The same bits as in launches of their own.
+@pytest.mark.parametrize("T,E,d,F,Fs,schedule", [
+    (BESIDE, 60, 1280, 704, 2112, "two"), (BESIDE + 1, 60, 1280, 704, 2112, "early"), (EARLY, 60, 1280, 704, 2112, "early"), (EARLY + 1, 60, 1280, 704, 2112, "late"),
+    (EARLY + 1, 60, 1280, 704, 2176, "early"), (511, 60, 1280, 704, 2176, "early"), (300, 60, 1280, 1408, 64, "early"),
+    (257, 52, 1024, 704, 704, "early"), (257, 50, 1024, 704, 704, "two"), (300, 60, 1280, 704, 2816, "early"), (300, 60, 1280, 704, 2880, "two"),
+    (300, 60, 128, 704, 2816, "two")])
+def test_schedules_beside_a_shared_expert(c2r, T, E, d, F, Fs, schedule):
+    assert ffn_shared_schedule(T, E, 4, d, F, Fs) == schedule
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + Fs)
+    normal = lambda *shape: torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16).mul_(0.05)
+    weights, shared = [normal(E, F, d), normal(E, F, d), normal(E, d, F)], (normal(1, Fs, d), normal(1, Fs, d), normal(1, d, Fs))
+    x, Wg = normal(T, d).mul_(20), torch.randn((d, E), generator=g, device="cuda")
+    a, b = (c2r.C2RLayer(T, d, E, 4, F, torch.bfloat16, Wg, None, None, *weights, shared=shared, fuse_shared=f) for f in (True, False))
+    ref = b.forward(x).clone()
+    for _ in range(4):
+        a.h.fill_(float("nan"))
+        a.h_shared.fill_(float("nan"))
+        assert torch.equal(a.forward(x), ref)
+        assert torch.equal(a.y_perm, b.y_perm) and torch.equal(a.y_shared, b.y_shared)
+
+
+# A narrow model's layer takes no longer than its two passes and the stages around them (62 us, 42 of them the passes; 86 with both passes in one
+# launch, whose few down tiles are chains that nothing runs beside)
+def test_narrow_model_costs_no_more_than_its_passes(c2r):
+    T, E, K, d, F, Fs = 363, 8, 1, 512, 4096, 2048
+    normal = lambda *shape: torch.randn(shape, device="cuda", dtype=torch.bfloat16)
+    weights, shared = (normal(E, F, d), normal(E, F, d), normal(E, d, F)), (normal(1, Fs, d), normal(1, Fs, d), normal(1, d, Fs))
+    x, Wg = normal(T, d), torch.randn((d, E), device="cuda")
+    layer = c2r.C2RLayer(T, d, E, K, F, torch.bfloat16, Wg, None, None, *weights, shared=shared)
+    layer.forward(x)
+    idx = layer.idx.clone()
+    _, offsets, perm, _ = c2r.permute(None, idx, E)[:4]
+    h, hs = torch.empty((T * K, F), dtype=torch.bfloat16, device="cuda"), torch.empty((T, Fs), dtype=torch.bfloat16, device="cuda")
+    y, ys = torch.empty((T * K, d), dtype=torch.bfloat16, device="cuda"), torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+
+    def passes():
+        c2r.expert_ffn_gate_up_with_shared(x, perm, K, offsets, weights[0], weights[1], h, shared[0], shared[1], hs)
+        c2r.expert_ffn_down_with_shared(h, offsets, weights[2], y, hs, shared[2], ys)
+
+    best = []
+    for call in (passes, lambda: layer.forward(x)):
+        times = []
+        for _ in range(12):
+            beg, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            beg.record()
+            for _ in range(16):
+                call()
+            end.record()
+            torch.cuda.synchronize()
+            times.append(beg.elapsed_time(end) / 16 * 1e3)
+        best.append(min(times))
+    assert best[1] < 1.15 * (best[0] + 20), best
 
 
 # one group alone: both passes in one launch (more items in ffn_mid's down pass than workgroups: 511 rows of d 4160) and a launch each (as many: d 4096)
