@@ -1212,14 +1212,16 @@ static bool both_in_tiles(const FfnLaunch &up, const FfnLaunch &down, int likely
 //     195 / 195, 1000 tokens 226 / 248; 32 experts 520 tokens 179 / 172, 560 tokens 176 / 165; 16 of d 4096, F 2048 / 8192, 450 tokens 291 / 285, 520 tokens
 //     314 / 303, 640 tokens 338 / 341;
 //   3 and 2.5, 60 experts, F 1408 / 4224 and 3520: 300 tokens 165 / 157, 155.6 / 154, 390 tokens 159 / 160, 158 / 161, 420 tokens 159 / 161, 152.5 / 157, 512
-//     tokens 163 / 166, 160 / 164;
+//     tokens 163 / 166, 160 / 164; 32 experts, K 2, F 1408 / 4224, 409 tokens 189 / 168, 494 tokens 179 / 159;
 //   2 and less: 260 tokens 148 / 145.5 (F 1408 / 2816), 151 / 135 (1408 / 1408), 390 tokens 156 / 158, 153 / 153, 480 tokens 156 / 158, 640 tokens 196 / 200.
-// (Where both_fills, either way is ahead of a launch per pass up to 390 rows.)
-constexpr int BOTH_EARLY_UP_TO = 390, BOTH_EARLY_LONG_UP_TO = 600;
+// Of drawn shapes (as in both_fills) early is ahead / behind by more than 3 %, ratio 3, 391 to 600 tokens, in 30 / 7 of 80, ratio 4 in 28 / 3 of 110, ratio 2 in
+// 13 / 12 of 91; 601 to 640 tokens, ratio 3, in 1 / 1 of 15, ratio 4 in 10 / 3 of 27, ratio 5 in 15 / 0 of 26.  (Where both_fills, either way is ahead of a launch
+// per pass up to 390 rows.)
+constexpr int BOTH_EARLY_UP_TO = 390, BOTH_EARLY_LONG_UP_TO = 600, BOTH_EARLY_LONGEST_UP_TO = 640;
 static bool ffn_down_early(const FfnLaunch &down) {
     if (!down.has_single || !down.has_ragged) return false;
     const FfnProblem &R = down.p[0], &S = down.p[1];
-    return S.A_cap <= (S.Kdim > 3 * R.Kdim ? BOTH_EARLY_LONG_UP_TO : BOTH_EARLY_UP_TO);
+    return S.A_cap <= (S.Kdim > 4 * R.Kdim ? BOTH_EARLY_LONGEST_UP_TO : S.Kdim >= 3 * R.Kdim ? BOTH_EARLY_LONG_UP_TO : BOTH_EARLY_UP_TO);
 }
 
 // Whether the down pass may write while the gate/up pass still reads: its outputs meet nothing else of the two (but for one in the place of

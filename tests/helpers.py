@@ -147,7 +147,8 @@ def ffn_shared_schedule(T, E, K, d, F, Fs):
     mid = T <= _mid_limits("SINGLE")[1][1] and T * K // E <= _mid_limits("RAGGED")[1][2]
     if gate_up < ffn_tiles_limit() or mid and (T <= ffn_both_limit("BESIDE") or not fills):
         return "two"
-    return "early" if T <= ffn_both_limit("EARLY_LONG_UP_TO" if Fs > 3 * F else "EARLY_UP_TO") else "late"
+    limit = "EARLY_LONGEST_UP_TO" if Fs > 4 * F else "EARLY_LONG_UP_TO" if Fs >= 3 * F else "EARLY_UP_TO"
+    return "early" if T <= ffn_both_limit(limit) else "late"
 
 
 def _mid_limits(side):

@@ -67,7 +67,7 @@ def test_layer_with_shared_expert(c2r, T, d, F, Fs):
         assert torch.equal(a.y_perm, b.y_perm) and torch.equal(a.y_shared, b.y_shared)
 
 
-BESIDE, EARLY, LONG = ffn_both_limit("BESIDE"), ffn_both_limit("EARLY_UP_TO"), ffn_both_limit("EARLY_LONG_UP_TO")
+BESIDE, EARLY, LONG, LONGEST = (ffn_both_limit(n) for n in ("BESIDE", "EARLY_UP_TO", "EARLY_LONG_UP_TO", "EARLY_LONGEST_UP_TO"))
 
 
 # the layer call on either side of the rules that give a pass to this kernel or that: rows of a shared expert (its down tiles early), 125 likely
@@ -181,11 +181,13 @@ def test_shared_expert_down_tiles_early(c2r, T, E, d, F, Fs):
 
 
 # the rules for as many rows of a shared expert as ffn_mid's down pass takes: the last rows and the first (a launch per pass or one; the down tiles
-# early or late, for a shared contraction of three times the routed one and of more), one expert and one step of the shared contraction more or
+# early or late, for a shared contraction of under three times the routed one, of three and of more than four), one expert and one step of the shared
+# contraction more or
 # less (down tiles, k-slices), a narrow model; 64-row down tiles and whole ones, one column tile of gate/up.  The same bits as in launches of their own.
 @pytest.mark.parametrize("T,E,d,F,Fs,schedule", [
-    (BESIDE, 60, 1280, 704, 2112, "two"), (BESIDE + 1, 60, 1280, 704, 2112, "early"), (EARLY, 60, 1280, 704, 2112, "early"), (EARLY + 1, 60, 1280, 704, 2112, "late"),
-    (EARLY + 1, 60, 1280, 704, 2176, "early"), (511, 60, 1280, 704, 2176, "early"), (300, 60, 1280, 1408, 64, "early"),
+    (BESIDE, 60, 1280, 704, 2048, "two"), (BESIDE + 1, 60, 1280, 704, 2048, "early"), (EARLY, 60, 1280, 704, 2048, "early"), (EARLY + 1, 60, 1280, 704, 2048, "late"),
+    (EARLY + 1, 60, 1280, 704, 2112, "early"), (511, 60, 1280, 704, 2112, "early"), (300, 60, 1280, 1408, 64, "early"),
+    (LONG, 60, 128, 704, 2816, "early"), (LONG + 1, 60, 128, 704, 2816, "late"), (LONGEST, 60, 128, 704, 2880, "early"), (LONGEST + 1, 60, 128, 704, 2880, "late"),
     (257, 52, 1024, 704, 704, "early"), (257, 50, 1024, 704, 704, "two"), (300, 60, 1280, 704, 2816, "early"), (300, 60, 1280, 704, 2880, "two"),
     (300, 60, 128, 704, 2816, "two")])
 def test_schedules_beside_a_shared_expert(c2r, T, E, d, F, Fs, schedule):
