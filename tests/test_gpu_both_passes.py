@@ -206,8 +206,8 @@ def test_schedules_beside_a_shared_expert(c2r, T, E, d, F, Fs, schedule):
         assert torch.equal(a.y_perm, b.y_perm) and torch.equal(a.y_shared, b.y_shared)
 
 
-# A narrow model's layer takes no longer than its two passes and the stages around them (62 us, 42 of them the passes; 86 with both passes in one
-# launch, whose few down tiles are chains that nothing runs beside)
+# A narrow model's layer takes no longer than its two passes and the stages around them (62 us; 86 with both passes in one launch, whose few
+# down tiles are chains that nothing runs beside)
 def test_narrow_model_costs_no_more_than_its_passes(c2r):
     T, E, K, d, F, Fs = 363, 8, 1, 512, 4096, 2048
     normal = lambda *shape: torch.randn(shape, device="cuda", dtype=torch.bfloat16)
